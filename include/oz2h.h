@@ -312,7 +312,7 @@ typedef struct oz2h_saved_residues oz2h_saved_residues;
  * Computes the residues of X (stored as the op says: side A, op N: rows x K; side
  * B, op N: K x rows; OZ2H_OP_T the transposes) with the plan's moduli, into device
  * memory the handle owns (one hipMalloc of about G * round_up(rows, 256) *
- * round_up(K, 128) bytes).  The kernels run asynchronously on `stream`; the
+ * round_up(K, 128) bytes, K rounded to 256 above 1024).  The kernels run asynchronously on `stream`; the
  * handle is ready for launches ordered after them.  X is not read afterwards.
  */
 int oz2h_residues_create(const oz2h_plan *plan, int32_t side, int64_t rows, oz2h_op op, oz2h_cmat X,

@@ -112,7 +112,8 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // residue GEMM block tiles (output rows x columns): 128 x 128 (waves of 64 x 64),
-// 256 x 128 (waves of 128 x 64) and 128 x 256 (waves of 64 x 128)
+// 256 x 128 (waves of 128 x 64), 128 x 256 (waves of 64 x 128), and, chosen automatically
+// only, 256 x 256 (eight waves of 128 x 64)
 struct GemmCfg {
     int bm, bn;
 };
@@ -125,13 +126,27 @@ GemmCfg tile_cfg(int tile) {
     }
 }
 
-// automatic choice: the larger tile when it pads the output by at most 1/16 more
-// than 128 x 128 and still leaves at least two blocks per compute unit per modulus
-// batch of 8 moduli; otherwise 128 x 128
-GemmCfg choose_gemm(int64_t M, int64_t N, int tile) {
+// k padding of the INT8 planes: the 256 x 256 kernel takes pairs of 128-byte k-tiles, so long
+// contractions are padded to 256 (at most a ninth more); short ones only to 128
+int64_t kpad_for(int64_t K) { return round_up(std::max<int64_t>(K, 1), K > 1024 ? 2 * GBK : GBK); }
+
+// Automatic choice for L moduli (L = 0: no 256 x 256 tiles).
+// 256 x 256 (k_resgemm8) from 320 (modulus, tile) items on, where the output pads to at most
+// 1/16 more than with 128 x 128 tiles, or 1/3 more from kpad = 1024 on.  Whole products, the
+// other tiles against it: 2048^3 p = 256: 2161 / 1741 us; 1024 x 1024 x 256, p = 53 (368
+// items): 95 / 94; 512 x 512 x 1024, p = 256 (280 items, the second round of 256 blocks nearly
+// empty): 209 / 214; 896 x 896 x 4096, p = 256 (pads 1.31 times): 1267 / 997; with K = 256:
+// 223 / 223; 640 x 640 x 1024 (1.44 times): 288 / 307.
+// Else 256 x 128 when it pads at most 1/16 more and leaves two blocks per compute unit per
+// batch of 8 moduli, else 128 x 128.
+GemmCfg choose_gemm(int64_t M, int64_t N, int tile, int64_t kpad, int L) {
     if (tile != OZ2H_TILE_AUTO) return tile_cfg(tile);
     const int64_t a128 = round_up(M, 128) * round_up(N, 128);
     const int64_t a256 = round_up(M, 256) * round_up(N, 128);
+    const int64_t sq = round_up(M, 256) * round_up(N, 256);
+    if (kpad % (2 * GBK) == 0 && L * (sq / (256 * 256)) >= 320 &&
+        (sq * 16 <= a128 * 17 || (kpad >= 1024 && sq * 3 <= a128 * 4)))
+        return {256, 256};
     const int64_t blocks = a256 / (256 * 128);
     if (M >= 256 && a256 * 16 <= a128 * 17 && blocks * 8 >= 2 * 256) return {256, 128};
     return {128, 128};
@@ -145,12 +160,13 @@ struct Layout {
 
 size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N);
 
-Layout layout_for(const PlanHost &h, int64_t M, int64_t N) {
+// compact: the least padding, for a workspace of fixed size
+Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool compact = false) {
     Layout w{};
-    w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile);
+    w.kpad = compact ? round_up(std::max<int64_t>(h.K, 1), GBK) : kpad_for(h.K);
+    w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, compact ? 0 : h.L);
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
-    w.kpad = round_up(std::max<int64_t>(h.K, 1), GBK);
     size_t off = 0;
     w.off_e = off;
     off = align_up(off + sizeof(int32_t) * w.mpad);
@@ -298,6 +314,23 @@ XcdMap xcd_map_for(GemmCfg cfg, dim3 &grid) {
     return xm;
 }
 
+// The 256 x 256 kernel over every (modulus, tile): one persistent block per compute unit.
+constexpr int kGemm8Blocks = 256;   // compute units of an MI355X (a multiple of the 8 XCDs)
+
+int launch_gemm8(const oz2h_plan *pl, int64_t mpad, int64_t npad, const GemmArgsZ &g, int mode, hipStream_t s) {
+    const PlanHost &h = pl->h;
+    dim3 grid((unsigned)(npad / 256), (unsigned)(mpad / 256), 1);
+    Gemm8Args a{g, h.L, h.L1, (int)grid.y, (int)grid.x, {}};
+    a.xm = xcd_map_for(GemmCfg{256, 256}, grid);
+    const int64_t items = (int64_t)a.tm * a.tn * h.L;
+    const unsigned nb = (unsigned)std::min<int64_t>(kGemm8Blocks, round_up(items, 8));
+    if (mode == ZADD) k_resgemm8<ZADD><<<nb, 512, 0, s>>>(a);
+    else if (mode == ZSUB) k_resgemm8<ZSUB><<<nb, 512, 0, s>>>(a);
+    else if (mode == ZGAUSS) k_resgemm8<ZGAUSS><<<nb, 512, 0, s>>>(a);
+    else k_resgemm8<ZSTORE><<<nb, 512, 0, s>>>(a);
+    return check_launch("residue GEMM");
+}
+
 template <bool RAW>
 int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b, int64_t kpad,
                        int64_t a_ps, int64_t b_ps, const ModInfo *mi, int L, int16_t *v,
@@ -315,6 +348,10 @@ int launch_resgemm(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npad,
                    const int8_t *a, const int8_t *b, int16_t *v, hipStream_t s, int64_t a_ps = 0,
                    int64_t b_ps = 0) {
     const PlanHost &h = pl->h;
+    if (cfg.bm == 256 && cfg.bn == 256)
+        return launch_gemm8(pl, mpad, npad,
+                            GemmArgsZ{{a, b, kpad, a_ps ? a_ps : mpad * kpad, b_ps ? b_ps : npad * kpad,
+                                       pl->d_info, v, mpad * npad, npad, nullptr}, nullptr}, ZSTORE, s);
     dim3 grid((unsigned)(npad / cfg.bn), (unsigned)(mpad / cfg.bm), (unsigned)h.L);
     return launch_gemm_kernel<false>(cfg, grid, a, b, kpad, a_ps ? a_ps : mpad * kpad,
                                      b_ps ? b_ps : npad * kpad, pl->d_info, h.L, v, mpad * npad,
@@ -590,10 +627,11 @@ F64Layout layout_f64(const oz2h_plan *pl, int64_t M, int64_t N) {
     const PlanHost &h = pl->h;
     const PlanHost *h8 = pl->i8 ? &pl->i8->h : nullptr;
     F64Layout w{};
-    w.cfg = h8 ? choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h8->tile) : GemmCfg{128, 128};
+    w.kpad = round_up(std::max<int64_t>(h.K, 1), GBK);
+    w.cfg = h8 ? choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h8->tile, w.kpad, 0)
+               : GemmCfg{128, 128};
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
-    w.kpad = round_up(std::max<int64_t>(h.K, 1), GBK);
     const size_t g8 = h8 ? (size_t)h8->G : 0;
     size_t off = 0;
     w.off_e = off;
@@ -712,7 +750,7 @@ int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op o
                  oz2h_cmat A, oz2h_op opB, oz2h_cmat B, bool round, oz2h_mat *C, int8_t *chat_sign,
                  uint64_t *chat_mag, int nlc, int32_t *e_out, int32_t *f_out, void *ws,
                  size_t ws_bytes, hipStream_t s, hipEvent_t *ev = nullptr,
-                 const SideCache *ca = nullptr, const SideCache *cb = nullptr) {
+                 const SideCache *ca = nullptr, const SideCache *cb = nullptr, bool compact = false) {
     int st = check_plan(pl);
     if (st) return st;
     const PlanHost &h = pl->h;
@@ -747,7 +785,7 @@ int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op o
         return run_pipeline_f64(pl, M, N, K, opA, A, opB, B, round, C, chat_sign, chat_mag, nlc, e_out,
                                 f_out, ws, ws_bytes, s, ev);
     }
-    const Layout w = layout_for(h, M, N);
+    const Layout w = layout_for(h, M, N, compact);
     if (!ws) return fail(OZ2H_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws) % kAlign) return fail(OZ2H_EINVAL, "workspace must be 256-byte aligned");
     if (ws_bytes < w.total)
@@ -1113,7 +1151,7 @@ int oz2h_residues_create(const oz2h_plan *plan, int32_t side, int64_t rows, oz2h
     r->rows = rows;
     r->K = K;
     r->rpad = round_up(rows, 256);
-    r->kpad = round_up(K, GBK);
+    r->kpad = kpad_for(K);
     r->p = h.p;
     r->t = h.t;
     r->G = h.G;
@@ -1201,10 +1239,10 @@ struct ZLayout {
 
 ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K) {
     ZLayout w{};
-    w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile);
+    w.kpad = kpad_for(K);
+    w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, h.L);
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
-    w.kpad = round_up(std::max<int64_t>(K, 1), GBK);
     w.nsets = scheme == 3 ? 3 : 2;
     size_t off = 0;
     w.off_e = off;
@@ -1237,6 +1275,7 @@ int launch_resgemm_z(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npa
     const PlanHost &h = pl->h;
     dim3 grid((unsigned)(npad / cfg.bn), (unsigned)(mpad / cfg.bm), (unsigned)h.L);
     const GemmArgsZ g{{a, b, kpad, mpad * kpad, npad * kpad, pl->d_info, v, mpad * npad, npad, nullptr}, v2};
+    if (cfg.bm == 256 && cfg.bn == 256) return launch_gemm8(pl, mpad, npad, g, mode, s);
     const XcdMap xm = xcd_map_for(cfg, grid);
 #define OZ2H_ZG(WM, WN)                                                                        \
     do {                                                                                       \
@@ -1395,8 +1434,10 @@ int oz2h_gemm_noalloc(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, oz
                       oz2h_cmat A, oz2h_op opB, oz2h_cmat B, oz2h_mat C, hipStream_t stream) {
     int st = check_plan(plan);
     if (st || (st = need_int8(plan, "oz2h_gemm_noalloc"))) return st;
+    bool compact = false;
     if (M > 0 && N > 0 && K > 0) {
-        const size_t need = layout_for(plan->h, M, N).total;
+        compact = layout_for(plan->h, M, N).total > kScratchBytes;
+        const size_t need = layout_for(plan->h, M, N, compact).total;
         if (need > kScratchBytes)
             return fail(OZ2H_ERANGE, "product needs %zu bytes of scratch, the static scratch holds %zu",
                         need, kScratchBytes);
@@ -1404,7 +1445,7 @@ int oz2h_gemm_noalloc(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, oz
     void *ws = nullptr;
     if ((st = scratch_for(plan->device, &ws))) return st;
     return run_pipeline(plan, M, N, K, opA, A, opB, B, true, &C, nullptr, nullptr, 0, nullptr,
-                        nullptr, ws, kScratchBytes, stream);
+                        nullptr, ws, kScratchBytes, stream, nullptr, nullptr, nullptr, compact);
 }
 
 
@@ -1432,10 +1473,10 @@ BwdLayout bwd_layout(const PlanHost &h) {
     const int64_t M = h.gM, N = h.gN, K = h.K;
     const int64_t orows[2] = {M, K}, ocols[2] = {K, N}, contr[2] = {N, M};
     for (int sd = 0; sd < 2; ++sd) {
-        b.cfg[sd] = choose_gemm(orows[sd], ocols[sd], h.tile);
+        b.kpad[sd] = kpad_for(contr[sd]);
+        b.cfg[sd] = choose_gemm(orows[sd], ocols[sd], h.tile, b.kpad[sd], h.L);
         b.mpad[sd] = round_up(orows[sd], b.cfg[sd].bm);
         b.npad[sd] = round_up(ocols[sd], b.cfg[sd].bn);
-        b.kpad[sd] = round_up(contr[sd], GBK);
         size_t off = 0;
         b.off_x[sd] = off;
         off = align_up(off + sizeof(int32_t) * (sd == 0 ? b.mpad[sd] : b.npad[sd]));
@@ -1689,7 +1730,10 @@ int oz2h_residue_gemm(const oz2h_plan *plan, int64_t mpad, int64_t npad, int64_t
     if (kpad > kMaxK + GBK) return fail(OZ2H_ERANGE, "K too large for exact INT32 accumulation");
     if (!a_planes || !b_planes || !v) return fail(OZ2H_EINVAL, "NULL pointer");
     GemmCfg cfg = tile_cfg(plan->h.tile);
-    if (plan->h.tile == OZ2H_TILE_AUTO && mpad % 256 == 0) cfg = {256, 128};
+    if (plan->h.tile == OZ2H_TILE_AUTO && mpad % 256 == 0) {
+        cfg = choose_gemm(mpad, npad, OZ2H_TILE_AUTO, kpad, npad % 256 == 0 ? plan->h.L : 0);
+        if (cfg.bn != 256) cfg = {256, 128};
+    }
     if (mpad % cfg.bm || npad % cfg.bn)
         return fail(OZ2H_EINVAL, "mpad, npad must be multiples of the %dx%d tile", cfg.bm, cfg.bn);
     st = launch_resgemm(plan, cfg, mpad, npad, kpad, a_planes, b_planes, v, stream);
@@ -1881,7 +1925,7 @@ void tune_store(uint64_t sig, const TuneRec &r) {
 // tile class (oz2h_tile - 1) of product b under the plan's tile setting
 int item_class(const oz2h_batched_plan *bp, int b) {
     if (bp->tile != OZ2H_TILE_AUTO) return bp->tile - 1;
-    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO);
+    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO, bp->pd[b].kpad, 0);
     return c.bm == 256 ? OZ2H_TILE_256x128 - 1 : (c.bn == 256 ? OZ2H_TILE_128x256 - 1 : OZ2H_TILE_128x128 - 1);
 }
 

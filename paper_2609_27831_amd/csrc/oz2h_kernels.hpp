@@ -1231,6 +1231,391 @@ __global__ __launch_bounds__(256) void k_resgemm_z(GemmArgsZ args, int L, XcdMap
     gemm_tile<WM, WN, false, 3, MODE, GemmArgsZ>(args, mt, nt, L - 1 - (int)zi);
 }
 
+// ---- 256 x 256 tiles
+
+// LDS of the 256 x 256 kernel: two stages of four 16 KiB parts (128 rows of one 128-byte
+// k-tile), one object per part so that the compiler can tell a read of one part from a load
+// still filling another
+template <int S, int P>
+__device__ __forceinline__ int8_t *gemm8_part() {
+    __shared__ __attribute__((aligned(1024))) int8_t st[128 * TBK];
+    return st;
+}
+
+// chunk swizzle of a B part: the 16 rows of a fragment are 8 a + 4 y + b (a, b < 4; y fixed)
+__device__ __forceinline__ int lds_swz_b(int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); }
+
+// s_waitcnt immediate: at most `vm` vector-memory operations outstanding, no LDS operation
+constexpr int vmlgkm_imm(int vm) { return (vm & 0xF) | (((vm >> 4) & 3) << 14) | (0x7 << 4); }
+
+// Arguments of the 256 x 256 kernel: GemmArgsZ's fields plus the moduli split (one-limb moduli
+// 0 .. L1 - 1 own planes 0 .. L1 - 1, two-limb ones three planes each after them) and the
+// work list: tiles tm x tn of each modulus, dealt by XCD rectangle when xm.on.
+struct Gemm8Args {
+    GemmArgsZ g;
+    int L, L1, tm, tn;
+    XcdMap xm;
+};
+
+// Residue GEMM with 256 x 256 tiles: eight waves, two per SIMD, each 128 x 64 of the tile
+// (wave (wr, wc): rows 64 wr .. of both 128-row halves of A, columns 64 wc .. in two 32-column
+// groups of B), as 16 x 16 x 64 int8 products (one lane: one output row, four consecutive
+// columns of B's fragment).
+//
+// The k-loop alternates two phases per 128-byte k-tile T:
+//   phase 0: read A0(T), B1(T) from LDS;        multiply A0 by B0, B1
+//   phase 1: read A1(T), B0(T + 1) from LDS;    multiply A1 by B1, B0
+// (B0(T + 1) is read one phase early, which makes every phase 12 LDS reads and 32 products.)
+// The waves of a SIMD run half a phase apart: while one reads, the other multiplies; a barrier
+// ends each half phase.  A part's LDS slot is free once both wave groups have read it, so its
+// next load goes out a phase later, after that phase's LDS reads (before them the LDS reads
+// wait behind the loads' issue: 2.70 against 2.91 POP/s raw at 8192^3), and is waited for two
+// phases after that, just before the barrier in front of its first reader.
+//
+// What bounds it: the power limit.  On operands of zeros the loop runs at 4.34 POP/s (88 % of
+// the 4.95 of a loop of products alone), on random ones at 2.91, where products alone reach
+// 4.05 (3.35 with 32 x 32 x 32 products, whose accumulators move twice as often).
+//
+// A block walks its share of the (modulus, tile) list as one stream of k-tiles: the loads run
+// two k-tiles ahead across products, tiles and moduli, so nothing drains between tiles.  At
+// the end of a product the two accumulator halves are folded (or reduced and stored) in the
+// read halves of the next two phases, beside the other group's multiplies.
+// lambdas of the kernel: inlined whatever their size (their captures live in registers)
+#define OZ2H_INL __attribute__((always_inline))
+template <int MODE>
+__global__ __launch_bounds__(512, 2) void k_resgemm8(Gemm8Args) {
+    // The arguments are read where they are used, mostly between products, through a pointer
+    // the compiler cannot see behind: kept in registers they and what follows from them would
+    // spill (the k-loop holds 230 of 256 vector registers).
+    typedef const __attribute__((address_space(4))) Gemm8Args cargs;
+    auto kargs = []() OZ2H_INL {
+        cargs *p = (cargs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return p;
+    };
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 2, wc = wave & 3;
+    const int kpad = (int)kargs()->g.kpad;
+    const int nk = kpad / TBK;
+
+    // item: tile u of modulus L - 1 - zi; a block's items go on by its XCD's (or the whole)
+    // number of blocks.  All of it is uniform and kept in scalar registers.
+    struct Item {
+        uint32_t zi, u;
+    };
+    auto uni = [](uint32_t v) OZ2H_INL { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+    auto unip = [&](const int8_t *p) OZ2H_INL {
+        const uint64_t v = (uint64_t)p;
+        return (const int8_t *)(((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v));
+    };
+    auto step = [&](Item it, uint32_t by) OZ2H_INL {
+        cargs *ka = kargs();
+        const uint32_t t8 = ka->xm.on ? ka->xm.h * ka->xm.w : (uint32_t)(ka->tm * ka->tn);
+        const uint32_t u = it.u + by, q = uni(u / t8);
+        return Item{uni(it.zi + q), uni(u - q * t8)};
+    };
+    auto next = [&](Item it) OZ2H_INL { return step(it, kargs()->xm.on ? gridDim.x >> 3 : gridDim.x); };
+    auto tile_of = [&](Item it, int &mt, int &nt) OZ2H_INL {
+        cargs *ka = kargs();
+        const uint32_t on = ka->xm.on, x8 = blockIdx.x & 7u, cols = on ? ka->xm.w : (uint32_t)ka->tn;
+        const uint32_t r = uni(it.u / cols), c = it.u - r * cols, q = uni(x8 / ka->xm.rx);
+        mt = (int)uni(on ? q * ka->xm.h + r : r);
+        nt = (int)uni(on ? (x8 - q * ka->xm.rx) * ka->xm.w + c : c);
+    };
+    Item item = step(Item{0, 0}, kargs()->xm.on ? blockIdx.x >> 3 : blockIdx.x);
+    if (item.zi >= (uint32_t)kargs()->L) return;   // no work: the whole block leaves
+
+    // loads: load i of wave w fills LDS rows 64 i + 8 w .. + 7 of a part (lane -> row lane / 8,
+    // physical chunk lane % 8); row R of part Bh is column 64 (R / 32) + 32 h + R % 32
+    uint32_t va[2], vb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int R = 64 * i + 8 * wave + (lane >> 3);
+        va[i] = (uint32_t)(R * kpad) + (((lane & 7) ^ lds_swz(R)) << 4);
+        vb[i] = (uint32_t)(((R >> 5) * 64 + (R & 31)) * kpad) + (((lane & 7) ^ lds_swz_b(R)) << 4);
+    }
+    // load cursor: the k-tile loaded next (two ahead of the multiplies); the A rows and k
+    // offset of the one before it
+    struct Cursor {
+        Item it;
+        const int8_t *a, *b;   // the product's tile rows and columns in its planes
+        int prods, ko;         // products left in the item (this one included), k offset
+    };
+    auto open = [&](Item it) OZ2H_INL {
+        cargs *ka = kargs();
+        const int l = ka->L - 1 - (int)it.zi, l1 = ka->L1;
+        const int g0 = l < l1 ? l : l1 + 3 * (l - l1);
+        int mt, nt;
+        tile_of(it, mt, nt);
+        return Cursor{it, unip(ka->g.A + g0 * ka->g.a_ps + (int64_t)mt * 256 * kpad),
+                      unip(ka->g.B + g0 * ka->g.b_ps + (int64_t)nt * 256 * kpad), l < l1 ? 1 : 3, 0};
+    };
+    Cursor cur = open(item);
+    const int8_t *pa = cur.a;
+    int pko = 0;
+    auto advance = [&]() OZ2H_INL {   // at the end of the list the last k-tile repeats
+        pa = cur.a;
+        pko = cur.ko;
+        if (cur.ko + TBK < kpad) {
+            cur.ko += TBK;
+        } else if (cur.prods > 1) {
+            cargs *ka = kargs();
+            --cur.prods;
+            cur.ko = 0;
+            cur.a = unip(cur.a + ka->g.a_ps);
+            cur.b = unip(cur.b + ka->g.b_ps);
+        } else {
+            const Item n = next(cur.it);
+            if (n.zi < (uint32_t)kargs()->L) cur = open(n);
+        }
+    };
+    // parts: 0 A0, 1 B0, 2 B1, 3 A1 of the tile rows or columns at p, k offset ko
+    auto issue = [&](auto s_, auto p_, const int8_t *p, int ko) OZ2H_INL {
+        constexpr int S = decltype(s_)::value, P = decltype(p_)::value;
+        int8_t *dst = gemm8_part<S, P>();
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 256 * kpad, 0x00020000);
+        const int so = ko + (P == 3 ? 128 * kpad : P == 2 ? 32 * kpad : 0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (__attribute__((address_space(3))) void *)(dst + (8 * i + wave) * 1024), 16,
+                P == 0 || P == 3 ? va[i] : vb[i], so, 0, 0);
+    };
+
+    v4i acc[2][2][4][2];   // [A half][B group][16-row block][fragment y]
+    auto clear = [&](v4i (&h)[2][4][2]) OZ2H_INL {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) h[c][x][y] = v4i{};
+    };
+    clear(acc[0]);
+    clear(acc[1]);
+
+    v4i fa[4][2], fb0[2][2], fb1[2][2], fb2[2][2];
+    const int fr = lane & 15, frb = (fr >> 2) * 8 + (fr & 3);
+    int foa[2], fob[2][2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        foa[ks] = (wr * 64 + fr) * TBK + (((4 * ks + (lane >> 4)) ^ lds_swz(fr)) << 4);
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+            fob[y][ks] = (wc * 32 + frb + 4 * y) * TBK + (((4 * ks + (lane >> 4)) ^ lds_swz_b(frb + 4 * y)) << 4);
+    }
+    auto read_a = [&](const int8_t *p) OZ2H_INL {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) fa[x][ks] = *(const v4i *)(p + x * 16 * TBK + foa[ks]);
+    };
+    auto read_b = [&](const int8_t *p, v4i (&f)[2][2]) OZ2H_INL {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) f[y][ks] = *(const v4i *)(p + fob[y][ks]);
+    };
+    auto mult = [&](v4i (&c)[4][2], v4i (&f)[2][2]) OZ2H_INL {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    c[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[y][ks], fa[x][ks], c[x][y], 0, 0, 0);
+    };
+    auto fence = [&]() OZ2H_INL {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto barrier = [&]() OZ2H_INL {
+        fence();
+        __builtin_amdgcn_s_barrier();
+        fence();
+    };
+
+    // the product being multiplied
+    auto products = [&](Item it) OZ2H_INL { return kargs()->L - 1 - (int)it.zi < kargs()->L1 ? 1 : 3; };
+    int prod = 0, nprod = products(item);
+
+    // (acc w) mod m, centred: x w is exact (x < 2^31, w < 2^13) and x (w / m) off by less than
+    // 2^-20, which is inside 1 / (2 m), the least distance of the quotient from a half-integer
+    // for odd m (for m = 128 it is exact); added to 1.5 2^52 the residue is in the low word
+    constexpr double kMagic = 6755399441055744.0;
+    // the end of a product for one accumulator half (rows 128 H ..): folded in place, or after
+    // the last product reduced, stored as 16-byte runs of eight columns and cleared
+    auto finish = [&](auto h_) OZ2H_INL {
+        constexpr int H = decltype(h_)::value;
+        v4i (&h)[2][4][2] = acc[H];
+        cargs *ka = kargs();
+        const int l = ka->L - 1 - (int)item.zi;
+        typedef const __attribute__((address_space(4))) ModInfo cinfo;
+        cinfo *mi = (cinfo *)ka->g.mi + l;
+        const double md = (double)mi->m, inv_m = mi->inv_m;
+        const double w = (double)mi->kc[prod], wi = w * inv_m;
+        auto residue = [&](int32_t a) OZ2H_INL {
+            const double x = (double)a;
+            const double q = rint(x * wi);
+            return (int32_t)(uint32_t)__builtin_bit_cast(uint64_t, fma(-q, md, fma(x, w, kMagic)));
+        };
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) h[c][x][y][e] = residue(h[c][x][y][e]);
+                __builtin_amdgcn_sched_barrier(0);   // eight at a time: few registers
+            }
+        if (prod + 1 < nprod) return;
+        int mt, nt, ln = lane;
+        asm volatile("" : "+v"(ln));   // nothing of this address lives through the k-loop
+        tile_of(item, mt, nt);
+        const int64_t ldv = ka->g.ldv;
+        int16_t *base = ka->g.V + (int64_t)l * ka->g.v_ps +
+                        ((int64_t)mt * 256 + 128 * H + wr * 64 + (ln & 15)) * ldv + nt * 256 + wc * 64 +
+                        (ln >> 4) * 8;
+        int64_t o2 = 0;
+        if constexpr (MODE == ZGAUSS) o2 = ka->g.V2 - ka->g.V;
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                int16_t *dst = base + (int64_t)(16 * x) * ldv + 32 * c;
+                int32_t r[8];
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) r[4 * y + e] = h[c][x][y][e];
+                auto pack = [&](const int32_t (&t)[8]) OZ2H_INL {
+                    v4i o;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        o[i] = (int)__builtin_amdgcn_perm((uint32_t)t[2 * i + 1], (uint32_t)t[2 * i], 0x05040100u);
+                    return o;
+                };
+                if constexpr (MODE == ZSTORE) {
+                    *(v4i *)dst = pack(r);
+                } else {
+                    const v4i p1 = *(const v4i *)dst;
+                    v4i p2 = v4i{};
+                    if constexpr (MODE == ZGAUSS) p2 = *(const v4i *)(dst + o2);
+                    int32_t s1[8], s2[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int32_t t1 = (int16_t)((uint32_t)p1[i / 2] >> (16 * (i % 2)));
+                        const int32_t t2 = (int16_t)((uint32_t)p2[i / 2] >> (16 * (i % 2)));
+                        if constexpr (MODE == ZADD) s1[i] = centred_mod((double)(t1 + r[i]), md, inv_m);
+                        if constexpr (MODE == ZSUB) s1[i] = centred_mod((double)(t1 - r[i]), md, inv_m);
+                        if constexpr (MODE == ZGAUSS) {
+                            s1[i] = centred_mod((double)(t1 - t2), md, inv_m);
+                            s2[i] = centred_mod((double)(r[i] - t1 - t2), md, inv_m);
+                        }
+                    }
+                    *(v4i *)dst = pack(s1);
+                    if constexpr (MODE == ZGAUSS) *(v4i *)(dst + o2) = pack(s2);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        clear(h);
+    };
+    // vector-memory operations issued after the loads a phase waits for: the loads of two
+    // phases, and the stores of a half (8) where an item ended: in this phase, in the phase
+    // before it, or (their loads came first) a k-tile ago.  Fewer is always safe.
+    constexpr int kSt = MODE == ZSTORE ? 8 : 0;
+    auto half_end = [&](int stores) OZ2H_INL {   // 0, 1 or 2 halves' stores among them
+        fence();
+        if (stores == 2) __builtin_amdgcn_s_waitcnt(vmlgkm_imm(8 + 2 * kSt));
+        else if (stores == 1) __builtin_amdgcn_s_waitcnt(vmlgkm_imm(8 + kSt));
+        else __builtin_amdgcn_s_waitcnt(vmlgkm_imm(8));
+        barrier();
+    };
+
+    // prologue: in the order the k-loop would have issued them
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    issue(I0{}, I1{}, cur.b, 0);
+    issue(I0{}, I0{}, cur.a, 0);
+    issue(I0{}, I2{}, cur.b, 0);
+    advance();
+    issue(I0{}, I3{}, pa, pko);
+    issue(I1{}, I1{}, cur.b, cur.ko);
+    issue(I1{}, I0{}, cur.a, cur.ko);
+    issue(I1{}, I2{}, cur.b, cur.ko);
+    advance();   // pa: k-tile 1, cur: k-tile 2
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+    barrier();
+    read_b(gemm8_part<0, 1>(), fb0);
+    half_end(0);
+    if (wr == 1) barrier();   // the second wave group runs half a phase behind
+
+    // One k-tile in stage S; pa / cur are k-tiles T + 1 / T + 2.  LAST: the product's last one,
+    // whose lower half is finished before phase 1's reads (their registers are free then).
+    // st0, st1: halves whose stores the waits of phase 0 and 1 may leave behind.
+    int st0 = 0, st1 = 0;
+    auto ktile = [&](auto s_, auto last_) OZ2H_INL {
+        constexpr int S = decltype(s_)::value;
+        constexpr bool LAST = decltype(last_)::value != 0;
+        using SN = std::integral_constant<int, S ^ 1>;
+        v4i (&fc)[2][2] = S ? fb2 : fb0;
+        v4i (&fn)[2][2] = S ? fb0 : fb2;
+        // phase 0
+        read_b(gemm8_part<S, 2>(), fb1);
+        read_a(gemm8_part<S, 0>());
+        fence();
+        issue(SN{}, I3{}, pa, pko);
+        issue(s_, I1{}, cur.b, cur.ko);
+        half_end(st0);
+        st0 = st1 ? 1 : 0;   // a k-tile after an item's end: the upper half's stores remain
+        mult(acc[0][0], fc);
+        mult(acc[0][1], fb1);
+        barrier();
+        // phase 1
+        if constexpr (LAST) {
+            finish(I0{});
+            if (prod + 1 == nprod && !st1) st1 = 1;
+            fence();
+        }
+        read_a(gemm8_part<S, 3>());
+        read_b(gemm8_part<S ^ 1, 1>(), fn);
+        fence();
+        issue(s_, I0{}, cur.a, cur.ko);
+        issue(s_, I2{}, cur.b, cur.ko);
+        advance();
+        half_end(st1);
+        st1 = 0;
+        mult(acc[1][1], fb1);
+        mult(acc[1][0], fc);
+        barrier();
+    };
+    // products one after the other; the k-tiles of each are even in number, so that it starts
+    // in stage 0.  Its upper half is finished before the next product's first reads.
+    for (;;) {
+        for (int k = 2; k < nk; k += 2) {
+            ktile(I0{}, I0{});
+            ktile(I1{}, I0{});
+        }
+        ktile(I0{}, I0{});
+        ktile(I1{}, I1{});
+        finish(I1{});
+        if (++prod == nprod) {
+            st0 = st1 = 2;
+            prod = 0;
+            item = next(item);
+            nprod = products(item);
+            if (item.zi >= (uint32_t)kargs()->L) break;
+        }
+        fence();
+    }
+    if (wr == 0) barrier();
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no load still writing LDS past the block's end
+}
+
 // Residue planes of a sum of two operands (3M: Ar + Ai, Br + Bi) from the planes of
 // each: per modulus l, s = x + y reduced to the centred residue s - rint(s/m) m (the
 // quotient in fp32 is exact: |s| <= m + 3 < 2^15 and s/m is at least 1/(2m) from a
