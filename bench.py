@@ -215,7 +215,7 @@ def kernel_names(plan, flags):
     if (flags & oz2h.FLAG_RESIDUES_MMA) and plan.nw32 >= 8:
         res = "k_residues_mma"
     else:
-        res = "k_residues_row" if plan.nw32 >= 32 else "k_residues"
+        res = "k_residues_row" if plan.nw32 >= 24 else "k_residues"
     if (flags & oz2h.FLAG_CRT_MMA) and 16 <= plan.nd32 <= 32 and plan.L <= 127:
         crt = "k_crt_mma"
     else:

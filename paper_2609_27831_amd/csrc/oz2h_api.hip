@@ -32,7 +32,8 @@ struct oz2h_plan {
     ModInfo *d_info = nullptr;
     double *d_resid = nullptr;
     double *d_resid_row = nullptr;
-    ResGroup *d_rgrp = nullptr;
+    ResRowUnit *d_rrunits = nullptr;
+    ResUnitGroup *d_rgrp = nullptr;
     int8_t *d_rmma_w = nullptr;
     ResRowBlock *d_rmma_rb = nullptr;
     int8_t *d_crt_afr = nullptr;
@@ -211,86 +212,90 @@ int launch_exponents(int64_t rows, int64_t count, const int8_t *sign, const int3
     return check_launch("exponent scan");
 }
 
-int launch_residues(const oz2h_plan *pl, int64_t rows, int64_t count, const uint64_t *limbs,
-                    const int32_t *exp, const int8_t *sign, int64_t rs, int64_t cs,
-                    const int32_t *erow, int64_t rpad, int64_t kpad, int8_t *planes,
-                    hipStream_t s, int t = -1, const int32_t *koff = nullptr) {
+// one operand side of stage 2: planes of rpad x kpad bytes; koff (nullable): per-contraction
+// exponent offsets
+ResSide res_side(int64_t rows, int64_t count, const uint64_t *limbs, const int32_t *exp, const int8_t *sign,
+                 int64_t rs, int64_t cs, const int32_t *erow, int64_t rpad, int64_t kpad, int8_t *planes,
+                 const int32_t *koff = nullptr) {
+    return ResSide{limbs, exp, sign, rs, cs, rows, count, kpad, rpad * kpad, erow, koff, planes};
+}
+
+// stage 2 of one or two operand sides (n), integers of width t (-1: the plan's)
+int launch_residues(const oz2h_plan *pl, const ResSide *sides, int n, hipStream_t s, int t = -1) {
     const PlanHost &h = pl->h;
     if (t < 0) t = h.t;
     const int nl = (h.p + 63) / 64;
-    const int64_t ps = rpad * kpad;
+    auto rpad = [](const ResSide &d) { return d.plane_stride / d.kpad; };
     if ((h.flags & OZ2H_FLAG_RESIDUES_MMA) && h.nw32 >= kResMmaMinWords) {
         // matrix-core residues: waves of 64 entries, as many per block as fit 64 KiB
         const size_t wl = (size_t)res_mma_wave_lds(h.rnq);
         const int rbm = 4 * wl <= 65536 ? 4 : (2 * wl <= 65536 ? 2 : 1);
         const int kw = res_waves_k(rbm);
-        const int64_t nblk = (kpad / (64 * kw)) * (rpad / (rbm / kw));
-        if (nblk > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
-        const dim3 grid((unsigned)nblk);
-        const ResMmaArgs a{limbs, exp, sign, rs, cs, rows, count, kpad, ps, erow, koff,
-                           h.p, nl, t, h.nw32, h.rnq, h.rnrb, res_mma_es(h.rnq),
-                           pl->d_rmma_w, pl->d_rmma_rb, planes};
+        if (h.rnq > kResMmaMaxQ)
+            return fail(OZ2H_ERANGE, "residues: integers of %d words exceed the kernel's k-steps", h.nw32);
+        for (int i = 0; i < n; ++i) {
+            const ResSide &d = sides[i];
+            const int64_t nblk = (d.kpad / (64 * kw)) * (rpad(d) / (rbm / kw));
+            if (nblk > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
+            const dim3 grid((unsigned)nblk);
+            const ResMmaArgs a{d.limbs, d.exps, d.signs, d.rs, d.cs, d.rows, d.count, d.kpad, d.plane_stride,
+                               d.erow, d.koff, h.p, nl, t, h.nw32, h.rnq, h.rnrb, res_mma_es(h.rnq),
+                               pl->d_rmma_w, pl->d_rmma_rb, d.planes};
 #define OZ2H_RES_MMA(NQ)                                                             \
     do {                                                                             \
         if (rbm == 4) k_residues_mma<4, NQ><<<grid, 256, 4 * wl, s>>>(a);            \
         else if (rbm == 2) k_residues_mma<2, NQ><<<grid, 128, 2 * wl, s>>>(a);       \
         else k_residues_mma<1, NQ><<<grid, 64, wl, s>>>(a);                          \
     } while (0)
-        if (h.rnq <= 2) OZ2H_RES_MMA(2);
-        else if (h.rnq <= 4) OZ2H_RES_MMA(4);
-        else if (h.rnq <= 8) OZ2H_RES_MMA(8);
-        else if (h.rnq <= 12) OZ2H_RES_MMA(12);
-        else if (h.rnq <= kResMmaMaxQ) OZ2H_RES_MMA(kResMmaMaxQ);
-        else return fail(OZ2H_ERANGE, "residues: integers of %d words exceed the kernel's k-steps", h.nw32);
+            if (h.rnq <= 2) OZ2H_RES_MMA(2);
+            else if (h.rnq <= 4) OZ2H_RES_MMA(4);
+            else if (h.rnq <= 8) OZ2H_RES_MMA(8);
+            else if (h.rnq <= 12) OZ2H_RES_MMA(12);
+            else OZ2H_RES_MMA(kResMmaMaxQ);
 #undef OZ2H_RES_MMA
+        }
         return check_launch("residues");
     }
-    if (h.nw32 >= kResRowMinWords && res_row_lds(h.rnwp) <= 65536) {
+    if (h.nw32 > kResMaxWords) {
         // VALU kernel with row broadcasts: blocks of 128 entries of one row
-        const int64_t nblk = (kpad / 128) * rpad;
-        if (nblk > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
-        const ResRowArgs a{limbs, exp, sign, rs, cs, rows, count, kpad, ps, erow, koff,
-                           h.p, nl, t, h.nw32, h.rnwp, h.L, h.rg16, pl->d_resid_row, pl->d_info, planes};
-        k_residues_row<<<dim3((unsigned)nblk), 256, res_row_lds(h.rnwp), s>>>(a);
+        if (res_row_lds(h.rnwp) > 65536)
+            return fail(OZ2H_ERANGE, "residues: integers of %d words exceed the kernel's LDS", h.nw32);
+        for (int i = 0; i < n; ++i) {
+            const ResSide &d = sides[i];
+            const int64_t nblk = (d.kpad / 128) * rpad(d);
+            if (nblk > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
+            const ResRowArgs a{d, h.p, nl, t, h.rnw, h.rnwp, h.rg16, pl->d_resid_row, pl->d_rrunits};
+            k_residues_row<<<dim3((unsigned)nblk), 256, res_row_lds(h.rnwp), s>>>(a);
+        }
         return check_launch("residues");
     }
-    // entry-per-thread VALU kernel, word columns <= 64 KiB per block
-    const int rb = h.nw32 <= 64 ? 4 : (h.nw32 <= 128 ? 2 : 1);
-    const int kw = res_waves_k(rb);
-    const int64_t nblk = (kpad / (64 * kw)) * (rpad / (rb / kw));
-    if (nblk > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
-    const dim3 grid((unsigned)nblk);
-    const size_t lds = (size_t)h.nw32 * 64 * rb * sizeof(uint32_t);
-    const ResArgs a{limbs, exp, sign, rs, cs, rows, count, kpad, ps, erow, h.p, nl, t, h.nw32,
-                    pl->d_resid, pl->d_rgrp, h.L, h.lgroups, planes, koff};
-    // integers of at most kResRegWords words keep them in registers (one instantiation per
-    // word count)
-#define OZ2H_RES_NW(KG, NW) k_residues<4, KG, 1, NW><<<grid, 256, lds, s>>>(a)
-#define OZ2H_RES(KG)                                                                   \
-    do {                                                                               \
-        if (rb == 4 && h.nw32 <= kResRegWords) {                                       \
-            switch (h.nw32) {                                                          \
-                case 1: OZ2H_RES_NW(KG, 1); break;                                     \
-                case 2: OZ2H_RES_NW(KG, 2); break;                                     \
-                case 3: OZ2H_RES_NW(KG, 3); break;                                     \
-                case 4: OZ2H_RES_NW(KG, 4); break;                                     \
-                case 5: OZ2H_RES_NW(KG, 5); break;                                     \
-                case 6: OZ2H_RES_NW(KG, 6); break;                                     \
-                case 7: OZ2H_RES_NW(KG, 7); break;                                     \
-                case 8: OZ2H_RES_NW(KG, 8); break;                                     \
-                case 9: OZ2H_RES_NW(KG, 9); break;                                     \
-                case 10: OZ2H_RES_NW(KG, 10); break;                                     \
-                case 11: OZ2H_RES_NW(KG, 11); break;                                     \
-                default: OZ2H_RES_NW(KG, 12); break;                                   \
-            }                                                                          \
-        } else if (rb == 4) k_residues<4, KG, 1><<<grid, 256, lds, s>>>(a);            \
-        else if (rb == 2) k_residues<2, KG, 1><<<grid, 128, lds, s>>>(a);              \
-        else k_residues<1, KG, 1><<<grid, 64, lds, s>>>(a);                            \
-    } while (0)
-    if (h.kg == kModGroupWide) OZ2H_RES(kModGroupWide);
-    else OZ2H_RES(kModGroup);
-#undef OZ2H_RES
+    // entry kernel: both sides in one launch
+    int64_t nblk[2] = {0, 0};
+    for (int i = 0; i < n; ++i) nblk[i] = (sides[i].kpad / 128) * (rpad(sides[i]) / res_block_rows(h.nw32));
+    if (nblk[0] + nblk[1] > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
+    const ResArgs a{{sides[0], sides[n - 1]}, nblk[0],
+                    {pl->d_resid, pl->d_rgrp, h.p, nl, t, h.nw32, h.rgroups}};
+    const dim3 grid((unsigned)(nblk[0] + nblk[1]));
+    const size_t lds = res_wave_lds(h.nw32) * kResWaves;
+#define OZ2H_RES_NW(NW) case NW: k_residues<NW><<<grid, 64 * kResWaves, lds, s>>>(a); break
+    switch (h.nw32) {
+        OZ2H_RES_NW(1);
+        OZ2H_RES_NW(2);
+        OZ2H_RES_NW(3);
+        OZ2H_RES_NW(4);
+        OZ2H_RES_NW(5);
+        OZ2H_RES_NW(6);
+        OZ2H_RES_NW(7);
+        OZ2H_RES_NW(8);
+        OZ2H_RES_NW(9);
+        OZ2H_RES_NW(10);
+        OZ2H_RES_NW(11);
+        OZ2H_RES_NW(12);
+        default: k_residues<0><<<grid, 64 * kResWaves, lds, s>>>(a);
+    }
 #undef OZ2H_RES_NW
+    static_assert(kResRegWords == 12, "one case per word count");
+    static_assert(res_wave_lds(kResMaxWords) * kResWaves <= 65536, "LDS of the widest block");
     return check_launch("residues");
 }
 
@@ -529,7 +534,10 @@ int upload_plan(oz2h_plan *pl) {
     off = align_up(off + n_res);
     const size_t o_rrow = off;
     off = align_up(off + n_rrow);
-    const size_t n_rg = sizeof(ResGroup) * h.resgrp.size();
+    const size_t n_rru = sizeof(ResRowUnit) * h.resrow_units.size();
+    const size_t o_rru = off;
+    off = align_up(off + n_rru);
+    const size_t n_rg = sizeof(ResUnitGroup) * h.resgrp.size();
     const size_t o_rg = off;
     off = align_up(off + n_rg);
     const size_t n_rw = h.rmma_w.size(), n_rrb = sizeof(ResRowBlock) * h.rmma_rb.size();
@@ -560,7 +568,9 @@ int upload_plan(oz2h_plan *pl) {
     pl->d_info = (ModInfo *)(b + o_info);
     pl->d_resid = (double *)(b + o_res);
     pl->d_resid_row = (double *)(b + o_rrow);
-    pl->d_rgrp = (ResGroup *)(b + o_rg);
+    pl->d_rrunits = (ResRowUnit *)(b + o_rru);
+    if (n_rru) OZ2H_HIP(hipMemcpy(pl->d_rrunits, h.resrow_units.data(), n_rru, hipMemcpyHostToDevice));
+    pl->d_rgrp = (ResUnitGroup *)(b + o_rg);
     pl->d_rmma_w = (int8_t *)(b + o_rw);
     pl->d_rmma_rb = (ResRowBlock *)(b + o_rrb);
     pl->d_crt_afr = (int8_t *)(b + o_cafr);
@@ -707,10 +717,11 @@ int run_pipeline_f64(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_
         (st = launch_exponents(N, K, B.sign, B.exp, b_rs, b_cs, nullptr, f, s)))
         return st;
     if (ev) OZ2H_HIP(hipEventRecord(ev[1], s));
-    if (pl->i8 &&
-        ((st = launch_residues(pl->i8, M, K, A.limbs, A.exp, A.sign, a_rs, a_cs, e, w.mpad, w.kpad, a8, s)) ||
-         (st = launch_residues(pl->i8, N, K, B.limbs, B.exp, B.sign, b_rs, b_cs, f, w.npad, w.kpad, b8, s))))
-        return st;
+    if (pl->i8) {
+        const ResSide sd[2] = {res_side(M, K, A.limbs, A.exp, A.sign, a_rs, a_cs, e, w.mpad, w.kpad, a8),
+                               res_side(N, K, B.limbs, B.exp, B.sign, b_rs, b_cs, f, w.npad, w.kpad, b8)};
+        if ((st = launch_residues(pl->i8, sd, 2, s))) return st;
+    }
     if ((st = launch_residues_f64(pl, M, K, A.limbs, A.exp, A.sign, a_rs, a_cs, e, w.mpad, w.kpad, af, s)) ||
         (st = launch_residues_f64(pl, N, K, B.limbs, B.exp, B.sign, b_rs, b_cs, f, w.npad, w.kpad, bf, s)))
         return st;
@@ -808,10 +819,13 @@ int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op o
     if (!ca && (st = launch_exponents(M, K, A.sign, A.exp, a_rs, a_cs, nullptr, e, s))) return st;
     if (!cb && (st = launch_exponents(N, K, B.sign, B.exp, b_rs, b_cs, nullptr, f, s))) return st;
     if (ev) OZ2H_HIP(hipEventRecord(ev[1], s));
-    if (!ca && (st = launch_residues(pl, M, K, A.limbs, A.exp, A.sign, a_rs, a_cs, e, w.mpad, w.kpad, ap, s)))
-        return st;
-    if (!cb && (st = launch_residues(pl, N, K, B.limbs, B.exp, B.sign, b_rs, b_cs, f, w.npad, w.kpad, bp, s)))
-        return st;
+    {
+        ResSide sd[2];
+        int n = 0;
+        if (!ca) sd[n++] = res_side(M, K, A.limbs, A.exp, A.sign, a_rs, a_cs, e, w.mpad, w.kpad, ap);
+        if (!cb) sd[n++] = res_side(N, K, B.limbs, B.exp, B.sign, b_rs, b_cs, f, w.npad, w.kpad, bp);
+        if (n && (st = launch_residues(pl, sd, n, s))) return st;
+    }
     if (ev) OZ2H_HIP(hipEventRecord(ev[2], s));
     if ((st = launch_resgemm(pl, w.cfg, w.mpad, w.npad, w.kpad, apc, bpc, u, s, a_ps, b_ps))) return st;
     if (ev) OZ2H_HIP(hipEventRecord(ev[3], s));
@@ -1163,8 +1177,8 @@ int oz2h_residues_create(const oz2h_plan *plan, int32_t side, int64_t rows, oz2h
     r->planes = (int8_t *)r->dbuf + off_p;
     const int64_t rs = rows_first ? X.ld : 1, cs = rows_first ? 1 : X.ld;
     st = launch_exponents(rows, K, X.sign, X.exp, rs, cs, nullptr, r->e, stream);
-    if (!st) st = launch_residues(plan, rows, K, X.limbs, X.exp, X.sign, rs, cs, r->e, r->rpad, r->kpad,
-                                  r->planes, stream);
+    const ResSide sd = res_side(rows, K, X.limbs, X.exp, X.sign, rs, cs, r->e, r->rpad, r->kpad, r->planes);
+    if (!st) st = launch_residues(plan, &sd, 1, stream);
     if (st) {
         (void)hipFree(r->dbuf);
         return st;
@@ -1364,11 +1378,11 @@ int oz2h_zgemm(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N, int6
     if ((st = launch_exponents2(M, K, Ar, Ai, a_rs, a_cs, ai_rs, ai_cs, e, s))) return st;
     if ((st = launch_exponents2(N, K, Br, Bi, b_rs, b_cs, bi_rs, bi_cs, f, s))) return st;
     // stage 2: the residue planes of each part at those exponents
-    if ((st = launch_residues(plan, M, K, Ar.limbs, Ar.exp, Ar.sign, a_rs, a_cs, e, w.mpad, w.kpad, ap[0], s)) ||
-        (st = launch_residues(plan, M, K, Ai.limbs, Ai.exp, Ai.sign, ai_rs, ai_cs, e, w.mpad, w.kpad, ap[1], s)) ||
-        (st = launch_residues(plan, N, K, Br.limbs, Br.exp, Br.sign, b_rs, b_cs, f, w.npad, w.kpad, bp[0], s)) ||
-        (st = launch_residues(plan, N, K, Bi.limbs, Bi.exp, Bi.sign, bi_rs, bi_cs, f, w.npad, w.kpad, bp[1], s)))
-        return st;
+    const ResSide sa[2] = {res_side(M, K, Ar.limbs, Ar.exp, Ar.sign, a_rs, a_cs, e, w.mpad, w.kpad, ap[0]),
+                           res_side(M, K, Ai.limbs, Ai.exp, Ai.sign, ai_rs, ai_cs, e, w.mpad, w.kpad, ap[1])};
+    const ResSide sb[2] = {res_side(N, K, Br.limbs, Br.exp, Br.sign, b_rs, b_cs, f, w.npad, w.kpad, bp[0]),
+                           res_side(N, K, Bi.limbs, Bi.exp, Bi.sign, bi_rs, bi_cs, f, w.npad, w.kpad, bp[1])};
+    if ((st = launch_residues(plan, sa, 2, s)) || (st = launch_residues(plan, sb, 2, s))) return st;
     // stage 3: Re = Ar Br - Ai Bi and Im = Ar Bi + Ai Br, combined mod m_l
     const auto gemm = [&](int ia, int ib, int16_t *v, int16_t *v2, int mode) {
         return launch_resgemm_z(plan, w.cfg, w.mpad, w.npad, w.kpad, ap[ia], bp[ib], v, v2, mode, s);
@@ -1601,9 +1615,8 @@ int oz2h_gemm_backward(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, c
         int8_t *lp = (int8_t *)(wb + b.off_l[0]), *rp = (int8_t *)(wb + b.off_r[0]);
         int16_t *v = (int16_t *)(wb + b.off_v[0]);
         if ((st = launch_exponents(M, N, W.sign, W.exp, W.ld, 1, fc, hx, stream))) return st;
-        if ((st = launch_residues(plan, M, N, W.limbs, W.exp, W.sign, W.ld, 1, hx, b.mpad[0],
-                                  b.kpad[0], lp, stream, h.tw[0], fc)))
-            return st;
+        const ResSide sd = res_side(M, N, W.limbs, W.exp, W.sign, W.ld, 1, hx, b.mpad[0], b.kpad[0], lp, fc);
+        if ((st = launch_residues(plan, &sd, 1, stream, h.tw[0]))) return st;
         if ((st = launch_plane_transpose(bh, N, K, f.kpad, f.npad * f.kpad, rp, b.kpad[0],
                                          b.npad[0], h.G, stream)))
             return st;
@@ -1619,9 +1632,8 @@ int oz2h_gemm_backward(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, c
         int8_t *lp = (int8_t *)(wb + b.off_l[1]), *rp = (int8_t *)(wb + b.off_r[1]);
         int16_t *v = (int16_t *)(wb + b.off_v[1]);
         if ((st = launch_exponents(N, M, W.sign, W.exp, 1, W.ld, e, gx, stream))) return st;
-        if ((st = launch_residues(plan, N, M, W.limbs, W.exp, W.sign, 1, W.ld, gx, b.npad[1],
-                                  b.kpad[1], rp, stream, h.tw[1], e)))
-            return st;
+        const ResSide sd = res_side(N, M, W.limbs, W.exp, W.sign, 1, W.ld, gx, b.npad[1], b.kpad[1], rp, e);
+        if ((st = launch_residues(plan, &sd, 1, stream, h.tw[1]))) return st;
         if ((st = launch_plane_transpose(ah, M, K, f.kpad, f.mpad * f.kpad, lp, b.kpad[1],
                                          b.mpad[1], h.G, stream)))
             return st;
@@ -1715,8 +1727,8 @@ int oz2h_residues(const oz2h_plan *plan, int64_t rows, int64_t count, const uint
         return fail(OZ2H_EINVAL, "rpad must be a positive multiple of 128 >= rows, kpad of 128 >= count");
     if (!planes || (rows > 0 && count > 0 && (!limbs || !exp || !sign || !erow)))
         return fail(OZ2H_EINVAL, "NULL pointer");
-    st = launch_residues(plan, rows, count, limbs, exp, sign, rs, cs, erow, rpad, kpad, planes,
-                         stream);
+    const ResSide sd = res_side(rows, count, limbs, exp, sign, rs, cs, erow, rpad, kpad, planes);
+    st = launch_residues(plan, &sd, 1, stream);
     return st ? st : ok();
 }
 
@@ -1804,12 +1816,11 @@ struct BatchCrtClass {
 // products runs as two chunks on two streams: the second chunk's residues beside the first
 // chunk's GEMMs, its GEMMs beside the first chunk's CRT, so that the matrix cores and the
 // vector ALUs of a compute unit work at the same time.
-// residue launch classes: moduli group width (kModGroup, kModGroupWide) x the word count of
-// integers that stay in registers (1 .. kResRegWords, or 0: LDS words)
-constexpr int kResClasses = 2 * (kResRegWords + 1);
-inline int res_class(int kg, int nw32, int rb) {
-    const int nw = rb == 4 && nw32 <= kResRegWords ? nw32 : 0;
-    return (kg == kModGroupWide ? 1 : 0) * (kResRegWords + 1) + nw;
+// residue launch classes: integers of 1 .. kResRegWords words (one instantiation each), wider
+// ones of the entry kernel, and those of the row-broadcast kernel
+constexpr int kResClasses = kResRegWords + 2;
+inline int res_class(int nw32) {
+    return nw32 <= kResRegWords ? nw32 - 1 : nw32 <= kResMaxWords ? kResRegWords : kResRegWords + 1;
 }
 
 struct BatchChunk {
@@ -1817,11 +1828,11 @@ struct BatchChunk {
     Seg *d_fill_segs = nullptr, *d_exp_segs = nullptr;
     int n_fill_segs = 0, n_exp_segs = 0;
     int64_t fill_blocks = 0, exp_blocks = 0;
-    // residues: one launch per class (moduli group width, and the word count of integers
-    // that keep their words in registers: res_class)
+    // residues: one launch per class (res_class)
     Seg *d_res_segs[kResClasses] = {};
     int n_res_segs[kResClasses] = {};
     int64_t res_blocks[kResClasses] = {};
+    size_t res_lds[kResClasses] = {};   // of a block
     std::vector<BatchCrtClass> crt;
     // grouped GEMM: one item list (and launch) per block tile class c = oz2h_tile - 1
     GemmItem *d_items[3] = {nullptr, nullptr, nullptr};
@@ -1839,8 +1850,6 @@ struct oz2h_batched_plan {
     void *dbuf = nullptr;
     ProbDev *d_probs = nullptr;
     std::vector<BatchChunk> chunks;
-    int res_rb = 4;
-    size_t res_lds = 0;
     // grouped GEMM: tile setting (OZ2H_TILE_AUTO: each product in the class a plain call
     // would choose for it) and resident blocks per compute unit (0: one block per item)
     int tile = OZ2H_TILE_128x128;
@@ -2051,34 +2060,29 @@ int launch_batched_front(oz2h_batched_plan *bp, const BatchChunk &ch, char *ws, 
         const unsigned nb = (unsigned)ch.res_blocks[c];
         const Seg *sg = ch.d_res_segs[c];
         const int ns = ch.n_res_segs[c];
-        const int nw = c % (kResRegWords + 1);
-#define OZ2H_GRES_NW(KG, NW) k_residues_grouped<4, KG, NW><<<nb, 256, bp->res_lds, s>>>(bp->d_probs, sg, ns, ws)
-#define OZ2H_GRES(KG)                                                                             \
-    do {                                                                                          \
-        switch (nw) {                                                                             \
-            case 1: OZ2H_GRES_NW(KG, 1); break;                                                   \
-            case 2: OZ2H_GRES_NW(KG, 2); break;                                                   \
-            case 3: OZ2H_GRES_NW(KG, 3); break;                                                   \
-            case 4: OZ2H_GRES_NW(KG, 4); break;                                                   \
-            case 5: OZ2H_GRES_NW(KG, 5); break;                                                   \
-            case 6: OZ2H_GRES_NW(KG, 6); break;                                                   \
-            case 7: OZ2H_GRES_NW(KG, 7); break;                                                   \
-            case 8: OZ2H_GRES_NW(KG, 8); break;                                                   \
-            case 9: OZ2H_GRES_NW(KG, 9); break;                                                   \
-            case 10: OZ2H_GRES_NW(KG, 10); break;                                                   \
-            case 11: OZ2H_GRES_NW(KG, 11); break;                                                   \
-            case 12: OZ2H_GRES_NW(KG, 12); break;                                                   \
-            default:                                                                              \
-                if (bp->res_rb == 4) k_residues_grouped<4, KG><<<nb, 256, bp->res_lds, s>>>(bp->d_probs, sg, ns, ws); \
-                else if (bp->res_rb == 2) k_residues_grouped<2, KG><<<nb, 128, bp->res_lds, s>>>(bp->d_probs, sg, ns, ws); \
-                else k_residues_grouped<1, KG><<<nb, 64, bp->res_lds, s>>>(bp->d_probs, sg, ns, ws); \
-        }                                                                                         \
-    } while (0)
-        static_assert(kResRegWords == 12, "one case per word count");
-        if (c / (kResRegWords + 1) == 0) OZ2H_GRES(kModGroup);
-        else OZ2H_GRES(kModGroupWide);
-#undef OZ2H_GRES
+        const size_t lds = ch.res_lds[c];
+#define OZ2H_GRES_NW(NW) \
+    case NW - 1: k_residues_grouped<NW><<<nb, 64 * kResWaves, lds, s>>>(bp->d_probs, sg, ns, ws); break
+        switch (c) {
+            OZ2H_GRES_NW(1);
+            OZ2H_GRES_NW(2);
+            OZ2H_GRES_NW(3);
+            OZ2H_GRES_NW(4);
+            OZ2H_GRES_NW(5);
+            OZ2H_GRES_NW(6);
+            OZ2H_GRES_NW(7);
+            OZ2H_GRES_NW(8);
+            OZ2H_GRES_NW(9);
+            OZ2H_GRES_NW(10);
+            OZ2H_GRES_NW(11);
+            OZ2H_GRES_NW(12);
+            case kResRegWords:
+                k_residues_grouped<0><<<nb, 64 * kResWaves, lds, s>>>(bp->d_probs, sg, ns, ws);
+                break;
+            default: k_residues_row_grouped<<<nb, 256, lds, s>>>(bp->d_probs, sg, ns, ws);
+        }
 #undef OZ2H_GRES_NW
+        static_assert(kResRegWords == 12, "one case per word count");
         if ((st = check_launch("grouped residues"))) return st;
     }
     return OZ2H_OK;
@@ -2220,7 +2224,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
 
     // device table layout
     size_t off = 0;
-    std::vector<size_t> o_info(count), o_res(count), o_rg(count), o_crt(count), o_pd(count),
+    std::vector<size_t> o_info(count), o_res(count), o_rrow(count), o_rru(count), o_rg(count), o_crt(count), o_pd(count),
         o_phd(count), o_cafr(count);
     for (int b = 0; b < count; ++b) {
         const PlanHost &h = bp->hosts[b];
@@ -2228,8 +2232,12 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         off = align_up(off + sizeof(ModInfo) * h.L);
         o_res[b] = off;
         off = align_up(off + sizeof(double) * h.resid_tab.size());
+        o_rrow[b] = off;
+        off = align_up(off + sizeof(double) * h.resid_row.size());
+        o_rru[b] = off;
+        off = align_up(off + sizeof(ResRowUnit) * h.resrow_units.size());
         o_rg[b] = off;
-        off = align_up(off + sizeof(ResGroup) * h.resgrp.size());
+        off = align_up(off + sizeof(ResUnitGroup) * h.resgrp.size());
         o_crt[b] = off;
         off = align_up(off + sizeof(double) * h.crt_digits.size());
         o_pd[b] = off;
@@ -2271,7 +2279,10 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         P.t = h.t;
         P.nw32 = h.nw32;
         P.L = h.L;
-        P.lgroups = h.lgroups;
+        P.rgroups = h.rgroups;
+        P.nw = h.rnw;
+        P.nwp = h.rnwp;
+        P.rg16 = h.rg16;
         P.G = h.G;
         P.nd32 = h.nd32;
         P.crt_dc = h.crt_dc;
@@ -2315,11 +2326,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
     }
 
     // segment tables per chunk: exponent fill/fix (256 rows per block), exponent scan (row
-    // blocks x contraction chunks, as the plain scan), residues per moduli group width
-    int maxw = 1;
-    for (int b = 0; b < count; ++b) maxw = std::max(maxw, bp->pd[b].nw32);
-    bp->res_rb = maxw <= 64 ? 4 : (maxw <= 128 ? 2 : 1);
-    bp->res_lds = (size_t)maxw * 64 * bp->res_rb * sizeof(uint32_t);
+    // blocks x contraction chunks, as the plain scan), residues per class
     struct ChunkSegs {
         std::vector<Seg> fill, exp, res[kResClasses];
         std::vector<std::vector<Seg>> crt;
@@ -2339,9 +2346,13 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
                 const int64_t nbk = contig ? (P.K + kExpChunk - 1) / kExpChunk : (P.K + kExpRowsK - 1) / kExpRowsK;
                 cs.exp.push_back(Seg{ch.exp_blocks, b, sd, nbr});
                 ch.exp_blocks += nbr * nbk;
-                const int c = res_class(bp->hosts[b].kg, bp->pd[b].nw32, bp->res_rb);
-                const int kw = res_waves_k(bp->res_rb);
-                const int64_t nbx = P.kpad / (64 * kw), nby = P.rpad[sd] / (bp->res_rb / kw);
+                const int c = res_class(P.nw32);
+                const bool row = P.nw32 > kResMaxWords;
+                const int64_t nbx = P.kpad / 128, nby = row ? P.rpad[sd] : P.rpad[sd] / res_block_rows(P.nw32);
+                const size_t lds = row ? res_row_lds(P.nwp) : kResWaves * res_wave_lds(P.nw32);
+                if (lds > 65536)
+                    return fail(OZ2H_ERANGE, "problem %d: integers of %d words exceed the residue kernels", b, P.nw32);
+                ch.res_lds[c] = std::max(ch.res_lds[c], lds);
                 cs.res[c].push_back(Seg{ch.res_blocks[c], b, sd, nbx});
                 ch.res_blocks[c] += nbx * nby;
             }
@@ -2436,7 +2447,9 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         ProbDev &P = bp->pd[b];
         P.mi = (const ModInfo *)(db + o_info[b]);
         P.resid = (const double *)(db + o_res[b]);
-        P.rgrp = (const ResGroup *)(db + o_rg[b]);
+        P.resid_row = (const double *)(db + o_rrow[b]);
+        P.rrunits = (const ResRowUnit *)(db + o_rru[b]);
+        P.rgrp = (const ResUnitGroup *)(db + o_rg[b]);
         P.crt = (const double *)(db + o_crt[b]);
         P.pd = (const uint32_t *)(db + o_pd[b]);
         P.phd = (const uint32_t *)(db + o_phd[b]);
@@ -2448,8 +2461,13 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         if (!h.crt_afr.empty())
             OZ2H_HIP(hipMemcpy(db + o_cafr[b], h.crt_afr.data(), h.crt_afr.size(), hipMemcpyHostToDevice));
         OZ2H_HIP(hipMemcpy(db + o_info[b], h.info.data(), sizeof(ModInfo) * h.L, hipMemcpyHostToDevice));
-        OZ2H_HIP(hipMemcpy(db + o_res[b], h.resid_tab.data(), sizeof(double) * h.resid_tab.size(), hipMemcpyHostToDevice));
-        OZ2H_HIP(hipMemcpy(db + o_rg[b], h.resgrp.data(), sizeof(ResGroup) * h.resgrp.size(), hipMemcpyHostToDevice));
+        if (!h.resid_tab.empty())
+            OZ2H_HIP(hipMemcpy(db + o_res[b], h.resid_tab.data(), sizeof(double) * h.resid_tab.size(), hipMemcpyHostToDevice));
+        if (!h.resid_row.empty()) {
+            OZ2H_HIP(hipMemcpy(db + o_rrow[b], h.resid_row.data(), sizeof(double) * h.resid_row.size(), hipMemcpyHostToDevice));
+            OZ2H_HIP(hipMemcpy(db + o_rru[b], h.resrow_units.data(), sizeof(ResRowUnit) * h.resrow_units.size(), hipMemcpyHostToDevice));
+        }
+        if (!h.resgrp.empty()) OZ2H_HIP(hipMemcpy(db + o_rg[b], h.resgrp.data(), sizeof(ResUnitGroup) * h.resgrp.size(), hipMemcpyHostToDevice));
         OZ2H_HIP(hipMemcpy(db + o_crt[b], h.crt_digits.data(), sizeof(double) * h.crt_digits.size(), hipMemcpyHostToDevice));
         OZ2H_HIP(hipMemcpy(db + o_pd[b], h.p_digits.data(), sizeof(uint32_t) * h.nd32, hipMemcpyHostToDevice));
         OZ2H_HIP(hipMemcpy(db + o_phd[b], h.ph_digits.data(), sizeof(uint32_t) * h.nd32, hipMemcpyHostToDevice));

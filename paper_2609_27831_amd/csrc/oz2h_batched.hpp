@@ -22,11 +22,12 @@ struct ProbDev {
     uint64_t dig_off;     // CRT digit columns in global memory (classes with large nd32)
     int64_t dig_stride;   // entries per digit row there
     int64_t K, kpad;
-    int32_t p, nl, t, nw32, L, lgroups, G;
+    int32_t p, nl, t, nw32, L, rgroups, nw, nwp, rg16, G;
     int32_t nd32, crt_dc, crt_nc, crt_ndpad;
     const ModInfo *mi;
-    const double *resid, *crt;
-    const ResGroup *rgrp;
+    const double *resid, *resid_row, *crt;
+    const ResUnitGroup *rgrp;
+    const ResRowUnit *rrunits;
     const uint32_t *pd, *phd;
     uint64_t *climbs;
     int32_t *cexp;
@@ -103,25 +104,39 @@ __global__ __launch_bounds__(256) void k_exp_scan_grouped(const ProbDev *__restr
     }
 }
 
-__device__ __forceinline__ ResArgs res_args(const ProbDev &P, int side, char *ws) {
-    return ResArgs{P.limbs[side], P.exps[side], P.signs[side], P.rs[side], P.cs[side],
+__device__ __forceinline__ ResSide res_side(const ProbDev &P, int side, char *ws) {
+    return ResSide{P.limbs[side], P.exps[side], P.signs[side], P.rs[side], P.cs[side],
                    P.rows[side], P.K, P.kpad, P.rpad[side] * P.kpad,
-                   (const int32_t *)(ws + P.erow_off[side]), P.p, P.nl, P.t, P.nw32, P.resid,
-                   P.rgrp, P.L, P.lgroups, (int8_t *)(ws + P.planes_off[side]), nullptr};
+                   (const int32_t *)(ws + P.erow_off[side]), nullptr, (int8_t *)(ws + P.planes_off[side])};
 }
 
-// stage 2, grouped: segment (prod, side) is a (kpad / (64 KW)) x (rpad / (RB / KW)) grid of
-// blocks, KW = res_waves_k(RB); one launch per moduli group width KG (the plans' kg)
-template <int RB, int KG, int NW = 0>
-__global__ __launch_bounds__(64 * RB) void k_residues_grouped(const ProbDev *__restrict__ probs,
-                                                              const Seg *__restrict__ segs,
-                                                              int nseg, char *ws) {
-    extern __shared__ uint32_t words[];
+// stage 2, grouped: segment (prod, side) is the plain launch's grid of that side; one launch per
+// word count up to kResRegWords, one for wider integers (NW = 0), one for the row kernel
+template <int NW>
+__global__ __launch_bounds__(64 * kResWaves) void k_residues_grouped(
+    const ProbDev *__restrict__ probs, const Seg *__restrict__ segs, int nseg, char *ws) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t words[];
     const int si = find_seg(segs, nseg, blockIdx.x);
     const Seg sg = segs[si];
+    const ProbDev &P = probs[sg.prod];
     const int64_t lb = (int64_t)blockIdx.x - sg.first;
-    const ResArgs a = res_args(probs[sg.prod], sg.side, ws);
-    residue_block<RB, KG, 1, NW>(a, lb % sg.nbx, lb / sg.nbx, words);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const ResTab tb{P.resid, P.rgrp, P.p, P.nl, P.t, P.nw32, P.rgroups};
+    residue_wave<NW>(res_side(P, sg.side, ws), tb, lb % sg.nbx,
+                     (lb / sg.nbx * kResWaves + wave) * (res_ept(NW ? NW : 31) / 2),
+                     words + wave * (res_wave_lds(NW ? NW : P.nw32) / 4));
+}
+
+__global__ __launch_bounds__(256) void k_residues_row_grouped(const ProbDev *__restrict__ probs,
+                                                              const Seg *__restrict__ segs, int nseg,
+                                                              char *ws) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t smem_rr[];
+    const int si = find_seg(segs, nseg, blockIdx.x);
+    const Seg sg = segs[si];
+    const ProbDev &P = probs[sg.prod];
+    const int64_t lb = (int64_t)blockIdx.x - sg.first;
+    const ResRowArgs a{res_side(P, sg.side, ws), P.p, P.nl, P.t, P.nw, P.nwp, P.rg16, P.resid_row, P.rrunits};
+    residues_row_block(a, lb % sg.nbx, lb / sg.nbx, smem_rr);
 }
 
 // one work item of the grouped GEMM: output tile (mt, nt) of modulus l of product prod

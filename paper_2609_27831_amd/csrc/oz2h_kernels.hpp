@@ -22,6 +22,9 @@
 
 namespace oz2h {
 
+// lambdas of kernels that must be inlined whatever their size (their captures live in registers)
+#define OZ2H_INL __attribute__((always_inline))
+
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
@@ -119,6 +122,7 @@ __global__ void k_exp_fix(int32_t *__restrict__ p, int64_t n) {
 #define OZ2H_G(T) const __attribute__((address_space(1))) T
 typedef __attribute__((address_space(1))) int8_t g_i8;
 typedef __attribute__((address_space(1))) uint32_t g_u32;
+typedef __attribute__((address_space(1))) uint16_t g_u16;
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4u g_v4u;
 
@@ -146,10 +150,11 @@ __device__ __forceinline__ ModInfo load_info(OZ2H_G(ModInfo) *p) {
 // alignbit(m_j, m_{j-1}, 32 - r); for sh < 0 the same pass collects the round bit
 // (position -sh - 1) and the sticky bits below it, and a round-up carries through the
 // words.  A shift below -(32 nd + 2) drops every bit, the round bit included (a^ = 0).
-// The limbs stream through a ring of two registers, loaded two limbs ahead with clamped
-// unconditional loads, so that the loads of one entry overlap.
-__device__ __forceinline__ int build_words(OZ2H_G(uint64_t) *__restrict__ sl, int s, int64_t sh,
-                                           int p, int nw, uint32_t *col, int st) {
+// The significand is read through feed(limb), which calls limb(x) for each limb in turn from
+// the lowest (limbs at and above nlimb may be anything).
+template <class Feed>
+__device__ __forceinline__ int build_words_from(Feed feed, int s, int64_t sh, int p, int nw, uint32_t *col,
+                                                int st) {
     for (int w = 0; w < nw; ++w) col[w * st] = 0u;
     if (s == 0) return 0;
     const int nlimb = (p + 63) >> 6;
@@ -179,21 +184,15 @@ __device__ __forceinline__ int build_words(OZ2H_G(uint64_t) *__restrict__ sl, in
         }
         prev = cur;
     };
-    auto ld = [&](int l) { return sl[min(l, nlimb - 1)]; };
-    uint64_t r0 = ld(0), r1 = ld(1);
-    auto limb = [&](int l, uint64_t &r) {
-        uint64_t x = l < nlimb ? r : 0ull;
+    int l = 0;
+    feed([&](uint64_t x) {
+        if (l >= nlimb) x = 0ull;
         if (l == nlimb - 1) x &= topm;
-        r = ld(l + 2);
         word(2 * l, (uint32_t)x);
         word(2 * l + 1, (uint32_t)(x >> 32));
-    };
-    // limbs 0 .. nlimb - 1, then one more word of zeros for the carry-out of the shift
-    for (int l = 0; l < nlimb; l += 2) {
-        limb(l, r0);
-        limb(l + 1, r1);
-    }
-    word(2 * ((nlimb + 1) & ~1), 0u);
+        ++l;
+    });
+    word(2 * l, 0u);   // one more word of zeros for the carry-out of the shift
     if (rbit && (sticky || (col[0] & 1u))) {   // round half to even: add one
         for (int w = 0; w < nw; ++w) {
             const uint32_t v = col[w * st] + 1u;
@@ -205,31 +204,43 @@ __device__ __forceinline__ int build_words(OZ2H_G(uint64_t) *__restrict__ sl, in
     return nz ? s : 0;
 }
 
-// Residues of a^ (stage 2).  One thread per entry (r, k) of a rows x count
-// operand side; a block covers 64 consecutive k of RB rows, so a wave stores
-// 64 contiguous int8 per plane.  The integer a^ of the entry is built once into
-// an LDS column of 32-bit words; the moduli are then swept in groups of 8 with
-// fp64 FMAs against centred 2^(32 w) mod m weights (every partial sum is an
-// exact integer below 2^53), read with wave-uniform scalar loads.  Reduction:
-// r = a - rint(a/m) m.  The quotient is exact for the odd one-limb moduli (a is
-// below 2^51, so a/m stays 1/(2m) away from a half-integer, farther than the
-// rounding error) and at worst off by one for a two-limb modulus, so |r| <= 127
-// for every one-limb modulus (|r| <= 64 for m = 128, ties included) and
-// |r| <= (m + 3)/2 for a two-limb one, whose balanced base-128 split
-// r = r0 + 128 r1 then has |r0|, |r1|, |r0 + r1| <= 127.  Any representative
-// of a^ mod m within these bounds gives the same exact GEMM result mod m.
-struct ResArgs {
+// The limbs from memory: a ring of two registers, loaded two limbs ahead with clamped
+// unconditional loads, so that the loads of one entry overlap.
+__device__ __forceinline__ int build_words(OZ2H_G(uint64_t) *__restrict__ sl, int s, int64_t sh,
+                                           int p, int nw, uint32_t *col, int st) {
+    const int nlimb = (p + 63) >> 6;
+    return build_words_from(
+        [&](auto limb) {
+            auto ld = [&](int l) { return sl[min(l, nlimb - 1)]; };
+            uint64_t r0 = ld(0), r1 = ld(1);
+            for (int l = 0; l < nlimb; l += 2) {
+                const uint64_t x0 = r0, x1 = r1;
+                r0 = ld(l + 2);
+                limb(x0);
+                r1 = ld(l + 3);
+                limb(x1);
+            }
+        },
+        s, sh, p, nw, col, st);
+}
+
+// One operand side as the residue kernels read it: logical rows x count entries, entry (r, k)
+// at r rs + k cs; planes of rpad x kpad bytes.
+struct ResSide {
     const uint64_t *limbs;
     const int32_t *exps;
     const int8_t *signs;
     int64_t rs, cs, rows, count, kpad, plane_stride;
     const int32_t *erow;
-    int p, nl, t, nw32;
-    const double *tab;
-    const ResGroup *rgrp;
-    int L, lgroups;
-    int8_t *planes;
     const int32_t *koff;   // nullable per-contraction exponent offsets (exponent folding)
+    int8_t *planes;
+};
+
+// The plan's part of the entry kernel's arguments.
+struct ResTab {
+    const double *tab;          // [passes][nw32][res_pass_units]
+    const ResUnitGroup *grp;    // [groups]
+    int p, nl, t, nw32, groups;
 };
 
 // a wave-uniform plane pointer held in scalar registers, so that a store through it with a
@@ -273,182 +284,6 @@ __device__ __forceinline__ uint32_t quad_transpose_bytes(uint32_t w, QuadSel sel
 // different L2s.  Grids: (kpad / (64 KW)) x (rpad / (RB / KW)) blocks, launched as a 1-D grid
 // with the k blocks fastest (no 65535 limit on the rows).
 __host__ __device__ constexpr int res_waves_k(int rb) { return rb >= 2 ? 2 : 1; }
-// The VALU kernel with EPT entries per thread: a wave covers 64 EPT consecutive k of one
-// row (EPT = 2: a whole 128-byte plane line, one wave per row).
-__host__ __device__ constexpr int res_kw(int rb, int ept) { return ept >= 2 ? 1 : res_waves_k(rb); }
-// k entries a block covers
-__host__ __device__ constexpr int res_block_k(int rb, int ept) { return 64 * ept * res_kw(rb, ept); }
-
-// The pointers are passed as __restrict__ parameters (kept as scoped no-alias
-// information when inlined), so the compiler knows that the plane stores do
-// not clobber the constant tables and reads those with scalar loads.
-// EPT entries per thread share every constant the thread reads: entry e of a lane is
-// k = kbase + 64 e + lane, its words in the LDS column words + e BD + tid (stride EPT BD).
-// NW > 0 (integers of exactly NW words): the words are read from LDS once, as doubles with
-// the entry's sign applied, and stay in registers for every group of moduli.
-template <int RB, int KG, int EPT = 1, int NW = 0>
-__device__ __forceinline__ void residue_block_r(
-    const uint64_t *__restrict__ limbs, const int32_t *__restrict__ exps,
-    const int8_t *__restrict__ signs, const int32_t *__restrict__ erow,
-    const int32_t *__restrict__ koff, const double *__restrict__ tab,
-    const ResGroup *__restrict__ rgrp, int8_t *__restrict__ planes, int64_t rs, int64_t cs,
-    int64_t rows, int64_t count, int64_t kpad, int64_t plane_stride, int p, int nl, int t,
-    int nw32, int L, int lgroups, int64_t bx, int64_t by, uint32_t *words) {
-    constexpr int BD = 64 * RB;
-    constexpr int ST = BD * EPT;   // word stride of an LDS column
-    const int tid = threadIdx.x;
-    constexpr int KW = res_kw(RB, EPT);
-    const int lane = tid & 63;
-    const int64_t kbase = (bx * KW + (tid >> 6) % KW) * 64 * EPT;
-    const int64_t r = by * (RB / KW) + (tid >> 6) / KW;
-
-    OZ2H_G(int8_t) *gsigns = (OZ2H_G(int8_t) *)signs;
-    OZ2H_G(int32_t) *gexps = (OZ2H_G(int32_t) *)exps;
-    OZ2H_G(int32_t) *gerow = (OZ2H_G(int32_t) *)erow;
-    OZ2H_G(int32_t) *gkoff = (OZ2H_G(int32_t) *)koff;
-    double sgn[EPT];
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        const int64_t k = kbase + 64 * e + lane;
-        int s = 0;
-        int64_t sh = 0, idx = 0;
-        if (r < rows && k < count) {
-            idx = r * rs + k * cs;
-            s = gsigns[idx];
-            sh = (int64_t)t - p + gexps[idx] + (koff ? gkoff[k] : 0) - gerow[r];
-        }
-        s = build_words((OZ2H_G(uint64_t) *)limbs + idx * nl, s, sh, p, nw32, words + e * BD + tid, ST);
-        sgn[e] = s < 0 ? -1.0 : 1.0;
-    }
-
-    // the tables live in global memory: say so, so that pointers read from a
-    // descriptor (the grouped kernels) still qualify for scalar loads
-    typedef const __attribute__((address_space(1))) double gdouble;
-    gdouble *gtab = (gdouble *)tab;
-    OZ2H_G(ResGroup) *grec = (OZ2H_G(ResGroup) *)rgrp;
-    // per-plane base of this block's region (uniform, 64-bit) + a 32-bit lane offset within
-    // it (below (RB / KW) kpad + 128 < 2^32 whatever the plane size): scalar-base stores, no
-    // per-lane 64-bit address arithmetic
-    const int64_t r0b = by * (RB / KW), k0b = bx * res_block_k(RB, EPT);
-    planes += r0b * kpad + k0b;
-    const uint32_t loff = (uint32_t)((r - r0b) * kpad + (kbase + lane - k0b));   // entry 0
-    // packed stores: lane 4 a + q writes entries 4 a .. 4 a + 3 of plane q of four
-    const QuadSel qsel = quad_sel(lane);
-    const int64_t qoff = (int64_t)(lane & 3) * plane_stride + (int64_t)(loff & ~3u);
-    const uint32_t *col = words + tid;
-    double xw[NW > 0 ? NW : 1][EPT];
-    if constexpr (NW > 0) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) xw[w][e] = (double)col[e * BD + w * ST] * sgn[e];
-    }
-    // the signed integer's multiply-add sum for modulus g of the group
-    auto sacc = [&](const double (&acc)[EPT][KG], int e, int g) { return NW > 0 ? acc[e][g] : acc[e][g] * sgn[e]; };
-    for (int grp = 0; grp < lgroups; ++grp) {
-        double acc[EPT][KG];
-#pragma unroll
-        for (int e = 0; e < EPT; ++e)
-#pragma unroll
-            for (int g = 0; g < KG; ++g) acc[e][g] = 0.0;
-        gdouble *c = gtab + (size_t)grp * nw32 * KG;   // uniform: scalar loads
-        if constexpr (NW > 0) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int g = 0; g < KG; ++g) {
-                    const double cg = c[w * KG + g];
-#pragma unroll
-                    for (int e = 0; e < EPT; ++e) acc[e][g] = fma(xw[w][e], cg, acc[e][g]);
-                }
-        } else {
-            for (int w = 0; w < nw32; ++w) {
-                double x[EPT];
-#pragma unroll
-                for (int e = 0; e < EPT; ++e) x[e] = (double)col[e * BD + w * ST];
-#pragma unroll
-                for (int g = 0; g < KG; ++g) {
-                    const double cg = c[w * KG + g];
-#pragma unroll
-                    for (int e = 0; e < EPT; ++e) acc[e][g] = fma(x[e], cg, acc[e][g]);
-                }
-            }
-        }
-        OZ2H_G(ResGroup) *R = grec + grp;
-        const uint32_t two = R->two;
-        // a full group of one kind owns consecutive planes from that of its first modulus:
-        // dword stores after a quad byte transpose, four planes per store
-        if ((grp + 1) * KG <= L && (two == 0u || two == (1u << KG) - 1u)) {
-            const uint32_t gb = R->g0[0];
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                int ri[KG];
-#pragma unroll
-                for (int g = 0; g < KG; ++g) {
-                    const double a = sacc(acc, e, g);
-                    ri[g] = (int)fma(-rint(a * R->inv_m[g]), R->md[g], a);
-                }
-                auto store4 = [&](uint32_t gp, int b0, int b1, int b2, int b3) {
-                    g_i8 *pb = uniform_ptr((g_i8 *)planes + (int64_t)gp * plane_stride);
-                    *(g_u32 *)(pb + qoff + 64 * e) = quad_transpose_bytes(pack_bytes(b0, b1, b2, b3), qsel);
-                };
-                if (two == 0u) {
-#pragma unroll
-                    for (int g = 0; g < KG; g += 4) store4(gb + g, ri[g], ri[g + 1], ri[g + 2], ri[g + 3]);
-                } else {
-                    int pl[3 * KG];   // (r0, r1, r0 + r1) of each modulus, in plane order
-#pragma unroll
-                    for (int g = 0; g < KG; ++g) {
-                        const int r0 = ((ri[g] + 64) & 127) - 64;   // balanced base-128 split
-                        const int r1 = (ri[g] - r0) >> 7;
-                        pl[3 * g] = r0;
-                        pl[3 * g + 1] = r1;
-                        pl[3 * g + 2] = r0 + r1;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 3 * KG; j += 4) store4(gb + j, pl[j], pl[j + 1], pl[j + 2], pl[j + 3]);
-                }
-            }
-            continue;
-        }
-#pragma unroll
-        for (int g = 0; g < KG; ++g) {
-            if (grp * KG + g >= L) break;
-            g_i8 *pb = (g_i8 *)planes + (int64_t)R->g0[g] * plane_stride;
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const double a = sacc(acc, e, g);
-                const int ri = (int)fma(-rint(a * R->inv_m[g]), R->md[g], a);
-                const uint32_t lo = loff + 64 * e;
-                if (!((two >> g) & 1u)) {
-                    pb[lo] = (int8_t)ri;
-                } else {
-                    const int r0 = ((ri + 64) & 127) - 64;   // balanced base-128 split
-                    const int r1 = (ri - r0) >> 7;
-                    pb[lo] = (int8_t)r0;
-                    pb[plane_stride + lo] = (int8_t)r1;
-                    pb[2 * plane_stride + lo] = (int8_t)(r0 + r1);
-                }
-            }
-        }
-    }
-}
-
-template <int RB, int KG, int EPT = 1, int NW = 0>
-__device__ __forceinline__ void residue_block(const ResArgs &a, int64_t bx, int64_t by,
-                                              uint32_t *words) {
-    residue_block_r<RB, KG, EPT, NW>(a.limbs, a.exps, a.signs, a.erow, a.koff, a.tab, a.rgrp, a.planes,
-                                 a.rs, a.cs, a.rows, a.count, a.kpad, a.plane_stride, a.p, a.nl, a.t,
-                                 a.nw32, a.L, a.lgroups, bx, by, words);
-}
-
-template <int RB, int KG, int EPT, int NW = 0>
-__global__ __launch_bounds__(64 * RB) void k_residues(ResArgs a) {
-    extern __shared__ uint32_t words[];
-    const int64_t nbx = a.kpad / res_block_k(RB, EPT);
-    residue_block<RB, KG, EPT, NW>(a, (int64_t)blockIdx.x % nbx, (int64_t)blockIdx.x / nbx, words);
-}
-
 // lanes of one wave hand data over through LDS: keep the compiler from moving LDS
 // accesses across this point (LDS itself serves a wave's instructions in order)
 __device__ __forceinline__ void wave_lds_sync() {
@@ -457,21 +292,271 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Residues of a^ on the vector ALUs with row broadcasts (stage 2, no MFMA).  The residue
-// of a^ = sum_w x_w 2^(32 w) modulo m is sum_w x_w c_w with the centred c_w = 2^(32 w) mod m
-// (an exact fp64 integer, |sum| < 2^53), then a^ - rint(a^/m) m.  Each lane of a 16-lane row
-// owns one modulus of a group of 16 and keeps that modulus's weights c_w in registers; the
-// row works on one entry at a time, its 32-bit words spread over the row's lanes (lane j
-// holds word 16 c + j of chunk c), and each multiply-add takes the word from lane w % 16 by
-// a DPP row broadcast (v_fmac_f64 with row_newbcast): no constant loads in the inner loop.
+// Residues of a^ (stage 2), integers of up to kResMaxWords words.  The words of an entry are
+// dotted with centred 2^(32 w) mod M weights by exact fp64 FMAs (every partial sum an integer
+// below 2^53).  M is one two-limb modulus, or the PRODUCT of two one-limb moduli: the sum is
+// then reduced by either, so that a pair costs the multiply-adds of one modulus.
+// Reduction: r = x - rint(x / m) m.  For the one-limb moduli |x| < 2^51 (integers of up to 16
+// words; wider ones are first reduced by the pair's product), so x / m is at least 1 / (2 m)
+// away from a half-integer and its rounding error below that: the quotient is exact, up to
+// either tie of the even modulus 128, and |r| <= 127.  For a two-limb modulus it is at worst off
+// by one, |r| <= (m + 3) / 2, whose balanced base-128 split r = r0 + 128 r1 has |r0|, |r1|,
+// |r0 + r1| <= 127.  Any representative of a^ mod m within these bounds gives the same exact
+// GEMM result mod m.  x is added to 1.5 2^52, so that r is the low word of the last FMA.
+//
+// A wave takes RW rows x 128 consecutive k (RW = EPT / 2).  Its entries' words are built with
+// one lane per entry (so that the operand is read along its rows) into LDS, word-major; then
+// each lane takes EPT consecutive k: one LDS read gives a word of all of them, and a residue's
+// EPT bytes leave as one store, 128 bytes per row of a plane.  The weights and moduli are
+// wave-uniform scalar loads; units go in groups of four of one kind.  NW > 0 (integers of
+// exactly NW words): EPT = 4, the words stay in registers, as signed doubles, for every group.
+// NW = 0 (wider ones): EPT = 2, which leaves LDS for two waves per SIMD at 31 words; the words
+// are read again for every four groups.
+//
+// What bounds it: up to 12 words the plane stores and operand reads (8192^3, p = 113: 8.4 GB,
+// 1.8 ms at the rate of a copy) and VALU issue about as much, above that issue and LDS.
+// Against one entry per lane and every modulus on its own, bytes exchanged between lanes:
+// both sides 3.62 to 2.65 ms at 8192^3, p = 113; 1.95 to 1.42 ms at 4096^3, p = 256; 1.24 to
+// 1.08 ms at 2048^3, p = 512.
+constexpr int kResWaves = 4;   // waves per block
+__host__ __device__ constexpr int res_ept(int nw) { return nw <= kResRegWords ? 4 : 2; }
+__host__ __device__ constexpr int res_block_rows(int nw) { return kResWaves * res_ept(nw) / 2; }
+__host__ __device__ constexpr size_t res_wave_lds(int nw) { return (size_t)64 * res_ept(nw) * 4 * (nw + 1); }
+
+template <int NW>
+__device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb, int64_t bx, int64_t by,
+                                             uint32_t *words) {
+    constexpr int EPT = NW > 0 ? 4 : 2, NE = 64 * EPT;
+    constexpr int NG = NW > 0 ? 1 : 4;   // groups per pass over the words
+    typedef uint32_t vEu __attribute__((ext_vector_type(EPT)));
+    typedef typename std::conditional<EPT == 4, uint32_t, uint16_t>::type bytes_t;
+    typedef __attribute__((address_space(1))) bytes_t g_bytes;
+    const int lane = threadIdx.x & 63;
+    const int nw = NW > 0 ? NW : tb.nw32;
+    const int64_t r0 = by, k0 = bx * 128;   // the wave's first row and k
+    uint32_t *sgn = words + (size_t)nw * NE;   // sign bits of the entries
+    g_i8 *planes = (g_i8 *)a.planes + r0 * a.kpad + k0;
+    const uint32_t loff =
+        EPT == 4 ? (uint32_t)((lane >> 5) * a.kpad + 4 * (lane & 31)) : (uint32_t)(2 * lane);
+    // the tables are read-only for the launch: scalar loads whatever is stored in between
+    typedef const __attribute__((address_space(4))) ResUnitGroup cgrp;
+    typedef const __attribute__((address_space(4))) double cdouble;
+    cgrp *grec = (cgrp *)tb.grp;
+    if (r0 >= a.rows || k0 >= a.count) {   // padding only
+        const int64_t G = grec[tb.groups - 1].g0 + grec[tb.groups - 1].nplanes;
+        for (int64_t g = 0; g < G; ++g) *(g_bytes *)(planes + g * a.plane_stride + loff) = 0;
+        return;
+    }
+
+    // the words of the wave's entries: pass e, lane -> row r0 + e / 2, k = k0 + 64 (e % 2) + lane
+    OZ2H_G(int8_t) *gsigns = (OZ2H_G(int8_t) *)a.signs;
+    OZ2H_G(int32_t) *gexps = (OZ2H_G(int32_t) *)a.exps;
+    OZ2H_G(int32_t) *gerow = (OZ2H_G(int32_t) *)a.erow;
+    OZ2H_G(int32_t) *gkoff = (OZ2H_G(int32_t) *)a.koff;
+    OZ2H_G(uint64_t) *glimbs = (OZ2H_G(uint64_t) *)a.limbs;
+    int s[EPT];
+    int64_t sh[EPT], idx[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {   // an entry outside the operand reads entry (r0, k0), as 0
+        const int64_t r = r0 + (e >> 1), k = k0 + 64 * (e & 1) + lane;
+        const bool in = r < a.rows && k < a.count;
+        const int64_t rr = in ? r : r0, kk = in ? k : k0;
+        idx[e] = rr * a.rs + kk * a.cs;
+        s[e] = in ? gsigns[idx[e]] : 0;
+        sh[e] = (int64_t)tb.t - tb.p + gexps[idx[e]] + (a.koff ? gkoff[kk] : 0) - gerow[rr];
+    }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int ent = 64 * e + lane;
+        const int sg = build_words(glimbs + idx[e] * tb.nl, s[e], sh[e], tb.p, nw, words + ent, NE);
+        sgn[ent] = sg < 0 ? 0x80000000u : 0u;
+    }
+    wave_lds_sync();
+
+    // lane: entries EPT lane .. (EPT = 4: row lane / 32, k = 4 (lane % 32) ..; 2: k = 2 lane ..)
+    const vEu *wrow = (const vEu *)words + lane;
+    const vEu sb = *((const vEu *)sgn + lane);
+    auto signed_word = [&](uint32_t w, uint32_t sbit) {
+        const uint64_t d = __builtin_bit_cast(uint64_t, (double)w);
+        return __builtin_bit_cast(double, d ^ ((uint64_t)sbit << 32));
+    };
+    double xw[NW > 0 ? NW : 1][EPT];
+    if constexpr (NW > 0) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const vEu q = wrow[w * 64];
+#pragma unroll
+            for (int i = 0; i < EPT; ++i) xw[w][i] = signed_word(q[i], sb[i]);
+        }
+    }
+    constexpr double kMagic = 6755399441055744.0;   // 1.5 2^52
+    auto low = [](double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); };
+    cdouble *gtab = (cdouble *)tb.tab;
+    for (int g = 0; g < tb.groups; g += NG) {
+        double acc[NG][kResUnits][EPT];
+#pragma unroll
+        for (int n = 0; n < NG; ++n)
+#pragma unroll
+            for (int u = 0; u < kResUnits; ++u)
+#pragma unroll
+                for (int i = 0; i < EPT; ++i) acc[n][u][i] = 0.0;
+        cdouble *cg = gtab + (size_t)g * nw * kResUnits;   // [nw][NG groups][units]
+        if constexpr (NW > 0) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int u = 0; u < kResUnits; ++u) {
+                    const double c = cg[w * kResUnits + u];
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i) acc[0][u][i] = fma(xw[w][i], c, acc[0][u][i]);
+                }
+        } else {
+            // the next word and its weights load while one is multiplied
+            constexpr int NU = NG * kResUnits;
+            struct Word {
+                vEu q;
+                double c[NU];
+            };
+            auto load = [&](int w, Word &o) OZ2H_INL {
+                o.q = wrow[w * 64];
+#pragma unroll
+                for (int u = 0; u < NU; ++u) o.c[u] = cg[w * NU + u];
+            };
+            auto mult = [&](const Word &o) OZ2H_INL {
+                double x[EPT];
+#pragma unroll
+                for (int i = 0; i < EPT; ++i) x[i] = signed_word(o.q[i], sb[i]);
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i)
+                        acc[u / kResUnits][u % kResUnits][i] = fma(x[i], o.c[u], acc[u / kResUnits][u % kResUnits][i]);
+            };
+            Word wa, wb;
+            load(0, wa);
+            for (int w = 0; w < nw; w += 2) {
+                load(min(w + 1, nw - 1), wb);
+                __builtin_amdgcn_sched_barrier(0);
+                mult(wa);
+                __builtin_amdgcn_sched_barrier(0);
+                if (w + 1 >= nw) break;
+                load(min(w + 2, nw - 1), wa);
+                __builtin_amdgcn_sched_barrier(0);
+                mult(wb);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+            if (n && g + n >= tb.groups) break;
+            cgrp *R = grec + g + n;
+            g_i8 *pb = uniform_ptr(planes + (int64_t)R->g0 * a.plane_stride);
+            const int np = R->nplanes;
+            // a full group without guards, so that its constants load at once
+            auto pairs = [&](auto full_) OZ2H_INL {
+                constexpr bool FULL = decltype(full_)::value;
+#pragma unroll
+                for (int u = 0; u < kResUnits; ++u) {
+                    double y[EPT];
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i) {
+                        double &x = acc[n][u][i];
+                        if (NW == 0 && nw > kResExactWords) x = fma(-rint(x * R->inv2[u]), R->m2[u], x);
+                        y[i] = x + kMagic;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        if (!FULL && 2 * u + j >= np) break;
+                        uint32_t b[EPT];
+#pragma unroll
+                        for (int i = 0; i < EPT; ++i)
+                            b[i] = low(fma(-rint(acc[n][u][i] * R->inv[2 * u + j]), R->md[2 * u + j], y[i]));
+                        uint32_t v = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u);
+                        if constexpr (EPT == 4)
+                            v = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), v, 0x05040100u);
+                        *(g_bytes *)(pb + (int64_t)(2 * u + j) * a.plane_stride + loff) = (bytes_t)v;
+                    }
+                }
+            };
+            auto twos = [&](auto full_) OZ2H_INL {
+                constexpr bool FULL = decltype(full_)::value;
+                typedef short s2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                for (int u = 0; u < kResUnits; ++u) {
+                    if (!FULL && 3 * u >= np) break;
+                    uint32_t r[EPT];
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i) {
+                        const double x = acc[n][u][i];
+                        r[i] = low(fma(-rint(x * R->inv[u]), R->md[u], x + kMagic));
+                    }
+                    // the residues as packed pairs: r1 = (r + 64) >> 7, r0 = r - 128 r1
+                    uint32_t q0[EPT / 2], q1[EPT / 2], qs[EPT / 2];
+#pragma unroll
+                    for (int h = 0; h < EPT / 2; ++h) {
+                        const s2 v = __builtin_bit_cast(
+                            s2, (uint32_t)__builtin_amdgcn_perm(r[2 * h + 1], r[2 * h], 0x05040100u));
+                        const s2 v1 = (v + (short)64) >> (short)7;
+                        q1[h] = __builtin_bit_cast(uint32_t, v1);
+                        q0[h] = __builtin_bit_cast(uint32_t, (s2)(v - v1 * (short)128));
+                        qs[h] = __builtin_bit_cast(uint32_t, (s2)(v - v1 * (short)127));
+                    }
+                    auto put = [&](int pl, const uint32_t (&q)[EPT / 2]) OZ2H_INL {
+                        *(g_bytes *)(pb + (int64_t)(3 * u + pl) * a.plane_stride + loff) =
+                            (bytes_t)__builtin_amdgcn_perm(q[EPT / 2 - 1], q[0], 0x06040200u);
+                    };
+                    put(0, q0);
+                    put(1, q1);
+                    put(2, qs);
+                }
+            };
+            if (!R->two) {
+                if (np == 2 * kResUnits) pairs(std::true_type{});
+                else pairs(std::false_type{});
+            } else {
+                if (np == 3 * kResUnits) twos(std::true_type{});
+                else twos(std::false_type{});
+            }
+        }
+    }
+}
+
+// both sides of a product (or one: blocks0 = all) in one launch: the first blocks0 blocks are
+// side 0's; a side is a 1-D grid of kpad / 128 (fastest) x rpad / res_block_rows blocks
+struct ResArgs {
+    ResSide side[2];
+    int64_t blocks0;
+    ResTab tab;
+};
+
+template <int NW>
+__global__ __launch_bounds__(64 * kResWaves) void k_residues(ResArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t words[];
+    const int sd = (int64_t)blockIdx.x >= a.blocks0;
+    const ResSide sa = a.side[sd];
+    const int64_t lb = (int64_t)blockIdx.x - (sd ? a.blocks0 : 0), nbx = sa.kpad / 128;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    residue_wave<NW>(sa, a.tab, lb % nbx, (lb / nbx * kResWaves + wave) * (res_ept(NW ? NW : 31) / 2),
+                     words + wave * (res_wave_lds(NW ? NW : a.tab.nw32) / 4));
+}
+
+// Residues of a^ on the vector ALUs with row broadcasts (stage 2, no MFMA; wide integers).  The
+// residue of a^ = sum_w x_w 2^(32 w) modulo m is sum_w x_w c_w with the centred
+// c_w = 2^(32 w) mod M (an exact fp64 integer, |sum| < 2^53), reduced by m.  M is one two-limb
+// modulus, or the product of two one-limb moduli, whose sum is first reduced by M and then by
+// either: a unit.  The x_w are signed base-2^32 digits of the signed integer (|x_w| <= 2^31:
+// half the bound of magnitude words, and no sign left to apply).  Each lane of a 16-lane row
+// owns one unit of a group of 16 and keeps that unit's weights c_w in registers; the row works
+// on one entry at a time, its digits spread over the row's lanes (lane j holds digit 16 c + j
+// of chunk c), and each multiply-add takes the digit from lane w % 16 by a DPP row broadcast
+// (v_fmac_f64 with row_newbcast): no constant loads in the inner loop.
 // A block of four waves covers 128 consecutive k of one row of the operand side:
-//   phase 1: threads 0-127 build their entry's words into LDS (word w of entry e at
-//            words[w * kResRowS + e]: a row of 16 lanes reading 16 words of one entry, and
+//   phase 1: threads 0-127 build their entry's digits into LDS (digit w of entry e at
+//            words[w * kResRowS + e]: a row of 16 lanes reading 16 digits of one entry, and
 //            the four rows four entries 16 apart, hit 64 different banks);
-//   phase 2: wave v takes entry half h = v & 1 (entries 64 h ..) and the moduli groups
-//            g = v >> 1, v >> 1 + 2, ..; row q of the wave takes entries 64 h + 16 q + i,
-//            i < 16, four at a time (four independent accumulators per lane);
-//   stores:  a lane holds its modulus's residues of 16 consecutive entries, packs their bytes
+//   phase 2: wave v takes the groups v, v + 4, .. for all 128 entries; row q of the wave takes
+//            entries 64 s + 16 q + i (i < 16, s = 0, 1), eight at a time;
+//   stores:  a lane holds its unit's residues of 16 consecutive entries, packs their bytes
 //            in registers and stores 16 bytes per plane.
 constexpr int kResRowS = 129;   // LDS word stride of the row-broadcast residue kernel
 
@@ -485,14 +570,14 @@ __device__ __forceinline__ void fmac_rowbcast(double &acc, double x, double c) {
                  : "v"(x), "v"(c), "n"(LANE));
 }
 
-// four words as doubles, followed by the two wait states a DPP read of them needs
-__device__ __forceinline__ void cvt4_words(uint32_t a, uint32_t b, uint32_t c, uint32_t d, double &x0,
+// four signed digits as doubles, followed by the two wait states a DPP read of them needs
+__device__ __forceinline__ void cvt4_digits(uint32_t a, uint32_t b, uint32_t c, uint32_t d, double &x0,
                                            double &x1, double &x2, double &x3) {
     asm volatile(
-        "v_cvt_f64_u32 %0, %4\n\t"
-        "v_cvt_f64_u32 %1, %5\n\t"
-        "v_cvt_f64_u32 %2, %6\n\t"
-        "v_cvt_f64_u32 %3, %7\n\t"
+        "v_cvt_f64_i32 %0, %4\n\t"
+        "v_cvt_f64_i32 %1, %5\n\t"
+        "v_cvt_f64_i32 %2, %6\n\t"
+        "v_cvt_f64_i32 %3, %7\n\t"
         "s_nop 1"
         : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3)
         : "v"(a), "v"(b), "v"(c), "v"(d));
@@ -511,83 +596,77 @@ __device__ __forceinline__ void row_fmas(double (&a)[NE], const double (&x)[NE],
 }
 
 struct ResRowArgs {
-    const uint64_t *limbs;
-    const int32_t *exps;
-    const int8_t *signs;
-    int64_t rs, cs, rows, count, kpad, plane_stride;
-    const int32_t *erow;
-    const int32_t *koff;   // nullable per-contraction exponent offsets (exponent folding)
-    int p, nl, t, nw32, nwp, L, rg16;
-    const double *tab;     // [rg16][16][nwp]
-    const ModInfo *mi;
-    int8_t *planes;
+    ResSide d;
+    int p, nl, t, nw, nwp, groups;   // digits; padded to a multiple of 4 (the weights' stride)
+    const double *tab;               // [16 groups][nwp]
+    const ResRowUnit *units;         // [16 groups]
 };
 
-__host__ __device__ constexpr size_t res_row_lds(int nwp) {
-    return (size_t)nwp * kResRowS * 4 + 128 * 8;
-}
+__host__ __device__ constexpr size_t res_row_lds(int nwp) { return (size_t)nwp * kResRowS * 4; }
 
-// EPR entries per row of a wave and group (16: wave v takes the entry half v & 1 and the
-// groups v >> 1, v >> 1 + 2, ..; 32: wave v takes all 128 entries and the groups v, v + 4,
-// .., so that every weight it loads serves twice the multiply-adds).  Row q's entries are
-// 64 s + 16 q + i (i < 16) for its half(s) s.  (Measured at 4096^2: EPR 32 is 4 % faster
-// than 16 at p = 2048; loading the next chunk's weights ahead was slower, and spilled.)
-template <int EPR>
-__device__ __forceinline__ void residues_row_block(const ResRowArgs &a, uint32_t *smem) {
-    constexpr int NH = EPR / 16;   // entry halves per wave
-    uint32_t *words = smem;
-    double *sgn = (double *)(smem + (size_t)a.nwp * kResRowS);
+__device__ __forceinline__ void residues_row_block(const ResRowArgs &a, int64_t bx, int64_t r, uint32_t *words) {
+    const ResSide &d = a.d;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t nbx = a.kpad / 128;
-    const int64_t bx = (int64_t)blockIdx.x % nbx, r = (int64_t)blockIdx.x / nbx;
     const int64_t k0 = bx * 128;
+    int8_t *prow = d.planes + r * d.kpad + k0;   // the block's segment of plane 0
+    if (r >= d.rows || k0 >= d.count) {          // padding only
+        const ResRowUnit *last = a.units + 16 * a.groups - 1;
+        const int64_t G = (int64_t)last->g0 + last->nplanes;
+        for (int64_t g = wv; g < G; g += 4) *(g_u16 *)((g_i8 *)prow + g * d.plane_stride + 2 * lane) = 0;
+        return;
+    }
 
-    // phase 1: the words of the block's 128 entries
+    // phase 1: the signed digits of the block's 128 entries
     if (tid < 128) {
-        OZ2H_G(int8_t) *gsigns = (OZ2H_G(int8_t) *)a.signs;
-        OZ2H_G(int32_t) *gexps = (OZ2H_G(int32_t) *)a.exps;
+        OZ2H_G(int8_t) *gsigns = (OZ2H_G(int8_t) *)d.signs;
+        OZ2H_G(int32_t) *gexps = (OZ2H_G(int32_t) *)d.exps;
         const int64_t k = k0 + tid;
         int s = 0;
         int64_t sh = 0, idx = 0;
-        if (r < a.rows && k < a.count) {
-            idx = r * a.rs + k * a.cs;
+        if (k < d.count) {
+            idx = r * d.rs + k * d.cs;
             s = gsigns[idx];
-            sh = (int64_t)a.t - a.p + gexps[idx] + (a.koff ? a.koff[k] : 0) - a.erow[r];
+            sh = (int64_t)a.t - a.p + gexps[idx] + (d.koff ? d.koff[k] : 0) - d.erow[r];
         }
-        s = build_words((OZ2H_G(uint64_t) *)a.limbs + idx * a.nl, s, sh, a.p, a.nwp, words + tid,
-                        kResRowS);
-        sgn[tid] = s < 0 ? -1.0 : 1.0;
+        uint32_t *col = words + tid;
+        s = build_words((OZ2H_G(uint64_t) *)d.limbs + idx * a.nl, s, sh, a.p, a.nwp, col, kResRowS);
+        // sum of +-w 2^(32 i) in digits of [-2^31, 2^31): the top digit has room (|a^| < 2^(32 nw - 1))
+        int64_t cy = 0;
+        for (int w = 0; w < a.nw; ++w) {
+            const int64_t m = (int64_t)col[w * kResRowS];
+            const int64_t v = (s < 0 ? -m : m) + cy;
+            const int32_t x = (int32_t)v;
+            col[w * kResRowS] = (uint32_t)x;
+            cy = (v - x) >> 32;
+        }
     }
     __syncthreads();
 
     // phase 2
     const int j = lane & 15, q = lane >> 4;
-    const int h0 = NH == 2 ? 0 : (wv & 1);        // first entry half of this wave
-    const int g0w = NH == 2 ? wv : (wv >> 1), gstep = NH == 2 ? 4 : 2;
-    // words past the full 16-word chunks: chunks of 4, and a last chunk of 2 when at most two
-    // words remain (the words past nw32 are zero in LDS)
-    const int nfull = a.nw32 >> 4, nrem = a.nw32 & 15;
+    // digits past the full 16-digit chunks: chunks of 4, and a last chunk of 2 when at most two
+    // digits remain (the digits past nw are zero in LDS)
+    const int nfull = a.nw >> 4, nrem = a.nw & 15;
     const int ntail = (nrem & 3) == 3 ? (nrem >> 2) + 1 : nrem >> 2;
     const bool tail2 = (nrem & 3) == 1 || (nrem & 3) == 2;
-    int8_t *prow = a.planes + r * a.kpad + k0;   // the block's segment of plane 0
-    for (int g = g0w; g < a.rg16; g += gstep) {
-        const int l = 16 * g + j;
-        const bool live = l < a.L;
-        const ModInfo mi = live ? load_info((OZ2H_G(ModInfo) *)a.mi + l) : ModInfo{};
+    constexpr double kMagic = 6755399441055744.0;   // 1.5 2^52: an integer added to it is its low word
+    auto low = [](double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); };
+    for (int g = wv; g < a.groups; g += 4) {
+        const ResRowUnit *gu = a.units + 16 * g + j;
         const double *crow = a.tab + ((size_t)g * 16 + j) * a.nwp;
-        double acc[EPR];
+        double acc[32];
 #pragma unroll
-        for (int i = 0; i < EPR; ++i) acc[i] = 0.0;
-        // one NC-word chunk (NC = 16, 4 or 2) from word w0 with the weights c
+        for (int i = 0; i < 32; ++i) acc[i] = 0.0;
+        // one NC-digit chunk (NC = 16, 4 or 2) from digit w0 with the weights c
         auto chunk = [&](auto nc_, int w0, const double *c) {
             constexpr int NC = decltype(nc_)::value;
             const uint32_t *wr = words + (size_t)(w0 + (j & (NC - 1))) * kResRowS + 16 * q;
 #pragma unroll
-            for (int eb = 0; eb < EPR / 8; ++eb) {
-                const int e = 64 * (h0 + eb / 2) + 8 * (eb % 2);   // + 16 q, entries e .. e + 7
+            for (int eb = 0; eb < 4; ++eb) {
+                const int e = 64 * (eb / 2) + 8 * (eb % 2);   // + 16 q, entries e .. e + 7
                 double x[8], a8[8];
-                cvt4_words(wr[e], wr[e + 1], wr[e + 2], wr[e + 3], x[0], x[1], x[2], x[3]);
-                cvt4_words(wr[e + 4], wr[e + 5], wr[e + 6], wr[e + 7], x[4], x[5], x[6], x[7]);
+                cvt4_digits(wr[e], wr[e + 1], wr[e + 2], wr[e + 3], x[0], x[1], x[2], x[3]);
+                cvt4_digits(wr[e + 4], wr[e + 5], wr[e + 6], wr[e + 7], x[4], x[5], x[6], x[7]);
 #pragma unroll
                 for (int u = 0; u < 8; ++u) a8[u] = acc[8 * eb + u];
                 row_fmas<NC, 8>(a8, x, c);
@@ -614,47 +693,61 @@ __device__ __forceinline__ void residues_row_block(const ResRowArgs &a, uint32_t
             chunk(std::integral_constant<int, 2>{}, 16 * nfull + 4 * ntail, c2);
         }
 
-        // per entry half: lane (q, j) holds the residues of its modulus for the 16 consecutive
-        // entries 64 hs + 16 q + i; their bytes are packed in registers and leave as one
-        // 16-byte store per plane (the four rows of a wave write 64 contiguous bytes of each
-        // of its planes)
+        // per entry half: lane (q, j) holds its unit's sums for the 16 consecutive entries
+        // 64 hs + 16 q + i; the residues' bytes are packed in registers and leave as one 16-byte
+        // store per plane (the four rows of a wave write 64 contiguous bytes of each plane).
+        // (Split and packed two residues to a register: 14 instead of 21 instructions per
+        // modulus and entry with the sign and the conversion the digits and kMagic save.)
+        const ResRowUnit ru = *gu;
+        typedef short s2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int hh = 0; hh < NH; ++hh) {
-            const int hs = h0 + hh;
-            if (live) {
-                const double md = (double)mi.m;
-                const double *sg = sgn + 64 * hs + 16 * q;
-                g_i8 *dst = (g_i8 *)prow + (int64_t)mi.g0 * a.plane_stride + 64 * hs + 16 * q;
-                auto resid = [&](int i) {
-                    const double x = acc[16 * hh + i] * sg[i];
-                    return (int)fma(-rint(x * mi.inv_m), md, x);
-                };
-                v4u b0;
-                if (mi.nprod == 1) {
+        for (int hs = 0; hs < 2; ++hs) {
+            g_i8 *dst = (g_i8 *)prow + (int64_t)ru.g0 * d.plane_stride + 64 * hs + 16 * q;
+            if (ru.nplanes == 3) {
+                v4u b0, b1, b2;
 #pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4)
-                        b0[i4] = pack_bytes(resid(4 * i4), resid(4 * i4 + 1), resid(4 * i4 + 2),
-                                            resid(4 * i4 + 3));
-                    *(g_v4u *)dst = b0;
-                } else {
-                    v4u b1, b2;
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    uint32_t q0[2], q1[2], qs[2];
 #pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        int r0[4], r1[4];
+                    for (int h = 0; h < 2; ++h) {
+                        uint32_t rr[2];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int ri = resid(4 * i4 + u);
-                            r0[u] = ((ri + 64) & 127) - 64;   // balanced base-128 split
-                            r1[u] = (ri - r0[u]) >> 7;
+                        for (int u = 0; u < 2; ++u) {
+                            const double x = acc[16 * hs + 4 * i4 + 2 * h + u];
+                            rr[u] = low(fma(-rint(x * ru.inv[0]), ru.md[0], x + kMagic));
                         }
-                        b0[i4] = pack_bytes(r0[0], r0[1], r0[2], r0[3]);
-                        b1[i4] = pack_bytes(r1[0], r1[1], r1[2], r1[3]);
-                        b2[i4] = pack_bytes(r0[0] + r1[0], r0[1] + r1[1], r0[2] + r1[2], r0[3] + r1[3]);
+                        // r = r0 + 128 r1, balanced
+                        const s2 v = __builtin_bit_cast(s2, (uint32_t)__builtin_amdgcn_perm(rr[1], rr[0], 0x05040100u));
+                        const s2 v1 = (v + (short)64) >> (short)7;
+                        q1[h] = __builtin_bit_cast(uint32_t, v1);
+                        q0[h] = __builtin_bit_cast(uint32_t, (s2)(v - v1 * (short)128));
+                        qs[h] = __builtin_bit_cast(uint32_t, (s2)(v - v1 * (short)127));
                     }
-                    *(g_v4u *)dst = b0;
-                    *(g_v4u *)(dst + a.plane_stride) = b1;
-                    *(g_v4u *)(dst + 2 * a.plane_stride) = b2;
+                    b0[i4] = __builtin_amdgcn_perm(q0[1], q0[0], 0x06040200u);
+                    b1[i4] = __builtin_amdgcn_perm(q1[1], q1[0], 0x06040200u);
+                    b2[i4] = __builtin_amdgcn_perm(qs[1], qs[0], 0x06040200u);
                 }
+                *(g_v4u *)dst = b0;
+                *(g_v4u *)(dst + d.plane_stride) = b1;
+                *(g_v4u *)(dst + 2 * d.plane_stride) = b2;
+            } else if (ru.nplanes) {
+                v4u b0, b1;
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    uint32_t r0[4], r1[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        double x = acc[16 * hs + 4 * i4 + u];
+                        x = fma(-rint(x * ru.inv2), ru.m2, x);
+                        const double y = x + kMagic;
+                        r0[u] = low(fma(-rint(x * ru.inv[0]), ru.md[0], y));
+                        r1[u] = low(fma(-rint(x * ru.inv[1]), ru.md[1], y));
+                    }
+                    b0[i4] = pack_bytes((int)r0[0], (int)r0[1], (int)r0[2], (int)r0[3]);
+                    b1[i4] = pack_bytes((int)r1[0], (int)r1[1], (int)r1[2], (int)r1[3]);
+                }
+                *(g_v4u *)dst = b0;
+                if (ru.nplanes == 2) *(g_v4u *)(dst + d.plane_stride) = b1;
             }
         }
     }
@@ -662,7 +755,8 @@ __device__ __forceinline__ void residues_row_block(const ResRowArgs &a, uint32_t
 
 __global__ __launch_bounds__(256) void k_residues_row(ResRowArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem_rr[];
-    residues_row_block<32>(a, smem_rr);
+    const int64_t nbx = a.d.kpad / 128;
+    residues_row_block(a, (int64_t)blockIdx.x % nbx, (int64_t)blockIdx.x / nbx, smem_rr);
 }
 
 // Residues of a^ on the matrix cores (stage 2).  For every modulus the residue of an
@@ -1280,8 +1374,6 @@ struct Gemm8Args {
 // two k-tiles ahead across products, tiles and moduli, so nothing drains between tiles.  At
 // the end of a product the two accumulator halves are folded (or reduced and stored) in the
 // read halves of the next two phases, beside the other group's multiplies.
-// lambdas of the kernel: inlined whatever their size (their captures live in registers)
-#define OZ2H_INL __attribute__((always_inline))
 template <int MODE>
 __global__ __launch_bounds__(512, 2) void k_resgemm8(Gemm8Args) {
     // The arguments are read where they are used, mostly between products, through a pointer

@@ -367,8 +367,81 @@ void build_residue_mma_tables(PlanHost &h, const std::vector<uint32_t> &mods) {
     }
 }
 
+// Tables of the entry residue kernel: units (pairs of consecutive one-limb moduli, then single
+// two-limb moduli) in groups of kResUnits of one kind, and each unit's centred 2^(32 w) mod M.
+void build_residue_groups(PlanHost &h, const std::vector<uint32_t> &mods) {
+    if (h.nw32 > kResMaxWords) return;   // the row-broadcast kernel's
+    auto group = [&](int l0, int nmod, bool two) {
+        const int per = two ? 1 : 2;
+        ResUnitGroup R{};
+        R.g0 = h.info[l0].g0;
+        R.nplanes = (uint32_t)(two ? 3 * nmod : nmod);
+        R.two = two;
+        const int pu = res_pass_units(h.nw32), u0 = (int)h.resgrp.size() * kResUnits;   // first unit
+        const size_t base = (size_t)(u0 / pu) * h.nw32 * pu + u0 % pu;
+        h.resid_tab.resize((size_t)(u0 / pu + 1) * h.nw32 * pu, 0.0);
+        for (int u = 0; u * per < nmod; ++u) {
+            uint64_t M = 1;
+            for (int j = u * per; j < std::min(nmod, (u + 1) * per); ++j) {
+                R.inv[j] = h.info[l0 + j].inv_m;
+                R.md[j] = (double)mods[l0 + j];
+                M *= mods[l0 + j];
+            }
+            R.m2[u] = (double)M;
+            R.inv2[u] = 1.0 / (double)M;
+            uint64_t x = 1 % M;
+            for (int w = 0; w < h.nw32; ++w) {
+                int64_t c = (int64_t)x;
+                if (c > (int64_t)((M - 1) / 2)) c -= (int64_t)M;
+                h.resid_tab[base + (size_t)w * pu + u] = (double)c;
+                x = (x << 32) % M;
+            }
+        }
+        h.resgrp.push_back(R);
+    };
+    for (int l = 0; l < h.L1; l += 2 * kResUnits) group(l, std::min(2 * kResUnits, h.L1 - l), false);
+    for (int l = h.L1; l < h.L; l += kResUnits) group(l, std::min(kResUnits, h.L - l), true);
+    h.rgroups = (int)h.resgrp.size();
+}
+
+// Tables of the row-broadcast residue kernel: per lane (unit) one row of rnwp weights, read in
+// 16-digit chunks; units as above, 16 to a group.  Integers are |a| <= 2^wide, one digit more
+// where the signed digits need it.
+void build_residue_rows(PlanHost &h, const std::vector<uint32_t> &mods, int wide) {
+    if (h.nw32 <= kResMaxWords) return;
+    h.rnw = (wide + 2 + 31) / 32;
+    h.rnwp = (h.rnw + 3) / 4 * 4;
+    const int n1 = (h.L1 + 1) / 2, n = n1 + h.L2;
+    h.rg16 = (n + 15) / 16;
+    h.resid_row.assign((size_t)h.rg16 * 16 * h.rnwp, 0.0);
+    h.resrow_units.assign((size_t)h.rg16 * 16, ResRowUnit{});
+    for (int u = 0; u < 16 * h.rg16; ++u) {
+        ResRowUnit &R = h.resrow_units[u];
+        R.g0 = (uint32_t)h.G;   // past the last unit: no planes
+        if (u >= n) continue;
+        const int l0 = u < n1 ? 2 * u : h.L1 + (u - n1), nm = u < n1 ? std::min(2, h.L1 - l0) : 1;
+        uint64_t M = 1;
+        for (int k = 0; k < nm; ++k) {
+            R.inv[k] = h.info[l0 + k].inv_m;
+            R.md[k] = (double)mods[l0 + k];
+            M *= mods[l0 + k];
+        }
+        R.m2 = (double)M;
+        R.inv2 = 1.0 / (double)M;
+        R.g0 = h.info[l0].g0;
+        R.nplanes = u < n1 ? (uint32_t)nm : 3u;
+        uint64_t x = 1 % M;
+        for (int w = 0; w < h.rnw; ++w) {
+            int64_t v = (int64_t)x;
+            if (v > (int64_t)((M - 1) / 2)) v -= (int64_t)M;
+            h.resid_row[(size_t)u * h.rnwp + w] = (double)v;
+            x = (x << 32) % M;
+        }
+    }
+}
+
 int build_plan(int p, int t, int64_t K, const std::vector<uint32_t> &mods_in, PlanHost &h,
-               std::string &err, int wmax, bool allow_wide, const std::vector<uint32_t> *extra) {
+               std::string &err, int wmax, const std::vector<uint32_t> *extra) {
     if (mods_in.empty() || (int)mods_in.size() > kMaxModuli) {
         err = "need 1..512 moduli";
         return -1;
@@ -465,47 +538,8 @@ int build_plan(int p, int t, int64_t K, const std::vector<uint32_t> &mods_in, Pl
     if (cst) return cst;
     build_crt_mma_tables(h, mods, P);
 
-    // residue weights: centred 2^(32 w) mod m, grouped by kg moduli (16 for wide sets:
-    // each word read then feeds twice the FMAs)
-    h.kg = allow_wide && h.L >= kWideL ? kModGroupWide : kModGroup;
-    const int kg = h.kg;
-    h.lgroups = (h.L + kg - 1) / kg;
-    h.resgrp.assign(h.lgroups, ResGroup{});
-    for (int l = 0; l < h.L; ++l) {
-        ResGroup &R = h.resgrp[l / kg];
-        const int g = l % kg;
-        R.inv_m[g] = h.info[l].inv_m;
-        R.md[g] = (double)h.info[l].m;
-        R.g0[g] = h.info[l].g0;
-        if (h.info[l].nprod == 3) R.two |= 1u << g;
-    }
-    h.resid_tab.assign((size_t)h.lgroups * h.nw32 * kg, 0.0);
-    for (int l = 0; l < h.L; ++l) {
-        const uint64_t m = mods[l];
-        uint64_t x = 1 % m;
-        for (int w = 0; w < h.nw32; ++w) {
-            int64_t c = (int64_t)x;
-            if (c > (int64_t)((m - 1) / 2)) c -= (int64_t)m;
-            h.resid_tab[((size_t)(l / kg) * h.nw32 + w) * kg + (l % kg)] =
-                (double)c;
-            x = ((x << 32) % m);
-        }
-    }
-    // the VALU kernel's table: per group of 16 moduli, one row of rnwp words per modulus,
-    // which the lane of that modulus reads in 16-word chunks
-    h.rnwp = (h.nw32 + 3) / 4 * 4;
-    h.rg16 = (h.L + 15) / 16;
-    h.resid_row.assign((size_t)h.rg16 * 16 * h.rnwp, 0.0);
-    for (int l = 0; l < h.L; ++l) {
-        const uint64_t m = mods[l];
-        uint64_t x = 1 % m;
-        for (int w = 0; w < h.nw32; ++w) {
-            int64_t c = (int64_t)x;
-            if (c > (int64_t)((m - 1) / 2)) c -= (int64_t)m;
-            h.resid_row[(size_t)l * h.rnwp + w] = (double)c;
-            x = (x << 32) % m;
-        }
-    }
+    build_residue_groups(h, mods);
+    build_residue_rows(h, mods, std::max(t, wmax));
     build_residue_mma_tables(h, mods);
     return 0;
 }
@@ -599,7 +633,7 @@ int build_plan_f64(int p, int t, int64_t K, const std::vector<uint32_t> &m8,
             }
     }
     if (!m8.empty()) {
-        const int st = build_plan(p, t, K, m8, *h8, err, 0, true, &m64);
+        const int st = build_plan(p, t, K, m8, *h8, err, 0, &m64);
         if (st) return st;
     }
     h = PlanHost{};

@@ -8,16 +8,21 @@
 
 namespace oz2h {
 
-constexpr int kModGroup = 8;          // moduli per group in the residue kernel (small L)
-constexpr int kModGroupWide = 16;     // ... and for wide moduli sets (L >= kWideL)
-constexpr int kWideL = 96;
 constexpr int kResMmaMinWords = 8;    // with the matrix-core residue variant selected, integers
                                       // of >= this many 32-bit words (t >= 224) take it, narrower
                                       // ones the fp64 kernel
-constexpr int kResRowMinWords = 32;  // VALU residues: integers of >= this many words (t >= 992)
-constexpr int kResRegWords = 12;     // VALU residues: integers of <= this many words stay in registers
-                                      // take the row-broadcast kernel (faster from about there
-                                      // on at 4096^2), narrower ones the entry-per-thread kernel
+// VALU residues: integers of >= this many words (t >= 736) take the row-broadcast kernel,
+// narrower ones the entry kernel, whose LDS holds an entry's words (both sides at 2048^3: 21
+// words 1.70 ms against 1.95 with rows, 26 words 3.10 against 2.41)
+constexpr int kResRowMinWords = 24;
+constexpr int kResMaxWords = kResRowMinWords - 1;
+constexpr int kResRegWords = 12;     // entry kernel: integers of <= this many words stay in registers
+constexpr int kResUnits = 4;         // ... units (a pair of one-limb moduli, or one two-limb
+                                     // modulus) per group
+// ... units per pass over an entry's words: a group's, or (words read again for each pass) four
+constexpr int res_pass_units(int nw) { return nw <= kResRegWords ? kResUnits : 4 * kResUnits; }
+constexpr int kResExactWords = 16;   // ... words up to which a pair's sum stays below 2^51, so
+                                     // that its quotients by either modulus are exact
 constexpr int kCrtRowMinDigits = 32;  // CRTs of more digits take the row-broadcast kernels
 constexpr int kMaxModuli = 512;       // fp64-exact CRT digit sums need L * 2^44 < 2^53
 constexpr int kMaxWords = 256;        // fp64-exact residue sums need nw32 * 2^45 < 2^53
@@ -37,16 +42,29 @@ struct ModInfo {
     int32_t pad;
 };
 
-// One group of up to kModGroupWide moduli as the residue kernel reads it
-// (wave-uniform scalar loads, 384 bytes).
-struct ResGroup {
-    double inv_m[kModGroupWide];   // fl(1/m)
-    double md[kModGroupWide];      // m as a double
-    uint32_t g0[kModGroupWide];    // first INT8 plane of the modulus
-    uint32_t two;                  // bit g: modulus g is two-limb (three planes)
-    uint32_t pad[15];
+// One group of up to kResUnits units of one kind as the entry kernel reads it (wave-uniform
+// scalar loads): pairs of consecutive one-limb moduli (2 u, 2 u + 1 of the group; the last one
+// may be alone), or two-limb moduli u.  A group's planes are consecutive.
+struct ResUnitGroup {
+    double inv[2 * kResUnits];   // fl(1/m) of modulus j of the group
+    double md[2 * kResUnits];    // m as a double
+    double inv2[kResUnits];      // pairs: fl(1/M) and M of the product M of unit u's moduli
+    double m2[kResUnits];
+    uint32_t g0, nplanes;        // first plane, planes
+    uint32_t two;                // 1: two-limb moduli
+    uint32_t pad[5];
 };
-static_assert(sizeof(ResGroup) == 384, "ResGroup layout");
+static_assert(sizeof(ResUnitGroup) == 224, "ResUnitGroup layout");
+
+// One unit of the row-broadcast residue kernel, one lane's (nplanes 3: a two-limb modulus; 2: a
+// pair of one-limb moduli; 1: one alone; 0: past the last unit).
+struct ResRowUnit {
+    double inv[2], md[2];   // fl(1/m) and m of its moduli
+    double inv2, m2;        // pairs: of their product
+    uint32_t g0, nplanes;   // first plane, planes
+    uint32_t pad[2];
+};
+static_assert(sizeof(ResRowUnit) == 64, "ResRowUnit layout");
 
 // One block of 32 weight rows of the MFMA residue kernel as it reads it (wave-uniform
 // scalar loads, 768 bytes).  Rows [0, n1) are one-limb moduli; rows p0 + 2 j and
@@ -99,8 +117,7 @@ struct PlanHost {
     int64_t gM = 0, gN = 0;
     int tw[2] = {0, 0};    // widths of the upstream gradient W for dA = W B^T and dB = A^T W
     int nd32 = 0;          // 32-bit digits of the CRT accumulator
-    int kg = kModGroup;    // moduli per residue group: kModGroup, or kModGroupWide for L >= kWideL
-    int lgroups = 0;       // ceil(L / kg)
+    int rgroups = 0;       // entry residue kernel: unit groups (integers of <= kResMaxWords words)
     int crt_dc = 0;        // CRT digit chunk (digits accumulated per pass)
     int crt_nc = 0;        // CRT passes
     int crt_ndpad = 0;     // crt_dc * crt_nc
@@ -108,12 +125,14 @@ struct PlanHost {
     int pbits = 0;         // bit length of P
     std::vector<uint32_t> moduli;    // L, one-limb first
     std::vector<ModInfo> info;       // L
-    std::vector<double> resid_tab;   // [lgroups][nw32][kg]: centred 2^(32w) mod m
-    int rnwp = 0;          // VALU residues: words per integer padded to a multiple of 4
-    int rg16 = 0;          // ... groups of 16 moduli
-    std::vector<double> resid_row;   // [rg16][16 moduli][rnwp words]: centred 2^(32w) mod m
-                                     // (0 past L and past nw32)
-    std::vector<ResGroup> resgrp;    // [lgroups]
+    std::vector<double> resid_tab;   // [passes][nw32][res_pass_units]: centred 2^(32w) mod M
+    int rnw = 0;           // row-broadcast residues: signed base-2^32 digits of an integer
+    int rnwp = 0;          // ... padded to a multiple of 4
+    int rg16 = 0;          // ... groups of 16 units
+    std::vector<double> resid_row;   // [rg16][16 units][rnwp]: centred 2^(32w) mod M
+                                     // (0 past the last unit and past rnw)
+    std::vector<ResRowUnit> resrow_units;   // [16 rg16]
+    std::vector<ResUnitGroup> resgrp;   // [rgroups]
     int rnb = 0;           // MFMA residues: magnitude bytes (4 nw32), then two correction bytes
     int rnq = 0;           // ... 32-byte k-steps covering rnb + 2 bytes
     int rnrb = 0;          // ... blocks of 32 weight rows
@@ -152,8 +171,7 @@ int select_moduli_bits(double need, std::vector<uint32_t> &mods, double &log2P, 
 // moduli of the same CRT (a mixed plan's binary64 moduli), whose product enters the
 // direct-CRT weights (P / m_l)^-1 mod m_l.
 int build_plan(int p, int t, int64_t K, const std::vector<uint32_t> &mods, PlanHost &out,
-               std::string &err, int wmax = 0, bool allow_wide = true,
-               const std::vector<uint32_t> *extra = nullptr);
+               std::string &err, int wmax = 0, const std::vector<uint32_t> *extra = nullptr);
 
 // Largest binary64 modulus for contraction length K (Eq. fp64bound, capped so that a
 // residue splits into two 11-bit CRT terms).
