@@ -39,6 +39,8 @@ struct oz2h_plan {
     int8_t *d_crt_afr = nullptr;
     double *d_crt = nullptr;
     double *d_crt_row = nullptr;
+    CrtUnit *d_crt_units = nullptr;
+    double *d_crt_udig = nullptr;
     uint32_t *d_pd = nullptr;
     uint32_t *d_phd = nullptr;
     F64Mod *d_f64 = nullptr;        // binary64 moduli (binary64 and mixed plans)
@@ -363,11 +365,11 @@ int launch_resgemm(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npad,
                                      npad, nullptr, s);
 }
 
-// CRT launch shape.  Up to 32 digits per entry the digit columns live in LDS
-// (two entries per thread, block of 256, columns <= 48 KiB); above that, in a
-// global-memory region (GDIG), so that blocks stay 256 threads wide whatever nd32
-// is and LDS holds only slices of the digit constants (read with scalar loads when
-// the columns are in LDS).
+// Launch shape of the CRT by single moduli (plain residues of the stage call; the batched form
+// above kCrtUnitMaxDigits digits).  Digit columns in LDS: two entries per thread up to 64 digits,
+// blocks of up to 256, columns <= 48 KiB.  Digit columns in global memory (gdig): blocks stay
+// 256 threads wide whatever nd32 is and LDS holds only slices of the digit constants (read with
+// scalar loads when the columns are in LDS).
 struct CrtCfg {
     int ept, bd, LB;
     size_t lds;
@@ -393,6 +395,27 @@ CrtCfg crt_config(const PlanHost &h, int64_t M, int64_t N, bool allow_gdig) {
     const int64_t per = (int64_t)c.bd * c.ept;
     c.nb = (unsigned)((std::max<int64_t>(M * N, 1) + per - 1) / per);
     c.gstride = (int64_t)c.nb * per;
+    return c;
+}
+
+// Launch shape of the unit CRT: blocks of one wave (more, smaller blocks fill the LDS better:
+// 4096^2, p = 256 0.95 against 1.03 ms with four waves), two columns per thread, or one where
+// the digits of two would leave too few waves (29 digits at 2048^2: 0.45 against 0.51 ms) or
+// the entries are few (256^2, p = 128: 11.1 against 13.5 us).
+constexpr int kCrtUnitThreads = 64;
+constexpr int crt_unit_ept(int nd) { return nd > 26 ? 1 : 2; }
+#define OZ2H_CRT_UNIT_DIGITS(X) \
+    X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24) X(26) X(28) X(30) X(32) X(36) X(40) X(44) X(48)
+struct CrtUnitsCfg {
+    int ept;
+    size_t lds;
+    unsigned nb;
+};
+CrtUnitsCfg crt_units_config(const PlanHost &h, int64_t M, int64_t N, bool grouped = false) {
+    CrtUnitsCfg c{};
+    c.ept = !grouped && M * N <= 262144 ? 1 : crt_unit_ept(h.crt_und);
+    c.lds = (size_t)h.crt_und * kCrtUnitThreads * c.ept * sizeof(uint32_t);
+    c.nb = (unsigned)((M * ((N + c.ept - 1) / c.ept) + kCrtUnitThreads - 1) / kCrtUnitThreads);
     return c;
 }
 
@@ -426,9 +449,8 @@ RowCrtCfg row_crt_config(const PlanHost &h, int64_t M, int64_t ldv) {
 }
 
 size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N) {
-    if (row_crt_eligible(h)) return row_crt_config(h, M, round_up(std::max<int64_t>(N, 1), 256)).bytes;
-    const CrtCfg c = crt_config(h, M, N, true);
-    return c.gdig ? (size_t)h.nd32 * (size_t)c.gstride * sizeof(uint32_t) : 0;
+    if (h.nd32 <= kCrtUnitMaxDigits) return 0;
+    return row_crt_config(h, M, round_up(std::max<int64_t>(N, 1), 256)).bytes;
 }
 
 // gdig: device buffer of crt_gdig_bytes(h, M, N) bytes, or NULL (digit columns in LDS)
@@ -439,15 +461,15 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
     const PlanHost &h = pl->h;
     if (tsum < 0) tsum = 2 * h.t;
     if (M * N == 0) return OZ2H_OK;
-    const CrtCfg c = crt_config(h, M, N, gdig != nullptr && !weight);
+    const CrtCfg c = crt_config(h, M, N, !weight);
     const unsigned nb = c.nb;
     const int bd = c.bd, ept = c.ept;
     const size_t lds = c.lds;
     const CrtArgs ca{u, u_ps, ldu, M, N, pl->d_info, h.L, pl->d_crt, h.crt_ndpad, h.crt_nc, h.nd32,
                      pl->d_pd, pl->d_phd, e, f, tsum, h.p, osign, oexp, olimbs, ldc, chat, nlc, c.LB,
-                     c.gdig ? gdig : nullptr, c.gstride, pl->d_crt_afr, h.crt_nbk, h.crt_kq,
-                     h.crt_nt, h.crt_inv_ptop};
-    if (gdig && row_crt_eligible(h) && !crt_mma_eligible(h, c)) {
+                     nullptr, 0, pl->d_crt_afr, h.crt_nbk, h.crt_kq,
+                     h.crt_nt, h.crt_inv_ptop, pl->d_crt_units, pl->d_crt_udig, h.crt_npair};
+    if (gdig && row_crt_eligible(h) && !crt_mma_eligible(h, c) && (weight || h.nd32 > kCrtUnitMaxDigits)) {
         // row-broadcast CRT: the planes must hold M * ldu entries each, 32-byte aligned rows
         const RowCrtCfg rc = row_crt_config(h, M, ldu);
         if (ldu % 16 == 0 && u_ps >= M * ldu && u_ps % 16 == 0 && ((uintptr_t)u % 32) == 0) {
@@ -477,36 +499,46 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
         else k_crt_mma<kCrtMmaMaxQ, false, false><<<nbm, 256, ldsm, s>>>(ca);
         return check_launch("CRT");
     }
-#define OZ2H_CRT(DC, E, R, W, G) k_crt<DC, E, R, W, G><<<nb, bd, lds, s>>>(ca)
-#define OZ2H_CRT_E(DC, R, W, G)               \
-    if (ept == 2) OZ2H_CRT(DC, 2, R, W, G);    \
-    else OZ2H_CRT(DC, 1, R, W, G);
-#define OZ2H_CRT_DC(R, W, G)                          \
-    switch (h.crt_dc) {                               \
-        case 4: OZ2H_CRT_E(4, R, W, G) break;         \
-        case 8: OZ2H_CRT_E(8, R, W, G) break;         \
-        case 12: OZ2H_CRT_E(12, R, W, G) break;       \
-        case 16: OZ2H_CRT_E(16, R, W, G) break;       \
-        case 20: OZ2H_CRT_E(20, R, W, G) break;       \
-        case 24: OZ2H_CRT_E(24, R, W, G) break;       \
-        case 28: OZ2H_CRT_E(28, R, W, G) break;       \
-        default: OZ2H_CRT_E(32, R, W, G) break;       \
-    }
-    if (weight) {
-        OZ2H_CRT_DC(false, true, false)
-    } else if (c.gdig) {
-        if (round) {
-            OZ2H_CRT_DC(true, false, true)
-        } else {
-            OZ2H_CRT_DC(false, false, true)
+    if (!weight && h.nd32 <= kCrtUnitMaxDigits && u_ps % 2 == 0 && ldu % 2 == 0 && (uintptr_t)u % 4 == 0) {
+        const CrtUnitsCfg uc = crt_units_config(h, M, N);
+        const int ut = kCrtUnitThreads;
+#define OZ2H_CRTU(ND)                                                                                \
+    case ND:                                                                                         \
+        if constexpr (crt_unit_ept(ND) == 2) {                                                       \
+            if (uc.ept == 2) {                                                                       \
+                if (round) k_crt_units<ND, 2, true><<<uc.nb, ut, uc.lds, s>>>(ca);                   \
+                else k_crt_units<ND, 2, false><<<uc.nb, ut, uc.lds, s>>>(ca);                        \
+                break;                                                                               \
+            }                                                                                        \
+        }                                                                                            \
+        if (round) k_crt_units<ND, 1, true><<<uc.nb, ut, uc.lds, s>>>(ca);                           \
+        else k_crt_units<ND, 1, false><<<uc.nb, ut, uc.lds, s>>>(ca);                                \
+        break;
+        switch (h.crt_und) {
+            OZ2H_CRT_UNIT_DIGITS(OZ2H_CRTU)
+            default: return fail(OZ2H_EINVAL, "CRT: no kernel for %d digits", h.nd32);
         }
-    } else if (round) {
-        OZ2H_CRT_DC(true, false, false)
-    } else {
-        OZ2H_CRT_DC(false, false, false)
+#undef OZ2H_CRTU
+        return check_launch("CRT");
     }
-#undef OZ2H_CRT_DC
-#undef OZ2H_CRT_E
+    // plain residues (weighted here), and layouts the kernels above do not take
+    if (!weight) return fail(OZ2H_EINVAL, "CRT: layout of the weighted residues");
+#define OZ2H_CRT(DC)                                                              \
+    case DC:                                                                      \
+        if (ept == 2) k_crt<DC, 2, false, true, false><<<nb, bd, lds, s>>>(ca);   \
+        else k_crt<DC, 1, false, true, false><<<nb, bd, lds, s>>>(ca);            \
+        break
+    switch (h.crt_dc) {
+        OZ2H_CRT(4);
+        OZ2H_CRT(8);
+        OZ2H_CRT(12);
+        OZ2H_CRT(16);
+        OZ2H_CRT(20);
+        OZ2H_CRT(24);
+        OZ2H_CRT(28);
+        OZ2H_CRT(32);
+        default: return fail(OZ2H_EINVAL, "CRT: no kernel for %d digits a pass", h.crt_dc);
+    }
 #undef OZ2H_CRT
     return check_launch("CRT");
 }
@@ -552,6 +584,11 @@ int upload_plan(oz2h_plan *pl) {
     off = align_up(off + n_crt);
     const size_t o_crow = off;
     off = align_up(off + n_crow);
+    const size_t n_cu = sizeof(CrtUnit) * h.crt_units.size(), n_cud = sizeof(double) * h.crt_udig.size();
+    const size_t o_cu = off;
+    off = align_up(off + n_cu);
+    const size_t o_cud = off;
+    off = align_up(off + n_cud);
     const size_t o_pd = off;
     off = align_up(off + n_pd);
     const size_t o_phd = off;
@@ -590,6 +627,10 @@ int upload_plan(oz2h_plan *pl) {
     if (n_rrb) OZ2H_HIP(hipMemcpy(pl->d_rmma_rb, h.rmma_rb.data(), n_rrb, hipMemcpyHostToDevice));
     if (n_cafr) OZ2H_HIP(hipMemcpy(pl->d_crt_afr, h.crt_afr.data(), n_cafr, hipMemcpyHostToDevice));
     OZ2H_HIP(hipMemcpy(pl->d_crt, h.crt_digits.data(), n_crt, hipMemcpyHostToDevice));
+    pl->d_crt_units = (CrtUnit *)(b + o_cu);
+    pl->d_crt_udig = (double *)(b + o_cud);
+    if (n_cu) OZ2H_HIP(hipMemcpy(pl->d_crt_units, h.crt_units.data(), n_cu, hipMemcpyHostToDevice));
+    if (n_cud) OZ2H_HIP(hipMemcpy(pl->d_crt_udig, h.crt_udig.data(), n_cud, hipMemcpyHostToDevice));
     if (n_crow) OZ2H_HIP(hipMemcpy(pl->d_crt_row, h.crt_row.data(), n_crow, hipMemcpyHostToDevice));
     OZ2H_HIP(hipMemcpy(pl->d_pd, h.p_digits.data(), n_pd, hipMemcpyHostToDevice));
     OZ2H_HIP(hipMemcpy(pl->d_phd, h.ph_digits.data(), n_pd, hipMemcpyHostToDevice));
@@ -697,7 +738,6 @@ int run_pipeline_f64(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_
                      oz2h_cmat A, oz2h_op opB, oz2h_cmat B, bool round, oz2h_mat *C,
                      int8_t *chat_sign, uint64_t *chat_mag, int nlc, int32_t *e_out, int32_t *f_out,
                      void *ws, size_t ws_bytes, hipStream_t s, hipEvent_t *ev) {
-    const PlanHost &h = pl->h;
     const F64Layout w = layout_f64(pl, M, N);
     if (!ws) return fail(OZ2H_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws) % kAlign) return fail(OZ2H_EINVAL, "workspace must be 256-byte aligned");
@@ -1805,6 +1845,7 @@ int oz2h_crt(const oz2h_plan *plan, int64_t M, int64_t N, const int16_t *u, int6
 // width, entries per thread and digit-column placement (or the matrix-core CRT)
 struct BatchCrtClass {
     int dc, ept, bd, LB;
+    int und;           // unit CRT: digits per unit (0: another kernel)
     bool gdig, mma;
     size_t lds;
     Seg *d_segs;
@@ -2092,33 +2133,27 @@ int launch_batched_crt(oz2h_batched_plan *bp, const BatchChunk &ch, char *ws, hi
     for (auto &c : ch.crt) {
         if (!c.blocks) continue;
         const unsigned nb = (unsigned)c.blocks;
-#define OZ2H_GCRT(DC, E, G) \
-    k_crt_grouped<DC, E, G><<<nb, c.bd, c.lds, s>>>(bp->d_probs, c.d_segs, c.nseg, ws, c.LB)
-#define OZ2H_GCRT_DC(E, G)                     \
-    switch (c.dc) {                            \
-        case 4: OZ2H_GCRT(4, E, G); break;     \
-        case 8: OZ2H_GCRT(8, E, G); break;     \
-        case 12: OZ2H_GCRT(12, E, G); break;   \
-        case 16: OZ2H_GCRT(16, E, G); break;   \
-        case 20: OZ2H_GCRT(20, E, G); break;   \
-        case 24: OZ2H_GCRT(24, E, G); break;   \
-        case 28: OZ2H_GCRT(28, E, G); break;   \
-        default: OZ2H_GCRT(32, E, G); break;   \
-    }
+#define OZ2H_GCRTU(ND)                                                                                         \
+    case ND:                                                                                                   \
+        k_crt_units_grouped<ND, crt_unit_ept(ND)><<<nb, kCrtUnitThreads, c.lds, s>>>(bp->d_probs, c.d_segs, c.nseg, ws); \
+        break;
+#define OZ2H_GCRT(DC, E) k_crt_grouped<DC, E><<<nb, c.bd, c.lds, s>>>(bp->d_probs, c.d_segs, c.nseg, ws, c.LB)
         if (c.mma) {
             k_crt_mma_grouped<kCrtMmaMaxQ><<<nb, 256, c.lds, s>>>(bp->d_probs, c.d_segs, c.nseg, ws);
-        } else if (c.gdig) {
-            if (c.ept == 2) {
-                OZ2H_GCRT_DC(2, true)
-            } else {
-                OZ2H_GCRT_DC(1, true)
+        } else if (c.und) {
+            switch (c.und) {
+                OZ2H_CRT_UNIT_DIGITS(OZ2H_GCRTU)
+                default: return fail(OZ2H_EINVAL, "grouped CRT: no kernel for %d digits", c.und);
             }
-        } else if (c.ept == 2) {
-            OZ2H_GCRT_DC(2, false)
-        } else {
-            OZ2H_GCRT_DC(1, false)
+        } else {   // more than 48 digits: passes of 22 to 32, one entry per thread above 64 digits
+            if (c.dc == 28 && c.ept == 2) OZ2H_GCRT(28, 2);
+            else if (c.dc == 32 && c.ept == 2) OZ2H_GCRT(32, 2);
+            else if (c.dc == 24 && c.ept == 1) OZ2H_GCRT(24, 1);
+            else if (c.dc == 28 && c.ept == 1) OZ2H_GCRT(28, 1);
+            else if (c.dc == 32 && c.ept == 1) OZ2H_GCRT(32, 1);
+            else return fail(OZ2H_EINVAL, "grouped CRT: no kernel for %d digits a pass", c.dc);
         }
-#undef OZ2H_GCRT_DC
+#undef OZ2H_GCRTU
 #undef OZ2H_GCRT
         int st = check_launch("grouped CRT");
         if (st) return st;
@@ -2224,7 +2259,8 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
 
     // device table layout
     size_t off = 0;
-    std::vector<size_t> o_info(count), o_res(count), o_rrow(count), o_rru(count), o_rg(count), o_crt(count), o_pd(count),
+    std::vector<size_t> o_info(count), o_res(count), o_rrow(count), o_rru(count), o_rg(count), o_cu(count),
+        o_cud(count), o_crt(count), o_pd(count),
         o_phd(count), o_cafr(count);
     for (int b = 0; b < count; ++b) {
         const PlanHost &h = bp->hosts[b];
@@ -2238,6 +2274,10 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         off = align_up(off + sizeof(ResRowUnit) * h.resrow_units.size());
         o_rg[b] = off;
         off = align_up(off + sizeof(ResUnitGroup) * h.resgrp.size());
+        o_cu[b] = off;
+        off = align_up(off + sizeof(CrtUnit) * h.crt_units.size());
+        o_cud[b] = off;
+        off = align_up(off + sizeof(double) * h.crt_udig.size());
         o_crt[b] = off;
         off = align_up(off + sizeof(double) * h.crt_digits.size());
         o_pd[b] = off;
@@ -2359,41 +2399,39 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         bool big = ch.exp_blocks > INT32_MAX;
         for (int c = 0; c < kResClasses; ++c) big = big || ch.res_blocks[c] > INT32_MAX;
         if (big) return fail(OZ2H_ERANGE, "batched plan: too many blocks for one launch");
-        // CRT classes: (digit chunk, entries per thread, digit columns in LDS or global
-        // memory), the same shapes a plain call would take (crt_config); digit chunk -1: the
-        // matrix-core CRT, under the rule a plain call applies
+        // CRT classes: the unit kernel by its digits; above that (digit chunk, entries per
+        // thread), digit columns in global memory; digit chunk -1: the matrix-core CRT, under the
+        // rule a plain call applies
         std::map<std::tuple<int, int, int>, std::vector<int>> classes;
         for (int b : ch.prods) {
             const PlanHost &h = bp->hosts[b];
             const CrtCfg cc = crt_config(h, probs[b].M, probs[b].N, true);
             if (crt_mma_eligible(h, cc)) classes[std::make_tuple(-1, 1, 0)].push_back(b);
-            else classes[std::make_tuple(h.crt_dc, cc.ept, (int)cc.gdig)].push_back(b);
+            else if (h.nd32 <= kCrtUnitMaxDigits) classes[std::make_tuple(0, crt_unit_ept(h.crt_und), h.crt_und)].push_back(b);
+            else classes[std::make_tuple(h.crt_dc, cc.ept, 0)].push_back(b);
         }
         for (auto &kv : classes) {
             BatchCrtClass c{};
             c.dc = std::get<0>(kv.first);
             c.ept = std::get<1>(kv.first);
-            c.gdig = std::get<2>(kv.first) != 0;
+            c.und = std::get<2>(kv.first);
+            c.mma = c.dc < 0;
+            c.gdig = c.dc > 0;
             int maxnd = 1, maxL = 1;
             for (int b : kv.second) {
                 maxnd = std::max(maxnd, bp->hosts[b].nd32);
                 maxL = std::max(maxL, bp->hosts[b].L);
             }
-            c.mma = c.dc < 0;
-            c.bd = 256;
-            size_t cols = 0;
-            if (c.mma) {
-                cols = (size_t)256 * maxnd * 4;   // 256 entries per block, one column each
-            } else if (!c.gdig) {
-                while (c.bd > 64 && (size_t)maxnd * c.bd * c.ept * 4 > 49152) c.bd /= 2;
-                cols = (((size_t)maxnd * c.bd * c.ept + 3) & ~(size_t)3) * 4;
-            }
+            c.bd = c.und ? kCrtUnitThreads : 256;
             c.LB = c.gdig ? std::max(1, std::min(maxL, (int)(32768 / (sizeof(double) * (c.dc + 1))))) : maxL;
-            c.lds = c.gdig ? (size_t)c.LB * (c.dc + 1) * sizeof(double) : cols;
+            c.lds = c.mma ? (size_t)256 * maxnd * 4   // 256 entries per block, one column each
+                    : c.und ? (size_t)c.und * kCrtUnitThreads * c.ept * 4
+                            : (size_t)c.LB * (c.dc + 1) * sizeof(double);
             std::vector<Seg> segs;
             for (int b : kv.second) {
                 const int64_t per = (int64_t)c.bd * c.ept;
-                const int64_t nb = (probs[b].M * probs[b].N + per - 1) / per;
+                const int64_t nb = c.und ? crt_units_config(bp->hosts[b], probs[b].M, probs[b].N, true).nb
+                                         : (probs[b].M * probs[b].N + per - 1) / per;
                 segs.push_back(Seg{c.blocks, b, 0, nb});
                 c.blocks += nb;
                 ProbDev &P = bp->pd[b];
@@ -2451,6 +2489,13 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         P.rrunits = (const ResRowUnit *)(db + o_rru[b]);
         P.rgrp = (const ResUnitGroup *)(db + o_rg[b]);
         P.crt = (const double *)(db + o_crt[b]);
+        P.crt_units = (const CrtUnit *)(db + o_cu[b]);
+        P.crt_udig = (const double *)(db + o_cud[b]);
+        P.crt_npair = h.crt_npair;
+        if (!h.crt_units.empty()) {
+            OZ2H_HIP(hipMemcpy(db + o_cu[b], h.crt_units.data(), sizeof(CrtUnit) * h.crt_units.size(), hipMemcpyHostToDevice));
+            OZ2H_HIP(hipMemcpy(db + o_cud[b], h.crt_udig.data(), sizeof(double) * h.crt_udig.size(), hipMemcpyHostToDevice));
+        }
         P.pd = (const uint32_t *)(db + o_pd[b]);
         P.phd = (const uint32_t *)(db + o_phd[b]);
         P.crt_afr = (const int8_t *)(db + o_cafr[b]);

@@ -36,6 +36,9 @@ struct ProbDev {
     const int8_t *crt_afr;   // matrix-core CRT tables (plan fields of the same names)
     int32_t crt_nbk, crt_kq, crt_nt;
     double crt_inv_ptop;
+    const CrtUnit *crt_units;
+    const double *crt_udig;
+    int32_t crt_npair;
 };
 
 struct Seg {
@@ -164,21 +167,34 @@ __global__ __launch_bounds__(256) void k_resgemm_grouped(const ProbDev *__restri
     }
 }
 
-// stages 4-5, grouped: segment prod is a 1-D grid of CRT blocks
-template <int DC, int EPT, bool GDIG>
+__device__ __forceinline__ CrtArgs crt_args(const ProbDev &P, char *ws, int LB, bool gdig) {
+    return CrtArgs{(const int16_t *)(ws + P.v_off), P.rpad[0] * P.rpad[1], P.rpad[1], P.rows[0],
+                   P.rows[1], P.mi, P.L, P.crt, P.crt_ndpad, P.crt_nc, P.nd32, P.pd, P.phd,
+                   (const int32_t *)(ws + P.erow_off[0]), (const int32_t *)(ws + P.erow_off[1]),
+                   2 * P.t, P.p, P.csign, P.cexp, P.climbs, P.ldc, nullptr, 0, LB,
+                   gdig ? (uint32_t *)(ws + P.dig_off) : nullptr, P.dig_stride,
+                   P.crt_afr, P.crt_nbk, P.crt_kq, P.crt_nt, P.crt_inv_ptop,
+                   P.crt_units, P.crt_udig, P.crt_npair};
+}
+
+// stages 4-5, grouped: segment prod is a 1-D grid of the plain launch's CRT blocks, by units or
+// (more digits) with digit columns in global memory
+template <int ND, int EPT>
+__global__ __launch_bounds__(256) void k_crt_units_grouped(const ProbDev *__restrict__ probs,
+                                                           const Seg *__restrict__ segs, int nseg,
+                                                           char *ws) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t sdig[];
+    const Seg sg = segs[find_seg(segs, nseg, blockIdx.x)];
+    crt_units_block<ND, EPT, true>(crt_args(probs[sg.prod], ws, 0, false), (int64_t)blockIdx.x - sg.first, sdig);
+}
+
+template <int DC, int EPT>
 __global__ __launch_bounds__(256) void k_crt_grouped(const ProbDev *__restrict__ probs,
                                                      const Seg *__restrict__ segs, int nseg,
                                                      char *ws, int LB) {
     extern __shared__ __attribute__((aligned(16))) uint32_t sdig[];
-    const int si = find_seg(segs, nseg, blockIdx.x);
-    const Seg sg = segs[si];
-    const ProbDev &P = probs[sg.prod];
-    const CrtArgs a{(const int16_t *)(ws + P.v_off), P.rpad[0] * P.rpad[1], P.rpad[1], P.rows[0],
-                    P.rows[1], P.mi, P.L, P.crt, P.crt_ndpad, P.crt_nc, P.nd32, P.pd, P.phd,
-                    (const int32_t *)(ws + P.erow_off[0]), (const int32_t *)(ws + P.erow_off[1]),
-                    2 * P.t, P.p, P.csign, P.cexp, P.climbs, P.ldc, nullptr, 0, LB,
-                    GDIG ? (uint32_t *)(ws + P.dig_off) : nullptr, P.dig_stride};
-    crt_block<DC, EPT, true, false, GDIG>(a, (int64_t)blockIdx.x - sg.first, sdig);
+    const Seg sg = segs[find_seg(segs, nseg, blockIdx.x)];
+    crt_block<DC, EPT, true, false, true>(crt_args(probs[sg.prod], ws, LB, true), (int64_t)blockIdx.x - sg.first, sdig);
 }
 
 // stages 4-5, grouped, on the matrix cores (products whose plan has the tables)
@@ -190,11 +206,7 @@ __global__ __launch_bounds__(256) void k_crt_mma_grouped(const ProbDev *__restri
     const int si = find_seg(segs, nseg, blockIdx.x);
     const Seg sg = segs[si];
     const ProbDev &P = probs[sg.prod];
-    const CrtArgs a{(const int16_t *)(ws + P.v_off), P.rpad[0] * P.rpad[1], P.rpad[1], P.rows[0],
-                    P.rows[1], P.mi, P.L, P.crt, P.crt_ndpad, P.crt_nc, P.nd32, P.pd, P.phd,
-                    (const int32_t *)(ws + P.erow_off[0]), (const int32_t *)(ws + P.erow_off[1]),
-                    2 * P.t, P.p, P.csign, P.cexp, P.climbs, P.ldc, nullptr, 0, 0, nullptr, 0,
-                    P.crt_afr, P.crt_nbk, P.crt_kq, P.crt_nt, P.crt_inv_ptop};
+    const CrtArgs a = crt_args(P, ws, 0, false);
     crt_mma_block<KQ, true>(a, (int64_t)blockIdx.x - sg.first, sdig);
 }
 

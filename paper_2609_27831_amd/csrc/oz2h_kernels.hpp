@@ -1866,16 +1866,19 @@ struct CrtArgs {
     const int8_t *afr;
     int nbk, kq, nt;
     double inv_ptop;
+    // unit CRT (k_crt_units): units, their digits, pairs among them (an even number)
+    const CrtUnit *units;
+    const double *udig;   // [units][ND]
+    int npair;
 };
 
-// Lift and (ROUND) rounding of one output entry e from its digit column sd (stride
+// Lift and (ROUND) rounding of output entry (i, j) from its digit column sd (stride
 // cst): on the fast path the column holds c^ in two's complement over nd32 digits
 // (sign = carry < 0); on the slow path it holds R = S - (alpha - 1) P in [0, 3P).
 template <bool ROUND>
-__device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t e, uint32_t *sd, int64_t cst,
+__device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t i, int64_t j, uint32_t *sd, int64_t cst,
                                            bool slow, int64_t carry) {
     const int nd32 = a.nd32, p = a.p;
-    const int64_t N = a.N;
     const uint32_t *__restrict__ Phd = a.Phd;
     const int nl = (p + 63) / 64;
     bool neg;
@@ -1904,9 +1907,9 @@ __device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t e, uint32_t
     }
     int top = nd32 - 1;
     while (top >= 0 && mag(top) == 0) --top;
-    const int64_t i = e / N, j = e - i * N;
 
     if (!ROUND) {
+        const int64_t e = i * a.N + j;
         __attribute__((address_space(1))) uint64_t *o =
             (__attribute__((address_space(1))) uint64_t *)a.chat_mag + e * a.nlc;
         for (int w = 0; w < a.nlc; ++w)
@@ -1965,11 +1968,10 @@ template <int DC, int EPT, bool ROUND, bool WEIGHT, bool GDIG = false>
 __device__ __forceinline__ void crt_block(const CrtArgs &a, int64_t blk, uint32_t *sdig) {
     const int tid = threadIdx.x, bd = blockDim.x, st = bd * EPT;
     const int64_t cst = GDIG ? a.gstride : (int64_t)st;   // digit stride of a column
-    const int nd32 = a.nd32, L = a.L, LB = a.LB, ndpad = a.ndpad, p = a.p;
+    const int nd32 = a.nd32, L = a.L, LB = a.LB, ndpad = a.ndpad;
     const int64_t N = a.N, v_ps = a.v_ps;
     // global-memory views (pointers from a descriptor are generic otherwise)
     OZ2H_G(uint32_t) *Pd = (OZ2H_G(uint32_t) *)a.Pd;
-    const uint32_t *__restrict__ Phd = a.Phd;
     OZ2H_G(ModInfo) *mi = (OZ2H_G(ModInfo) *)a.mi;
     // digit constants and 1/m: read-only for the launch and wave-uniform.  With LDS digit
     // columns (two entries per thread) the constant address space puts them on the scalar
@@ -2142,13 +2144,143 @@ __device__ __forceinline__ void crt_block(const CrtArgs &a, int64_t blk, uint32_
 
 #pragma unroll
     for (int q = 0; q < EPT; ++q)
-        if (live[q]) crt_finish<ROUND>(a, idx[q], col(q), cst, slow[q], carry[q]);
+        if (live[q]) crt_finish<ROUND>(a, idx[q] / N, idx[q] % N, col(q), cst, slow[q], carry[q]);
 }
 
 template <int DC, int EPT, bool ROUND, bool WEIGHT, bool GDIG>
 __global__ __launch_bounds__(256) void k_crt(CrtArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t sdig[];
     crt_block<DC, EPT, ROUND, WEIGHT, GDIG>(a, blockIdx.x, sdig);
+}
+
+// The same by units, for digit sums that fit one pass (nd32 <= 48, digit columns in LDS).  Two
+// one-limb moduli a, b enter as one term: v_a (P / m_a) + v_b (P / m_b) = V P / (m_a m_b) with
+// V = v_a m_b + v_b m_a, which takes the multiply-adds of one modulus.  The sums stay exact:
+// the plan takes pairs while sum_u max |V_u| < 2^22 - 2^15, the bound crt_block's carry pass
+// needs.  A thread takes EPT adjacent columns of a row; V of a pair is one v_dot2_i32_i16 per
+// entry.  The digit constants are wave-uniform scalar loads (SGPR operands of the FMAs), ND
+// (crt_unit_digits) per unit; v planes are read four moduli ahead.
+//
+// What bounds it: VALU issue (FMAs with a scalar operand issue at 50 to 60 TFLOP/s at the two
+// to four waves per SIMD that registers and digit columns leave), at 8192^2, p = 113 the v
+// planes as much (7 GB).  Against single moduli in blocks of 512 entries: 2.76 to 1.74 ms at
+// 8192^2, p = 113; 1.76 to 0.95 ms at 4096^2, p = 256; 25 to 11 us at 256^2, p = 128.
+template <int ND, int EPT, bool ROUND>
+__device__ __forceinline__ void crt_units_block(const CrtArgs &a, int64_t blk, uint32_t *sdig) {
+    static_assert(EPT == 1 || EPT == 2, "one column or two adjacent ones");
+    const int tid = threadIdx.x, bd = blockDim.x, cst = bd * EPT;
+    const int nd32 = a.nd32, L = a.L, npair = a.npair;
+    const int64_t v_ps = a.v_ps, cols = (a.N + EPT - 1) / EPT;
+    typedef const __attribute__((address_space(4))) double cdouble;
+    typedef const __attribute__((address_space(4))) CrtUnit cunit;
+    typedef const __attribute__((address_space(4))) uint32_t cu32;
+    typedef typename std::conditional<EPT == 2, int32_t, int16_t>::type raw_t;
+    cdouble *ud = (cdouble *)a.udig;
+    cunit *cu = (cunit *)a.units;
+
+    const int64_t idx = blk * bd + tid, total = a.M * cols;
+    const bool live = idx < total;   // a dead thread reads entry (0, 0) and writes nothing
+    int64_t i = 0, j = 0;
+    if (live) {
+        i = total >> 32 ? idx / cols : (int64_t)((uint32_t)idx / (uint32_t)cols);
+        j = (idx - i * cols) * EPT;
+    }
+    OZ2H_G(int16_t) *vp = (OZ2H_G(int16_t) *)a.V + i * a.ldv + j;
+    auto load = [&](int l) OZ2H_INL { return (int)*(OZ2H_G(raw_t) *)(vp + (int64_t)l * v_ps); };
+
+    double acc[EPT][ND], asum[EPT];
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+        asum[q] = 0.0;
+#pragma unroll
+        for (int d = 0; d < ND; ++d) acc[q][d] = 0.0;
+    }
+    // unit u with the terms x of the thread's entries
+    auto unit = [&](int u, const double (&x)[EPT]) OZ2H_INL {
+        cdouble *dl = ud + (size_t)u * ND;
+        const double inv = cu[u].inv;
+#pragma unroll
+        for (int q = 0; q < EPT; ++q) asum[q] = fma(x[q], inv, asum[q]);
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            const double w = dl[d];
+#pragma unroll
+            for (int q = 0; q < EPT; ++q) acc[q][d] = fma(x[q], w, acc[q][d]);
+        }
+    };
+    auto pair = [&](int u, int ra, int rb) OZ2H_INL {
+        typedef short s2 __attribute__((ext_vector_type(2)));
+        const s2 mm = __builtin_bit_cast(s2, cu[u].mm);   // (m_b, m_a)
+        double x[EPT];
+#pragma unroll
+        for (int q = 0; q < EPT; ++q) {
+            const uint32_t w = __builtin_amdgcn_perm((uint32_t)rb, (uint32_t)ra, q ? 0x07060302u : 0x05040100u);
+            x[q] = (double)__builtin_amdgcn_sdot2(__builtin_bit_cast(s2, w), mm, 0, false);
+        }
+        unit(u, x);
+    };
+    auto single = [&](int u, int r) OZ2H_INL {
+        double x[EPT];
+        x[0] = (double)(int16_t)r;
+        if constexpr (EPT == 2) x[1] = (double)(r >> 16);
+        unit(u, x);
+    };
+    int ring[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) ring[f] = load(min(f, L - 1));
+    int l = 0, u = 0;   // next modulus and unit
+    for (; u < npair; u += 2, l += 4) {
+        const int r0 = ring[0], r1 = ring[1], r2 = ring[2], r3 = ring[3];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) ring[f] = load(min(l + 4 + f, L - 1));
+        pair(u, r0, r1);
+        pair(u + 1, r2, r3);
+    }
+    for (; l + 4 <= L; l += 4, u += 4) {
+        int r[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            r[f] = ring[f];
+            ring[f] = load(min(l + 4 + f, L - 1));
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) single(u + f, r[f]);
+    }
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+        if (l + f < L) single(u + f, ring[f]);
+
+    // beta and S - beta P, as in crt_block
+    cu32 *Pd = (cu32 *)a.Pd;
+    bool slow[EPT];
+    double cy[EPT];
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+        const double r = rint(asum[q]);
+        slow[q] = fabs(asum[q] - r) > 0.5 - 0x1p-30;
+        const double beta = slow[q] ? floor(asum[q]) - 1.0 : r;   // alpha - 1 when slow
+        uint32_t *sd = sdig + q * bd + tid;
+        cy[q] = 0.0;
+#pragma unroll
+        for (int k = 0; k < ND; ++k) {
+            if (k < nd32) {
+                const double x = fma(-beta, (double)Pd[k], acc[q][k] + cy[q]);
+                const double hi = floor(x * 0x1p-32);
+                sd[k * cst] = (uint32_t)fma(-hi, 0x1p32, x);
+                cy[q] = hi;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < EPT; ++q)
+        if (live && j + q < a.N)
+            crt_finish<ROUND>(a, i, j + q, sdig + q * bd + tid, cst, slow[q], cy[q] < 0.0 ? -1 : 0);
+}
+
+template <int ND, int EPT, bool ROUND>
+__global__ __launch_bounds__(256) void k_crt_units(CrtArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t sdig[];
+    crt_units_block<ND, EPT, ROUND>(a, blockIdx.x, sdig);
 }
 
 // Direct CRT on the matrix cores (digit columns in LDS: nd32 <= 32, L <= 127).  The
@@ -2289,7 +2421,7 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
         cy = x >> 32;
     }
     const int64_t e = e0 + lane;
-    if (e < MN) crt_finish<ROUND>(a, e, col, 256, slow, cy + carry);
+    if (e < MN) crt_finish<ROUND>(a, e / N, e % N, col, 256, slow, cy + carry);
 }
 
 template <int KQ, bool ROUND, bool WEIGHT>
@@ -2582,7 +2714,7 @@ __global__ __launch_bounds__(64) void k_crt_row_finish(CrtArgs a, CrtRowArgs r) 
     }
     if (g < ng) pass(g, da, ca);
     const int64_t sgn = !slow && (int32_t)col[64 * (nd32 - 1)] < 0 ? -1 : 0;
-    crt_finish<ROUND>(a, i * a.N + jj, col, 64, slow, sgn);
+    crt_finish<ROUND>(a, i, jj, col, 64, slow, sgn);
 }
 
 // planes [G][R][C] (int8, row stride ldi) -> [G][Co][Ro] (row stride Ro), zero where

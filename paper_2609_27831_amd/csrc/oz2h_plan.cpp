@@ -247,6 +247,63 @@ void build_crt_mma_tables(PlanHost &h, const std::vector<uint32_t> &mods, const 
 // Digit tables of the direct CRT over h.L terms: S = sum_l v_l coef_l with coef_l = P / m_l
 // (or a multiple of it), as balanced base-2^32 digits (|d| <= 2^31), plus P's digits and
 // the top-digit estimate of S / P.
+// Balanced base-2^32 digits of a into out[0 .. n); false if they do not fit.
+bool balanced_digits(const Nat &a, int n, double *out) {
+    int64_t carry = 0;
+    for (int k = 0; k < n; ++k) {
+        int64_t x = (k < (int)a.size() ? (int64_t)a[k] : 0) + carry;
+        if (x >= (int64_t)1 << 31) {
+            x -= (int64_t)1 << 32;
+            carry = 1;
+        } else {
+            carry = 0;
+        }
+        out[k] = (double)x;
+    }
+    return !carry && (int)a.size() <= n;
+}
+
+// Terms of the unit CRT: pairs of the leading one-limb moduli (an even number of pairs, while
+// sum_u max |V_u| leaves the digit sums exact), then single terms.
+int crt_unit_tables(PlanHost &h, const std::vector<Nat> &coef, std::string &err) {
+    h.crt_und = crt_unit_digits(h.nd32);
+    auto vmax = [&](int l) { return (int64_t)h.info[l].m / 2; };   // centred (or a binary64 term's 11 bits)
+    int64_t sum = 0;
+    for (int l = 0; l < h.L; ++l) sum += std::min<int64_t>(vmax(l), 8095);
+    auto cost = [&](int u) {   // what pair u adds to the sum over its two moduli on their own
+        const int64_t a = h.info[2 * u].m, b = h.info[2 * u + 1].m;
+        return vmax(2 * u) * b + vmax(2 * u + 1) * a - vmax(2 * u) - vmax(2 * u + 1);
+    };
+    const int64_t limit = ((int64_t)1 << 22) - ((int64_t)1 << 15);
+    const int n1 = h.backend == kBackendInt8 ? h.L1 / 2 : 0;
+    h.crt_npair = 0;
+    for (int u = 0; u + 2 <= n1 && sum + cost(u) + cost(u + 1) < limit; u += 2) {
+        sum += cost(u) + cost(u + 1);
+        h.crt_npair += 2;
+    }
+    const int n = h.L - h.crt_npair;
+    h.crt_units.assign(n, CrtUnit{});
+    h.crt_udig.assign((size_t)n * h.crt_und, 0.0);
+    for (int u = 0; u < n; ++u) {
+        const bool pair = u < h.crt_npair;
+        const int l = pair ? 2 * u : u + h.crt_npair;
+        const uint32_t a = h.info[l].m;
+        h.crt_units[u].inv = h.info[l].inv_m;
+        Nat M = coef[l];
+        if (pair) {   // P / (m_a m_b)
+            const uint32_t b = h.info[l + 1].m;
+            M = nat_divexact_small(M, b);
+            h.crt_units[u].inv = 1.0 / ((double)a * (double)b);
+            h.crt_units[u].mm = b | a << 16;
+        }
+        if (!balanced_digits(M, h.crt_und, &h.crt_udig[(size_t)u * h.crt_und])) {
+            err = "internal error: CRT unit digits too short";
+            return -1;
+        }
+    }
+    return 0;
+}
+
 int crt_tables(PlanHost &h, const Nat &P, const std::vector<Nat> &coef, std::string &err) {
     h.pbits = nat_bitlen(P);
     h.nd32 = (h.pbits + 31) / 32 + 2;   // two digits of headroom (subsection on the batched CRT)
@@ -255,23 +312,14 @@ int crt_tables(PlanHost &h, const Nat &P, const std::vector<Nat> &coef, std::str
     h.crt_dc = ((per + 3) / 4) * 4;   // a multiple of 4 (two digits per LDS read, little padding)
     h.crt_ndpad = h.crt_dc * h.crt_nc;
     h.crt_digits.assign((size_t)h.L * h.crt_ndpad, 0.0);
-    for (int l = 0; l < h.L; ++l) {
-        const Nat &Ml = coef[l];
-        int64_t carry = 0;
-        for (int k = 0; k < h.crt_ndpad; ++k) {
-            int64_t x = (k < (int)Ml.size() ? (int64_t)Ml[k] : 0) + carry;
-            if (x >= (int64_t)1 << 31) {
-                x -= (int64_t)1 << 32;
-                carry = 1;
-            } else {
-                carry = 0;
-            }
-            h.crt_digits[(size_t)l * h.crt_ndpad + k] = (double)x;
-        }
-        if (carry || (int)Ml.size() > h.crt_ndpad) {
+    for (int l = 0; l < h.L; ++l)
+        if (!balanced_digits(coef[l], h.crt_ndpad, &h.crt_digits[(size_t)l * h.crt_ndpad])) {
             err = "internal error: CRT digit table too short";
             return -1;
         }
+    if (h.nd32 <= kCrtUnitMaxDigits) {
+        const int st = crt_unit_tables(h, coef, err);
+        if (st) return st;
     }
     // S/P from the top crt_nt digits of S: S_top / P_top with X_top = X / 2^(32 (nd32 - nt))
     // (P's digits below the top nt are dropped: P_top keeps at least 64 of P's bits)

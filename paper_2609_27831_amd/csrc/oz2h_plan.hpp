@@ -23,7 +23,14 @@ constexpr int kResUnits = 4;         // ... units (a pair of one-limb moduli, or
 constexpr int res_pass_units(int nw) { return nw <= kResRegWords ? kResUnits : 4 * kResUnits; }
 constexpr int kResExactWords = 16;   // ... words up to which a pair's sum stays below 2^51, so
                                      // that its quotients by either modulus are exact
-constexpr int kCrtRowMinDigits = 32;  // CRTs of more digits take the row-broadcast kernels
+constexpr int kCrtRowMinDigits = 32;  // the row-broadcast CRT's least digits (plus one); plain residues
+                                      // (the stage call) take it from there on
+// CRTs of at most this many digits take the unit kernel, wider ones the row-broadcast kernels
+// (2048^2 entries, units against rows: 37 digits 0.65 / 1.26 ms, 45: 1.24 / 1.46, 56: 2.1 - 2.3 /
+// 2.3, 62: 2.6 - 2.8 / 2.6)
+constexpr int kCrtUnitMaxDigits = 48;
+// ... its digits in steps of 2 up to 32 and of 4 above, one kernel each
+constexpr int crt_unit_digits(int nd32) { return nd32 <= 32 ? (nd32 + 1) / 2 * 2 : (nd32 + 3) / 4 * 4; }
 constexpr int kMaxModuli = 512;       // fp64-exact CRT digit sums need L * 2^44 < 2^53
 constexpr int kMaxWords = 256;        // fp64-exact residue sums need nw32 * 2^45 < 2^53
 constexpr int64_t kMaxK = 133000;     // K * 127^2 < 2^31, the cap the paper's implementation uses
@@ -80,6 +87,14 @@ struct ResRowBlock {
     uint32_t pad[29];
 };
 static_assert(sizeof(ResRowBlock) == 768, "ResRowBlock layout");
+
+// One term of the unit CRT: a pair of one-limb moduli a, b, or one modulus.
+struct CrtUnit {
+    double inv;      // fl(1 / (m_a m_b)), or fl(1 / m)
+    uint32_t mm;     // pairs: m_b | m_a << 16
+    uint32_t pad;
+};
+static_assert(sizeof(CrtUnit) == 16, "CrtUnit layout");
 
 // One modulus of the binary64 backend as its kernels read it (32 bytes).
 struct F64Mod {
@@ -139,6 +154,10 @@ struct PlanHost {
     std::vector<int8_t> rmma_w;          // [rnrb][rnq][64 lanes][16]: MFMA A fragments
     std::vector<ResRowBlock> rmma_rb;    // [rnrb]
     std::vector<double> crt_digits;  // [L][crt_ndpad]: balanced base-2^32 digits of P/m
+    int crt_und = 0;       // unit CRT (nd32 <= kCrtUnitMaxDigits): digits per unit, crt_unit_digits(nd32)
+    int crt_npair = 0;     // ... pairs (an even number), ahead of the single moduli
+    std::vector<CrtUnit> crt_units;
+    std::vector<double> crt_udig;    // [units][crt_und]: balanced base-2^32 digits
     int crt_ndg = 0;       // row-broadcast CRT: groups of 16 digits
     int crt_lpad = 0;      // ... moduli padded to a multiple of 16
     std::vector<double> crt_row;     // [16 crt_ndg][crt_lpad]: digit d of P/m_l at [d][l]
