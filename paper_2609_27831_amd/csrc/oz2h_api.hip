@@ -194,23 +194,74 @@ Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool compact = false)
     return w;
 }
 
-// shared exponents of a rows x count side (entry (r, k) at r*rs + k*cs)
-// koff (nullable): per-contraction-index exponent offsets added before the max
-int launch_exponents(int64_t rows, int64_t count, const int8_t *sign, const int32_t *exp,
-                     int64_t rs, int64_t cs, const int32_t *koff, int32_t *out, hipStream_t s) {
-    if (rows <= 0) return OZ2H_OK;
-    const unsigned nb = (unsigned)((rows + 255) / 256);
-    k_fill_i32<<<nb, 256, 0, s>>>(out, rows, INT_MIN);
-    if (count > 0) {
-        if (cs == 1) {
-            dim3 grid((unsigned)((rows + 3) / 4), (unsigned)((count + kExpChunk - 1) / kExpChunk));
-            k_exp_kcontig<<<grid, 256, 0, s>>>(sign, exp, rows, count, rs, koff, out);
+// One operand side of stage 1: entry (r, k) at r * rs + k * cs; koff (nullable): per-contraction
+// exponent offsets added before the max.  Rows per block (2^lr), measured at 2^lr = 8 .. 64:
+// contiguous rows take a wave each (16), fewer where blocks would be few and rows long (4096
+// rows of 4096: 23 us with up to 1024 threads per row, 30 with 64); strided ones 32, a line of
+// exponents (4096^2: 49 us against 63 with 16 and 58 with 64), 16 below 1024 rows (389 rows of
+// 1003: 9 against 10 us), and no more than there are.
+ExpSide exp_side(int64_t rows, int64_t count, const int8_t *sign, const int32_t *exp, int64_t rs, int64_t cs,
+                 const int32_t *koff, int32_t *out) {
+    ExpSide d{};
+    d.part[0] = ExpPart{sign, exp, rs, cs};
+    d.nparts = 1;
+    d.rows = std::max<int64_t>(rows, 0);
+    d.koff = koff;
+    d.out = out;
+    if (cs == 1) {
+        d.lr = 4;
+        while (d.lr > 0 && (d.rows >> d.lr) < 512 && (int64_t)(kExpThreads >> d.lr) * 4 < count) --d.lr;
+    } else {
+        d.lr = d.rows >= 1024 ? 5 : 4;
+        while (d.lr > 0 && ((int64_t)1 << (d.lr - 1)) >= d.rows) --d.lr;
+    }
+    d.nb = (d.rows + ((int64_t)1 << d.lr) - 1) >> d.lr;
+    return d;
+}
+
+// the same over the two parts of a complex side, one exponent per row for both
+ExpSide exp_side2(int64_t rows, int64_t count, const oz2h_cmat &X, const oz2h_cmat &Y, int64_t xrs, int64_t xcs,
+                  int64_t yrs, int64_t ycs, int32_t *out) {
+    ExpSide d = exp_side(rows, count, X.sign, X.exp, xrs, xcs, nullptr, out);
+    d.part[1] = ExpPart{Y.sign, Y.exp, yrs, ycs};
+    d.nparts = 2;
+    return d;
+}
+
+// A long contraction over few blocks of rows leaves most of the chip idle: such a side splits
+// the contraction over blocks and combines partial maxima with atomicMax (a fill before and a
+// fix of all-zero rows after).  256 rows of 16384 on both sides: 54 us against 85 in one launch;
+// 4096 rows of 4096: 70 against 50.
+bool exp_split(const ExpSide &d, int64_t count) { return count > 8192 && d.nb < 128 && d.nb > 0; }
+int launch_exponents_split(const ExpSide &d, int64_t count, hipStream_t s) {
+    const unsigned nb = (unsigned)((d.rows + 255) / 256);
+    k_fill_i32<<<nb, 256, 0, s>>>(d.out, d.rows, INT_MIN);
+    for (int q = 0; q < d.nparts; ++q) {
+        const ExpPart &p = d.part[q];
+        if (p.cs == 1) {
+            dim3 grid((unsigned)((d.rows + 3) / 4), (unsigned)((count + kExpChunk - 1) / kExpChunk));
+            k_exp_kcontig<<<grid, 256, 0, s>>>(p.sign, p.exps, d.rows, count, p.rs, d.koff, d.out);
         } else {
             dim3 grid(nb, (unsigned)((count + kExpRowsK - 1) / kExpRowsK));
-            k_exp_generic<<<grid, 256, 0, s>>>(sign, exp, rows, count, rs, cs, koff, out);
+            k_exp_generic<<<grid, 256, 0, s>>>(p.sign, p.exps, d.rows, count, p.rs, p.cs, d.koff, d.out);
         }
     }
-    k_exp_fix<<<nb, 256, 0, s>>>(out, rows);
+    k_exp_fix<<<nb, 256, 0, s>>>(d.out, d.rows);
+    return check_launch("exponent scan");
+}
+
+// shared exponents of one or two sides (a side of no rows launches nothing)
+int launch_exponents(int64_t count, ExpSide x, ExpSide y, hipStream_t s) {
+    for (ExpSide *d : {&x, &y})
+        if (exp_split(*d, count)) {
+            const int st = launch_exponents_split(*d, count, s);
+            if (st) return st;
+            *d = ExpSide{};
+        }
+    const int64_t nb = x.nb + y.nb;
+    if (!nb) return OZ2H_OK;
+    if (nb > INT32_MAX) return fail(OZ2H_ERANGE, "exponent scan: too many rows for one launch");
+    k_exponents<<<(unsigned)nb, kExpThreads, 0, s>>>(ExpArgs{{x, y}, std::max<int64_t>(count, 0)});
     return check_launch("exponent scan");
 }
 
@@ -753,8 +804,8 @@ int run_pipeline_f64(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_
     const int64_t b_rs = opB == OZ2H_OP_N ? 1 : B.ld, b_cs = opB == OZ2H_OP_N ? B.ld : 1;
     int st;
     if (ev) OZ2H_HIP(hipEventRecord(ev[0], s));
-    if ((st = launch_exponents(M, K, A.sign, A.exp, a_rs, a_cs, nullptr, e, s)) ||
-        (st = launch_exponents(N, K, B.sign, B.exp, b_rs, b_cs, nullptr, f, s)))
+    if ((st = launch_exponents(K, exp_side(M, K, A.sign, A.exp, a_rs, a_cs, nullptr, e),
+                               exp_side(N, K, B.sign, B.exp, b_rs, b_cs, nullptr, f), s)))
         return st;
     if (ev) OZ2H_HIP(hipEventRecord(ev[1], s));
     if (pl->i8) {
@@ -856,8 +907,9 @@ int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op o
     const int64_t b_rs = opB == OZ2H_OP_N ? 1 : B.ld, b_cs = opB == OZ2H_OP_N ? B.ld : 1;
 
     if (ev) OZ2H_HIP(hipEventRecord(ev[0], s));
-    if (!ca && (st = launch_exponents(M, K, A.sign, A.exp, a_rs, a_cs, nullptr, e, s))) return st;
-    if (!cb && (st = launch_exponents(N, K, B.sign, B.exp, b_rs, b_cs, nullptr, f, s))) return st;
+    if ((st = launch_exponents(K, ca ? ExpSide{} : exp_side(M, K, A.sign, A.exp, a_rs, a_cs, nullptr, e),
+                               cb ? ExpSide{} : exp_side(N, K, B.sign, B.exp, b_rs, b_cs, nullptr, f), s)))
+        return st;
     if (ev) OZ2H_HIP(hipEventRecord(ev[1], s));
     {
         ResSide sd[2];
@@ -1216,7 +1268,7 @@ int oz2h_residues_create(const oz2h_plan *plan, int32_t side, int64_t rows, oz2h
     r->e = (int32_t *)r->dbuf;
     r->planes = (int8_t *)r->dbuf + off_p;
     const int64_t rs = rows_first ? X.ld : 1, cs = rows_first ? 1 : X.ld;
-    st = launch_exponents(rows, K, X.sign, X.exp, rs, cs, nullptr, r->e, stream);
+    st = launch_exponents(K, exp_side(rows, K, X.sign, X.exp, rs, cs, nullptr, r->e), ExpSide{}, stream);
     const ResSide sd = res_side(rows, K, X.limbs, X.exp, X.sign, rs, cs, r->e, r->rpad, r->kpad, r->planes);
     if (!st) st = launch_residues(plan, &sd, 1, stream);
     if (st) {
@@ -1259,30 +1311,6 @@ int oz2h_gemm_from_residues(const oz2h_plan *plan, int64_t M, int64_t N, int64_t
 // ---------------------------------------------------------------- complex products
 
 namespace {
-
-// the exponent scan of two operands into one shared exponent per row (atomicMax
-// combines the partial maxima of both)
-int launch_exponents2(int64_t rows, int64_t count, const oz2h_cmat &X, const oz2h_cmat &Y,
-                      int64_t xrs, int64_t xcs, int64_t yrs, int64_t ycs, int32_t *out, hipStream_t s) {
-    if (rows <= 0) return OZ2H_OK;
-    const unsigned nb = (unsigned)((rows + 255) / 256);
-    k_fill_i32<<<nb, 256, 0, s>>>(out, rows, INT_MIN);
-    if (count > 0) {
-        for (int part = 0; part < 2; ++part) {
-            const oz2h_cmat &Z = part ? Y : X;
-            const int64_t rs = part ? yrs : xrs, cs = part ? ycs : xcs;
-            if (cs == 1) {
-                dim3 grid((unsigned)((rows + 3) / 4), (unsigned)((count + kExpChunk - 1) / kExpChunk));
-                k_exp_kcontig<<<grid, 256, 0, s>>>(Z.sign, Z.exp, rows, count, rs, nullptr, out);
-            } else {
-                dim3 grid(nb, (unsigned)((count + kExpRowsK - 1) / kExpRowsK));
-                k_exp_generic<<<grid, 256, 0, s>>>(Z.sign, Z.exp, rows, count, rs, cs, nullptr, out);
-            }
-        }
-    }
-    k_exp_fix<<<nb, 256, 0, s>>>(out, rows);
-    return check_launch("exponent scan");
-}
 
 struct ZLayout {
     GemmCfg cfg;
@@ -1415,8 +1443,9 @@ int oz2h_zgemm(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N, int6
     const int64_t ai_rs = opA == OZ2H_OP_N ? Ai.ld : 1, ai_cs = opA == OZ2H_OP_N ? 1 : Ai.ld;
     const int64_t b_rs = opB == OZ2H_OP_N ? 1 : Br.ld, b_cs = opB == OZ2H_OP_N ? Br.ld : 1;
     const int64_t bi_rs = opB == OZ2H_OP_N ? 1 : Bi.ld, bi_cs = opB == OZ2H_OP_N ? Bi.ld : 1;
-    if ((st = launch_exponents2(M, K, Ar, Ai, a_rs, a_cs, ai_rs, ai_cs, e, s))) return st;
-    if ((st = launch_exponents2(N, K, Br, Bi, b_rs, b_cs, bi_rs, bi_cs, f, s))) return st;
+    if ((st = launch_exponents(K, exp_side2(M, K, Ar, Ai, a_rs, a_cs, ai_rs, ai_cs, e),
+                               exp_side2(N, K, Br, Bi, b_rs, b_cs, bi_rs, bi_cs, f), s)))
+        return st;
     // stage 2: the residue planes of each part at those exponents
     const ResSide sa[2] = {res_side(M, K, Ar.limbs, Ar.exp, Ar.sign, a_rs, a_cs, e, w.mpad, w.kpad, ap[0]),
                            res_side(M, K, Ai.limbs, Ai.exp, Ai.sign, ai_rs, ai_cs, e, w.mpad, w.kpad, ap[1])};
@@ -1654,7 +1683,7 @@ int oz2h_gemm_backward(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, c
         int32_t *hx = (int32_t *)(wb + b.off_x[0]);
         int8_t *lp = (int8_t *)(wb + b.off_l[0]), *rp = (int8_t *)(wb + b.off_r[0]);
         int16_t *v = (int16_t *)(wb + b.off_v[0]);
-        if ((st = launch_exponents(M, N, W.sign, W.exp, W.ld, 1, fc, hx, stream))) return st;
+        if ((st = launch_exponents(N, exp_side(M, N, W.sign, W.exp, W.ld, 1, fc, hx), ExpSide{}, stream))) return st;
         const ResSide sd = res_side(M, N, W.limbs, W.exp, W.sign, W.ld, 1, hx, b.mpad[0], b.kpad[0], lp, fc);
         if ((st = launch_residues(plan, &sd, 1, stream, h.tw[0]))) return st;
         if ((st = launch_plane_transpose(bh, N, K, f.kpad, f.npad * f.kpad, rp, b.kpad[0],
@@ -1671,7 +1700,7 @@ int oz2h_gemm_backward(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, c
         int32_t *gx = (int32_t *)(wb + b.off_x[1]);
         int8_t *lp = (int8_t *)(wb + b.off_l[1]), *rp = (int8_t *)(wb + b.off_r[1]);
         int16_t *v = (int16_t *)(wb + b.off_v[1]);
-        if ((st = launch_exponents(N, M, W.sign, W.exp, 1, W.ld, e, gx, stream))) return st;
+        if ((st = launch_exponents(M, exp_side(N, M, W.sign, W.exp, 1, W.ld, e, gx), ExpSide{}, stream))) return st;
         const ResSide sd = res_side(N, M, W.limbs, W.exp, W.sign, 1, W.ld, gx, b.npad[1], b.kpad[1], rp, e);
         if ((st = launch_residues(plan, &sd, 1, stream, h.tw[1]))) return st;
         if ((st = launch_plane_transpose(ah, M, K, f.kpad, f.mpad * f.kpad, lp, b.kpad[1],
@@ -1752,7 +1781,7 @@ int oz2h_exponents(int64_t rows, int64_t count, const int8_t *sign, const int32_
     if (rows < 0 || count < 0) return fail(OZ2H_EINVAL, "negative dimension");
     if (rows == 0) return ok();
     if (!out || (count > 0 && (!sign || !exp))) return fail(OZ2H_EINVAL, "NULL pointer");
-    st = launch_exponents(rows, count, sign, exp, rs, cs, nullptr, out, stream);
+    st = launch_exponents(count, exp_side(rows, count, sign, exp, rs, cs, nullptr, out), ExpSide{}, stream);
     return st ? st : ok();
 }
 
