@@ -522,11 +522,9 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
 size_t oz2h_batched_workspace_size(const oz2h_batched_plan *plan);
 /*
  * Autotuner: times whole runs for every block tile setting of the grouped GEMM
- * (per product as plain calls choose, or 128x128, 256x128, 128x256 for all),
+ * (per product as plain calls choose, or 128x128, 256x128, 128x256 for all) and
  * every persistent schedule (1, 2 or 4 resident blocks per compute unit, or one
- * block per work item) and both GEMM LDS depths (three stages, or two, which
- * leave room on a compute unit for the other chunk's residue and CRT blocks),
- * keeps the fastest, then times it replayed as a HIP graph against the same
+ * block per work item), keeps the fastest, then times it replayed as a HIP graph against the same
  * launches issued directly and keeps the faster mode for oz2h_batched_run.  The
  * result goes to an in-process cache keyed by the batch's shapes (and, if the
  * environment variable OZ2H_TUNE_CACHE names a file, is appended there, one line
@@ -560,7 +558,8 @@ int oz2h_batched_get_config(const oz2h_batched_plan *plan, int32_t *tile, int32_
                             int64_t *gemm_items);
 /* Sets the tile setting (0..3) and blocks per compute unit (0..16) by hand. */
 int oz2h_batched_set_config(oz2h_batched_plan *plan, int32_t tile, int32_t blocks_per_cu);
-/* LDS stages of the grouped GEMM (2 or 3) and the mode of oz2h_batched_run (1: graph
+/* LDS stages of the grouped GEMM (2 or 3; recorded with a tuned configuration, the GEMM has
+   one depth and runs the same with either) and the mode of oz2h_batched_run (1: graph
    replay, 0: direct launches); the setter takes the same values, OZ2H_EINVAL otherwise. */
 int oz2h_batched_get_schedule(const oz2h_batched_plan *plan, int32_t *gemm_stages, int32_t *graph);
 int oz2h_batched_set_schedule(oz2h_batched_plan *plan, int32_t gemm_stages, int32_t graph);

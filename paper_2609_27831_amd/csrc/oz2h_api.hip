@@ -114,9 +114,9 @@ int check_flags(uint32_t flags) {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// residue GEMM block tiles (output rows x columns): 128 x 128 (waves of 64 x 64),
-// 256 x 128 (waves of 128 x 64), 128 x 256 (waves of 64 x 128), and, chosen automatically
-// only, 256 x 256 (eight waves of 128 x 64)
+// residue GEMM block tiles (output rows x columns): 128 x 128 (four waves of 64 x 64), 256 x 128
+// and 128 x 256 (eight waves) on request, and, chosen automatically only, 256 x 256 (eight waves
+// of 128 x 64) and 256 x 64 or 64 x 256 (four waves)
 struct GemmCfg {
     int bm, bn;
 };
@@ -135,23 +135,19 @@ int64_t kpad_for(int64_t K) { return round_up(std::max<int64_t>(K, 1), K > 1024 
 
 // Automatic choice for L moduli (L = 0: no 256 x 256 tiles).
 // 256 x 256 (k_resgemm8) from 320 (modulus, tile) items on, where the output pads to at most
-// 1/16 more than with 128 x 128 tiles, or 1/3 more from kpad = 1024 on.  Whole products, the
-// other tiles against it: 2048^3 p = 256: 2161 / 1741 us; 1024 x 1024 x 256, p = 53 (368
-// items): 95 / 94; 512 x 512 x 1024, p = 256 (280 items, the second round of 256 blocks nearly
-// empty): 209 / 214; 896 x 896 x 4096, p = 256 (pads 1.31 times): 1267 / 997; with K = 256:
-// 223 / 223; 640 x 640 x 1024 (1.44 times): 288 / 307.
-// Else 256 x 128 when it pads at most 1/16 more and leaves two blocks per compute unit per
-// batch of 8 moduli, else 128 x 128.
+// 1/16 more than with 128 x 128 tiles, or 1/3 more from kpad = 1024 on.  GEMM stage, 128 x 128
+// against it: 1024^3, p = 256: 178 / 155 us; 3328 x 3072 x 768, p = 256: 1290 / 1085;
+// 512 x 512 x 1024, p = 256 (280 items, the second round of 256 blocks nearly empty) and
+// 640 x 640 x 1024 (pads 1.44 times) were even or worse.
+// Else 128 x 128: with three blocks per compute unit it beats 256 x 128 (3328 x 3072 x 640,
+// p = 256: 1154 / 1504 us; 2048 x 2048 x 384, p = 512: 617 / 796; 1024^3: even).
 GemmCfg choose_gemm(int64_t M, int64_t N, int tile, int64_t kpad, int L) {
     if (tile != OZ2H_TILE_AUTO) return tile_cfg(tile);
     const int64_t a128 = round_up(M, 128) * round_up(N, 128);
-    const int64_t a256 = round_up(M, 256) * round_up(N, 128);
     const int64_t sq = round_up(M, 256) * round_up(N, 256);
     if (kpad % (2 * GBK) == 0 && L * (sq / (256 * 256)) >= 320 &&
         (sq * 16 <= a128 * 17 || (kpad >= 1024 && sq * 3 <= a128 * 4)))
         return {256, 256};
-    const int64_t blocks = a256 / (256 * 128);
-    if (M >= 256 && a256 * 16 <= a128 * 17 && blocks * 8 >= 2 * 256) return {256, 128};
     return {128, 128};
 }
 
@@ -168,6 +164,12 @@ Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool compact = false)
     Layout w{};
     w.kpad = compact ? round_up(std::max<int64_t>(h.K, 1), GBK) : kpad_for(h.K);
     w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, compact ? 0 : h.L);
+    // up to 64 columns or rows against many: most loads go to the large side's planes, which are
+    // read once (4096 x 8 x 4096, p = 256: 471 us against 513 with 128 x 128 tiles)
+    if (!compact && !h.grad && h.tile == OZ2H_TILE_AUTO && !(h.flags & OZ2H_FLAG_RESIDUES_MMA)) {
+        if (N <= 64 && M >= 256) w.cfg = {256, 64};
+        else if (M <= 64 && N >= 256) w.cfg = {64, 256};
+    }
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
     size_t off = 0;
@@ -389,15 +391,33 @@ int launch_gemm8(const oz2h_plan *pl, int64_t mpad, int64_t npad, const GemmArgs
     return check_launch("residue GEMM");
 }
 
+// Blocks that have a compute unit to themselves take four LDS stages and read a k-tile ahead of
+// its products (1024 x 1024 x 4096, one plane: 19.0 us against 22.5; 128 x 128 x 4096, p = 256,
+// 66 moduli: 56 / 79); more blocks, or few k-tiles, do better with two stages and three blocks per unit
+// (3328 x 3072 x 384, p = 256: 1015 / 827; 384 x 384 x 4096, p = 113, 360 blocks: 67 / 64).
+bool gemm_deep(dim3 grid, int64_t kpad) {
+    return (int64_t)grid.x * grid.y * grid.z <= kGemm8Blocks && kpad >= 512;
+}
+
 template <bool RAW>
 int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b, int64_t kpad,
                        int64_t a_ps, int64_t b_ps, const ModInfo *mi, int L, int16_t *v,
                        int64_t v_ps, int64_t ldv, int32_t *craw, hipStream_t s) {
     const GemmArgs g{a, b, kpad, a_ps, b_ps, mi, v, v_ps, ldv, craw};
     const XcdMap xm = xcd_map_for(cfg, grid);
-    if (cfg.bm == 256 && cfg.bn == 128) k_resgemm<128, 64, RAW><<<grid, 256, 0, s>>>(g, L, xm);
-    else if (cfg.bm == 128 && cfg.bn == 256) k_resgemm<64, 128, RAW><<<grid, 256, 0, s>>>(g, L, xm);
-    else k_resgemm<64, 64, RAW><<<grid, 256, 0, s>>>(g, L, xm);
+    // plain int32 products have no fold for other blocks to cover: 4096^3 86 / 91 us
+    const bool deep = gemm_deep(grid, g.kpad) || (RAW && cfg.bm == cfg.bn);
+#define OZ2H_G(WR, WC)                                                                      \
+    do {                                                                                    \
+        if (deep) k_resgemm<WR, WC, 4, RAW><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);        \
+        else k_resgemm<WR, WC, 2, RAW><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);             \
+    } while (0)
+    if (cfg.bm == 256 && cfg.bn == 128) OZ2H_G(4, 2);
+    else if (cfg.bm == 128 && cfg.bn == 256) OZ2H_G(2, 4);
+    else if (!RAW && cfg.bn == 64) OZ2H_G(4, 1);
+    else if (!RAW && cfg.bm == 64) OZ2H_G(1, 4);
+    else OZ2H_G(2, 2);
+#undef OZ2H_G
     return check_launch("residue GEMM");
 }
 
@@ -1359,15 +1379,17 @@ int launch_resgemm_z(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npa
     const GemmArgsZ g{{a, b, kpad, mpad * kpad, npad * kpad, pl->d_info, v, mpad * npad, npad, nullptr}, v2};
     if (cfg.bm == 256 && cfg.bn == 256) return launch_gemm8(pl, mpad, npad, g, mode, s);
     const XcdMap xm = xcd_map_for(cfg, grid);
-#define OZ2H_ZG(WM, WN)                                                                        \
-    do {                                                                                       \
-        if (mode == ZADD) k_resgemm_z<WM, WN, ZADD><<<grid, 256, 0, s>>>(g, h.L, xm);          \
-        else if (mode == ZSUB) k_resgemm_z<WM, WN, ZSUB><<<grid, 256, 0, s>>>(g, h.L, xm);     \
-        else k_resgemm_z<WM, WN, ZGAUSS><<<grid, 256, 0, s>>>(g, h.L, xm);                     \
+    const bool deep = gemm_deep(grid, kpad);
+#define OZ2H_ZG(WR, WC, ST)                                                                            \
+    do {                                                                                               \
+        if (mode == ZADD) k_resgemm_z<WR, WC, ST, ZADD><<<grid, 64 * WR * WC, 0, s>>>(g, h.L, xm);     \
+        else if (mode == ZSUB) k_resgemm_z<WR, WC, ST, ZSUB><<<grid, 64 * WR * WC, 0, s>>>(g, h.L, xm); \
+        else k_resgemm_z<WR, WC, ST, ZGAUSS><<<grid, 64 * WR * WC, 0, s>>>(g, h.L, xm);                \
     } while (0)
-    if (cfg.bm == 256 && cfg.bn == 128) OZ2H_ZG(128, 64);
-    else if (cfg.bm == 128 && cfg.bn == 256) OZ2H_ZG(64, 128);
-    else OZ2H_ZG(64, 64);
+    if (cfg.bm == 256 && cfg.bn == 128) OZ2H_ZG(4, 2, 2);
+    else if (cfg.bm == 128 && cfg.bn == 256) OZ2H_ZG(2, 4, 2);
+    else if (deep) OZ2H_ZG(2, 2, 4);
+    else OZ2H_ZG(2, 2, 2);
 #undef OZ2H_ZG
     return check_launch("complex residue GEMM");
 }
@@ -1813,7 +1835,6 @@ int oz2h_residue_gemm(const oz2h_plan *plan, int64_t mpad, int64_t npad, int64_t
     GemmCfg cfg = tile_cfg(plan->h.tile);
     if (plan->h.tile == OZ2H_TILE_AUTO && mpad % 256 == 0) {
         cfg = choose_gemm(mpad, npad, OZ2H_TILE_AUTO, kpad, npad % 256 == 0 ? plan->h.L : 0);
-        if (cfg.bn != 256) cfg = {256, 128};
     }
     if (mpad % cfg.bm || npad % cfg.bn)
         return fail(OZ2H_EINVAL, "mpad, npad must be multiples of the %dx%d tile", cfg.bm, cfg.bn);
@@ -1924,8 +1945,8 @@ struct oz2h_batched_plan {
     // would choose for it) and resident blocks per compute unit (0: one block per item)
     int tile = OZ2H_TILE_128x128;
     int bpc = 2;
-    // GEMM LDS stages (2 leaves room on a compute unit for the other chunk's residue and CRT
-    // blocks) and whether oz2h_batched_run replays a graph or launches directly
+    // GEMM LDS stages as set or read from a saved configuration (the kernel has one depth) and
+    // whether oz2h_batched_run replays a graph or launches directly
     int stages = 3;
     bool use_graph = true;
     size_t ws_bytes = 0;
@@ -2098,15 +2119,9 @@ int launch_batched_gemm(oz2h_batched_plan *bp, const BatchChunk &ch, char *ws, h
         // bpc > 0: a persistent grid of bpc blocks per compute unit; bpc = 0: one block per item
         const int grid = bp->bpc > 0 ? (int)std::min<int64_t>(n, (int64_t)bp->ncu * bp->bpc) : n;
         const GemmItem *it = ch.d_items[c];
-#define OZ2H_GG(NS)                                                                                   \
-    do {                                                                                              \
-        if (c == OZ2H_TILE_256x128 - 1) k_resgemm_grouped<128, 64, NS><<<grid, 256, 0, s>>>(bp->d_probs, it, n, ws); \
-        else if (c == OZ2H_TILE_128x256 - 1) k_resgemm_grouped<64, 128, NS><<<grid, 256, 0, s>>>(bp->d_probs, it, n, ws); \
-        else k_resgemm_grouped<64, 64, NS><<<grid, 256, 0, s>>>(bp->d_probs, it, n, ws);          \
-    } while (0)
-        if (bp->stages == 2) OZ2H_GG(2);
-        else OZ2H_GG(3);
-#undef OZ2H_GG
+        if (c == OZ2H_TILE_256x128 - 1) k_resgemm_grouped<4, 2><<<grid, 512, 0, s>>>(bp->d_probs, it, n, ws);
+        else if (c == OZ2H_TILE_128x256 - 1) k_resgemm_grouped<2, 4><<<grid, 512, 0, s>>>(bp->d_probs, it, n, ws);
+        else k_resgemm_grouped<2, 2><<<grid, 256, 0, s>>>(bp->d_probs, it, n, ws);
         int st = check_launch("grouped residue GEMM");
         if (st) return st;
     }
@@ -2688,26 +2703,22 @@ int oz2h_batched_tune(oz2h_batched_plan *plan, void *ws, size_t ws_bytes, hipStr
     TuneRec b{plan->tile, plan->bpc, plan->stages, 1};
     const int tiles[4] = {OZ2H_TILE_AUTO, OZ2H_TILE_128x128, OZ2H_TILE_256x128, OZ2H_TILE_128x256};
     const int bpcs[4] = {1, 2, 4, 0};
-    const int stage_counts[2] = {3, 2};
-    for (int ns : stage_counts)
-        for (int ti : tiles)
-            for (int bc : bpcs) {
-                if (st) break;
-                plan->tile = ti;
-                plan->bpc = bc;
-                plan->stages = ns;
-                if ((st = upload_items(plan))) break;
-                float acc = 0;
-                time_runs(direct, acc);
-                if (!st && acc < best) {
-                    best = acc;
-                    b = TuneRec{ti, bc, ns, 1};
-                }
+    for (int ti : tiles)
+        for (int bc : bpcs) {
+            if (st) break;
+            plan->tile = ti;
+            plan->bpc = bc;
+            if ((st = upload_items(plan))) break;
+            float acc = 0;
+            time_runs(direct, acc);
+            if (!st && acc < best) {
+                best = acc;
+                b = TuneRec{ti, bc, plan->stages, 1};
             }
+        }
     if (!st) {
         plan->tile = b.tile;
         plan->bpc = b.bpc;
-        plan->stages = b.stages;
         drop_graph(plan);
         st = upload_items(plan);
     }

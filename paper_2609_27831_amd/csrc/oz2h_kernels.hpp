@@ -1095,18 +1095,29 @@ __device__ __forceinline__ int32_t centred_mod(double x, double md, double inv_m
 // aligned rows, and over any 8 aligned rows
 __device__ __forceinline__ int lds_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
-// One (2 WM) x (2 WN) output tile of one modulus per block; four waves in 2x2,
-// each a WM x WN sub-tile of v_mfma_i32_32x32x32_i8 blocks (exact int32 sums,
-// K * 127^2 < 2^31).  k-tiles of 128 bytes move global -> LDS by direct loads
-// (global_load_lds_dwordx4: no register staging, no LDS store instructions) into a
-// three-stage LDS ring, two tiles ahead of the multiplies.  A tile row is 128 bytes
-// = eight 16-byte chunks, chunk c of row r stored at c ^ lds_swz(r): the 16 rows a
-// ds_read_b128 serves per LDS cycle (64 banks of 4 bytes, two 128-byte rows per bank
-// period) then hit 16 different 16-byte bank groups, and so do any 8 consecutive rows.
-// The lane order of a direct load fixes the LDS side (16 bytes per lane, consecutive),
-// so the swizzle is applied to the global addresses: load i of wave w fills LDS rows
-// 32 i + 8 w .. + 7, lane -> row 32 i + 8 w + lane / 8, physical chunk lane % 8, which
-// holds logical chunk (lane % 8) ^ lds_swz(row).
+// One (64 WR) x (64 WC) output tile of one modulus per block; WR x WC waves, each a 64 x 64
+// sub-tile of v_mfma_i32_16x16x64_i8 blocks (exact int32 sums, K * 127^2 < 2^31).  B's fragment
+// is the first operand and its rows are taken as 8 a + 4 y + b, so a lane ends with runs of eight
+// consecutive columns of one row: a wave's 16-byte stores fill 64-byte pieces.
+// k-tiles of 64 bytes move global -> LDS by direct loads (no register staging) into ST stages:
+// two, one tile ahead of the multiplies, or four, three ahead, for blocks alone on their compute
+// unit.  Planes are padded to 128 bytes, so every product has an even number of k-tiles and
+// starts in stage 0 (with four stages and an odd number of pairs, two steps of the last round
+// only load).  The products of a modulus and their k-tiles are
+// plain loops with no branch around the accumulators (a branch at a product's end inside the
+// k-loop moved all of them between the register files every k-tile).
+//
+// What bounds it: latency and the work per product (fold, stores).  Three blocks per compute
+// unit (146 registers, 32 KiB of LDS each) cover one block's loads, folds and stores with the
+// others' products.  Against one block per unit with 128-byte k-tiles, three stages and 2-byte
+// stores: 3328 x 3072 x 384, p = 256 1060 to 812 us; 2048 x 2048 x 128, p = 512 540 to 361;
+// 1024 x 1024 x 384, p = 256 112 to 82; 517 x 389 x 1003, p = 113 41 to 38.  Four blocks (128
+// registers, spills in the fold) 1111 us on the first, a 256 x 128 tile of eight waves 1061.
+//
+// An LDS row is four 16-byte chunks, chunk c of row r stored at c ^ swz(r): the 16 rows a
+// ds_read_b128 serves per LDS cycle (64 banks of 4 bytes, four 64-byte rows per bank period) then
+// hit 16 different 16-byte bank groups.  The lane order of a direct load fixes the LDS side (16
+// bytes per lane, consecutive), so the swizzle is applied to the global addresses.
 // The output is v_l = c_l (P/m_l)^-1 mod m_l as a centred int16: the reduction
 // mod m_l and the first step of the direct CRT are fused here.
 // A two-limb modulus runs its three Karatsuba products (planes r0, r1, r0 + r1:
@@ -1129,9 +1140,10 @@ struct GemmArgs {
 
 // LDS stage S of the direct-load GEMM: one object per stage, so that the compiler can
 // tell a read of one stage from a load still filling another
-template <int WM, int WN, int S>
+constexpr int SBK = 64;   // k-tile of the four-wave kernels
+template <int WR, int WC, int S>
 __device__ __forceinline__ int8_t *gemm_stage() {
-    __shared__ __attribute__((aligned(1024))) int8_t st[(2 * WM + 2 * WN) * TBK];
+    __shared__ __attribute__((aligned(1024))) int8_t st[64 * (WR + WC) * SBK];
     return st;
 }
 
@@ -1151,18 +1163,30 @@ struct GemmArgsZ : GemmArgs {
 //   ZGAUSS  (t1, t2) = (V, V2);  V = t1 - t2;  V2 = x - t1 - t2   (3M's last product)
 enum GemmMode { ZSTORE = 0, ZADD = 1, ZSUB = 2, ZGAUSS = 3 };
 
-// one output tile (mt, nt) of modulus l with an NS-stage LDS ring, NS - 1 tiles ahead
-template <int WM, int WN, bool RAW, int NS = 3, int MODE = ZSTORE, class Args = GemmArgs>
+// 16 bytes per lane from base + voff + soff (of the wave-uniform range base .. base + bytes) into
+// the wave's 1 KiB of LDS at dst
+__device__ __forceinline__ void load_lds(const int8_t *base, int bytes, int8_t *dst, uint32_t voff, int soff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00020000),
+                                             (__attribute__((address_space(3))) void *)dst, 16, voff, soff, 0, 0);
+#endif
+}
+
+// waves per SIMD the register allocation aims at
+constexpr int gemm_waves(int nw, int st) { return nw == 4 && st == 2 ? 3 : 2; }
+
+// one output tile (mt, nt) of modulus l
+template <int WR, int WC, int ST, bool RAW, int MODE = ZSTORE, class Args = GemmArgs>
 __device__ __forceinline__ void gemm_tile(const Args &args, int64_t mt, int64_t nt, int l) {
-    static_assert(NS == 2 || NS == 3, "two or three LDS stages");
-    constexpr int BM = 2 * WM, BN = 2 * WN, FM = WM / 32, FN = WN / 32;
-    constexpr int NLA = BM / 32, NL = (BM + BN) / 32;   // direct loads per wave per k-tile
+    constexpr int NW = WR * WC, BM = 64 * WR, BN = 64 * WC;
+    constexpr int FM = 4, FN = 2;                           // 16-row fragments, groups of 32 columns
+    constexpr int NLA = 4 / WC, NL = NLA + 4 / WR;          // direct loads per wave per k-tile
     const int8_t *__restrict__ A = args.A;
     const int8_t *__restrict__ B = args.B;
     const int64_t kpad = args.kpad, a_ps = args.a_ps, b_ps = args.b_ps, ldv = args.ldv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
+    const int wr = wave / WC, wc = wave % WC;
     const int64_t m0 = mt * BM, n0 = nt * BN;
 
     uint32_t g0 = 0, nprod = 1;
@@ -1178,174 +1202,204 @@ __device__ __forceinline__ void gemm_tile(const Args &args, int64_t mt, int64_t 
         kc[1] = info.kc[1];
         kc[2] = info.kc[2];
     }
-    const int nk = (int)(kpad / TBK);   // kpad is a multiple of 128
-    const int ntile = (int)nprod * nk;
+    // kpad is a multiple of 128: an even number of k-tiles
 
+    // load i of wave w fills 16 rows of A or B, lane -> row lane / 4, chunk lane % 4
+    auto swz_a = [](int r) OZ2H_INL { return (r >> 2) & 3; };
+    auto swz_b = [](int r) OZ2H_INL { return (r >> 3) & 3; };
     uint32_t goff[NL];
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        const int R = 32 * i + 8 * wave + (lane >> 3);
-        const int rl = i < NLA ? R : R - BM;
-        goff[i] = (uint32_t)(rl * kpad) + ((((lane & 7) ^ lds_swz(R))) << 4);
+        const int R = 16 * (NW * (i < NLA ? i : i - NLA) + wave) + (lane >> 2);
+        goff[i] = (uint32_t)(R * kpad) + (((lane & 3) ^ (i < NLA ? swz_a(R) : swz_b(R))) << 4);
     }
-    const int8_t *Ab = A + m0 * kpad, *Bb = B + n0 * kpad;
-    auto issue = [&](auto s_, int prod, int kt) {
-        int8_t *dst = gemm_stage<WM, WN, decltype(s_)::value>();
-        const int64_t ko = (int64_t)kt * TBK;
-        const int8_t *a = Ab + (int64_t)(g0 + prod) * a_ps + ko;
-        const int8_t *b = Bb + (int64_t)(g0 + prod) * b_ps + ko;
+    const int8_t *la = A + m0 * kpad + (int64_t)g0 * a_ps, *lb = B + n0 * kpad + (int64_t)g0 * b_ps;
+    auto issue = [&](auto s_, int ko) OZ2H_INL {
+        int8_t *dst = gemm_stage<WR, WC, decltype(s_)::value>();
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            __builtin_amdgcn_global_load_lds((const void *)((i < NLA ? a : b) + goff[i]),
-                                             (__attribute__((address_space(3))) void *)(dst + (4 * i + wave) * 1024),
-                                             16, 0, 0);
+            load_lds(i < NLA ? la : lb, (i < NLA ? BM : BN) * (int)kpad, dst + (NW * i + wave) * 1024, goff[i], ko);
     };
 
-    v16i acc[FM][FN];
+    v4i acc[FN][FM][2];
 #pragma unroll
-    for (int x = 0; x < FM; ++x)
-#pragma unroll
-        for (int y = 0; y < FN; ++y) acc[x][y] = v16i{};
-
-    const int frow = lane & 31;
-    v4i fa[2][FM], fb[2][FN];
-    auto fload = [&](int set, int ks, const int8_t *cA, const int8_t *cB) {
-        const int fo = frow * TBK + (((2 * ks + (lane >> 5)) ^ lds_swz(frow)) << 4);
-#pragma unroll
-        for (int x = 0; x < FM; ++x) fa[set][x] = *(const v4i *)(cA + (wr * WM + x * 32) * TBK + fo);
-#pragma unroll
-        for (int y = 0; y < FN; ++y) fb[set][y] = *(const v4i *)(cB + (wc * WN + y * 32) * TBK + fo);
-    };
-    auto fold = [&](int prod) {
-        const double w = (double)(prod == 0 ? kc[0] : prod == 1 ? kc[1] : kc[2]);
+    for (int c = 0; c < FN; ++c)
 #pragma unroll
         for (int x = 0; x < FM; ++x)
 #pragma unroll
-            for (int y = 0; y < FN; ++y)
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    acc[x][y][e] = centred_mod((double)acc[x][y][e] * w, md, inv_m);
-    };
+            for (int y = 0; y < 2; ++y) acc[c][x][y] = v4i{};
 
-    // (cp, ck): product and k-tile of tile T; (lp, lk): of the tile loaded next, clamped to
-    // the last one.  Every k-tile issues one tile (the last one again near the end), so the
-    // number of loads in flight behind a tile does not depend on the path taken.
-    int cp = 0, ck = 0, lp = 0, lk = 0;
-    auto advance = [&](int &pp, int &kk) {
-        if (++kk == nk) {
-            kk = 0;
-            ++pp;
-        }
-    };
-    auto advance_clamped = [&](int &pp, int &kk) {   // branch-free: selects only
-        const bool more = pp * nk + kk < ntile - 1, wrap = kk + 1 == nk;
-        pp = more && wrap ? pp + 1 : pp;
-        kk = more ? (wrap ? 0 : kk + 1) : kk;
-    };
-    auto mfma = [&](int set) {
+    const int fr = lane & 15, frb = (fr >> 2) * 8 + (fr & 3);
+    const int fo = (wr * 64 + fr) * SBK + (((lane >> 4) ^ swz_a(fr)) << 4);
+    const int go = (wc * 64 + frb) * SBK + (((lane >> 4) ^ swz_b(frb)) << 4);   // y = 1: 4 rows on
+    // (acc w) mod m, centred, as in the 256 x 256 kernel
+    auto fold = [&](int prod) OZ2H_INL {
+        constexpr double kMagic = 6755399441055744.0;
+        const double w = (double)(prod == 0 ? kc[0] : prod == 1 ? kc[1] : kc[2]), wi = w * inv_m;
 #pragma unroll
-        for (int x = 0; x < FM; ++x)
+        for (int c = 0; c < FN; ++c)
 #pragma unroll
-            for (int y = 0; y < FN; ++y)
-                acc[x][y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[set][x], fb[set][y], acc[x][y], 0, 0, 0);
+            for (int x = 0; x < FM; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const double v = (double)acc[c][x][y][e];
+                        acc[c][x][y][e] =
+                            (int32_t)(uint32_t)__builtin_bit_cast(uint64_t, fma(-rint(v * wi), md, fma(v, w, kMagic)));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // four at a time: few registers
+                }
     };
-    issue(std::integral_constant<int, 0>{}, lp, lk);
-    advance_clamped(lp, lk);
-    if constexpr (NS == 3) {
-        issue(std::integral_constant<int, 1>{}, lp, lk);
-        advance_clamped(lp, lk);
-    }
-    // one k-tile from stage S; the tile NS - 1 ahead goes into stage (S + NS - 1) % NS,
+    // one k-tile from stage S; the one ST - 1 ahead (k offset ko) goes into the stage before S,
     // which every wave finished reading before the barrier
-    auto body = [&](auto s_) {
-        constexpr int S = decltype(s_)::value, SN = (S + NS - 1) % NS;
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * NL));   // own loads of tile T landed
-        __builtin_amdgcn_s_barrier();                            // everyone's did
-        issue(std::integral_constant<int, SN>{}, lp, lk);
-        advance_clamped(lp, lk);
-        const int8_t *cA = gemm_stage<WM, WN, S>(), *cB = cA + BM * TBK;
-        fload(0, 0, cA, cB);
-        auto kstep = [&](auto kc_) {
-            constexpr int ks = decltype(kc_)::value;
-            if constexpr (ks + 1 < 4) fload((ks + 1) & 1, ks + 1, cA, cB);
-            mfma(ks & 1);
-#if OZ2H_GEMM_SCHED
-            if constexpr (ks + 1 < 4) __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, FM * FN, 0);
-#endif
-        };
-        kstep(std::integral_constant<int, 0>{});
-        kstep(std::integral_constant<int, 1>{});
-        kstep(std::integral_constant<int, 2>{});
-        kstep(std::integral_constant<int, 3>{});
-        if (!RAW && ck == nk - 1) fold(cp);
-        advance(cp, ck);
+    constexpr int FS = ST == 4 ? 2 : 1;   // fragment sets
+    v4i fa[FS][FM], fb[FS][FN][2];
+    auto fetch = [&](auto s_) OZ2H_INL {
+        constexpr int S = decltype(s_)::value, F = S % FS;
+        const int8_t *cA = gemm_stage<WR, WC, S>(), *cB = cA + BM * SBK;
+#pragma unroll
+        for (int x = 0; x < FM; ++x) fa[F][x] = *(const v4i *)(cA + x * 16 * SBK + fo);
+#pragma unroll
+        for (int c = 0; c < FN; ++c)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) fb[F][c][y] = *(const v4i *)(cB + (c * 32 + 4 * y) * SBK + go);
     };
-    int t0 = 0;
-    for (; t0 + NS <= ntile; t0 += NS) {
-        body(std::integral_constant<int, 0>{});
-        body(std::integral_constant<int, 1>{});
-        if constexpr (NS == 3) body(std::integral_constant<int, 2>{});
+    // two stages: wait for this k-tile and read it.  Four: wait for the next one and read that
+    // (the fragments of this one are there), so that a block alone on its unit multiplies while
+    // it reads
+    auto step = [&](auto s_, int ko) OZ2H_INL {
+        constexpr int S = decltype(s_)::value;
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(ST == 4 ? NL : 0));   // own loads of that tile landed
+        __builtin_amdgcn_s_barrier();                              // everyone's did
+        issue(std::integral_constant<int, (S + ST - 1) % ST>{}, ko);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(std::integral_constant<int, ST == 4 ? (S + 1) % ST : S>{});
+    };
+    auto multiply = [&](auto s_) OZ2H_INL {
+        constexpr int F = decltype(s_)::value % FS;
+#pragma unroll
+        for (int c = 0; c < FN; ++c)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int x = 0; x < FM; ++x)
+                    acc[c][x][y] =
+                        __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[F][c][y], fa[F][x], acc[c][x][y], 0, 0, 0);
+        if constexpr (ST == 4) {   // one read ahead of every two products
+#pragma unroll
+            for (int u = 0; u < FM + 2 * FN; ++u) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2 % ST>;
+    using I3 = std::integral_constant<int, 3 % ST>;
+    const int kp = (int)kpad;
+    issue(I0{}, 0);
+    if constexpr (ST == 4) {
+        issue(I1{}, SBK);
+        issue(I2{}, min(2 * SBK, kp - SBK));
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NL));
+        __builtin_amdgcn_s_barrier();
+        fetch(I0{});
     }
-    if (t0 < ntile) {
-        body(std::integral_constant<int, 0>{});
-        if (NS == 3 && t0 + 1 < ntile) body(std::integral_constant<int, 1>{});
-    }
+    int prod = 0;
+    do {
+        int ko = 0;
+        do {
+            // the next ST k-tiles: of this product, or the next one's first (after the last
+            // product any, not read); an offset past the end reads the last k-tile instead
+            const int nko = ko + ST * SBK;
+            const bool wrap = nko >= kp, more = wrap && prod + 1 < (int)nprod;
+            const int n0 = wrap ? 0 : nko;
+            if constexpr (ST == 2) {
+                step(I0{}, ko + SBK);
+                multiply(I0{});
+                la += more ? a_ps : 0;
+                lb += more ? b_ps : 0;
+                step(I1{}, n0);
+                multiply(I1{});
+            } else {
+                const bool full = nko <= kp;   // else two of the four k-tiles are none
+                step(I0{}, min(ko + 3 * SBK, kp - SBK));
+                multiply(I0{});
+                la += more ? a_ps : 0;
+                lb += more ? b_ps : 0;
+                step(I1{}, n0);
+                multiply(I1{});
+                step(I2{}, n0 + SBK);
+                if (full) multiply(I2{});
+                step(I3{}, min(n0 + 2 * SBK, kp - SBK));
+                if (full) multiply(I3{});
+            }
+            ko = nko;
+        } while (ko < kp);
+        if (!RAW) fold(prod);
+    } while (++prod < (int)nprod);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no load still writing LDS past the block's end
 
-    const int64_t lane_off = (m0 + wr * WM + 4 * (lane >> 5)) * ldv + n0 + wc * WN + (lane & 31);
+    // a lane's runs: row m0 + .. + 16 x + lane % 16, columns n0 + .. + 32 c + 8 (lane / 16) ..
+    const int64_t lane_off = (m0 + wr * 64 + fr) * ldv + n0 + wc * 64 + (lane >> 4) * 8;
     if (RAW) {
         int32_t *base = args.Craw + lane_off;
 #pragma unroll
         for (int x = 0; x < FM; ++x)
 #pragma unroll
-            for (int y = 0; y < FN; ++y)
+            for (int c = 0; c < FN; ++c)
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    base[(int64_t)(x * 32 + 8 * (e >> 2) + (e & 3)) * ldv + y * 32] = acc[x][y][e];
+                for (int y = 0; y < 2; ++y) *(v4i *)(base + (int64_t)(x * 16) * ldv + c * 32 + 4 * y) = acc[c][x][y];
         return;
     }
+    auto pack = [](const int32_t (&t)[8]) OZ2H_INL {
+        v4i o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            o[i] = (int)__builtin_amdgcn_perm((uint32_t)t[2 * i + 1], (uint32_t)t[2 * i], 0x05040100u);
+        return o;
+    };
     int16_t *base = args.V + (int64_t)l * args.v_ps + lane_off;
-    if constexpr (MODE == ZSTORE) {
 #pragma unroll
-        for (int x = 0; x < FM; ++x)
+    for (int x = 0; x < FM; ++x) {
+        // complex products: every old value of a row group is loaded before its first store, so
+        // the group waits once (stores count against the same counter as loads)
+        v4i p1[FN], p2[FN];
+        if constexpr (MODE != ZSTORE) {
 #pragma unroll
-            for (int y = 0; y < FN; ++y)
+            for (int c = 0; c < FN; ++c) {
+                int16_t *dst = base + (int64_t)(x * 16) * ldv + c * 32;
+                p1[c] = *(const v4i *)dst;
+                if constexpr (MODE == ZGAUSS) p2[c] = *(const v4i *)(dst + (args.V2 - args.V));
+            }
+        }
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    base[(int64_t)(x * 32 + 8 * (e >> 2) + (e & 3)) * ldv + y * 32] = (int16_t)acc[x][y][e];
-    } else {
-        int16_t *base2 = nullptr;
-        if constexpr (MODE == ZGAUSS) base2 = args.V2 + (int64_t)l * args.v_ps + lane_off;
-        // per row group x: every old value is loaded before the first store, so the group
-        // waits once (stores count against the same counter as loads: interleaved, each
-        // load would wait for the stores before it)
+        for (int c = 0; c < FN; ++c) {
+            int16_t *dst = base + (int64_t)(x * 16) * ldv + c * 32;
+            int32_t r[8];
 #pragma unroll
-        for (int x = 0; x < FM; ++x) {
-            int32_t t1[FN][16], t2[FN][16];
+            for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int y = 0; y < FN; ++y)
+                for (int e = 0; e < 4; ++e) r[4 * y + e] = acc[c][x][y][e];
+            if constexpr (MODE != ZSTORE) {
+                int32_t r2[8];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int64_t o = (int64_t)(x * 32 + 8 * (e >> 2) + (e & 3)) * ldv + y * 32;
-                    t1[y][e] = base[o];
-                    if constexpr (MODE == ZGAUSS) t2[y][e] = base2[o];
-                }
-#pragma unroll
-            for (int y = 0; y < FN; ++y)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int64_t o = (int64_t)(x * 32 + 8 * (e >> 2) + (e & 3)) * ldv + y * 32;
-                    const int32_t v = acc[x][y][e];
-                    if constexpr (MODE == ZADD) {
-                        base[o] = (int16_t)centred_mod((double)(t1[y][e] + v), md, inv_m);
-                    } else if constexpr (MODE == ZSUB) {
-                        base[o] = (int16_t)centred_mod((double)(t1[y][e] - v), md, inv_m);
-                    } else {
-                        base[o] = (int16_t)centred_mod((double)(t1[y][e] - t2[y][e]), md, inv_m);
-                        base2[o] = (int16_t)centred_mod((double)(v - t1[y][e] - t2[y][e]), md, inv_m);
+                for (int i = 0; i < 8; ++i) {
+                    const int32_t t1 = (int16_t)((uint32_t)p1[c][i / 2] >> (16 * (i % 2)));
+                    if constexpr (MODE == ZADD) r[i] = centred_mod((double)(t1 + r[i]), md, inv_m);
+                    if constexpr (MODE == ZSUB) r[i] = centred_mod((double)(t1 - r[i]), md, inv_m);
+                    if constexpr (MODE == ZGAUSS) {
+                        const int32_t t2 = (int16_t)((uint32_t)p2[c][i / 2] >> (16 * (i % 2)));
+                        r2[i] = centred_mod((double)(r[i] - t1 - t2), md, inv_m);
+                        r[i] = centred_mod((double)(t1 - t2), md, inv_m);
                     }
                 }
+                if constexpr (MODE == ZGAUSS) *(v4i *)(dst + (args.V2 - args.V)) = pack(r2);
+            }
+            *(v4i *)dst = pack(r);
         }
     }
 }
@@ -1361,8 +1415,8 @@ struct XcdMap {
 
 // plain launch: two-limb moduli (listed last) first; grid (N tiles, M tiles, moduli), or
 // with an XCD map a 1-D grid of the same blocks
-template <int WM, int WN, bool RAW>
-__global__ __launch_bounds__(256) void k_resgemm(GemmArgs args, int L, XcdMap xm) {
+template <int WR, int WC, int ST, bool RAW>
+__global__ __launch_bounds__(64 * WR * WC, gemm_waves(WR * WC, ST)) void k_resgemm(GemmArgs args, int L, XcdMap xm) {
     uint32_t mt = blockIdx.y, nt = blockIdx.x, zi = blockIdx.z;
     if (xm.on) {
         const uint32_t b = blockIdx.x, x = b & 7u, s = b >> 3, t8 = xm.h * xm.w;
@@ -1372,13 +1426,13 @@ __global__ __launch_bounds__(256) void k_resgemm(GemmArgs args, int L, XcdMap xm
         nt = (x % xm.rx) * xm.w + u % xm.w;
     }
     const int l = RAW ? 0 : L - 1 - (int)zi;
-    gemm_tile<WM, WN, RAW>(args, mt, nt, l);
+    gemm_tile<WR, WC, ST, RAW>(args, mt, nt, l);
 }
 
 // one residue GEMM of a complex product (the 3M / 4M schemes): the plain launch's block
 // order and tiles, the output combined into V (and V2) by MODE
-template <int WM, int WN, int MODE>
-__global__ __launch_bounds__(256) void k_resgemm_z(GemmArgsZ args, int L, XcdMap xm) {
+template <int WR, int WC, int ST, int MODE>
+__global__ __launch_bounds__(64 * WR * WC, gemm_waves(WR * WC, ST)) void k_resgemm_z(GemmArgsZ args, int L, XcdMap xm) {
     uint32_t mt = blockIdx.y, nt = blockIdx.x, zi = blockIdx.z;
     if (xm.on) {
         const uint32_t b = blockIdx.x, x = b & 7u, s = b >> 3, t8 = xm.h * xm.w;
@@ -1387,7 +1441,7 @@ __global__ __launch_bounds__(256) void k_resgemm_z(GemmArgsZ args, int L, XcdMap
         mt = (x / xm.rx) * xm.h + u / xm.w;
         nt = (x % xm.rx) * xm.w + u % xm.w;
     }
-    gemm_tile<WM, WN, false, 3, MODE, GemmArgsZ>(args, mt, nt, L - 1 - (int)zi);
+    gemm_tile<WR, WC, ST, false, MODE, GemmArgsZ>(args, mt, nt, L - 1 - (int)zi);
 }
 
 // ---- 256 x 256 tiles

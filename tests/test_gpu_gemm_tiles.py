@@ -1,0 +1,81 @@
+"""The four- and eight-wave residue GEMM tiles (marked gpu): both depths of the k-loop with even
+and odd counts of 128-byte k-tiles, one and three products per modulus, thin tiles, against int64
+products and against the same calls on another fixed tile, bit for bit."""
+import math
+
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import dev_mp, need_gpu
+from tests.test_gpu_gemm256 import _planes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oz():
+    need_gpu()
+    from paper_2609_27831_amd import oz2h
+    return oz2h
+
+
+# few blocks and kpad >= 512: four stages; otherwise two
+@pytest.mark.parametrize("p,mpad,npad,kpad,tile", [(53, 128, 128, 128, 1), (53, 128, 128, 512, 1), (256, 128, 128, 640, 1),
+                                                   (256, 256, 256, 640, 1), (53, 256, 128, 640, 2), (256, 512, 384, 384, 2),
+                                                   (53, 128, 256, 768, 3), (600, 128, 128, 128, 1), (600, 128, 128, 896, 1)])
+def test_stage_mod_m(oz, p, mpad, npad, kpad, tile):
+    import torch
+    plan = oz.Plan.create(p, kpad, oz.default_opts(tile=tile))
+    rng = np.random.default_rng(p + kpad)
+    A, B = _planes(rng, plan, mpad, kpad), _planes(rng, plan, npad, kpad)
+    print(f"residue gemm p={p} {mpad}x{npad}x{kpad} tile {tile}", flush=True)
+    v = oz.residue_gemm(plan, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda())
+    v = v.cpu().numpy().astype(np.int64)
+    P = math.prod(plan.moduli.tolist())
+    for li, m in enumerate(plan.moduli.tolist()):
+        g0 = li if li < plan.L1 else plan.L1 + 3 * (li - plan.L1)
+        a, b = A[g0].astype(np.float64), B[g0].astype(np.float64)
+        if m > 255:
+            a = a + 128.0 * A[g0 + 1]
+            b = b + 128.0 * B[g0 + 1]
+        prod = (a @ b.T).astype(np.int64)   # exact: below 2^53
+        minv = pow((P // m) % m, -1, m)
+        assert np.abs(v[li]).max() <= m // 2, f"modulus {m}: not centred"
+        assert np.array_equal(np.mod(v[li], m), np.mod(np.mod(prod, m) * minv, m)), f"modulus {m}"
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(128, 128, 128, 1)] + [(*s, t) for t in (1, 2, 3) for s in (
+    (256, 256, 640), (2304, 2048, 384), (256, 768, 1024))])
+def test_i8gemm(oz, M, N, K, tile):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A, B = (torch.randint(-127, 128, (r, K), dtype=torch.int8, device="cuda", generator=g) for r in (M, N))
+    print(f"i8gemm {M}x{N}x{K} tile {tile}", flush=True)
+    C = oz.i8gemm(A, B, tile)
+    ref = A.cpu().double().numpy() @ B.cpu().double().numpy().T   # exact: below 2^53
+    assert np.array_equal(C.cpu().numpy(), ref.astype(np.int32))
+
+
+# up to 64 rows or columns take 64-wide tiles; one more does not
+@pytest.mark.parametrize("M,N,K", [(300, 1, 130), (256, 64, 700), (257, 65, 130), (1, 300, 700), (64, 256, 130), (33, 900, 1100)])
+@pytest.mark.parametrize("p,flags", [(113, 0), (600, 0), (1024, 0), (300, 3)])
+def test_thin_products_against_square_tiles(oz, M, N, K, p, flags):
+    import torch
+    A, B = dev_mp(synth.mp_random(M, M, K, p, -9, 9)), dev_mp(synth.mp_random(N, K, N, p, -9, 9))
+    print(f"thin {M}x{N}x{K} p={p} flags={flags}", flush=True)
+    C = oz.gemm(oz.Plan.create(p, K, oz.default_opts(flags=flags)), A, B)
+    D = oz.gemm(oz.Plan.create(p, K, oz.default_opts(flags=flags, tile=oz.TILE_128x128)), A, B)
+    assert all(torch.equal(a, b) for a, b in ((C.sign, D.sign), (C.exp, D.exp), (C.limbs, D.limbs)))
+
+
+@pytest.mark.parametrize("scheme", [3, 4])
+def test_complex_depths(oz, scheme):
+    import torch
+    M, N, K, p = 100, 90, 600, 53
+    X = [dev_mp(synth.mp_random(20 + i, *s, p, -5, 5)) for i, s in enumerate([(M, K), (M, K), (K, N), (K, N)])]
+    print(f"complex scheme {scheme}", flush=True)
+    R = [oz.zgemm(oz.Plan.create(p, 2 * K, oz.default_opts(tile=t)), *X, scheme=scheme) for t in (0, 2, 3)]
+    for other in R[1:]:
+        for a, b in zip(R[0], other):
+            assert torch.equal(a.sign, b.sign) and torch.equal(a.exp, b.exp) and torch.equal(a.limbs, b.limbs)
