@@ -514,7 +514,8 @@ typedef struct oz2h_batched_plan oz2h_batched_plan;
  * of every large (product, modulus) tile grid.  o->tile fixes the block tile of
  * every product; OZ2H_TILE_AUTO takes a previously tuned configuration for the
  * same shapes if the process has one (see oz2h_batched_tune), else the tile a
- * plain call would choose for each product, one block per work item.
+ * plain call would choose for each product, one block per work item (and a launch
+ * of its own for a product of 256x256 tiles).
  */
 int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2h_opts *o,
                              oz2h_batched_plan **out);
@@ -553,7 +554,8 @@ int oz2h_batched_run_eager(oz2h_batched_plan *plan, void *workspace, size_t ws_b
                            hipStream_t stream);
 /* Current block tile setting (oz2h_tile; OZ2H_TILE_AUTO: per product), resident blocks
    per compute unit (0: one block per work item instead of a persistent grid), GEMM work
-   items (placeholders that keep the XCD alignment included). */
+   items (placeholders that keep the XCD alignment and the 256x256 tiles of products that
+   get a launch of their own included). */
 int oz2h_batched_get_config(const oz2h_batched_plan *plan, int32_t *tile, int32_t *blocks_per_cu,
                             int64_t *gemm_items);
 /* Sets the tile setting (0..3) and blocks per compute unit (0..16) by hand. */

@@ -377,8 +377,7 @@ XcdMap xcd_map_for(GemmCfg cfg, dim3 &grid) {
 // The 256 x 256 kernel over every (modulus, tile): one persistent block per compute unit.
 constexpr int kGemm8Blocks = 256;   // compute units of an MI355X (a multiple of the 8 XCDs)
 
-int launch_gemm8(const oz2h_plan *pl, int64_t mpad, int64_t npad, const GemmArgsZ &g, int mode, hipStream_t s) {
-    const PlanHost &h = pl->h;
+int launch_gemm8(const PlanHost &h, int64_t mpad, int64_t npad, const GemmArgsZ &g, int mode, hipStream_t s) {
     dim3 grid((unsigned)(npad / 256), (unsigned)(mpad / 256), 1);
     Gemm8Args a{g, h.L, h.L1, (int)grid.y, (int)grid.x, {}};
     a.xm = xcd_map_for(GemmCfg{256, 256}, grid);
@@ -427,7 +426,7 @@ int launch_resgemm(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npad,
                    int64_t b_ps = 0) {
     const PlanHost &h = pl->h;
     if (cfg.bm == 256 && cfg.bn == 256)
-        return launch_gemm8(pl, mpad, npad,
+        return launch_gemm8(h, mpad, npad,
                             GemmArgsZ{{a, b, kpad, a_ps ? a_ps : mpad * kpad, b_ps ? b_ps : npad * kpad,
                                        pl->d_info, v, mpad * npad, npad, nullptr}, nullptr}, ZSTORE, s);
     dim3 grid((unsigned)(npad / cfg.bn), (unsigned)(mpad / cfg.bm), (unsigned)h.L);
@@ -1377,7 +1376,7 @@ int launch_resgemm_z(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npa
     const PlanHost &h = pl->h;
     dim3 grid((unsigned)(npad / cfg.bn), (unsigned)(mpad / cfg.bm), (unsigned)h.L);
     const GemmArgsZ g{{a, b, kpad, mpad * kpad, npad * kpad, pl->d_info, v, mpad * npad, npad, nullptr}, v2};
-    if (cfg.bm == 256 && cfg.bn == 256) return launch_gemm8(pl, mpad, npad, g, mode, s);
+    if (cfg.bm == 256 && cfg.bn == 256) return launch_gemm8(h, mpad, npad, g, mode, s);
     const XcdMap xm = xcd_map_for(cfg, grid);
     const bool deep = gemm_deep(grid, kpad);
 #define OZ2H_ZG(WR, WC, ST)                                                                            \
@@ -1916,6 +1915,7 @@ inline int res_class(int nw32) {
 
 struct BatchChunk {
     std::vector<int> prods;
+    std::vector<int> big;   // of those, the ones with 256 x 256 GEMM tiles (upload_items)
     Seg *d_fill_segs = nullptr, *d_exp_segs = nullptr;
     int n_fill_segs = 0, n_exp_segs = 0;
     int64_t fill_blocks = 0, exp_blocks = 0;
@@ -2022,11 +2022,15 @@ void tune_store(uint64_t sig, const TuneRec &r) {
 // with skipped items), so each XCD's L2 holds only its rectangle's rows of A and columns of B.
 // Groups go in decreasing cost (longer k-loops first); groups of fewer than 8 tiles, which
 // have no such locality to gain, follow at the end in the same order.
-// tile class (oz2h_tile - 1) of product b under the plan's tile setting
+// tile class (oz2h_tile - 1) of product b under the plan's tile setting, or kBigTiles: 256 x 256
+// tiles where a plain call would take them, a launch per product (64 products of 128 .. 4096,
+// p = 53 .. 512: 28.9 ms with every product in the grouped launch, 26.4 so)
+constexpr int kBigTiles = 3;
 int item_class(const oz2h_batched_plan *bp, int b) {
     if (bp->tile != OZ2H_TILE_AUTO) return bp->tile - 1;
-    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO, bp->pd[b].kpad, 0);
-    return c.bm == 256 ? OZ2H_TILE_256x128 - 1 : (c.bn == 256 ? OZ2H_TILE_128x256 - 1 : OZ2H_TILE_128x128 - 1);
+    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO, bp->pd[b].kpad, 
+                                   bp->hosts[b].L);
+    return c.bm == 256 ? kBigTiles : OZ2H_TILE_128x128 - 1;
 }
 
 std::vector<GemmItem> make_items(const oz2h_batched_plan *bp, const BatchChunk &ch, GemmCfg cfg, int cls) {
@@ -2088,7 +2092,10 @@ std::vector<GemmItem> make_items(const oz2h_batched_plan *bp, const BatchChunk &
 }
 
 int upload_items(oz2h_batched_plan *bp) {
-    for (BatchChunk &ch : bp->chunks)
+    for (BatchChunk &ch : bp->chunks) {
+        ch.big.clear();
+        for (int b : ch.prods)
+            if (item_class(bp, b) == kBigTiles) ch.big.push_back(b);
         for (int c = 0; c < 3; ++c) {
             std::vector<GemmItem> items = make_items(bp, ch, tile_cfg(c + 1), c);
             if (ch.d_items[c]) (void)hipFree(ch.d_items[c]);
@@ -2101,6 +2108,7 @@ int upload_items(oz2h_batched_plan *bp) {
             OZ2H_HIP(hipMemcpy(ch.d_items[c], items.data(), items.size() * sizeof(GemmItem),
                                hipMemcpyHostToDevice));
         }
+    }
     return OZ2H_OK;
 }
 
@@ -2113,6 +2121,15 @@ void drop_graph(oz2h_batched_plan *bp) {
 }
 
 int launch_batched_gemm(oz2h_batched_plan *bp, const BatchChunk &ch, char *ws, hipStream_t s) {
+    for (int b : ch.big) {
+        const ProbDev &P = bp->pd[b];
+        const int st = launch_gemm8(bp->hosts[b], round_up(P.rows[0], 256), round_up(P.rows[1], 256),
+                                    GemmArgsZ{{(const int8_t *)(ws + P.planes_off[0]), (const int8_t *)(ws + P.planes_off[1]),
+                                               P.kpad, P.rpad[0] * P.kpad, P.rpad[1] * P.kpad, P.mi,
+                                               (int16_t *)(ws + P.v_off), P.rpad[0] * P.rpad[1], P.rpad[1], nullptr}, nullptr},
+                                    ZSTORE, s);
+        if (st) return st;
+    }
     for (int c = 0; c < 3; ++c) {
         const int n = ch.nitems[c];
         if (!n) continue;
@@ -2357,7 +2374,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         P.rpad[0] = round_up(q.M, 256);
         P.rpad[1] = round_up(q.N, 256);
         P.K = q.K;
-        P.kpad = round_up(q.K, GBK);
+        P.kpad = kpad_for(q.K);
         P.p = h.p;
         P.nl = (h.p + 63) / 64;
         P.t = h.t;
@@ -2624,7 +2641,11 @@ int oz2h_batched_get_config(const oz2h_batched_plan *plan, int32_t *tile, int32_
     if (blocks_per_cu) *blocks_per_cu = plan->bpc;
     if (gemm_items) {
         int64_t n = 0;
-        for (const BatchChunk &ch : plan->chunks) n += (int64_t)ch.nitems[0] + ch.nitems[1] + ch.nitems[2];
+        for (const BatchChunk &ch : plan->chunks) {
+            n += (int64_t)ch.nitems[0] + ch.nitems[1] + ch.nitems[2];
+            for (int b : ch.big)
+                n += plan->hosts[b].L * ((plan->pd[b].rows[0] + 255) / 256) * ((plan->pd[b].rows[1] + 255) / 256);
+        }
         *gemm_items = n;
     }
     return ok();

@@ -79,3 +79,27 @@ def test_complex_depths(oz, scheme):
     for other in R[1:]:
         for a, b in zip(R[0], other):
             assert torch.equal(a.sign, b.sign) and torch.equal(a.exp, b.exp) and torch.equal(a.limbs, b.limbs)
+
+
+def test_batch_of_every_gemm_class(oz):
+    """Products with 256 x 256 tiles (their own launches), ordinary and thin ones in one batch,
+    and the same batch with every product in the grouped launch, against plain calls."""
+    import torch
+    probs = []
+    for i, (M, N, K, p) in enumerate([(1024, 1000, 1100, 256), (130, 140, 150, 53), (20, 700, 90, 113), (1500, 1530, 250, 113),
+                                      (300, 300, 1025, 400), (770, 1020, 500, 512)]):
+        A, B = dev_mp(synth.mp_random(60 + i, M, K, p, -6, 6)), dev_mp(synth.mp_random(80 + i, K, N, p, -6, 6))
+        probs.append((A, B, oz.empty_mp(M, N, p), 0, 0))
+    bp = oz.BatchedPlan(probs)
+    ws = bp.workspace()
+    refs = [oz.gemm(oz.Plan.create(A.p, A.shape[1]), A, B) for A, B, _, _, _ in probs]
+    for tile in (oz.TILE_AUTO, oz.TILE_256x128, oz.TILE_AUTO):
+        bp.set_config(tile, 0)
+        print(f"batch over the GEMM classes, tile {tile}", flush=True)
+        for _ in range(2):
+            for _, _, C, _, _ in probs:
+                C.limbs.zero_()
+            bp.run(ws)
+            torch.cuda.synchronize()
+            for (_, _, C, _, _), R in zip(probs, refs):
+                assert torch.equal(R.sign, C.sign) and torch.equal(R.exp, C.exp) and torch.equal(R.limbs, C.limbs)
