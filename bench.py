@@ -216,10 +216,10 @@ def kernel_names(plan, flags):
         res = "k_residues_mma"
     else:
         res = "k_residues_row" if plan.nw32 >= 24 else "k_residues"
-    if (flags & oz2h.FLAG_CRT_MMA) and 16 <= plan.nd32 <= 32 and plan.L <= 127:
+    if (flags & oz2h.FLAG_CRT_MMA) and 16 <= plan.nd32 <= 160 and plan.L <= (127 if plan.nd32 <= 32 else 255):
         crt = "k_crt_mma"
     else:
-        crt = "k_crt_row_sums" if plan.nd32 > 32 else "k_crt"
+        crt = "k_crt_row_sums" if plan.nd32 > 48 else "k_crt_units"
     return res, crt
 
 

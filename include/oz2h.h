@@ -92,7 +92,9 @@ typedef struct {
  *                           words (t >= 224), the VALU kernel below that;
  *   OZ2H_FLAG_CRT_MMA       CRT digit sums as (bytes of v_l) x (bytes of P/m_l)
  *                           INT8 products; taken when the CRT has 16..32 digits
- *                           and L <= 127, the VALU kernel otherwise.
+ *                           and L <= 127, and by products other than batched
+ *                           ones on plans created with the flag also for 33..160
+ *                           digits and L <= 255; the VALU kernels otherwise.
  * Both variants give bit-identical results.
  *
  * Backend flags (read when the plan is created; oz2h_plan_set_flags cannot change

@@ -489,11 +489,13 @@ CrtUnitsCfg crt_units_config(const PlanHost &h, int64_t M, int64_t N, bool group
     return c;
 }
 
-// the matrix-core CRT (compared variant): selected by the plan's flags, digit columns in
-// LDS, tables built, enough digits to pay off
-bool crt_mma_eligible(const PlanHost &h, const CrtCfg &c) {
-    return (h.flags & OZ2H_FLAG_CRT_MMA) && !c.gdig && h.crt_mma && h.crt_kq <= kCrtMmaMaxQ &&
-           h.nd32 >= kCrtMmaMinDigits;
+// the matrix-core CRT (compared variant): selected by the plan's flags, tables built, enough
+// digits to pay off.  wide: its form beyond 32 digits (weighted residues of plain calls), against
+// the kernels below 2048^2 entries, p = 520 0.64 / 0.79 ms, 640 0.72 / 1.41, 1024 1.42 / 3.21,
+// 1400 2.90 / 4.70; 3072^2, p = 1024 3.2 / 7.5 (a plan whose flag is set after its creation has
+// no wide tables)
+bool crt_mma_eligible(const PlanHost &h, bool wide) {
+    return (h.flags & OZ2H_FLAG_CRT_MMA) && h.crt_mma && h.nd32 >= kCrtMmaMinDigits && (wide || h.nd32 <= 32);
 }
 
 // The row-broadcast CRT (wide moduli sets): entries e' = i * ldv + j over M rows of v planes
@@ -539,7 +541,7 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
                      pl->d_pd, pl->d_phd, e, f, tsum, h.p, osign, oexp, olimbs, ldc, chat, nlc, c.LB,
                      nullptr, 0, pl->d_crt_afr, h.crt_nbk, h.crt_kq,
                      h.crt_nt, h.crt_inv_ptop, pl->d_crt_units, pl->d_crt_udig, h.crt_npair};
-    if (gdig && row_crt_eligible(h) && !crt_mma_eligible(h, c) && (weight || h.nd32 > kCrtUnitMaxDigits)) {
+    if (gdig && row_crt_eligible(h) && !crt_mma_eligible(h, !weight) && (weight || h.nd32 > kCrtUnitMaxDigits)) {
         // row-broadcast CRT: the planes must hold M * ldu entries each, 32-byte aligned rows
         const RowCrtCfg rc = row_crt_config(h, M, ldu);
         if (ldu % 16 == 0 && u_ps >= M * ldu && u_ps % 16 == 0 && ((uintptr_t)u % 32) == 0) {
@@ -560,13 +562,35 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
             return check_launch("CRT finish");
         }
     }
-    if (crt_mma_eligible(h, c)) {
+    if (h.nd32 > 32 && crt_mma_eligible(h, !weight)) {
+        // one wave per block: 64 entries, a digit column each (an LDS of up to 40 KiB)
+        const unsigned nbm = (unsigned)((M * N + 63) / 64);
+        const size_t ldsm = (size_t)64 * h.nd32 * sizeof(uint32_t);
+#define OZ2H_CRTM(KQ)                                                                  \
+    case KQ:                                                                           \
+        if (round) k_crt_mma<KQ, true, false, 64><<<nbm, 64, ldsm, s>>>(ca);           \
+        else k_crt_mma<KQ, false, false, 64><<<nbm, 64, ldsm, s>>>(ca);                \
+        break
+        switch (h.crt_kq) {
+            OZ2H_CRTM(6);
+            OZ2H_CRTM(8);
+            OZ2H_CRTM(10);
+            OZ2H_CRTM(12);
+            OZ2H_CRTM(14);
+            OZ2H_CRTM(16);
+            default: return fail(OZ2H_EINVAL, "CRT: no kernel for %d steps", h.crt_kq);
+        }
+#undef OZ2H_CRTM
+        static_assert(kCrtMmaWideQ == 16, "one case per even step count");
+        return check_launch("CRT");
+    }
+    if (crt_mma_eligible(h, false)) {
         // matrix-core digit sums: 256 entries per block, one LDS digit column each
         const unsigned nbm = (unsigned)((M * N + 255) / 256);
         const size_t ldsm = (size_t)256 * h.nd32 * sizeof(uint32_t);
-        if (weight) k_crt_mma<kCrtMmaMaxQ, false, true><<<nbm, 256, ldsm, s>>>(ca);
-        else if (round) k_crt_mma<kCrtMmaMaxQ, true, false><<<nbm, 256, ldsm, s>>>(ca);
-        else k_crt_mma<kCrtMmaMaxQ, false, false><<<nbm, 256, ldsm, s>>>(ca);
+        if (weight) k_crt_mma<kCrtMmaMaxQ, false, true, 256><<<nbm, 256, ldsm, s>>>(ca);
+        else if (round) k_crt_mma<kCrtMmaMaxQ, true, false, 256><<<nbm, 256, ldsm, s>>>(ca);
+        else k_crt_mma<kCrtMmaMaxQ, false, false, 256><<<nbm, 256, ldsm, s>>>(ca);
         return check_launch("CRT");
     }
     if (!weight && h.nd32 <= kCrtUnitMaxDigits && u_ps % 2 == 0 && ldu % 2 == 0 && (uintptr_t)u % 4 == 0) {
@@ -1097,6 +1121,7 @@ int oz2h_plan_create(int32_t p, int64_t K, const oz2h_opts *o, oz2h_plan **out) 
     int st = select_moduli(p, K, o->guard_bits, o->t_bits, o->crt_margin, mods, t, lp, err);
     if (st) return fail(st, "%s", err.c_str());
     oz2h_plan *pl = new oz2h_plan();
+    pl->h.crt_mma_wide = (o->flags & OZ2H_FLAG_CRT_MMA) != 0;
     st = build_plan(p, t, K, mods, pl->h, err);
     if (st) {
         delete pl;
@@ -1648,6 +1673,7 @@ int oz2h_plan_create_grad(int32_t p, int64_t M, int64_t N, int64_t K, const oz2h
     st = select_moduli_bits(need, mods, lp, err);
     if (st) return fail(st, "%s", err.c_str());
     oz2h_plan *pl = new oz2h_plan();
+    pl->h.crt_mma_wide = (o->flags & OZ2H_FLAG_CRT_MMA) != 0;
     st = build_plan(p, t, K, mods, pl->h, err, std::max(twa, twb));
     if (st) {
         delete pl;
@@ -2467,7 +2493,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         for (int b : ch.prods) {
             const PlanHost &h = bp->hosts[b];
             const CrtCfg cc = crt_config(h, probs[b].M, probs[b].N, true);
-            if (crt_mma_eligible(h, cc)) classes[std::make_tuple(-1, 1, 0)].push_back(b);
+            if (crt_mma_eligible(h, false)) classes[std::make_tuple(-1, 1, 0)].push_back(b);
             else if (h.nd32 <= kCrtUnitMaxDigits) classes[std::make_tuple(0, crt_unit_ept(h.crt_und), h.crt_und)].push_back(b);
             else classes[std::make_tuple(h.crt_dc, cc.ept, 0)].push_back(b);
         }

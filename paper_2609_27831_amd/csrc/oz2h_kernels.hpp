@@ -2402,7 +2402,8 @@ __global__ __launch_bounds__(256) void k_crt_units(CrtArgs a) {
     crt_units_block<ND, EPT, ROUND>(a, blockIdx.x, sdig);
 }
 
-// Direct CRT on the matrix cores (digit columns in LDS: nd32 <= 32, L <= 127).  The
+// Direct CRT on the matrix cores (digit columns in LDS: nd32 <= 32, L <= 127, blocks of 256
+// entries; wider sets, up to nd32 <= kCrtMmaMaxDigits and L <= 255, blocks of 64).  The
 // digit sums S = sum_l v_l M_l are formed as the int8 product (byte rows of S) x
 // (entries) of the tables of build_crt_mma_tables with each v_l's two bytes; one wave
 // covers 64 consecutive entries as two 32-entry column blocks.
@@ -2417,19 +2418,25 @@ __global__ __launch_bounds__(256) void k_crt_units(CrtArgs a) {
 //   paper's alpha - 1 (at most two subtractions of P follow in crt_finish).  Then the
 //   column receives S - beta P and crt_finish lifts and rounds as in k_crt.
 constexpr int kCrtMmaMaxQ = 8;   // contraction steps of the matrix-core CRT (2 L + 1 <= 256)
+constexpr int kCrtMmaWideQ = 16; // ... of the wide form (2 L + 1 <= 512), in steps of two from 6 on
 // below this many digits (p <~ 180) the fp64 CRT is faster: the matrix-core kernel's
 // per-entry carry and subtraction passes outweigh its L x nd32 multiply-adds
 constexpr int kCrtMmaMinDigits = 16;
 
 // WEIGHT = true: the planes hold plain residues u_l (any representative, |u_l| < m_l),
 // weighted here to v_l = u_l (P/m_l)^-1 mod m_l (the stage-4 parity entry point).
-template <int KQ, bool ROUND, bool WEIGHT = false>
+// BT: threads of the block.  BT = 64 (the wide form): the tables have exactly KQ steps, so the
+// step loop has no guards and its loads go out together.  What bounds the wide form: the carries
+// and the subtraction per digit and the fragment reads (108 KiB per wave at 70 digits and 182
+// moduli); its products alone take 0.5 of 3.2 ms at 3072^2, p = 1024.
+template <int KQ, bool ROUND, bool WEIGHT = false, int BT = 256>
 __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uint32_t *sdig) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int h = lane >> 5, c = lane & 31;
     const int nd32 = a.nd32, L = a.L, kq = a.kq, nbk = a.nbk;
     const int64_t N = a.N, MN = a.M * N, v_ps = a.v_ps;
-    const int64_t e0 = blk * 256 + wv * 64;
+    constexpr bool EXACT = BT == 64;   // kq == KQ
+    const int64_t e0 = blk * BT + wv * 64;
     typedef const __attribute__((address_space(1))) uint16_t gu16;
     typedef const __attribute__((address_space(1))) v4i gv4i;
     typedef const __attribute__((address_space(4))) uint32_t cu32;
@@ -2448,7 +2455,7 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
         }
 #pragma unroll
         for (int q = 0; q < KQ; ++q) {
-            if (q < kq) {
+            if (EXACT || q < kq) {
                 const bool full = 16 * q + 16 <= L;   // wave-uniform
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
@@ -2490,14 +2497,14 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
 
     // S: eight digits per block of 32 byte rows, carried into this lane's LDS column
     gv4i *af = (gv4i *)a.afr + lane;
-    uint32_t *col = sdig + tid;   // digit k at col[256 k]
+    uint32_t *col = sdig + tid;   // digit k at col[BT k]
     int64_t carry = 0;
     for (int nb = 0; nb < nbk; ++nb) {
         v16i acc0 = v16i{}, acc1 = v16i{};
 #pragma unroll
         for (int q = 0; q < KQ; ++q)
-            if (q < kq) {
-                const v4i f = af[((size_t)nb * kq + q) * 64];
+            if (EXACT || q < kq) {
+                const v4i f = af[((size_t)nb * (EXACT ? KQ : kq) + q) * 64];
                 acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f, bf0[q], acc0, 0, 0, 0);
                 acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(f, bf1[q], acc1, 0, 0, 0);
             }
@@ -2520,33 +2527,33 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
             const int64_t D = (dk & 1) == h ? mine[dk >> 1] : got[dk >> 1];
             if (k < nd32) {
                 const int64_t x = D + carry;
-                col[256 * k] = (uint32_t)x;
+                col[BT * k] = (uint32_t)x;
                 carry = x >> 32;
             }
         }
     }
 
     // beta from S / P, then S - beta P into the column
-    double val = (double)(int32_t)col[256 * (nd32 - 1)];
-    for (int k = nd32 - 2; k >= nd32 - a.nt; --k) val = val * 4294967296.0 + (double)col[256 * k];
+    double val = (double)(int32_t)col[BT * (nd32 - 1)];
+    for (int k = nd32 - 2; k >= nd32 - a.nt; --k) val = val * 4294967296.0 + (double)col[BT * k];
     const double est = val * a.inv_ptop, r = rint(est);
     const bool slow = fabs(est - r) > 0.5 - 0x1p-30;
     const int64_t beta = slow ? (int64_t)floor(est) - 1 : (int64_t)r;
     cu32 *Pd = (cu32 *)a.Pd;
     int64_t cy = 0;
     for (int k = 0; k < nd32; ++k) {
-        const int64_t x = (int64_t)col[256 * k] - beta * (int64_t)Pd[k] + cy;
-        col[256 * k] = (uint32_t)x;
+        const int64_t x = (int64_t)col[BT * k] - beta * (int64_t)Pd[k] + cy;
+        col[BT * k] = (uint32_t)x;
         cy = x >> 32;
     }
     const int64_t e = e0 + lane;
-    if (e < MN) crt_finish<ROUND>(a, e / N, e % N, col, 256, slow, cy + carry);
+    if (e < MN) crt_finish<ROUND>(a, e / N, e % N, col, BT, slow, cy + carry);
 }
 
-template <int KQ, bool ROUND, bool WEIGHT>
-__global__ __launch_bounds__(256) void k_crt_mma(CrtArgs a) {
+template <int KQ, bool ROUND, bool WEIGHT, int BT>
+__global__ __launch_bounds__(BT, BT == 64 ? 2 : 1) void k_crt_mma(CrtArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t sdig[];
-    crt_mma_block<KQ, ROUND, WEIGHT>(a, blockIdx.x, sdig);
+    crt_mma_block<KQ, ROUND, WEIGHT, BT>(a, blockIdx.x, sdig);
 }
 
 // Direct CRT for wide moduli sets on the vector ALUs with row broadcasts (no MFMA), in two

@@ -199,7 +199,8 @@ int select_moduli_bits(double need, std::vector<uint32_t> &mods, double &log2P, 
     return 0;
 }
 
-// Tables of the matrix-core CRT (digit columns in LDS, nd32 <= 32, L <= 127).  The digit
+// Tables of the matrix-core CRT (digit columns in LDS; beyond nd32 = 32 only for plans whose
+// flags select it, an even number of contraction steps).  The digit
 // sums S = sum_l v_l M_l (M_l = P/m_l) are an int8 product: v_l = Lo + 256 Hi with Lo its
 // low byte (fed as Lo - 128) and Hi its signed high byte, so with b_{l,j} the balanced
 // base-256 digits of M_l the byte column j of S is
@@ -210,10 +211,12 @@ int select_moduli_bits(double need, std::vector<uint32_t> &mods, double &log2P, 
 void build_crt_mma_tables(PlanHost &h, const std::vector<uint32_t> &mods, const Nat &P) {
     h.crt_mma = false;
     h.crt_afr.clear();
-    if (h.nd32 > 32 || h.L > 127) return;
+    const bool wide = h.nd32 > 32;
+    if (wide ? !h.crt_mma_wide || h.nd32 > kCrtMmaMaxDigits || h.L > 255 : h.L > 127) return;
     const int nb = 4 * h.nd32;                // byte rows of S
     h.crt_nbk = (nb + 31) / 32;               // blocks of 32 byte rows (8 digits)
     h.crt_kq = (2 * h.L + 1 + 31) / 32;       // 32-byte contraction steps
+    if (wide) h.crt_kq += h.crt_kq % 2;
     const int rows = 32 * h.crt_nbk, kk = 32 * h.crt_kq;
     std::vector<int8_t> T((size_t)rows * kk, 0);
     Nat sum;
@@ -510,7 +513,9 @@ int build_plan(int p, int t, int64_t K, const std::vector<uint32_t> &mods_in, Pl
                 return -1;
             }
     }
+    const bool crt_mma_wide = h.crt_mma_wide;
     h = PlanHost{};
+    h.crt_mma_wide = crt_mma_wide;
     h.p = p;
     h.t = t;
     h.K = K;

@@ -29,6 +29,7 @@ constexpr int kCrtRowMinDigits = 32;  // the row-broadcast CRT's least digits (p
 // (2048^2 entries, units against rows: 37 digits 0.65 / 1.26 ms, 45: 1.24 / 1.46, 56: 2.1 - 2.3 /
 // 2.3, 62: 2.6 - 2.8 / 2.6)
 constexpr int kCrtUnitMaxDigits = 48;
+constexpr int kCrtMmaMaxDigits = 160;   // of the matrix-core CRT
 // ... its digits in steps of 2 up to 32 and of 4 above, one kernel each
 constexpr int crt_unit_digits(int nd32) { return nd32 <= 32 ? (nd32 + 1) / 2 * 2 : (nd32 + 3) / 4 * 4; }
 constexpr int kMaxModuli = 512;       // fp64-exact CRT digit sums need L * 2^44 < 2^53
@@ -161,7 +162,9 @@ struct PlanHost {
     int crt_ndg = 0;       // row-broadcast CRT: groups of 16 digits
     int crt_lpad = 0;      // ... moduli padded to a multiple of 16
     std::vector<double> crt_row;     // [16 crt_ndg][crt_lpad]: digit d of P/m_l at [d][l]
-    bool crt_mma = false;  // matrix-core CRT tables built (nd32 <= 32, L <= 127)
+    bool crt_mma_wide = false;   // set before build_plan: its tables beyond nd32 = 32 as well
+    bool crt_mma = false;  // matrix-core CRT tables built (nd32 <= 32, L <= 127; wide: nd32 <=
+                           // kCrtMmaMaxDigits, L <= 255)
     int crt_nbk = 0;       // ... blocks of 32 byte rows of S
     int crt_kq = 0;        // ... 32-byte contraction steps (2 L + 1 bytes)
     int crt_nt = 0;        // top digits of S that estimate S / P (every CRT kernel)
