@@ -328,9 +328,16 @@ int launch_residues(const oz2h_plan *pl, const ResSide *sides, int n, hipStream_
     int64_t nblk[2] = {0, 0};
     for (int i = 0; i < n; ++i) nblk[i] = (sides[i].kpad / 128) * (rpad(sides[i]) / res_block_rows(h.nw32));
     if (nblk[0] + nblk[1] > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
-    const ResArgs a{{sides[0], sides[n - 1]}, nblk[0],
+    // Few entries leave compute units idle or with one short-lived block: the unit groups are
+    // then shared out over up to four blocks, each building the words again (parts 1, 2, 3, 4, 6:
+    // 32 blocks, 16^3, p = 53 9.6, 8.8, 8.1, 8.1, 8.0 us; 128 blocks, 256^3, p = 128 17.7, 15.1,
+    // 16.8, 16.9, 18.8, 200^3, p = 256 35, 25, 24, 23, 24; 384 blocks, p = 256 35.9, 32.5, 38; 1152
+    // blocks, p = 113 29, 34, 40).
+    const int64_t blocks = nblk[0] + nblk[1];
+    const int parts = h.nw32 > kResRegWords || blocks > 512 ? 1 : std::min(blocks > 64 ? 2 : 4, h.rgroups);
+    const ResArgs a{{sides[0], sides[n - 1]}, nblk[0], parts,
                     {pl->d_resid, pl->d_rgrp, h.p, nl, t, h.nw32, h.rgroups}};
-    const dim3 grid((unsigned)(nblk[0] + nblk[1]));
+    const dim3 grid((unsigned)(nblk[0] + nblk[1]), parts);
     const size_t lds = res_wave_lds(h.nw32) * kResWaves;
 #define OZ2H_RES_NW(NW) case NW: k_residues<NW><<<grid, 64 * kResWaves, lds, s>>>(a); break
     switch (h.nw32) {

@@ -390,7 +390,7 @@ __host__ __device__ constexpr size_t res_wave_lds(int nw) { return (size_t)64 * 
 
 template <int NW>
 __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb, int64_t bx, int64_t by,
-                                             uint32_t *words) {
+                                             uint32_t *words, int part = 0, int parts = 1) {
     constexpr int EPT = NW > 0 ? 4 : 2, NE = 64 * EPT;
     constexpr int NG = NW > 0 ? 1 : 4;   // groups per pass over the words
     typedef uint32_t vEu __attribute__((ext_vector_type(EPT)));
@@ -408,6 +408,7 @@ __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb,
     typedef const __attribute__((address_space(4))) double cdouble;
     cgrp *grec = (cgrp *)tb.grp;
     if (r0 >= a.rows || k0 >= a.count) {   // padding only
+        if (part) return;
         const int64_t G = grec[tb.groups - 1].g0 + grec[tb.groups - 1].nplanes;
         for (int64_t g = 0; g < G; ++g) *(g_bytes *)(planes + g * a.plane_stride + loff) = 0;
         return;
@@ -457,7 +458,8 @@ __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb,
     constexpr double kMagic = 6755399441055744.0;   // 1.5 2^52
     auto low = [](double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); };
     cdouble *gtab = (cdouble *)tb.tab;
-    for (int g = 0; g < tb.groups; g += NG) {
+    const int gend = NG == 1 ? (part + 1) * tb.groups / parts : tb.groups;
+    for (int g = NG == 1 ? part * tb.groups / parts : 0; g < gend; g += NG) {
         double acc[NG][kResUnits][EPT];
 #pragma unroll
         for (int n = 0; n < NG; ++n)
@@ -591,6 +593,7 @@ __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb,
 struct ResArgs {
     ResSide side[2];
     int64_t blocks0;
+    int parts;   // grid.y: blocks sharing the unit groups (1 beyond kResRegWords words)
     ResTab tab;
 };
 
@@ -602,7 +605,7 @@ __global__ __launch_bounds__(64 * kResWaves) void k_residues(ResArgs a) {
     const int64_t lb = (int64_t)blockIdx.x - (sd ? a.blocks0 : 0), nbx = sa.kpad / 128;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     residue_wave<NW>(sa, a.tab, lb % nbx, (lb / nbx * kResWaves + wave) * (res_ept(NW ? NW : 31) / 2),
-                     words + wave * (res_wave_lds(NW ? NW : a.tab.nw32) / 4));
+                     words + wave * (res_wave_lds(NW ? NW : a.tab.nw32) / 4), blockIdx.y, a.parts);
 }
 
 // Residues of a^ on the vector ALUs with row broadcasts (stage 2, no MFMA; wide integers).  The

@@ -47,6 +47,24 @@ def test_planes_of_custom_sets(oz, c_oracle, n1, n2, p):
     check_residue_planes(oz, c_oracle, plan, X, "A", 150, f"{n1} + {n2} moduli p={p} t={t}")
 
 
+# the unit groups shared by two blocks (500 rows) and by none (2000) against four (few rows)
+@pytest.mark.parametrize("rows", [500, 2000])
+@pytest.mark.parametrize("p", [8, 53, 113, 256])
+def test_shared_groups(oz, rows, p):
+    import torch
+    K = 300
+    A, B = synth.mp_random(rows + p, rows, K, p, -20, 20), synth.mp_random(p, K, 40, p, -20, 20)
+    plan, dB = oz.Plan.create(p, K), dev_mp(B)
+    print(f"{rows} rows p={p}", flush=True)
+    C = oz.gemm(plan, dev_mp(A), dB)
+    for r0 in (0, rows - 9):
+        part = synth.mp_zeros(9, K, p)
+        part.sign[:], part.exp[:], part.limbs[:] = (getattr(A, n)[r0:r0 + 9] for n in ("sign", "exp", "limbs"))
+        R = oz.gemm(plan, dev_mp(part), dB)
+        for n in ("sign", "exp", "limbs"):
+            assert torch.equal(getattr(C, n)[r0:r0 + 9], getattr(R, n)), n
+
+
 def test_batch_of_every_residue_class(oz):
     import torch
     probs = []
