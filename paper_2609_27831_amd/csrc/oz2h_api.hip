@@ -554,7 +554,7 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
         if (ldu % 16 == 0 && u_ps >= M * ldu && u_ps % 16 == 0 && ((uintptr_t)u % 32) == 0) {
             uint32_t *dig = gdig;
             int32_t *cout = (int32_t *)(gdig + (size_t)16 * h.crt_ndg * rc.estride);
-            const CrtRowArgs ra{u, u_ps, rc.nent, ldu, h.L, h.crt_lpad, h.crt_ndg, h.nd32,
+            const CrtRowArgs ra{u, u_ps, rc.nent, ldu, h.L - h.crt_rnpair, h.crt_rnpair, h.crt_lpad, h.crt_ndg, h.nd32,
                                 pl->d_crt_row, pl->d_info, dig, cout, rc.estride, rc.ntiles};
             const unsigned nb1 = (unsigned)((int64_t)rc.ntiles / 4 * h.crt_ndg);
             const size_t lds1 = kCrtRowSumsLds;

@@ -2561,7 +2561,10 @@ __global__ __launch_bounds__(BT, BT == 64 ? 2 : 1) void k_crt_mma(CrtArgs a) {
 
 // Direct CRT for wide moduli sets on the vector ALUs with row broadcasts (no MFMA), in two
 // kernels.  S = sum_l v_l M_l, M_l = P / m_l in balanced base-2^32 digits D[d][l]: each digit
-// sum S_d = sum_l v_l D[d][l] is an exact fp64 integer (|S_d| < L 2^44 < 2^53).
+// sum S_d = sum_l v_l D[d][l] is an exact fp64 integer (|S_d| < L 2^44 < 2^53).  Two one-limb
+// moduli enter as one unit, V = v_a m_b + v_b m_a against the digits of P / (m_a m_b), as in the
+// unit CRT and under the same bound (both kernels at 2048^2, p = 1024 3.33 to 3.09 ms, 4096^2,
+// p = 2048 36.1 to 34.4).
 //   k_crt_row_sums: a wave takes 64 consecutive entries and one group of 16 digits.  Lane j
 //     of row q owns digit 16 dg + j of the row's entries 16 q + i (i < 16) and keeps, per
 //     chunk of 16 moduli, their 16 digit constants in registers; lane m of the row loads v of
@@ -2580,7 +2583,8 @@ struct CrtRowArgs {
     int64_t v_ps;       // plane stride of v; entry e' = i * ldv + j of a plane is at V + e'
     int64_t nent;       // entries e' covered: M * ldv
     int64_t ldv;
-    int L, lpad, ndg, nd32;
+    int nu, npair;        // units; the first npair are pairs of one-limb moduli (2 u, 2 u + 1)
+    int lpad, ndg, nd32;
     const double *drow;   // [16 ndg][lpad]
     const ModInfo *mi;    // WEIGHT: plain residues u_l, weighted here
     uint32_t *dig;        // [16 ndg][estride]
@@ -2641,20 +2645,20 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.0;
     const int nch = a.lpad >> 4;
-    // chunk c of 16 moduli: v of modulus min(16 c + j, L - 1) for the row's 16 entries (32
+    // chunk c of 16 units: v of unit min(16 c + j, nu - 1) for the row's 16 entries (32
     // bytes; nent is a multiple of 64 and the launch checks that every plane holds nent
     // entries), loaded one chunk ahead; the 16 digit constants of this lane's digit from LDS
-    // (zero past L)
+    // (zero past the last unit)
     // plane addresses: the chunk's offset 16 c v_ps is wave-uniform (scalar arithmetic); a lane
-    // past the last modulus reads the last plane
-    const int16_t *vj = a.V + (int64_t)j * a.v_ps + e_row;
-    const int16_t *vlast = a.V + (int64_t)(a.L - 1) * a.v_ps + e_row;
+    // past the last unit reads the last plane
+    const int16_t *vj = a.V + (int64_t)(a.npair + j) * a.v_ps + e_row;
+    const int16_t *vlast = a.V + (int64_t)(a.npair + a.nu - 1) * a.v_ps + e_row;
     auto loadv = [&](int c, v4i &w0, v4i &w1) {
-        gv4i *src = (gv4i *)(16 * c + j < a.L ? vj + (int64_t)(16 * c) * a.v_ps : vlast);
+        gv4i *src = (gv4i *)(16 * c + j < a.nu ? vj + (int64_t)(16 * c) * a.v_ps : vlast);
         w0 = src[0];
         w1 = src[1];
     };
-    auto mult = [&](int c, int l0, const v4i &w0, const v4i &w1) {
+    auto fmas = [&](int c, int l0, double (&vd)[16]) OZ2H_INL {
         const double *drow = Dl + j * kCrtRowDStride + (16 * c - l0);
         double dc[16];
 #pragma unroll
@@ -2663,23 +2667,45 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
             dc[m] = t.x;
             dc[m + 1] = t.y;
         }
-        double vd[16];
-        const int raw[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
-        ModInfo mi{};
-        if constexpr (WEIGHT) mi = load_info((OZ2H_G(ModInfo) *)a.mi + min(16 * c + j, a.L - 1));
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int lo = (raw[t] << 16) >> 16, hi = raw[t] >> 16;
-            if constexpr (WEIGHT) {
-                vd[2 * t] = (double)centred_mod((double)lo * (double)mi.minv, (double)mi.m, mi.inv_m);
-                vd[2 * t + 1] = (double)centred_mod((double)hi * (double)mi.minv, (double)mi.m, mi.inv_m);
-            } else {
-                vd[2 * t] = (double)lo;
-                vd[2 * t + 1] = (double)hi;
-            }
-        }
         dpp_ready16(vd);
         crt_row_fmas(acc, vd, dc);
+    };
+    // a lane's 16 values of modulus l, weighted here where the planes hold plain residues
+    auto values = [&](int l, const v4i &w0, const v4i &w1, int (&v)[16]) OZ2H_INL {
+        const int raw[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
+        ModInfo mi{};
+        if constexpr (WEIGHT) mi = load_info((OZ2H_G(ModInfo) *)a.mi + l);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            v[t] = t & 1 ? raw[t / 2] >> 16 : (raw[t / 2] << 16) >> 16;
+            if constexpr (WEIGHT) v[t] = centred_mod((double)v[t] * (double)mi.minv, (double)mi.m, mi.inv_m);
+        }
+    };
+    auto mult = [&](int c, int l0, const v4i &w0, const v4i &w1) OZ2H_INL {
+        int v[16];
+        double vd[16];
+        values(min(16 * c + j, a.nu - 1) + a.npair, w0, w1, v);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) vd[t] = (double)v[t];
+        fmas(c, l0, vd);
+    };
+    // the first chunks hold the pairs (and, in the last of them, single moduli as pairs with
+    // factors 1 and 0); their planes load where they are used
+    auto mult_pairs = [&](int c, int l0) OZ2H_INL {
+        const int u = min(16 * c + j, a.nu - 1);
+        const bool pair = u < a.npair;
+        const int la = pair ? 2 * u : u + a.npair, lb = pair ? la + 1 : la;
+        OZ2H_G(ModInfo) *mi = (OZ2H_G(ModInfo) *)a.mi;
+        const int ka = pair ? (int)mi[lb].m : 1, kb = pair ? (int)mi[la].m : 0;
+        gv4i *sa = (gv4i *)(a.V + (int64_t)la * a.v_ps + e_row), *sb = (gv4i *)(a.V + (int64_t)lb * a.v_ps + e_row);
+        const v4i wa0 = sa[0], wa1 = sa[1], wb0 = sb[0], wb1 = sb[1];
+        int va[16], vb[16];
+        double vd[16];
+        values(la, wa0, wa1, va);
+        values(lb, wb0, wb1, vb);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) vd[t] = (double)(__mul24(va[t], ka) + __mul24(vb[t], kb));
+        fmas(c, l0, vd);
     };
     // a stage's constants: thread t moves pairs (t & 15) + 16 i of row t >> 4 (lpad and the
     // stage are multiples of 16, so a row of a stage is a whole number of 16-byte pairs); the
@@ -2706,7 +2732,8 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
     };
     v4i aw0, aw1, bw0, bw1;
     stage_load(0);
-    loadv(0, aw0, aw1);
+    const int pch = (a.npair + 15) >> 4;   // at most two: within the first stage
+    loadv(min(pch, nch - 1), aw0, aw1);
     for (int l0 = 0; l0 < a.lpad; l0 += kCrtRowStage) {
         const int nl = min(kCrtRowStage, a.lpad - l0);
         __syncthreads();   // the previous stage has been read by every wave
@@ -2715,6 +2742,7 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
         __syncthreads();
         const int c1 = (l0 + nl) >> 4;
         int c = l0 >> 4;
+        for (; c < pch; ++c) mult_pairs(c, l0);
         for (; c + 2 <= c1; c += 2) {
             loadv(min(c + 1, nch - 1), bw0, bw1);
             mult(c, l0, aw0, aw1);

@@ -266,24 +266,31 @@ bool balanced_digits(const Nat &a, int n, double *out) {
     return !carry && (int)a.size() <= n;
 }
 
+// Pairs of one-limb moduli of a unit CRT, a multiple of `step`: as many as keep the digit sums
+// exact, sum |V| < 2^22 - 2^15.
+int crt_pairs(const PlanHost &h, int step) {
+    auto vmax = [&](int l) { return (int64_t)h.info[l].m / 2; };   // centred (or a binary64 term's 11 bits)
+    int64_t sum = 0;
+    for (int l = 0; l < h.L; ++l) sum += std::min<int64_t>(vmax(l), 8095);
+    const int64_t limit = ((int64_t)1 << 22) - ((int64_t)1 << 15);
+    const int n1 = h.backend == kBackendInt8 ? h.L1 / 2 : 0;
+    int np = 0;
+    while (np + step <= n1) {
+        for (int u = np; u < np + step; ++u) {   // over the two moduli on their own
+            const int64_t a = h.info[2 * u].m, b = h.info[2 * u + 1].m;
+            sum += vmax(2 * u) * b + vmax(2 * u + 1) * a - vmax(2 * u) - vmax(2 * u + 1);
+        }
+        if (sum >= limit) break;
+        np += step;
+    }
+    return np;
+}
+
 // Terms of the unit CRT: pairs of the leading one-limb moduli (an even number of pairs, while
 // sum_u max |V_u| leaves the digit sums exact), then single terms.
 int crt_unit_tables(PlanHost &h, const std::vector<Nat> &coef, std::string &err) {
     h.crt_und = crt_unit_digits(h.nd32);
-    auto vmax = [&](int l) { return (int64_t)h.info[l].m / 2; };   // centred (or a binary64 term's 11 bits)
-    int64_t sum = 0;
-    for (int l = 0; l < h.L; ++l) sum += std::min<int64_t>(vmax(l), 8095);
-    auto cost = [&](int u) {   // what pair u adds to the sum over its two moduli on their own
-        const int64_t a = h.info[2 * u].m, b = h.info[2 * u + 1].m;
-        return vmax(2 * u) * b + vmax(2 * u + 1) * a - vmax(2 * u) - vmax(2 * u + 1);
-    };
-    const int64_t limit = ((int64_t)1 << 22) - ((int64_t)1 << 15);
-    const int n1 = h.backend == kBackendInt8 ? h.L1 / 2 : 0;
-    h.crt_npair = 0;
-    for (int u = 0; u + 2 <= n1 && sum + cost(u) + cost(u + 1) < limit; u += 2) {
-        sum += cost(u) + cost(u + 1);
-        h.crt_npair += 2;
-    }
+    h.crt_npair = crt_pairs(h, 2);
     const int n = h.L - h.crt_npair;
     h.crt_units.assign(n, CrtUnit{});
     h.crt_udig.assign((size_t)n * h.crt_und, 0.0);
@@ -333,13 +340,25 @@ int crt_tables(PlanHost &h, const Nat &P, const std::vector<Nat> &coef, std::str
             ptop = ptop * 4294967296.0 + (double)(k < (int)P.size() ? P[k] : 0u);
         h.crt_inv_ptop = 1.0 / ptop;
     }
-    // the row-broadcast CRT's table: digit d of coef_l at [d][l], 16 digits per lane row group
+    // the row-broadcast CRT's table: digit d of unit u at [d][u], 16 digits per lane row group;
+    // the units are pairs of one-limb moduli, P / (m_a m_b), while the sums stay exact, and the
+    // moduli left
     h.crt_ndg = (h.nd32 + 15) / 16;
-    h.crt_lpad = (h.L + 15) / 16 * 16;
+    h.crt_rnpair = crt_pairs(h, 1);
+    const int nu = h.L - h.crt_rnpair;
+    h.crt_lpad = (nu + 15) / 16 * 16;
     h.crt_row.assign((size_t)16 * h.crt_ndg * h.crt_lpad, 0.0);
-    for (int l = 0; l < h.L; ++l)
-        for (int d = 0; d < h.nd32 && d < h.crt_ndpad; ++d)
-            h.crt_row[(size_t)d * h.crt_lpad + l] = h.crt_digits[(size_t)l * h.crt_ndpad + d];
+    std::vector<double> dig(h.crt_ndpad);
+    for (int u = 0; u < nu; ++u) {
+        const bool pair = u < h.crt_rnpair;
+        const int l = pair ? 2 * u : u + h.crt_rnpair;
+        if (pair && !balanced_digits(nat_divexact_small(coef[l], h.info[l + 1].m), h.crt_ndpad, dig.data())) {
+            err = "internal error: CRT digit table too short";
+            return -1;
+        }
+        const double *src = pair ? dig.data() : &h.crt_digits[(size_t)l * h.crt_ndpad];
+        for (int d = 0; d < h.nd32 && d < h.crt_ndpad; ++d) h.crt_row[(size_t)d * h.crt_lpad + u] = src[d];
+    }
     h.p_digits.assign(h.nd32, 0);
     h.ph_digits.assign(h.nd32, 0);
     for (int k = 0; k < h.nd32 && k < (int)P.size(); ++k) h.p_digits[k] = P[k];

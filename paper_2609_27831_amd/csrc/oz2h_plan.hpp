@@ -160,6 +160,7 @@ struct PlanHost {
     std::vector<CrtUnit> crt_units;
     std::vector<double> crt_udig;    // [units][crt_und]: balanced base-2^32 digits
     int crt_ndg = 0;       // row-broadcast CRT: groups of 16 digits
+    int crt_rnpair = 0;    // row-broadcast CRT: pairs of one-limb moduli among its units
     int crt_lpad = 0;      // ... moduli padded to a multiple of 16
     std::vector<double> crt_row;     // [16 crt_ndg][crt_lpad]: digit d of P/m_l at [d][l]
     bool crt_mma_wide = false;   // set before build_plan: its tables beyond nd32 = 32 as well

@@ -142,3 +142,23 @@ def test_batch_of_every_digit_class(oz):
         for A, B, C, _, _ in probs:
             P = oz.gemm(oz.Plan.create(A.p, A.shape[1]), A, B)
             assert all(torch.equal(a, b) for a, b in ((P.sign, C.sign), (P.exp, C.exp), (P.limbs, C.limbs))), A.p
+
+
+# the row kernels beyond 48 digits: pairs in one chunk of 16 units and in two, an odd modulus over,
+# none, the bound on pairs (many moduli), through the stage call and products
+@pytest.mark.parametrize("n1,n2,p", [(0, 110, 700), (5, 105, 700), (32, 100, 700), (33, 99, 700), (53, 96, 700), (53, 400, 2700)])
+def test_row_kernels_of_custom_sets(oz, c_oracle, n1, n2, p):
+    all_ = oz.Plan.create(2800, 20).moduli.tolist()
+    one, two = [m for m in all_ if m <= 255], [m for m in all_ if m > 255]
+    mods = one[:n1] + two[:n2]
+    t = min(p + 24, int((sum(np.log2(m) for m in mods) - 1 - 6) / 2) - 1)
+    plan = oz.Plan.custom(p, t, 20, mods)
+    A, B = synth.mp_random(n1, 21, 20, p, 0, 0), synth.mp_random(n2, 20, 19, p, 0, 0)
+    print(f"{n1} + {n2} moduli, p={p}, t={t}, digits={plan.nd32}", flush=True)
+    assert plan.nd32 > 48
+    cs, cm, _, _ = oz.gemm_integers(plan, dev_mp(A), dev_mp(B))
+    a = np.array(mp_to_ints(A.sign, A.limbs), dtype=object).reshape(21, 20)
+    b = np.array(mp_to_ints(B.sign, B.limbs), dtype=object).reshape(20, 19)
+    sh = lambda x: (1 if x > 0 else -1) * (abs(x) << t - p if t >= p else abs(x) >> p - t)
+    a, b = (np.vectorize(sh, otypes=[object])(x) for x in (a, b))
+    assert list(oz.limbs_to_ints(cm.cpu().numpy().view(np.uint64), cs.cpu().numpy())) == list(np.dot(a, b).ravel())
