@@ -563,7 +563,7 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
             int st = check_launch("CRT digit sums");
             if (st) return st;
             const unsigned nb2 = (unsigned)((rc.nent + 63) / 64);
-            const size_t lds2 = (size_t)64 * h.nd32 * sizeof(uint32_t);
+            const size_t lds2 = (size_t)kCrtFinS * h.nd32 * sizeof(uint32_t);
             if (round) k_crt_row_finish<true><<<nb2, 64, lds2, s>>>(ca, ra);
             else k_crt_row_finish<false><<<nb2, 64, lds2, s>>>(ca, ra);
             return check_launch("CRT finish");
@@ -572,7 +572,7 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
     if (h.nd32 > 32 && crt_mma_eligible(h, !weight)) {
         // one wave per block: 64 entries, a digit column each (an LDS of up to 40 KiB)
         const unsigned nbm = (unsigned)((M * N + 63) / 64);
-        const size_t ldsm = (size_t)64 * h.nd32 * sizeof(uint32_t);
+        const size_t ldsm = (size_t)kCrtFinS * h.nd32 * sizeof(uint32_t);
 #define OZ2H_CRTM(KQ)                                                                  \
     case KQ:                                                                           \
         if (round) k_crt_mma<KQ, true, false, 64><<<nbm, 64, ldsm, s>>>(ca);           \

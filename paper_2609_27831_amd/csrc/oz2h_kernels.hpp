@@ -1997,8 +1997,10 @@ struct CrtArgs {
 // Lift and (ROUND) rounding of output entry (i, j) from its digit column sd (stride
 // cst): on the fast path the column holds c^ in two's complement over nd32 digits
 // (sign = carry < 0); on the slow path it holds R = S - (alpha - 1) P in [0, 3P).
-template <bool ROUND>
-__device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t i, int64_t j, uint32_t *sd, int64_t cst,
+// STASH: the limbs go into the column (limb w in its digits 2 w and 2 w + 1) where no later one
+// reads them, and the result is true; else they are stored.
+template <bool ROUND, bool STASH = false>
+__device__ __forceinline__ bool crt_finish(const CrtArgs &a, int64_t i, int64_t j, uint32_t *sd, int64_t cst,
                                            bool slow, int64_t carry) {
     const int nd32 = a.nd32, p = a.p;
     const uint32_t *__restrict__ Phd = a.Phd;
@@ -2037,7 +2039,7 @@ __device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t i, int64_t 
         for (int w = 0; w < a.nlc; ++w)
             o[w] = (uint64_t)mag(2 * w) | ((uint64_t)mag(2 * w + 1) << 32);
         a.osign[e] = top < 0 ? 0 : (neg ? -1 : 1);
-        return;
+        return false;
     }
     const int64_t oi = i * a.ldc + j;
     __attribute__((address_space(1))) uint64_t *o =
@@ -2046,7 +2048,7 @@ __device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t i, int64_t 
         for (int w = 0; w < nl; ++w) o[w] = 0;
         a.osign[oi] = 0;
         a.oexp[oi] = 0;
-        return;
+        return false;
     }
     int64_t nb = 32 * (int64_t)top + (32 - __builtin_clz(mag(top)));
     const int64_t sh = nb - p;   // mant = RNE(mag / 2^sh)
@@ -2060,6 +2062,15 @@ __device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t i, int64_t 
     // three consecutive digits by funnel shifts, one pass from the bottom
     const int64_t q0 = sh >> 5;   // floor: sh < 0 reads zero digits below the column
     const int rsh = (int)(sh & 31);
+    const bool stash = STASH && q0 >= 0;   // limb w + 1 reads from digit q0 + 2 w + 3 on
+    auto put = [&](int w, uint64_t v) {
+        if (stash) {
+            sd[2 * w * cst] = (uint32_t)v;
+            sd[(2 * w + 1) * cst] = (uint32_t)(v >> 32);
+        } else {
+            o[w] = v;
+        }
+    };
     uint32_t prev = mag(q0);
     bool cy = inc;
     uint64_t last = 0;
@@ -2069,18 +2080,44 @@ __device__ __forceinline__ void crt_finish(const CrtArgs &a, int64_t i, int64_t 
                            __builtin_amdgcn_alignbit(d1, prev, rsh);
         last = v + (cy ? 1u : 0u);
         cy = cy && last == 0;
-        o[w] = last;
+        put(w, last);
         prev = d2;
     }
     const int pb = p - 64 * (nl - 1);   // bits of the top limb
     if (pb < 64 ? (last >> pb) != 0 : cy) {   // mant = 2^p - 1 rounded up to 2^p: renormalise
-        for (int w = 0; w < nl; ++w) o[w] = 0;
-        o[(p - 1) >> 6] = 1ull << ((p - 1) & 63);
+        for (int w = 0; w < nl; ++w) put(w, w == (p - 1) >> 6 ? 1ull << ((p - 1) & 63) : 0);
         nb += 1;
     }
     a.osign[oi] = neg ? -1 : 1;
     a.oexp[oi] = (int32_t)(nb + (int64_t)(a.erow ? a.erow[i] : 0) + (a.fcol ? a.fcol[j] : 0) -
                            (int64_t)a.tsum);
+    return stash;
+}
+
+// A wave whose lanes hold stashed limbs (crt_finish; columns kCrtFinS words apart, lane e's at
+// sdig + e; oi: its output entry) stores them with consecutive lanes at consecutive limbs: a lane
+// storing its own entry's limbs touches 64 lines with every store (CRT at 2048^2, row kernels,
+// p = 1024 3.03 to 2.83 ms, p = 800 2.19 to 2.05; no difference for records of whole lines,
+// p = 2048).
+constexpr int kCrtFinS = 65;   // LDS words between the digits of a column
+__device__ __forceinline__ void store_limbs(const CrtArgs &a, const uint32_t *sdig, bool stashed, int64_t oi) {
+    const uint64_t mask = __ballot(stashed);
+    if (!mask) return;
+    wave_lds_sync();
+    const int lane = threadIdx.x & 63, nl = (a.p + 63) / 64, q = 64 / nl, rm = 64 - q * nl;
+    int e = lane / nl, w = lane - e * nl;
+    for (int it = 0; it < nl; ++it) {   // limb w of the wave's entry e
+        const int64_t oe = __shfl(oi, e);
+        const uint32_t lo = sdig[2 * w * kCrtFinS + e], hi = sdig[(2 * w + 1) * kCrtFinS + e];
+        if ((mask >> e) & 1)
+            ((__attribute__((address_space(1))) uint64_t *)a.olimbs)[oe * nl + w] = (uint64_t)hi << 32 | lo;
+        e += q;
+        w += rm;
+        if (w >= nl) {
+            w -= nl;
+            ++e;
+        }
+    }
 }
 
 // LDS of a CRT block: bd * EPT digit columns of nd32 words (GDIG = false), or the
@@ -2439,6 +2476,7 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
     const int nd32 = a.nd32, L = a.L, kq = a.kq, nbk = a.nbk;
     const int64_t N = a.N, MN = a.M * N, v_ps = a.v_ps;
     constexpr bool EXACT = BT == 64;   // kq == KQ
+    constexpr int CS = BT == 64 ? kCrtFinS : BT;   // LDS words between the digits of a column
     const int64_t e0 = blk * BT + wv * 64;
     typedef const __attribute__((address_space(1))) uint16_t gu16;
     typedef const __attribute__((address_space(1))) v4i gv4i;
@@ -2500,7 +2538,7 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
 
     // S: eight digits per block of 32 byte rows, carried into this lane's LDS column
     gv4i *af = (gv4i *)a.afr + lane;
-    uint32_t *col = sdig + tid;   // digit k at col[BT k]
+    uint32_t *col = sdig + tid;   // digit k at col[CS k]
     int64_t carry = 0;
     for (int nb = 0; nb < nbk; ++nb) {
         v16i acc0 = v16i{}, acc1 = v16i{};
@@ -2530,27 +2568,29 @@ __device__ __forceinline__ void crt_mma_block(const CrtArgs &a, int64_t blk, uin
             const int64_t D = (dk & 1) == h ? mine[dk >> 1] : got[dk >> 1];
             if (k < nd32) {
                 const int64_t x = D + carry;
-                col[BT * k] = (uint32_t)x;
+                col[CS * k] = (uint32_t)x;
                 carry = x >> 32;
             }
         }
     }
 
     // beta from S / P, then S - beta P into the column
-    double val = (double)(int32_t)col[BT * (nd32 - 1)];
-    for (int k = nd32 - 2; k >= nd32 - a.nt; --k) val = val * 4294967296.0 + (double)col[BT * k];
+    double val = (double)(int32_t)col[CS * (nd32 - 1)];
+    for (int k = nd32 - 2; k >= nd32 - a.nt; --k) val = val * 4294967296.0 + (double)col[CS * k];
     const double est = val * a.inv_ptop, r = rint(est);
     const bool slow = fabs(est - r) > 0.5 - 0x1p-30;
     const int64_t beta = slow ? (int64_t)floor(est) - 1 : (int64_t)r;
     cu32 *Pd = (cu32 *)a.Pd;
     int64_t cy = 0;
     for (int k = 0; k < nd32; ++k) {
-        const int64_t x = (int64_t)col[BT * k] - beta * (int64_t)Pd[k] + cy;
-        col[BT * k] = (uint32_t)x;
+        const int64_t x = (int64_t)col[CS * k] - beta * (int64_t)Pd[k] + cy;
+        col[CS * k] = (uint32_t)x;
         cy = x >> 32;
     }
     const int64_t e = e0 + lane;
-    if (e < MN) crt_finish<ROUND>(a, e / N, e % N, col, BT, slow, cy + carry);
+    bool stashed = false;
+    if (e < MN) stashed = crt_finish<ROUND, ROUND && BT == 64>(a, e / N, e % N, col, CS, slow, cy + carry);
+    if constexpr (ROUND && BT == 64) store_limbs(a, sdig, stashed, e / N * a.ldc + e % N);
 }
 
 template <int KQ, bool ROUND, bool WEIGHT, int BT>
@@ -2799,79 +2839,83 @@ __global__ __launch_bounds__(64) void k_crt_row_finish(CrtArgs a, CrtRowArgs r) 
     const int tid = threadIdx.x;
     const int64_t ep = (int64_t)blockIdx.x * 64 + tid;
     const int64_t i = ep / r.ldv, jj = ep - i * r.ldv;
-    if (ep >= r.nent || jj >= a.N) return;
-    const int nd32 = a.nd32, nt = a.nt;
-    uint32_t *col = sdig + tid;   // digit k at col[64 k]
-    // groups holding digits below nd32 (at least three: this kernel runs for nd32 > 32)
-    const int ng = min(r.ndg, (nd32 + 15) / 16);
-    auto ldg = [&](int g, uint32_t (&dv)[16], int32_t &co) {
-        const int gc = min(g, ng - 1);
+    const bool live = ep < r.nent && jj < a.N;
+    bool stashed = false;
+    if (live) {
+        const int nd32 = a.nd32, nt = a.nt;
+        uint32_t *col = sdig + tid;   // digit k at col[kCrtFinS k]
+        // groups holding digits below nd32 (at least three: this kernel runs for nd32 > 32)
+        const int ng = min(r.ndg, (nd32 + 15) / 16);
+        auto ldg = [&](int g, uint32_t (&dv)[16], int32_t &co) {
+            const int gc = min(g, ng - 1);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) dv[u] = r.dig[(int64_t)(16 * gc + u) * r.estride + ep];
-        co = gc > 0 ? r.cout[(int64_t)(gc - 1) * r.estride + ep] : 0;
-    };
-    uint32_t da[16], db[16];
-    int32_t ca, cb;
+            for (int u = 0; u < 16; ++u) dv[u] = r.dig[(int64_t)(16 * gc + u) * r.estride + ep];
+            co = gc > 0 ? r.cout[(int64_t)(gc - 1) * r.estride + ep] : 0;
+        };
+        uint32_t da[16], db[16];
+        int32_t ca, cb;
 
-    // S's top nt digits (the highest as a signed digit) as one binary64 value
-    ldg(ng - 2, da, ca);
-    ldg(ng - 1, db, cb);
-    double val = 0.0;
-    {
-        const int base = 16 * (ng - 2), kb = nd32 - nt;
-        uint32_t top[32];
-        int64_t cy = ca;
+        // S's top nt digits (the highest as a signed digit) as one binary64 value
+        ldg(ng - 2, da, ca);
+        ldg(ng - 1, db, cb);
+        double val = 0.0;
+        {
+            const int base = 16 * (ng - 2), kb = nd32 - nt;
+            uint32_t top[32];
+            int64_t cy = ca;
 #pragma unroll
-        for (int u = 0; u < 32; ++u) {
-            const int64_t x = (int64_t)(u < 16 ? da[u] : db[u - 16]) + (u == 16 ? (int64_t)cb : 0) + cy;
-            top[u] = (uint32_t)x;
-            cy = x >> 32;
-        }
-        // Horner from the signed top digit down: the sign-extension digits cancel exactly
+            for (int u = 0; u < 32; ++u) {
+                const int64_t x = (int64_t)(u < 16 ? da[u] : db[u - 16]) + (u == 16 ? (int64_t)cb : 0) + cy;
+                top[u] = (uint32_t)x;
+                cy = x >> 32;
+            }
+            // Horner from the signed top digit down: the sign-extension digits cancel exactly
 #pragma unroll
-        for (int u = 31; u >= 0; --u) {
-            const int k = base + u;
-            if (k == nd32 - 1) val = (double)(int32_t)top[u];
-            else if (k >= kb && k < nd32) val = fma(val, 0x1p32, (double)top[u]);
+            for (int u = 31; u >= 0; --u) {
+                const int k = base + u;
+                if (k == nd32 - 1) val = (double)(int32_t)top[u];
+                else if (k >= kb && k < nd32) val = fma(val, 0x1p32, (double)top[u]);
+            }
         }
-    }
-    const double est = val * a.inv_ptop, rr = rint(est);
-    const bool slow = fabs(est - rr) > 0.5 - 0x1p-30;
-    const double beta = slow ? floor(est) - 1.0 : rr;   // |beta| <= L + 2
+        const double est = val * a.inv_ptop, rr = rint(est);
+        const bool slow = fabs(est - rr) > 0.5 - 0x1p-30;
+        const double beta = slow ? floor(est) - 1.0 : rr;   // |beta| <= L + 2
 
-    // c^ = S - beta P from the bottom, the next group's digits loading during a group
-    typedef const __attribute__((address_space(4))) uint32_t cu32;
-    cu32 *Pd = (cu32 *)a.Pd;
-    double cy = 0.0;
-    auto digit = [&](int k, uint32_t d, double add, uint32_t pk) {
-        const double x = fma(-beta, (double)pk, (double)d + add + cy);
-        const double hi = floor(x * 0x1p-32);
-        col[64 * k] = (uint32_t)fma(-hi, 0x1p32, x);
-        cy = hi;
-    };
-    auto pass = [&](int g, const uint32_t (&dv)[16], int32_t co) {
-        if (16 * g + 16 <= nd32) {   // a whole group: its 16 digits of P in one scalar load
-            uint32_t pk[16];
+        // c^ = S - beta P from the bottom, the next group's digits loading during a group
+        typedef const __attribute__((address_space(4))) uint32_t cu32;
+        cu32 *Pd = (cu32 *)a.Pd;
+        double cy = 0.0;
+        auto digit = [&](int k, uint32_t d, double add, uint32_t pk) {
+            const double x = fma(-beta, (double)pk, (double)d + add + cy);
+            const double hi = floor(x * 0x1p-32);
+            col[kCrtFinS * k] = (uint32_t)fma(-hi, 0x1p32, x);
+            cy = hi;
+        };
+        auto pass = [&](int g, const uint32_t (&dv)[16], int32_t co) {
+            if (16 * g + 16 <= nd32) {   // a whole group: its 16 digits of P in one scalar load
+                uint32_t pk[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) pk[u] = Pd[16 * g + u];
+                for (int u = 0; u < 16; ++u) pk[u] = Pd[16 * g + u];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) digit(16 * g + u, dv[u], u == 0 ? (double)co : 0.0, pk[u]);
-        } else {
-            for (int u = 0; u < 16 && 16 * g + u < nd32; ++u)
-                digit(16 * g + u, dv[u], u == 0 ? (double)co : 0.0, Pd[16 * g + u]);
+                for (int u = 0; u < 16; ++u) digit(16 * g + u, dv[u], u == 0 ? (double)co : 0.0, pk[u]);
+            } else {
+                for (int u = 0; u < 16 && 16 * g + u < nd32; ++u)
+                    digit(16 * g + u, dv[u], u == 0 ? (double)co : 0.0, Pd[16 * g + u]);
+            }
+        };
+        ldg(0, da, ca);
+        int g = 0;
+        for (; g + 2 <= ng; g += 2) {
+            ldg(g + 1, db, cb);
+            pass(g, da, ca);
+            ldg(g + 2, da, ca);
+            pass(g + 1, db, cb);
         }
-    };
-    ldg(0, da, ca);
-    int g = 0;
-    for (; g + 2 <= ng; g += 2) {
-        ldg(g + 1, db, cb);
-        pass(g, da, ca);
-        ldg(g + 2, da, ca);
-        pass(g + 1, db, cb);
+        if (g < ng) pass(g, da, ca);
+        const int64_t sgn = !slow && (int32_t)col[kCrtFinS * (nd32 - 1)] < 0 ? -1 : 0;
+        stashed = crt_finish<ROUND, ROUND>(a, i, jj, col, kCrtFinS, slow, sgn);
     }
-    if (g < ng) pass(g, da, ca);
-    const int64_t sgn = !slow && (int32_t)col[64 * (nd32 - 1)] < 0 ? -1 : 0;
-    crt_finish<ROUND>(a, i, jj, col, 64, slow, sgn);
+    if constexpr (ROUND) store_limbs(a, sdig, stashed, i * a.ldc + jj);
 }
 
 // planes [G][R][C] (int8, row stride ldi) -> [G][Co][Ro] (row stride Ro), zero where
