@@ -257,11 +257,14 @@ def time_plain(name, Ad, Bd, steps, warmup, flags=0):
     res_k, crt_k = kernel_names(plan, flags)
     # algorithmic work per stage (per launch = per step)
     res_bytes = (M * K + K * N) * (8 * nl + 5) + (M * K + K * N) * G
-    res_fma = (M * K + K * N) * L * nw32          # word x weight multiply-adds
+    units = L - plan.L1 // 2                       # a pair of one-limb moduli counts once
+    res_fma = (M * K + K * N) * units * nw32      # word x weight multiply-adds
     gemm_ops = G * 2.0 * M * N * K
     gemm_bytes = G * (M * K + K * N) + L * M * N * 2
     crt_bytes = L * M * N * 2 + M * N * (8 * nl + 5)
-    crt_fma = M * N * L * nd32                     # weight x digit multiply-adds
+    crt_fma = M * N * units * nd32                 # weight x digit multiply-adds
+    tiles = -(-M // 256) * -(-N // 256)
+    gemm_k = "k_resgemm8" if L * tiles >= 320 else "k_resgemm"
     phases = {n: {"ms": round(phase_ms[n], 4),
                   "effective_gflops": round(flops / (phase_ms[n] * 1e-3) / 1e9, 2)}
               for n in PHASES}
@@ -271,7 +274,7 @@ def time_plain(name, Ad, Bd, steps, warmup, flags=0):
         "kernel": res_k, "hbm_gbs": round(res_bytes / sec["residues"] / 1e9, 1),
         "fp64_tflops": round(2.0 * res_fma / sec["residues"] / 1e12, 2) if not res_k.endswith("_mma") else None,
         "counter_hbm_gbs": None})
-    phases["gemm"].update({"kernel": "k_resgemm", "int8_tops": round(gemm_tops, 1),
+    phases["gemm"].update({"kernel": gemm_k, "int8_tops": round(gemm_tops, 1),
                            "int8_mfma_pct_of_peak": round(100.0 * gemm_tops / PEAK_INT8_TOPS, 2)})
     phases["crt"].update({
         "kernel": crt_k, "hbm_gbs": round(crt_bytes / sec["crt"] / 1e9, 1),
@@ -284,10 +287,10 @@ def time_plain(name, Ad, Bd, steps, warmup, flags=0):
 
     def roof(ph):
         if ph == "gemm":
-            r = {"kernel": "k_resgemm", "bound": "mfma", "achieved": round(gemm_tops, 2),
+            r = {"kernel": gemm_k, "bound": "mfma", "achieved": round(gemm_tops, 2),
                  "peak": PEAK_INT8_TOPS, "unit": "TOP/s", "frac": round(gemm_tops / PEAK_INT8_TOPS, 4),
                  "algorithmic_bytes": gemm_bytes}
-            kern = "k_resgemm"
+            kern = gemm_k
         else:
             kern = phases[ph]["kernel"]
             fma = res_fma if ph == "residues" else crt_fma

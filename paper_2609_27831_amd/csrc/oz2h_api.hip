@@ -399,8 +399,8 @@ int launch_gemm8(const PlanHost &h, int64_t mpad, int64_t npad, const GemmArgsZ 
 
 // Blocks that have a compute unit to themselves take four LDS stages and read a k-tile ahead of
 // its products (1024 x 1024 x 4096, one plane: 19.0 us against 22.5; 128 x 128 x 4096, p = 256,
-// 66 moduli: 56 / 79); more blocks, or few k-tiles, do better with two stages and three blocks per unit
-// (3328 x 3072 x 384, p = 256: 1015 / 827; 384 x 384 x 4096, p = 113, 360 blocks: 67 / 64).
+// 66 moduli: 56 / 79); more blocks, or few k-tiles, do better with two stages and three blocks
+// per unit (3328 x 3072 x 384, p = 256: 1015 / 827; 384 x 384 x 4096, p = 113, 360 blocks: 67 / 64).
 bool gemm_deep(dim3 grid, int64_t kpad) {
     return (int64_t)grid.x * grid.y * grid.z <= kGemm8Blocks && kpad >= 512;
 }
@@ -413,17 +413,17 @@ int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b,
     const XcdMap xm = xcd_map_for(cfg, grid);
     // plain int32 products have no fold for other blocks to cover: 4096^3 86 / 91 us
     const bool deep = gemm_deep(grid, g.kpad) || (RAW && cfg.bm == cfg.bn);
-#define OZ2H_G(WR, WC)                                                                      \
+#define OZ2H_RGEMM(WR, WC)                                                                  \
     do {                                                                                    \
         if (deep) k_resgemm<WR, WC, 4, RAW><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);        \
         else k_resgemm<WR, WC, 2, RAW><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);             \
     } while (0)
-    if (cfg.bm == 256 && cfg.bn == 128) OZ2H_G(4, 2);
-    else if (cfg.bm == 128 && cfg.bn == 256) OZ2H_G(2, 4);
-    else if (!RAW && cfg.bn == 64) OZ2H_G(4, 1);
-    else if (!RAW && cfg.bm == 64) OZ2H_G(1, 4);
-    else OZ2H_G(2, 2);
-#undef OZ2H_G
+    if (cfg.bm == 256 && cfg.bn == 128) OZ2H_RGEMM(4, 2);
+    else if (cfg.bm == 128 && cfg.bn == 256) OZ2H_RGEMM(2, 4);
+    else if (!RAW && cfg.bn == 64) OZ2H_RGEMM(4, 1);
+    else if (!RAW && cfg.bm == 64) OZ2H_RGEMM(1, 4);
+    else OZ2H_RGEMM(2, 2);
+#undef OZ2H_RGEMM
     return check_launch("residue GEMM");
 }
 

@@ -14,10 +14,6 @@
 #include <cstdint>
 #include <type_traits>
 
-#ifndef OZ2H_GEMM_SCHED
-#define OZ2H_GEMM_SCHED 1
-#endif
-
 #include "oz2h_plan.hpp"
 
 namespace oz2h {
