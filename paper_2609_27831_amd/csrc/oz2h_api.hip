@@ -527,12 +527,21 @@ RowCrtCfg row_crt_config(const PlanHost &h, int64_t M, int64_t ldv) {
     return c;
 }
 
+// The unit kernel's range.  Beyond 32 digits its one chain per entry is long, and few entries do
+// better with the row kernels, which share an entry's digits out over lanes (p = 512, 37 digits:
+// 256^2 entries 36 us against 43; 2048^2 1.26 ms against 0.65; 8 x 61 at 44 digits a whole
+// product 58 us against 66).
+bool crt_units_take(const PlanHost &h, int64_t M, int64_t N) {
+    return h.nd32 <= 32 || (h.nd32 <= kCrtUnitMaxDigits && M * N >= 131072);
+}
+
+// (for every size beyond 32 digits, so that the need grows with M and N)
 size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N) {
-    if (h.nd32 <= kCrtUnitMaxDigits) return 0;
+    if (h.nd32 <= kCrtRowMinDigits) return 0;
     return row_crt_config(h, M, round_up(std::max<int64_t>(N, 1), 256)).bytes;
 }
 
-// gdig: device buffer of crt_gdig_bytes(h, M, N) bytes, or NULL (digit columns in LDS)
+// gdig: device buffer of crt_gdig_bytes(h, M, N) bytes, or NULL (none needed, or a stage call without)
 int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int64_t u_ps,
                int64_t ldu, const int32_t *e, const int32_t *f, bool round, bool weight,
                int8_t *osign, int32_t *oexp, uint64_t *olimbs, int64_t ldc, uint64_t *chat,
@@ -548,7 +557,7 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
                      pl->d_pd, pl->d_phd, e, f, tsum, h.p, osign, oexp, olimbs, ldc, chat, nlc, c.LB,
                      nullptr, 0, pl->d_crt_afr, h.crt_nbk, h.crt_kq,
                      h.crt_nt, h.crt_inv_ptop, pl->d_crt_units, pl->d_crt_udig, h.crt_npair};
-    if (gdig && row_crt_eligible(h) && !crt_mma_eligible(h, !weight) && (weight || h.nd32 > kCrtUnitMaxDigits)) {
+    if (gdig && row_crt_eligible(h) && !crt_mma_eligible(h, !weight) && (weight || !crt_units_take(h, M, N))) {
         // row-broadcast CRT: the planes must hold M * ldu entries each, 32-byte aligned rows
         const RowCrtCfg rc = row_crt_config(h, M, ldu);
         if (ldu % 16 == 0 && u_ps >= M * ldu && u_ps % 16 == 0 && ((uintptr_t)u % 32) == 0) {
@@ -600,7 +609,7 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
         else k_crt_mma<kCrtMmaMaxQ, false, false, 256><<<nbm, 256, ldsm, s>>>(ca);
         return check_launch("CRT");
     }
-    if (!weight && h.nd32 <= kCrtUnitMaxDigits && u_ps % 2 == 0 && ldu % 2 == 0 && (uintptr_t)u % 4 == 0) {
+    if (!weight && crt_units_take(h, M, N) && u_ps % 2 == 0 && ldu % 2 == 0 && (uintptr_t)u % 4 == 0) {
         const CrtUnitsCfg uc = crt_units_config(h, M, N);
         const int ut = kCrtUnitThreads;
 #define OZ2H_CRTU(ND)                                                                                \

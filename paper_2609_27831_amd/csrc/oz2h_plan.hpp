@@ -25,7 +25,7 @@ constexpr int kResExactWords = 16;   // ... words up to which a pair's sum stays
                                      // that its quotients by either modulus are exact
 constexpr int kCrtRowMinDigits = 32;  // the row-broadcast CRT's least digits (plus one); plain residues
                                       // (the stage call) take it from there on
-// CRTs of at most this many digits take the unit kernel, wider ones the row-broadcast kernels
+// CRTs of at most this many digits may take the unit kernel, wider ones the row-broadcast kernels
 // (2048^2 entries, units against rows: 37 digits 0.65 / 1.26 ms, 45: 1.24 / 1.46, 56: 2.1 - 2.3 /
 // 2.3, 62: 2.6 - 2.8 / 2.6)
 constexpr int kCrtUnitMaxDigits = 48;

@@ -109,8 +109,10 @@ def test_integers_next_to_half_P(oz, K):
     assert (P // 2 - max(ref)) / P < 2.0 ** -31
 
 
-# more than 2^18 entries: two columns per thread up to 26 digits; odd widths leave a column over
-@pytest.mark.parametrize("p,M,N", [(30, 513, 513), (150, 300, 875), (330, 515, 513)])
+# more than 2^18 entries: two columns per thread up to 26 digits; odd widths leave a column over;
+# 33 to 48 digits: the unit kernel from 2^17 entries on, against the row kernels for few
+@pytest.mark.parametrize("p,M,N", [(30, 513, 513), (150, 300, 875), (330, 515, 513), (460, 363, 363), (520, 512, 257),
+                                   (590, 363, 364), (660, 400, 331)])
 def test_two_columns_per_thread(oz, p, M, N):
     import torch
     K = 20

@@ -103,3 +103,16 @@ def test_batch_of_every_gemm_class(oz):
             torch.cuda.synchronize()
             for (_, _, C, _, _), R in zip(probs, refs):
                 assert torch.equal(R.sign, C.sign) and torch.equal(R.exp, C.exp) and torch.equal(R.limbs, C.limbs)
+
+
+@pytest.mark.parametrize("M,N,K,p", [(300, 9, 700, 113), (9, 300, 700, 113), (300, 64, 130, 1024), (70, 260, 1100, 256)])
+def test_thin_products_from_handles_and_without_a_workspace(oz, M, N, K, p):
+    A, B = dev_mp(synth.mp_random(M, M, K, p, -9, 9)), dev_mp(synth.mp_random(N, K, N, p, -9, 9))
+    plan = oz.Plan.create(p, K)
+    print(f"handles {M}x{N}x{K} p={p}", flush=True)
+    R = oz.gemm(oz.Plan.create(p, K, oz.default_opts(tile=oz.TILE_256x128)), A, B)
+    ra, rb = oz.Residues(plan, A, oz.SIDE_A), oz.Residues(plan, B, oz.SIDE_B)
+    out = oz.empty_mp(M, N, p)
+    for C in (oz.gemm_from_residues(plan, B=B, ra=ra), oz.gemm_from_residues(plan, A=A, rb=rb),
+              oz.gemm_from_residues(plan, ra=ra, rb=rb), oz.gemm_noalloc(plan, A, B, out=out)):
+        assert (C.sign == R.sign).all() and (C.exp == R.exp).all() and (C.limbs == R.limbs).all()
