@@ -332,9 +332,10 @@ int launch_residues(const oz2h_plan *pl, const ResSide *sides, int n, hipStream_
     // then shared out over up to four blocks, each building the words again (parts 1, 2, 3, 4, 6:
     // 32 blocks, 16^3, p = 53 9.6, 8.8, 8.1, 8.1, 8.0 us; 128 blocks, 256^3, p = 128 17.7, 15.1,
     // 16.8, 16.9, 18.8, 200^3, p = 256 35, 25, 24, 23, 24; 384 blocks, p = 256 35.9, 32.5, 38; 1152
-    // blocks, p = 113 29, 34, 40).
+    // blocks, p = 113 29, 34, 40; beyond 12 words, one part against this rule: 16^3, p = 512 34.4 /
+    // 18.6, 200^3, p = 700 75.5 / 53.6).
     const int64_t blocks = nblk[0] + nblk[1];
-    const int parts = h.nw32 > kResRegWords || blocks > 512 ? 1 : std::min(blocks > 64 ? 2 : 4, h.rgroups);
+    const int parts = blocks > 512 ? 1 : std::min(blocks > 64 ? 2 : 4, h.rgroups);
     const ResArgs a{{sides[0], sides[n - 1]}, nblk[0], parts,
                     {pl->d_resid, pl->d_rgrp, h.p, nl, t, h.nw32, h.rgroups}};
     const dim3 grid((unsigned)(nblk[0] + nblk[1]), parts);

@@ -454,8 +454,9 @@ __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb,
     constexpr double kMagic = 6755399441055744.0;   // 1.5 2^52
     auto low = [](double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); };
     cdouble *gtab = (cdouble *)tb.tab;
-    const int gend = NG == 1 ? (part + 1) * tb.groups / parts : tb.groups;
-    for (int g = NG == 1 ? part * tb.groups / parts : 0; g < gend; g += NG) {
+    const int passes = (tb.groups + NG - 1) / NG;   // this part's share of them
+    const int gend = min((part + 1) * passes / parts * NG, tb.groups);
+    for (int g = part * passes / parts * NG; g < gend; g += NG) {
         double acc[NG][kResUnits][EPT];
 #pragma unroll
         for (int n = 0; n < NG; ++n)
@@ -511,7 +512,7 @@ __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb,
         }
 #pragma unroll
         for (int n = 0; n < NG; ++n) {
-            if (n && g + n >= tb.groups) break;
+            if (n && g + n >= gend) break;
             cgrp *R = grec + g + n;
             g_i8 *pb = uniform_ptr(planes + (int64_t)R->g0 * a.plane_stride);
             const int np = R->nplanes;
@@ -589,7 +590,7 @@ __device__ __forceinline__ void residue_wave(const ResSide &a, const ResTab &tb,
 struct ResArgs {
     ResSide side[2];
     int64_t blocks0;
-    int parts;   // grid.y: blocks sharing the unit groups (1 beyond kResRegWords words)
+    int parts;   // grid.y: blocks sharing the unit groups
     ResTab tab;
 };
 

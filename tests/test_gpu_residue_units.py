@@ -49,7 +49,7 @@ def test_planes_of_custom_sets(oz, c_oracle, n1, n2, p):
 
 # the unit groups shared by two blocks (500 rows) and by none (2000) against four (few rows)
 @pytest.mark.parametrize("rows", [500, 2000])
-@pytest.mark.parametrize("p", [8, 53, 113, 256])
+@pytest.mark.parametrize("p", [8, 53, 113, 256, 400, 620])
 def test_shared_groups(oz, rows, p):
     import torch
     K = 300
