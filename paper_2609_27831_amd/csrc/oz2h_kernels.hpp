@@ -1733,98 +1733,23 @@ __global__ __launch_bounds__(512, 2) void k_resgemm8(Gemm8Args) {
             }
         clear(h);
     };
-    // vector-memory operations issued after the loads a phase waits for: the loads of two
-    // phases, and the stores of a half (8) where an item ended: in this phase, in the phase
-    // before it, or (their loads came first) a k-tile ago.  Fewer is always safe.
-    constexpr int kSt = MODE == ZSTORE ? 8 : 0;
-    auto half_end = [&](int stores) OZ2H_INL {   // 0, 1 or 2 halves' stores among them
+    // the operations the schedule below is written in; waits of half_end: every LDS read, and all
+    // but the newest vector-memory operations, 8 loads and the stores (8 each) of `stores` halves
+    constexpr int kSt = MODE == ZSTORE ? 8 : 0;   // (the other modes wait for theirs)
+    auto half_end = [&](int stores) OZ2H_INL {
         fence();
         if (stores == 2) __builtin_amdgcn_s_waitcnt(vmlgkm_imm(8 + 2 * kSt));
         else if (stores == 1) __builtin_amdgcn_s_waitcnt(vmlgkm_imm(8 + kSt));
         else __builtin_amdgcn_s_waitcnt(vmlgkm_imm(8));
         barrier();
     };
-
-    // prologue: in the order the k-loop would have issued them
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-    issue(I0{}, I1{}, cur.b, 0);
-    issue(I0{}, I0{}, cur.a, 0);
-    issue(I0{}, I2{}, cur.b, 0);
-    advance();
-    issue(I0{}, I3{}, pa, pko);
-    issue(I1{}, I1{}, cur.b, cur.ko);
-    issue(I1{}, I0{}, cur.a, cur.ko);
-    issue(I1{}, I2{}, cur.b, cur.ko);
-    advance();   // pa: k-tile 1, cur: k-tile 2
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
-    barrier();
-    read_b(gemm8_part<0, 1>(), fb0);
-    half_end(0);
-    if (wr == 1) barrier();   // the second wave group runs half a phase behind
-
-    // One k-tile in stage S; pa / cur are k-tiles T + 1 / T + 2.  LAST: the product's last one,
-    // whose lower half is finished before phase 1's reads (their registers are free then).
-    // st0, st1: halves whose stores the waits of phase 0 and 1 may leave behind.
-    int st0 = 0, st1 = 0;
-    auto ktile = [&](auto s_, auto last_) OZ2H_INL {
-        constexpr int S = decltype(s_)::value;
-        constexpr bool LAST = decltype(last_)::value != 0;
-        using SN = std::integral_constant<int, S ^ 1>;
-        v4i (&fc)[2][2] = S ? fb2 : fb0;
-        v4i (&fn)[2][2] = S ? fb0 : fb2;
-        // phase 0
-        read_b(gemm8_part<S, 2>(), fb1);
-        read_a(gemm8_part<S, 0>());
-        fence();
-        issue(SN{}, I3{}, pa, pko);
-        issue(s_, I1{}, cur.b, cur.ko);
-        half_end(st0);
-        st0 = st1 ? 1 : 0;   // a k-tile after an item's end: the upper half's stores remain
-        mult(acc[0][0], fc);
-        mult(acc[0][1], fb1);
-        barrier();
-        // phase 1
-        if constexpr (LAST) {
-            finish(I0{});
-            if (prod + 1 == nprod && !st1) st1 = 1;
-            fence();
-        }
-        read_a(gemm8_part<S, 3>());
-        read_b(gemm8_part<S ^ 1, 1>(), fn);
-        fence();
-        issue(s_, I0{}, cur.a, cur.ko);
-        issue(s_, I2{}, cur.b, cur.ko);
-        advance();
-        half_end(st1);
-        st1 = 0;
-        mult(acc[1][1], fb1);
-        mult(acc[1][0], fc);
-        barrier();
+    auto wait_vm = [&](auto n_) OZ2H_INL { __builtin_amdgcn_s_waitcnt(vmcnt_imm(decltype(n_)::value)); };
+    auto next_item = [&]() OZ2H_INL {
+        item = next(item);
+        nprod = products(item);
+        return item.zi < (uint32_t)kargs()->L;
     };
-    // products one after the other; the k-tiles of each are even in number, so that it starts
-    // in stage 0.  Its upper half is finished before the next product's first reads.
-    for (;;) {
-        for (int k = 2; k < nk; k += 2) {
-            ktile(I0{}, I0{});
-            ktile(I1{}, I0{});
-        }
-        ktile(I0{}, I0{});
-        ktile(I1{}, I1{});
-        finish(I1{});
-        if (++prod == nprod) {
-            st0 = st1 = 2;
-            prod = 0;
-            item = next(item);
-            nprod = products(item);
-            if (item.zi >= (uint32_t)kargs()->L) break;
-        }
-        fence();
-    }
-    if (wr == 0) barrier();
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no load still writing LDS past the block's end
+#include "oz2h_gemm8_schedule.inc"
 }
 
 // Residue planes of a sum of two operands (3M: Ar + Ai, Br + Bi) from the planes of
