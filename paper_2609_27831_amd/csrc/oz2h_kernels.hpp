@@ -2599,7 +2599,7 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
     const bool live = tile0 * 64 < a.nent;
     const int64_t tile = live ? tile0 : 0;
     const int q = lane >> 4, j = lane & 15;
-    const int64_t e_row = tile * 64 + 16 * q;   // this row's entries e_row + i
+    const int64_t e_row = crt_row_first(a.nent, tile, q);   // this row's entries e_row + i
     typedef const __attribute__((address_space(1))) v4i gv4i;
     typedef double d2 __attribute__((ext_vector_type(2)));
     const double *gsrc = a.drow + (size_t)16 * dg * a.lpad;
@@ -2608,7 +2608,7 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
     for (int i = 0; i < 16; ++i) acc[i] = 0.0;
     const int nch = a.lpad >> 4;
     // chunk c of 16 units: v of unit min(16 c + j, nu - 1) for the row's 16 entries (32
-    // bytes; nent is a multiple of 64 and the launch checks that every plane holds nent
+    // bytes; nent is a multiple of 16 and the launch checks that every plane holds nent
     // entries), loaded one chunk ahead; the 16 digit constants of this lane's digit from LDS
     // (zero past the last unit)
     // plane addresses: the chunk's offset 16 c v_ps is wave-uniform (scalar arithmetic); a lane

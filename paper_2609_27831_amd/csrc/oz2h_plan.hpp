@@ -25,6 +25,11 @@ constexpr int kResExactWords = 16;   // ... words up to which a pair's sum stays
                                      // that its quotients by either modulus are exact
 constexpr int kCrtRowMinDigits = 32;  // the row-broadcast CRT's least digits (plus one); plain residues
                                       // (the stage call) take it from there on
+// ... the first of the 16 entries that row q of a wave reads for its tile of 64: planes hold nent
+// entries, a multiple of 16, and a row of the last tile past them reads the last 16 again
+constexpr int64_t crt_row_first(int64_t nent, int64_t tile, int q) {
+    return 64 * tile + 16 * q < nent ? 64 * tile + 16 * q : nent - 16;
+}
 // CRTs of at most this many digits may take the unit kernel, wider ones the row-broadcast kernels
 // (2048^2 entries, units against rows: 37 digits 0.65 / 1.26 ms, 45: 1.24 / 1.46, 56: 2.1 - 2.3 /
 // 2.3, 62: 2.6 - 2.8 / 2.6)
