@@ -220,7 +220,10 @@ int oz2h_plan_get_info(const oz2h_plan *plan, oz2h_plan_info *info);
 int oz2h_plan_get_moduli(const oz2h_plan *plan, uint16_t *moduli);
 int oz2h_plan_get_moduli32(const oz2h_plan *plan, uint32_t *moduli);
 
-/* Bytes of device workspace oz2h_gemm / oz2h_gemm_integers need for M x N. */
+/* Bytes of device workspace oz2h_gemm / oz2h_gemm_integers take for M x N.  A workspace of
+   this size also serves every product of no more rows and columns on the same plan (with less
+   padding than that product's own size might allow for), whatever flags oz2h_plan_set_flags
+   gives the plan in between. */
 size_t oz2h_gemm_workspace_size(const oz2h_plan *plan, int64_t M, int64_t N);
 
 /*
@@ -286,7 +289,8 @@ int oz2h_gemm_integers(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K,
  *
  * Cr and Ci are p-bit outputs (ld >= N) and may not alias any input or each
  * other.  Workspace: oz2h_zgemm_workspace_size(plan, scheme, M, N) bytes of device
- * memory, 256-byte aligned (about (2 or 3) G (M + N) K + 4 L M N bytes).  K = 0
+ * memory, 256-byte aligned (about (2 or 3) G (M + N) K + 4 L M N bytes); it also serves
+ * products of no more rows and columns on the plan, as oz2h_gemm's does.  K = 0
  * writes zeros; M = 0 or N = 0 is a no-op.  Errors: OZ2H_EINVAL (scheme not 3 or
  * 4, a NULL pointer, ld too small, K not half the plan's K), OZ2H_ENOMEM (workspace
  * too small).  Asynchronous on `stream`.

@@ -159,14 +159,21 @@ struct Layout {
 
 size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N);
 
-// compact: the least padding, for a workspace of fixed size
-Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool compact = false) {
+// What pads a product's planes.  kFast: the GEMM tiles chosen for its shape.  kLeast: the
+// smallest tiles (or the plan's own), whose need never falls when M or N grows; a workspace
+// sized for a larger product serves a smaller one through it, whatever tiles that would take
+// by itself.  kLeastKept: the same next to residue handles, which fix the k padding.
+// No layout depends on the plan's flags, which may change between the size call and the product.
+enum Padding { kFast, kLeast, kLeastKept };
+
+Layout layout_for(const PlanHost &h, int64_t M, int64_t N, Padding pad = kFast) {
     Layout w{};
-    w.kpad = compact ? round_up(std::max<int64_t>(h.K, 1), GBK) : kpad_for(h.K);
-    w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, compact ? 0 : h.L);
+    w.kpad = pad == kLeast ? round_up(std::max<int64_t>(h.K, 1), GBK) : kpad_for(h.K);
+    w.cfg = pad != kFast ? tile_cfg(h.tile)
+                         : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, h.L);
     // up to 64 columns or rows against many: most loads go to the large side's planes, which are
     // read once (4096 x 8 x 4096, p = 256: 471 us against 513 with 128 x 128 tiles)
-    if (!compact && !h.grad && h.tile == OZ2H_TILE_AUTO && !(h.flags & OZ2H_FLAG_RESIDUES_MMA)) {
+    if (pad == kFast && !h.grad && h.tile == OZ2H_TILE_AUTO) {
         if (N <= 64 && M >= 256) w.cfg = {256, 64};
         else if (M <= 64 && N >= 256) w.cfg = {64, 256};
     }
@@ -177,23 +184,27 @@ Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool compact = false)
     off = align_up(off + sizeof(int32_t) * w.mpad);
     w.off_f = off;
     off = align_up(off + sizeof(int32_t) * w.npad);
+    w.off_u = off;
+    off = align_up(off + sizeof(int16_t) * (size_t)h.L * w.mpad * w.npad);
     w.off_a = off;
     off = align_up(off + (size_t)h.G * w.mpad * w.kpad);
     w.off_b = off;
     off = align_up(off + (size_t)h.G * w.npad * w.kpad);
-    w.off_u = off;
-    off = align_up(off + sizeof(int16_t) * (size_t)h.L * w.mpad * w.npad);
-    // digit columns of the CRT (large nd32 only): they reuse the residue planes, which
-    // are dead once the GEMMs are done, unless the planes are too small or must survive
-    // the call (a plan for backward products keeps them as the saved forward state)
-    const size_t dig = crt_gdig_bytes(h, M, N);
-    w.off_dig = w.off_a;
-    if (dig > 0 && (h.grad || dig > w.off_u - w.off_a)) {
-        w.off_dig = off;
-        off = align_up(off + dig);
-    }
-    w.total = off;
+    // digit columns of the CRT (large nd32 only): they reuse the residue planes, which are dead
+    // once the GEMMs are done, and may run past them, unless the planes must survive the call
+    // (a plan for backward products keeps them as the saved forward state)
+    const size_t dig = align_up(crt_gdig_bytes(h, M, N));
+    w.off_dig = h.grad ? off : w.off_a;
+    w.total = std::max(off, w.off_dig + dig);
     return w;
+}
+
+// Workspace of an M x N product on an INT8 plan, enough for every smaller one through kLeast or
+// kLeastKept; a forward that a backward reads (a grad plan's own M and N) has one layout alone.
+size_t gemm_need(const PlanHost &h, int64_t M, int64_t N) {
+    size_t n = std::max(layout_for(h, M, N).total, layout_for(h, M, N, kLeastKept).total);
+    if (h.grad && M >= h.gM && N >= h.gN) n = std::max(n, layout_for(h, h.gM, h.gN).total);
+    return n;
 }
 
 // One operand side of stage 1: entry (r, k) at r * rs + k * cs; koff (nullable): per-contraction
@@ -806,6 +817,8 @@ F64Layout layout_f64(const oz2h_plan *pl, int64_t M, int64_t N) {
     off = align_up(off + sizeof(int32_t) * w.mpad);
     w.off_f = off;
     off = align_up(off + sizeof(int32_t) * w.npad);
+    w.off_u = off;
+    off = align_up(off + sizeof(int16_t) * (size_t)h.L * w.mpad * w.npad);
     w.off_a8 = off;
     off = align_up(off + g8 * w.mpad * w.kpad);
     w.off_b8 = off;
@@ -814,15 +827,8 @@ F64Layout layout_f64(const oz2h_plan *pl, int64_t M, int64_t N) {
     off = align_up(off + sizeof(double) * (size_t)h.Lf * w.mpad * w.kpad);
     w.off_bf = off;
     off = align_up(off + sizeof(double) * (size_t)h.Lf * w.npad * w.kpad);
-    w.off_u = off;
-    off = align_up(off + sizeof(int16_t) * (size_t)h.L * w.mpad * w.npad);
-    const size_t dig = crt_gdig_bytes(h, M, N);
-    w.off_dig = w.off_a8;   // the planes are dead once the GEMMs are done
-    if (dig > w.off_u - w.off_a8) {
-        w.off_dig = off;
-        off = align_up(off + dig);
-    }
-    w.total = off;
+    w.off_dig = w.off_a8;   // over the planes, dead once the GEMMs are done, and past them
+    w.total = std::max(off, w.off_dig + align_up(crt_gdig_bytes(h, M, N)));
     return w;
 }
 
@@ -913,12 +919,13 @@ struct SideCache {
 };
 
 // shared body of oz2h_gemm, oz2h_gemm_integers and oz2h_gemm_from_residues; ca / cb
-// (nullable): cached stages 1-2 of side A / B, whose operand is then not read
+// (nullable): cached stages 1-2 of side A / B, whose operand is then not read; scratch: ws is
+// the library's own, which no backward reads
 int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op opA,
                  oz2h_cmat A, oz2h_op opB, oz2h_cmat B, bool round, oz2h_mat *C, int8_t *chat_sign,
                  uint64_t *chat_mag, int nlc, int32_t *e_out, int32_t *f_out, void *ws,
                  size_t ws_bytes, hipStream_t s, hipEvent_t *ev = nullptr,
-                 const SideCache *ca = nullptr, const SideCache *cb = nullptr, bool compact = false) {
+                 const SideCache *ca = nullptr, const SideCache *cb = nullptr, bool scratch = false) {
     int st = check_plan(pl);
     if (st) return st;
     const PlanHost &h = pl->h;
@@ -953,7 +960,9 @@ int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op o
         return run_pipeline_f64(pl, M, N, K, opA, A, opB, B, round, C, chat_sign, chat_mag, nlc, e_out,
                                 f_out, ws, ws_bytes, s, ev);
     }
-    const Layout w = layout_for(h, M, N, compact);
+    Layout w = layout_for(h, M, N);
+    const bool kept = h.grad && M == h.gM && N == h.gN && !ca && !cb && !scratch;   // for a backward
+    if (ws_bytes < w.total && !kept) w = layout_for(h, M, N, ca || cb ? kLeastKept : kLeast);
     if (!ws) return fail(OZ2H_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws) % kAlign) return fail(OZ2H_EINVAL, "workspace must be 256-byte aligned");
     if (ws_bytes < w.total)
@@ -1244,7 +1253,7 @@ int oz2h_plan_get_moduli32(const oz2h_plan *plan, uint32_t *moduli) {
 size_t oz2h_gemm_workspace_size(const oz2h_plan *plan, int64_t M, int64_t N) {
     if (!plan || M < 0 || N < 0) return 0;
     if (plan->h.backend != kBackendInt8) return layout_f64(plan, M, N).total;
-    return layout_for(plan->h, M, N).total;
+    return gemm_need(plan->h, M, N);
 }
 
 int oz2h_gemm(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, oz2h_op opA, oz2h_cmat A,
@@ -1386,10 +1395,12 @@ struct ZLayout {
     size_t off_e, off_f, off_a, off_b, off_vr, off_vi, off_dig, total;
 };
 
-ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K) {
+// pad: kFast or kLeast, as for plain products
+ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K, Padding pad = kFast) {
     ZLayout w{};
-    w.kpad = kpad_for(K);
-    w.cfg = choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, h.L);
+    w.kpad = pad == kLeast ? round_up(std::max<int64_t>(K, 1), GBK) : kpad_for(K);
+    w.cfg = pad == kLeast ? tile_cfg(h.tile)
+                          : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, h.L);
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
     w.nsets = scheme == 3 ? 3 : 2;
@@ -1398,22 +1409,16 @@ ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t
     off = align_up(off + sizeof(int32_t) * w.mpad);
     w.off_f = off;
     off = align_up(off + sizeof(int32_t) * w.npad);
-    w.off_a = off;
-    off = align_up(off + (size_t)w.nsets * h.G * w.mpad * w.kpad);
-    w.off_b = off;
-    off = align_up(off + (size_t)w.nsets * h.G * w.npad * w.kpad);
     w.off_vr = off;
     off = align_up(off + sizeof(int16_t) * (size_t)h.L * w.mpad * w.npad);
     w.off_vi = off;
     off = align_up(off + sizeof(int16_t) * (size_t)h.L * w.mpad * w.npad);
-    // the CRT digit columns reuse the planes (dead once the GEMMs are done) when they fit
-    const size_t dig = crt_gdig_bytes(h, M, N);
-    w.off_dig = w.off_a;
-    if (dig > w.off_vr - w.off_a) {
-        w.off_dig = off;
-        off = align_up(off + dig);
-    }
-    w.total = off;
+    w.off_a = off;
+    off = align_up(off + (size_t)w.nsets * h.G * w.mpad * w.kpad);
+    w.off_b = off;
+    off = align_up(off + (size_t)w.nsets * h.G * w.npad * w.kpad);
+    w.off_dig = w.off_a;   // the CRT digit columns: over the planes, dead by then, and past them
+    w.total = std::max(off, w.off_dig + align_up(crt_gdig_bytes(h, M, N)));
     return w;
 }
 
@@ -1456,7 +1461,9 @@ extern "C" {
 
 size_t oz2h_zgemm_workspace_size(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N) {
     if (!plan || (scheme != 3 && scheme != 4) || M < 0 || N < 0) return 0;
-    return zlayout_for(plan->h, scheme, M, N, plan->h.K / 2).total;
+    const int64_t K = plan->h.K / 2;
+    return std::max(zlayout_for(plan->h, scheme, M, N, K).total,
+                    zlayout_for(plan->h, scheme, M, N, K, kLeast).total);
 }
 
 int oz2h_zgemm(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N, int64_t K, oz2h_op opA,
@@ -1491,7 +1498,8 @@ int oz2h_zgemm(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N, int6
     if ((st = check_cmat(Ar, "Ar", ar, ac)) || (st = check_cmat(Ai, "Ai", ar, ac)) ||
         (st = check_cmat(Br, "Br", br, bc)) || (st = check_cmat(Bi, "Bi", br, bc)))
         return st;
-    const ZLayout w = zlayout_for(h, scheme, M, N, K);
+    ZLayout w = zlayout_for(h, scheme, M, N, K);
+    if (ws_bytes < w.total) w = zlayout_for(h, scheme, M, N, K, kLeast);
     if (!ws) return fail(OZ2H_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws) % kAlign) return fail(OZ2H_EINVAL, "workspace must be 256-byte aligned");
     if (ws_bytes < w.total)
@@ -1586,10 +1594,8 @@ int oz2h_gemm_noalloc(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, oz
                       oz2h_cmat A, oz2h_op opB, oz2h_cmat B, oz2h_mat C, hipStream_t stream) {
     int st = check_plan(plan);
     if (st || (st = need_int8(plan, "oz2h_gemm_noalloc"))) return st;
-    bool compact = false;
     if (M > 0 && N > 0 && K > 0) {
-        compact = layout_for(plan->h, M, N).total > kScratchBytes;
-        const size_t need = layout_for(plan->h, M, N, compact).total;
+        const size_t need = layout_for(plan->h, M, N, kLeast).total;
         if (need > kScratchBytes)
             return fail(OZ2H_ERANGE, "product needs %zu bytes of scratch, the static scratch holds %zu",
                         need, kScratchBytes);
@@ -1597,7 +1603,7 @@ int oz2h_gemm_noalloc(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, oz
     void *ws = nullptr;
     if ((st = scratch_for(plan->device, &ws))) return st;
     return run_pipeline(plan, M, N, K, opA, A, opB, B, true, &C, nullptr, nullptr, 0, nullptr,
-                        nullptr, ws, kScratchBytes, stream, nullptr, nullptr, nullptr, compact);
+                        nullptr, ws, kScratchBytes, stream, nullptr, nullptr, nullptr, true);
 }
 
 
