@@ -347,8 +347,14 @@ void oz2h_residues_destroy(oz2h_saved_residues *r);
  * workspace argument.  Its scratch is a file-scope device array of
  * oz2h_gemm_noalloc_max_bytes() bytes (128 MiB) that every GPU the library runs on
  * holds until the process ends; the call itself allocates nothing (no hipMalloc,
- * hipFree or allocating library routine).  Products whose workspace
- * (oz2h_gemm_workspace_size) exceeds that size return OZ2H_ERANGE.  Every call on
+ * hipFree or allocating library routine).  A product that does not fit with the
+ * least padding returns OZ2H_ERANGE and launches nothing.  With m, n and k = M, N and
+ * K rounded up to 128 (m or n to 256 on a plan with a fixed 256-row or 256-column
+ * tile) that takes 2 L m n + max(G (m + n) k, D) + 4 (m + n) bytes and up to 1280
+ * bytes of alignment, D = oz2h_crt_workspace_size(plan, M, N rounded up to 256) (on a
+ * plan for backward products G (m + n) k + D instead of the larger of the two).
+ * oz2h_gemm_workspace_size is no test of it: it may ask for more, to allow for
+ * larger tiles and residue handles.  Every call on
  * one GPU shares that GPU's scratch: calls that overlap on one GPU (other streams,
  * other threads) race, so callers serialise them.  Nothing in the scratch needs to
  * start at zero (every stage writes what the next one reads).

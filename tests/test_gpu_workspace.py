@@ -128,3 +128,26 @@ def _saved(oz, plan, A, B, n):
     ws = _ws(n)
     oz.gemm(plan, A, B, ws=ws)
     return ws
+
+
+@pytest.mark.parametrize("p,K", [(53, 2000), (113, 1100), (640, 1100), (1024, 64)])
+def test_noalloc_limit_is_the_stated_one(oz, p, K):
+    """The largest M of a column block of 128 that the header's formula lets through, and one more tile."""
+    N, plan = 128, oz.Plan.create(p, K)
+    cap = oz.lib().oz2h_gemm_noalloc_max_bytes()
+    k = -(-K // 128) * 128
+
+    def bytes_of(m):
+        dig = oz.lib().oz2h_crt_workspace_size(plan.handle, m, 256)
+        return 2 * plan.L * m * N + max(plan.G * (m + N) * k, dig) + 4 * (m + N)
+
+    m = 128
+    while bytes_of(m + 128) + 1280 <= cap:
+        m += 128
+    assert bytes_of(m) + 1280 <= cap < bytes_of(m + 128), "a case next to the limit is wanted"
+    A, B = _operands(82, m, N, K, p)
+    print(f"noalloc limit: {m} x {N} x {K}, p = {p}", flush=True)
+    assert _same(oz.gemm_noalloc(plan, A, B, out=oz.empty_mp(m, N, p)), oz.gemm(plan, A, B))
+    A = dev_mp(synth.mp_random(84, m + 128, K, p, -5, 5))
+    with pytest.raises(oz.Oz2hError):
+        oz.gemm_noalloc(plan, A, B, out=oz.empty_mp(m + 128, N, p))
