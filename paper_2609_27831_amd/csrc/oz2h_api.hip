@@ -129,8 +129,9 @@ GemmCfg tile_cfg(int tile) {
     }
 }
 
-// k padding of the INT8 planes: the 256 x 256 kernel takes pairs of 128-byte k-tiles, so long
-// contractions are padded to 256 (at most a ninth more); short ones only to 128
+// k padding of the INT8 planes that every GEMM takes: the 256 x 256 kernel goes by pairs of
+// 128-byte k-tiles, so long contractions are padded to 256 (at most a ninth more); short ones
+// only to 128.  Residue handles, whose products are not known yet, are padded so.
 int64_t kpad_for(int64_t K) { return round_up(std::max<int64_t>(K, 1), K > 1024 ? 2 * GBK : GBK); }
 
 // Automatic choice for L moduli (L = 0: no 256 x 256 tiles).
@@ -151,6 +152,11 @@ GemmCfg choose_gemm(int64_t M, int64_t N, int tile, int64_t kpad, int L) {
     return {128, 128};
 }
 
+// k padding of planes for these tiles alone
+int64_t kpad_of(GemmCfg cfg, int64_t K) {
+    return cfg.bm == 256 && cfg.bn == 256 ? kpad_for(K) : round_up(std::max<int64_t>(K, 1), GBK);
+}
+
 struct Layout {
     GemmCfg cfg;
     int64_t mpad, npad, kpad;
@@ -159,21 +165,19 @@ struct Layout {
 
 size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N);
 
-// What pads a product's planes.  kFast: the GEMM tiles chosen for its shape.  kLeast: the
-// smallest tiles (or the plan's own), whose need never falls when M or N grows; a workspace
-// sized for a larger product serves a smaller one through it, whatever tiles that would take
-// by itself.  kLeastKept: the same next to residue handles, which fix the k padding.
+// A product's workspace: with the GEMM tiles chosen for its shape, or (least) with the smallest
+// tiles, or the plan's own, whose need never falls when M or N grows; a workspace sized for a
+// larger product serves a smaller one through that, whatever tiles it would take by itself.
+// handles: next to residue handles, which fix the k padding.
 // No layout depends on the plan's flags, which may change between the size call and the product.
-enum Padding { kFast, kLeast, kLeastKept };
-
-Layout layout_for(const PlanHost &h, int64_t M, int64_t N, Padding pad = kFast) {
+Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool least = false, bool handles = false) {
     Layout w{};
-    w.kpad = pad == kLeast ? round_up(std::max<int64_t>(h.K, 1), GBK) : kpad_for(h.K);
-    w.cfg = pad != kFast ? tile_cfg(h.tile)
-                         : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, h.L);
+    w.cfg = least ? tile_cfg(h.tile)
+                  : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(h.K), h.L);
+    w.kpad = handles ? kpad_for(h.K) : kpad_of(w.cfg, h.K);
     // up to 64 columns or rows against many: most loads go to the large side's planes, which are
     // read once (4096 x 8 x 4096, p = 256: 471 us against 513 with 128 x 128 tiles)
-    if (pad == kFast && !h.grad && h.tile == OZ2H_TILE_AUTO) {
+    if (!least && !h.grad && h.tile == OZ2H_TILE_AUTO) {
         if (N <= 64 && M >= 256) w.cfg = {256, 64};
         else if (M <= 64 && N >= 256) w.cfg = {64, 256};
     }
@@ -199,10 +203,11 @@ Layout layout_for(const PlanHost &h, int64_t M, int64_t N, Padding pad = kFast) 
     return w;
 }
 
-// Workspace of an M x N product on an INT8 plan, enough for every smaller one through kLeast or
-// kLeastKept; a forward that a backward reads (a grad plan's own M and N) has one layout alone.
+// Workspace of an M x N product on an INT8 plan, with handles or not, enough for every smaller
+// one through the least layout; a forward that a backward reads (a grad plan's own M and N) has
+// one layout alone.
 size_t gemm_need(const PlanHost &h, int64_t M, int64_t N) {
-    size_t n = std::max(layout_for(h, M, N).total, layout_for(h, M, N, kLeastKept).total);
+    size_t n = std::max(layout_for(h, M, N, false, true).total, layout_for(h, M, N, true, true).total);
     if (h.grad && M >= h.gM && N >= h.gN) n = std::max(n, layout_for(h, h.gM, h.gN).total);
     return n;
 }
@@ -960,9 +965,10 @@ int run_pipeline(const oz2h_plan *pl, int64_t M, int64_t N, int64_t K, oz2h_op o
         return run_pipeline_f64(pl, M, N, K, opA, A, opB, B, round, C, chat_sign, chat_mag, nlc, e_out,
                                 f_out, ws, ws_bytes, s, ev);
     }
-    Layout w = layout_for(h, M, N);
-    const bool kept = h.grad && M == h.gM && N == h.gN && !ca && !cb && !scratch;   // for a backward
-    if (ws_bytes < w.total && !kept) w = layout_for(h, M, N, ca || cb ? kLeastKept : kLeast);
+    const bool handles = ca || cb;
+    Layout w = layout_for(h, M, N, false, handles);
+    const bool kept = h.grad && M == h.gM && N == h.gN && !handles && !scratch;   // for a backward
+    if (ws_bytes < w.total && !kept) w = layout_for(h, M, N, true, handles);
     if (!ws) return fail(OZ2H_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws) % kAlign) return fail(OZ2H_EINVAL, "workspace must be 256-byte aligned");
     if (ws_bytes < w.total)
@@ -1395,12 +1401,12 @@ struct ZLayout {
     size_t off_e, off_f, off_a, off_b, off_vr, off_vi, off_dig, total;
 };
 
-// pad: kFast or kLeast, as for plain products
-ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K, Padding pad = kFast) {
+// least: as for plain products
+ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K, bool least = false) {
     ZLayout w{};
-    w.kpad = pad == kLeast ? round_up(std::max<int64_t>(K, 1), GBK) : kpad_for(K);
-    w.cfg = pad == kLeast ? tile_cfg(h.tile)
-                          : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, w.kpad, h.L);
+    w.cfg = least ? tile_cfg(h.tile)
+                  : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(K), h.L);
+    w.kpad = kpad_of(w.cfg, K);
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
     w.nsets = scheme == 3 ? 3 : 2;
@@ -1463,7 +1469,7 @@ size_t oz2h_zgemm_workspace_size(const oz2h_plan *plan, int32_t scheme, int64_t 
     if (!plan || (scheme != 3 && scheme != 4) || M < 0 || N < 0) return 0;
     const int64_t K = plan->h.K / 2;
     return std::max(zlayout_for(plan->h, scheme, M, N, K).total,
-                    zlayout_for(plan->h, scheme, M, N, K, kLeast).total);
+                    zlayout_for(plan->h, scheme, M, N, K, true).total);
 }
 
 int oz2h_zgemm(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N, int64_t K, oz2h_op opA,
@@ -1499,7 +1505,7 @@ int oz2h_zgemm(const oz2h_plan *plan, int32_t scheme, int64_t M, int64_t N, int6
         (st = check_cmat(Br, "Br", br, bc)) || (st = check_cmat(Bi, "Bi", br, bc)))
         return st;
     ZLayout w = zlayout_for(h, scheme, M, N, K);
-    if (ws_bytes < w.total) w = zlayout_for(h, scheme, M, N, K, kLeast);
+    if (ws_bytes < w.total) w = zlayout_for(h, scheme, M, N, K, true);
     if (!ws) return fail(OZ2H_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws) % kAlign) return fail(OZ2H_EINVAL, "workspace must be 256-byte aligned");
     if (ws_bytes < w.total)
@@ -1595,7 +1601,7 @@ int oz2h_gemm_noalloc(const oz2h_plan *plan, int64_t M, int64_t N, int64_t K, oz
     int st = check_plan(plan);
     if (st || (st = need_int8(plan, "oz2h_gemm_noalloc"))) return st;
     if (M > 0 && N > 0 && K > 0) {
-        const size_t need = layout_for(plan->h, M, N, kLeast).total;
+        const size_t need = layout_for(plan->h, M, N, true).total;
         if (need > kScratchBytes)
             return fail(OZ2H_ERANGE, "product needs %zu bytes of scratch, the static scratch holds %zu",
                         need, kScratchBytes);
@@ -1631,8 +1637,8 @@ BwdLayout bwd_layout(const PlanHost &h) {
     const int64_t M = h.gM, N = h.gN, K = h.K;
     const int64_t orows[2] = {M, K}, ocols[2] = {K, N}, contr[2] = {N, M};
     for (int sd = 0; sd < 2; ++sd) {
-        b.kpad[sd] = kpad_for(contr[sd]);
-        b.cfg[sd] = choose_gemm(orows[sd], ocols[sd], h.tile, b.kpad[sd], h.L);
+        b.cfg[sd] = choose_gemm(orows[sd], ocols[sd], h.tile, kpad_for(contr[sd]), h.L);
+        b.kpad[sd] = kpad_of(b.cfg[sd], contr[sd]);
         b.mpad[sd] = round_up(orows[sd], b.cfg[sd].bm);
         b.npad[sd] = round_up(ocols[sd], b.cfg[sd].bn);
         size_t off = 0;
@@ -2083,8 +2089,8 @@ void tune_store(uint64_t sig, const TuneRec &r) {
 constexpr int kBigTiles = 3;
 int item_class(const oz2h_batched_plan *bp, int b) {
     if (bp->tile != OZ2H_TILE_AUTO) return bp->tile - 1;
-    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO, bp->pd[b].kpad, 
-                                   bp->hosts[b].L);
+    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO, bp->pd[b].kpad,
+                                  bp->hosts[b].L);
     return c.bm == 256 ? kBigTiles : OZ2H_TILE_128x128 - 1;
 }
 
@@ -2429,7 +2435,8 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         P.rpad[0] = round_up(q.M, 256);
         P.rpad[1] = round_up(q.N, 256);
         P.K = q.K;
-        P.kpad = kpad_for(q.K);
+        // (whatever tile setting the plan has now: oz2h_batched_set_config changes it)
+        P.kpad = kpad_of(choose_gemm(q.M, q.N, OZ2H_TILE_AUTO, kpad_for(q.K), h.L), q.K);
         P.p = h.p;
         P.nl = (h.p + 63) / 64;
         P.t = h.t;

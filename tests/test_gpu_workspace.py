@@ -151,3 +151,24 @@ def test_noalloc_limit_is_the_stated_one(oz, p, K):
     A = dev_mp(synth.mp_random(84, m + 128, K, p, -5, 5))
     with pytest.raises(oz.Oz2hError):
         oz.gemm_noalloc(plan, A, B, out=oz.empty_mp(m + 128, N, p))
+
+
+@pytest.mark.parametrize("K", [1100, 1300, 2049])
+def test_planes_are_padded_for_the_tiles_they_meet(oz, K):
+    """Planes of products with 128 x 128 tiles are padded to 128 along the contraction, not to 256."""
+    import torch
+    M, N, p = 120, 100, 113
+    k = -(-K // 128) * 128
+    A, B = _operands(86, M, N, K, p)
+    print(f"k padding, K = {K}", flush=True)
+    C = oz.gemm(oz.Plan.create(p, K), A, B)
+    out = oz.empty_mp(M, N, p)
+    bp = oz.BatchedPlan([(A, B, out, oz.OP_N, oz.OP_N)])
+    info = oz.Plan.create(p, K)
+    assert bp.workspace_size() <= info.G * 512 * k + 2 * info.L * 256 * 256 + 4096
+    bp.run(bp.workspace())
+    torch.cuda.synchronize()
+    assert _same(out, C)
+    # dA = W B^T contracts over N, dB = A^T W over M, both K here
+    grad = oz.Plan.create_grad(p, K, K, 120)
+    assert grad.backward_workspace_size() <= grad.G * (k + 128) * k + 2 * grad.L * k * 128 + 8 * k + 4096
