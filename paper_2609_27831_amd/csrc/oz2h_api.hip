@@ -157,6 +157,20 @@ int64_t kpad_of(GemmCfg cfg, int64_t K) {
     return cfg.bm == 256 && cfg.bn == 256 ? kpad_for(K) : round_up(std::max<int64_t>(K, 1), GBK);
 }
 
+// 256 x 64 (64 x 256) tiles for up to 64 columns (rows) against many of the large side, whose
+// planes are read once and take most loads.  They pay from 80 blocks on where the large side pads
+// to at most a sixth more than with 128 x 128 tiles, and from 300 blocks on in any case.  Whole
+// products, 128 x 128 against them, 8 columns, K = 4096: 4096 rows, p = 256 1121 / 1068 us;
+// 1000, p = 113 160 / 140; 512, p = 256 272 / 243; 256, p = 384 231 / 195 (89 blocks) but p = 256
+// 146 / 150 (70) and p = 113 66 / 69 (42); padding to 4/3 300, p = 256 178 / 201 (140), p = 512
+// 379 / 394 (214), p = 700 569 / 616 (268), but K = 1024, p = 1024 241 / 229 (360); to 6/5 600,
+// p = 256 298 / 285 and p = 113 at K = 1024 44.2 / 46.0.
+// Complex, backward and batched products keep square tiles: not measured with these.
+bool thin_tiles(int64_t large, int L) {
+    const int64_t blocks = L * ((large + 255) / 256);
+    return large >= 256 && (blocks >= 300 || (blocks >= 80 && round_up(large, 256) * 6 <= round_up(large, 128) * 7));
+}
+
 struct Layout {
     GemmCfg cfg;
     int64_t mpad, npad, kpad;
@@ -175,11 +189,9 @@ Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool least = false, b
     w.cfg = least ? tile_cfg(h.tile)
                   : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(h.K), h.L);
     w.kpad = handles ? kpad_for(h.K) : kpad_of(w.cfg, h.K);
-    // up to 64 columns or rows against many: most loads go to the large side's planes, which are
-    // read once (4096 x 8 x 4096, p = 256: 471 us against 513 with 128 x 128 tiles)
     if (!least && !h.grad && h.tile == OZ2H_TILE_AUTO) {
-        if (N <= 64 && M >= 256) w.cfg = {256, 64};
-        else if (M <= 64 && N >= 256) w.cfg = {64, 256};
+        if (N <= 64 && thin_tiles(M, h.L)) w.cfg = {256, 64};
+        else if (M <= 64 && thin_tiles(N, h.L)) w.cfg = {64, 256};
     }
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);

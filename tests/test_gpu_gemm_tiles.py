@@ -116,3 +116,16 @@ def test_thin_products_from_handles_and_without_a_workspace(oz, M, N, K, p):
     for C in (oz.gemm_from_residues(plan, B=B, ra=ra), oz.gemm_from_residues(plan, A=A, rb=rb),
               oz.gemm_from_residues(plan, ra=ra, rb=rb), oz.gemm_noalloc(plan, A, B, out=out)):
         assert (C.sign == R.sign).all() and (C.exp == R.exp).all() and (C.limbs == R.limbs).all()
+
+
+# on both sides of the rule for 64-wide tiles: blocks of 256 rows (80, or 300 where they pad by more than a sixth)
+@pytest.mark.parametrize("large,p", [(256, 256), (256, 384), (300, 384), (385, 384), (600, 384), (384, 1024), (385, 113)])
+def test_thin_rule(oz, large, p):
+    import torch
+    K, n = 520, 17
+    A, B = dev_mp(synth.mp_random(large, large, K, p, -9, 9)), dev_mp(synth.mp_random(p, K, n, p, -9, 9))
+    print(f"thin rule {large} x {n} x {K}, p = {p}", flush=True)
+    auto, square = oz.Plan.create(p, K), oz.Plan.create(p, K, oz.default_opts(tile=oz.TILE_128x128))
+    for X, Y, ops in ((A, B, (0, 0)), (B, A, (1, 1))):
+        C, D = oz.gemm(auto, X, Y, *ops), oz.gemm(square, X, Y, *ops)
+        assert all(torch.equal(a, b) for a, b in ((C.sign, D.sign), (C.exp, D.exp), (C.limbs, D.limbs)))
