@@ -341,15 +341,20 @@ int launch_residues(const oz2h_plan *pl, const ResSide *sides, int n, hipStream_
     }
     if (h.nw32 > kResMaxWords) {
         // VALU kernel with row broadcasts: blocks of 128 entries of one row
-        if (res_row_lds(h.rnwp) > 65536)
-            return fail(OZ2H_ERANGE, "residues: integers of %d words exceed the kernel's LDS", h.nw32);
+        const size_t lds = res_row_lds(h.rnwp);
+        const bool wide = h.rnwp > kResRowDigits;
+        if (wide)
+            OZ2H_HIP(hipFuncSetAttribute((const void *)k_residues_row<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds));
         for (int i = 0; i < n; ++i) {
             const ResSide &d = sides[i];
             const int64_t nblk = (d.kpad / 128) * rpad(d);
             if (nblk > INT32_MAX) return fail(OZ2H_ERANGE, "residues: operand too large for one launch");
             const ResRowArgs a{d, h.p, nl, t, h.rnw, h.rnwp, h.rg16, pl->d_resid_row, pl->d_rrunits};
-            k_residues_row<<<dim3((unsigned)nblk), 256, res_row_lds(h.rnwp), s>>>(a);
+            if (wide) k_residues_row<true><<<dim3((unsigned)nblk), 256, lds, s>>>(a);
+            else k_residues_row<false><<<dim3((unsigned)nblk), 256, lds, s>>>(a);
         }
+        static_assert(res_row_lds(kResRowDigits) <= 65536 && res_row_lds(kMaxWords + 4) <= 163840, "LDS of a block");
         return check_launch("residues");
     }
     // entry kernel: both sides in one launch
@@ -2525,7 +2530,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
                 const bool row = P.nw32 > kResMaxWords;
                 const int64_t nbx = P.kpad / 128, nby = row ? P.rpad[sd] : P.rpad[sd] / res_block_rows(P.nw32);
                 const size_t lds = row ? res_row_lds(P.nwp) : kResWaves * res_wave_lds(P.nw32);
-                if (lds > 65536)
+                if (row && P.nwp > kResRowDigits)
                     return fail(OZ2H_ERANGE, "problem %d: integers of %d words exceed the residue kernels", b, P.nw32);
                 ch.res_lds[c] = std::max(ch.res_lds[c], lds);
                 cs.res[c].push_back(Seg{ch.res_blocks[c], b, sd, nbx});

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void k_residues_row_grouped(const ProbDev *__r
     const ProbDev &P = probs[sg.prod];
     const int64_t lb = (int64_t)blockIdx.x - sg.first;
     const ResRowArgs a{res_side(P, sg.side, ws), P.p, P.nl, P.t, P.nw, P.nwp, P.rg16, P.resid_row, P.rrunits};
-    residues_row_block(a, lb % sg.nbx, lb / sg.nbx, smem_rr);
+    residues_row_block<false>(a, lb % sg.nbx, lb / sg.nbx, smem_rr);
 }
 
 // one work item of the grouped GEMM: output tile (mt, nt) of modulus l of product prod

@@ -669,6 +669,9 @@ struct ResRowArgs {
 
 __host__ __device__ constexpr size_t res_row_lds(int nwp) { return (size_t)nwp * kResRowS * 4; }
 
+// WIDE: more than kResRowDigits digits.  Units are single moduli, and a two-limb modulus's sum is
+// reduced before it meets 1.5 2^52 too.
+template <bool WIDE>
 __device__ __forceinline__ void residues_row_block(const ResRowArgs &a, int64_t bx, int64_t r, uint32_t *words) {
     const ResSide &d = a.d;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -778,7 +781,8 @@ __device__ __forceinline__ void residues_row_block(const ResRowArgs &a, int64_t 
                         uint32_t rr[2];
 #pragma unroll
                         for (int u = 0; u < 2; ++u) {
-                            const double x = acc[16 * hs + 4 * i4 + 2 * h + u];
+                            double x = acc[16 * hs + 4 * i4 + 2 * h + u];
+                            if constexpr (WIDE) x = fma(-rint(x * ru.inv2), ru.m2, x);
                             rr[u] = low(fma(-rint(x * ru.inv[0]), ru.md[0], x + kMagic));
                         }
                         // r = r0 + 128 r1, balanced
@@ -818,10 +822,11 @@ __device__ __forceinline__ void residues_row_block(const ResRowArgs &a, int64_t 
     }
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(256) void k_residues_row(ResRowArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem_rr[];
     const int64_t nbx = a.d.kpad / 128;
-    residues_row_block(a, (int64_t)blockIdx.x % nbx, (int64_t)blockIdx.x / nbx, smem_rr);
+    residues_row_block<WIDE>(a, (int64_t)blockIdx.x % nbx, (int64_t)blockIdx.x / nbx, smem_rr);
 }
 
 // Residues of a^ on the matrix cores (stage 2).  For every modulus the residue of an

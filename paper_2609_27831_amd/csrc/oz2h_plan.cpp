@@ -475,13 +475,14 @@ void build_residue_groups(PlanHost &h, const std::vector<uint32_t> &mods) {
 }
 
 // Tables of the row-broadcast residue kernel: per lane (unit) one row of rnwp weights, read in
-// 16-digit chunks; units as above, 16 to a group.  Integers are |a| <= 2^wide, one digit more
-// where the signed digits need it.
+// 16-digit chunks; units as above, 16 to a group (single moduli beyond kResRowDigits digits).
+// Integers are |a| <= 2^wide, one digit more where the signed digits need it.
 void build_residue_rows(PlanHost &h, const std::vector<uint32_t> &mods, int wide) {
     if (h.nw32 <= kResMaxWords) return;
     h.rnw = (wide + 2 + 31) / 32;
     h.rnwp = (h.rnw + 3) / 4 * 4;
-    const int n1 = (h.L1 + 1) / 2, n = n1 + h.L2;
+    const int per = h.rnwp > kResRowDigits ? 1 : 2;   // one-limb moduli per unit
+    const int n1 = (h.L1 + per - 1) / per, n = n1 + h.L2;
     h.rg16 = (n + 15) / 16;
     h.resid_row.assign((size_t)h.rg16 * 16 * h.rnwp, 0.0);
     h.resrow_units.assign((size_t)h.rg16 * 16, ResRowUnit{});
@@ -489,7 +490,7 @@ void build_residue_rows(PlanHost &h, const std::vector<uint32_t> &mods, int wide
         ResRowUnit &R = h.resrow_units[u];
         R.g0 = (uint32_t)h.G;   // past the last unit: no planes
         if (u >= n) continue;
-        const int l0 = u < n1 ? 2 * u : h.L1 + (u - n1), nm = u < n1 ? std::min(2, h.L1 - l0) : 1;
+        const int l0 = u < n1 ? per * u : h.L1 + (u - n1), nm = u < n1 ? std::min(per, h.L1 - l0) : 1;
         uint64_t M = 1;
         for (int k = 0; k < nm; ++k) {
             R.inv[k] = h.info[l0 + k].inv_m;

@@ -16,6 +16,10 @@ constexpr int kResMmaMinWords = 8;    // with the matrix-core residue variant se
 // words 1.70 ms against 1.95 with rows, 26 words 3.10 against 2.41)
 constexpr int kResRowMinWords = 24;
 constexpr int kResMaxWords = kResRowMinWords - 1;
+// ... of at most this many signed digits; wider integers (a grad plan whose t_bits lies far below
+// p: the gradient's width does not follow it) take its form with single moduli, one reduction
+// more and an LDS of up to 131 KiB
+constexpr int kResRowDigits = 124;
 constexpr int kResRegWords = 12;     // entry kernel: integers of <= this many words stay in registers
 constexpr int kResUnits = 4;         // ... units (a pair of one-limb moduli, or one two-limb
                                      // modulus) per group
@@ -38,7 +42,11 @@ constexpr int kCrtMmaMaxDigits = 160;   // of the matrix-core CRT
 // ... its digits in steps of 2 up to 32 and of 4 above, one kernel each
 constexpr int crt_unit_digits(int nd32) { return nd32 <= 32 ? (nd32 + 1) / 2 * 2 : (nd32 + 3) / 4 * 4; }
 constexpr int kMaxModuli = 512;       // fp64-exact CRT digit sums need L * 2^44 < 2^53
-constexpr int kMaxWords = 256;        // fp64-exact residue sums need nw32 * 2^45 < 2^53
+constexpr int kMaxWords = 256;        // words of the widest integer
+// fp64-exact residue sums, digits of up to 2^31 against centred weights below 2^15 (a pair's
+// product) or 2^13 (a two-limb modulus), the latter added to 1.5 2^52 unreduced
+static_assert(kResRowDigits <= 1 << (53 - 46) && kResRowDigits <= 1 << (51 - 44), "row-broadcast residues");
+static_assert(kMaxWords + 4 < 1 << (53 - 44), "row-broadcast residues of wide integers");
 constexpr int64_t kMaxK = 133000;     // K * 127^2 < 2^31, the cap the paper's implementation uses
 constexpr uint32_t kOneLimbMax = 255;    // centred residue fits int8
 constexpr uint32_t kTwoLimbMax = 16191;  // balanced base-128 halves fit int8 (and their sum)
