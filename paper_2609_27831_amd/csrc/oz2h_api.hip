@@ -134,6 +134,12 @@ GemmCfg tile_cfg(int tile) {
 // only to 128.  Residue handles, whose products are not known yet, are padded so.
 int64_t kpad_for(int64_t K) { return round_up(std::max<int64_t>(K, 1), K > 1024 ? 2 * GBK : GBK); }
 
+// the smallest tiles for M rows under this tile setting: a launch has at most 65535 rows of tiles
+GemmCfg least_gemm(int64_t M, int tile) {
+    if (tile == OZ2H_TILE_AUTO && M > (int64_t)65535 * 128) return {256, 128};
+    return tile_cfg(tile);
+}
+
 // Automatic choice for L moduli (L = 0: no 256 x 256 tiles).
 // 256 x 256 (k_resgemm8) from 320 (modulus, tile) items on, where the output pads to at most
 // 1/16 more than with 128 x 128 tiles, or 1/3 more from kpad = 1024 on.  GEMM stage, 128 x 128
@@ -149,7 +155,7 @@ GemmCfg choose_gemm(int64_t M, int64_t N, int tile, int64_t kpad, int L) {
     if (kpad % (2 * GBK) == 0 && L * (sq / (256 * 256)) >= 320 &&
         (sq * 16 <= a128 * 17 || (kpad >= 1024 && sq * 3 <= a128 * 4)))
         return {256, 256};
-    return {128, 128};
+    return least_gemm(M, tile);
 }
 
 // k padding of planes for these tiles alone
@@ -186,7 +192,7 @@ size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N);
 // No layout depends on the plan's flags, which may change between the size call and the product.
 Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool least = false, bool handles = false) {
     Layout w{};
-    w.cfg = least ? tile_cfg(h.tile)
+    w.cfg = least ? least_gemm(M, h.tile)
                   : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(h.K), h.L);
     w.kpad = handles ? kpad_for(h.K) : kpad_of(w.cfg, h.K);
     if (!least && !h.grad && h.tile == OZ2H_TILE_AUTO) {
@@ -1421,7 +1427,7 @@ struct ZLayout {
 // least: as for plain products
 ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K, bool least = false) {
     ZLayout w{};
-    w.cfg = least ? tile_cfg(h.tile)
+    w.cfg = least ? least_gemm(M, h.tile)
                   : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(K), h.L);
     w.kpad = kpad_of(w.cfg, K);
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
