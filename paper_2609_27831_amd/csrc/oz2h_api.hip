@@ -267,12 +267,15 @@ ExpSide exp_side2(int64_t rows, int64_t count, const oz2h_cmat &X, const oz2h_cm
 // A long contraction over few blocks of rows leaves most of the chip idle: such a side splits
 // the contraction over blocks and combines partial maxima with atomicMax (a fill before and a
 // fix of all-zero rows after).  256 rows of 16384 on both sides: 54 us against 85 in one launch;
-// 4096 rows of 4096: 70 against 50.
-bool exp_split(const ExpSide &d, int64_t count) { return count > 8192 && d.nb < 128 && d.nb > 0; }
+// 4096 rows of 4096: 70 against 50.  So does a side of so many rows that two of them would pass
+// a launch's 2^32 threads (the split scan of strided rows takes one per row).
+bool exp_split(const ExpSide &d, int64_t count) {
+    return (count > 8192 && d.nb < 128 && d.nb > 0) || 2 * d.nb * kExpThreads > UINT32_MAX;
+}
 int launch_exponents_split(const ExpSide &d, int64_t count, hipStream_t s) {
     const unsigned nb = (unsigned)((d.rows + 255) / 256);
     k_fill_i32<<<nb, 256, 0, s>>>(d.out, d.rows, INT_MIN);
-    for (int q = 0; q < d.nparts; ++q) {
+    for (int q = 0; count > 0 && q < d.nparts; ++q) {
         const ExpPart &p = d.part[q];
         if (p.cs == 1) {
             dim3 grid((unsigned)((d.rows + 3) / 4), (unsigned)((count + kExpChunk - 1) / kExpChunk));
@@ -296,7 +299,6 @@ int launch_exponents(int64_t count, ExpSide x, ExpSide y, hipStream_t s) {
         }
     const int64_t nb = x.nb + y.nb;
     if (!nb) return OZ2H_OK;
-    if (nb > INT32_MAX) return fail(OZ2H_ERANGE, "exponent scan: too many rows for one launch");
     k_exponents<<<(unsigned)nb, kExpThreads, 0, s>>>(ExpArgs{{x, y}, std::max<int64_t>(count, 0)});
     return check_launch("exponent scan");
 }
