@@ -235,7 +235,8 @@ size_t gemm_need(const PlanHost &h, int64_t M, int64_t N) {
 // contiguous rows take a wave each (16), fewer where blocks would be few and rows long (4096
 // rows of 4096: 23 us with up to 1024 threads per row, 30 with 64); strided ones 32, a line of
 // exponents (4096^2: 49 us against 63 with 16 and 58 with 64), 16 below 1024 rows (389 rows of
-// 1003: 9 against 10 us), and no more than there are.
+// 1003: 9 against 10 us), 8 where up to 128 have a long contraction (64 rows of 8192: 10.1
+// against 17.3 us, of 2048: 7.0 either way), and no more than there are.
 ExpSide exp_side(int64_t rows, int64_t count, const int8_t *sign, const int32_t *exp, int64_t rs, int64_t cs,
                  const int32_t *koff, int32_t *out) {
     ExpSide d{};
@@ -248,7 +249,7 @@ ExpSide exp_side(int64_t rows, int64_t count, const int8_t *sign, const int32_t 
         d.lr = 4;
         while (d.lr > 0 && (d.rows >> d.lr) < 512 && (int64_t)(kExpThreads >> d.lr) * 4 < count) --d.lr;
     } else {
-        d.lr = d.rows >= 1024 ? 5 : 4;
+        d.lr = d.rows >= 1024 ? 5 : d.rows <= 128 && count > 2048 ? 3 : 4;
         while (d.lr > 0 && ((int64_t)1 << (d.lr - 1)) >= d.rows) --d.lr;
     }
     d.nb = (d.rows + ((int64_t)1 << d.lr) - 1) >> d.lr;
@@ -266,11 +267,17 @@ ExpSide exp_side2(int64_t rows, int64_t count, const oz2h_cmat &X, const oz2h_cm
 
 // A long contraction over few blocks of rows leaves most of the chip idle: such a side splits
 // the contraction over blocks and combines partial maxima with atomicMax (a fill before and a
-// fix of all-zero rows after).  256 rows of 16384 on both sides: 54 us against 85 in one launch;
-// 4096 rows of 4096: 70 against 50.  So does a side of so many rows that two of them would pass
-// a launch's 2^32 threads (the split scan of strided rows takes one per row).
-bool exp_split(const ExpSide &d, int64_t count) {
-    return (count > 8192 && d.nb < 128 && d.nb > 0) || 2 * d.nb * kExpThreads > UINT32_MAX;
+// fix of all-zero rows after).  Contiguous rows from 8192 on (256 rows of 16384 on both sides: 54
+// us against 85 in one launch; 4096 rows of 4096: 70 against 50).  Strided ones earlier, as fewer
+// lanes read neighbours (one side alone, one launch / split: 300 rows of 3000 9.1 / 11.9 us, of
+// 4096 14.3 / 13.0, of 8192 28.2 / 17.8; 2000 of 4096 19.7 / 16.7, of 8192 36.1 / 26.7; 4000 of
+// 8192 40.7 / 39.9), and later again where the other side shares the launch, which costs 7 us by
+// itself.  So does a side of so many rows that two of them would pass a launch's 2^32 threads
+// (the split scan of strided rows takes one per row).
+bool exp_split(const ExpSide &d, int64_t count, bool alone) {
+    if (2 * d.nb * kExpThreads > UINT32_MAX) return true;
+    const bool strided = d.part[0].cs != 1 && d.rows > 128;
+    return d.nb > 0 && d.nb < 128 && count > (!strided ? 8192 : alone ? 3500 : 6144);
 }
 int launch_exponents_split(const ExpSide &d, int64_t count, hipStream_t s) {
     const unsigned nb = (unsigned)((d.rows + 255) / 256);
@@ -291,8 +298,9 @@ int launch_exponents_split(const ExpSide &d, int64_t count, hipStream_t s) {
 
 // shared exponents of one or two sides (a side of no rows launches nothing)
 int launch_exponents(int64_t count, ExpSide x, ExpSide y, hipStream_t s) {
+    const bool alone = !x.nb || !y.nb;
     for (ExpSide *d : {&x, &y})
-        if (exp_split(*d, count)) {
+        if (exp_split(*d, count, alone)) {
             const int st = launch_exponents_split(*d, count, s);
             if (st) return st;
             *d = ExpSide{};

@@ -3,6 +3,7 @@ partial rounds and long ones split over blocks, in both layouts, against numpy's
 import numpy as np
 import pytest
 
+import synth
 from tests.gpu_util import need_gpu
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +36,22 @@ def test_row_maxima(oz, rows, count, contig):
     rs, cs = (ld, 1) if contig else (1, ld)
     got = oz.exponents(torch.from_numpy(sign).cuda(), torch.from_numpy(exp).cuda(), rows, count, rs, cs)
     assert np.array_equal(got.cpu().numpy(), ref)
+
+
+# the lines of the rules for strided sides: 128 rows, a contraction of 2048, 3500 alone
+@pytest.mark.parametrize("rows,count", [(16, 2049), (128, 2049), (128, 8000), (129, 3500), (129, 3501), (300, 6000), (2000, 3600)])
+def test_strided_rows(oz, rows, count):
+    test_row_maxima(oz, rows, count, False)
+
+
+@pytest.mark.parametrize("K", [6144, 6145])
+def test_sides_of_one_product(oz, K):
+    """A strided side that shares the launch, or is split while the other is not, against sides on their own."""
+    import torch
+    M, N, p = 200, 210, 53
+    A, B = (oz.to_device(synth.mp_random(K + i, *s, p, -90, 90)) for i, s in enumerate([(M, K), (K, N)]))
+    plan = oz.Plan.create(p, K)
+    print(f"exponents of a product, K = {K}", flush=True)
+    C = oz.gemm(plan, A, B)
+    D = oz.gemm_from_residues(plan, ra=oz.Residues(plan, A, oz.SIDE_A), rb=oz.Residues(plan, B, oz.SIDE_B))
+    assert all(torch.equal(a, b) for a, b in ((C.sign, D.sign), (C.exp, D.exp), (C.limbs, D.limbs)))
