@@ -455,26 +455,41 @@ bool gemm_deep(dim3 grid, int64_t kpad) {
     return (int64_t)grid.x * grid.y * grid.z <= kGemm8Blocks && kpad >= 512;
 }
 
-template <bool RAW>
 int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b, int64_t kpad,
                        int64_t a_ps, int64_t b_ps, const ModInfo *mi, int L, int16_t *v,
-                       int64_t v_ps, int64_t ldv, int32_t *craw, hipStream_t s) {
-    const GemmArgs g{a, b, kpad, a_ps, b_ps, mi, v, v_ps, ldv, craw};
+                       int64_t v_ps, int64_t ldv, hipStream_t s) {
+    const GemmArgs g{a, b, kpad, a_ps, b_ps, mi, v, v_ps, ldv, nullptr};
     const XcdMap xm = xcd_map_for(cfg, grid);
-    // plain int32 products have no fold for other blocks to cover: 4096^3 86 / 91 us
-    const bool deep = gemm_deep(grid, g.kpad) || (RAW && cfg.bm == cfg.bn);
+    const bool deep = gemm_deep(grid, g.kpad);
 #define OZ2H_RGEMM(WR, WC)                                                                  \
     do {                                                                                    \
-        if (deep) k_resgemm<WR, WC, 4, RAW><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);        \
-        else k_resgemm<WR, WC, 2, RAW><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);             \
+        if (deep) k_resgemm<WR, WC, 4, false><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);      \
+        else k_resgemm<WR, WC, 2, false><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);           \
     } while (0)
     if (cfg.bm == 256 && cfg.bn == 128) OZ2H_RGEMM(4, 2);
     else if (cfg.bm == 128 && cfg.bn == 256) OZ2H_RGEMM(2, 4);
-    else if (!RAW && cfg.bn == 64) OZ2H_RGEMM(4, 1);
-    else if (!RAW && cfg.bm == 64) OZ2H_RGEMM(1, 4);
+    else if (cfg.bn == 64) OZ2H_RGEMM(4, 1);
+    else if (cfg.bm == 64) OZ2H_RGEMM(1, 4);
     else OZ2H_RGEMM(2, 2);
 #undef OZ2H_RGEMM
     return check_launch("residue GEMM");
+}
+
+// Plain int32 products: k_i8gemm, but k_resgemm where blocks of eight waves have a compute unit
+// each and the contraction is long (k_i8gemm / k_resgemm, 256 x 128: 1024 x 1024 x 4096 28.3 /
+// 26.4 us, 2048^3 19.4 / 18.8, 2048 x 2048 x 512 10.2 / 10.8, 4096^3, 512 blocks, 76.4 / 78.4).
+int launch_i8gemm(GemmCfg cfg, int64_t M, int64_t N, int64_t K, const int8_t *a, const int8_t *b, int32_t *c,
+                  hipStream_t s) {
+    dim3 grid((unsigned)(N / cfg.bn), (unsigned)(M / cfg.bm), 1);
+    const bool rg = cfg.bm != cfg.bn && gemm_deep(grid, K) && K >= 2048;
+    const XcdMap xm = xcd_map_for(cfg, grid);
+    const GemmArgs g{a, b, K, 0, 0, nullptr, nullptr, 0, N, c};
+    if (rg && cfg.bm == 256) k_resgemm<4, 2, 4, true><<<grid, 512, 0, s>>>(g, 1, xm);
+    else if (rg) k_resgemm<2, 4, 4, true><<<grid, 512, 0, s>>>(g, 1, xm);
+    else if (cfg.bm == 256) k_i8gemm<128, 64><<<grid, 256, 0, s>>>(a, b, K, c, N, xm);
+    else if (cfg.bn == 256) k_i8gemm<64, 128><<<grid, 256, 0, s>>>(a, b, K, c, N, xm);
+    else k_i8gemm<64, 64><<<grid, 256, 0, s>>>(a, b, K, c, N, xm);
+    return check_launch("INT8 GEMM");
 }
 
 // a_ps / b_ps: plane strides of the A and B planes (0: mpad * kpad, npad * kpad)
@@ -487,9 +502,8 @@ int launch_resgemm(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npad,
                             GemmArgsZ{{a, b, kpad, a_ps ? a_ps : mpad * kpad, b_ps ? b_ps : npad * kpad,
                                        pl->d_info, v, mpad * npad, npad, nullptr}, nullptr}, ZSTORE, s);
     dim3 grid((unsigned)(npad / cfg.bn), (unsigned)(mpad / cfg.bm), (unsigned)h.L);
-    return launch_gemm_kernel<false>(cfg, grid, a, b, kpad, a_ps ? a_ps : mpad * kpad,
-                                     b_ps ? b_ps : npad * kpad, pl->d_info, h.L, v, mpad * npad,
-                                     npad, nullptr, s);
+    return launch_gemm_kernel(cfg, grid, a, b, kpad, a_ps ? a_ps : mpad * kpad,
+                              b_ps ? b_ps : npad * kpad, pl->d_info, h.L, v, mpad * npad, npad, s);
 }
 
 // Launch shape of the CRT by single moduli (plain residues of the stage call; the batched form
@@ -1947,8 +1961,7 @@ int oz2h_i8gemm(int64_t M, int64_t N, int64_t K, const int8_t *A, const int8_t *
                     cfg.bm, cfg.bn);
     if (K > kMaxK) return fail(OZ2H_ERANGE, "K > 133000");
     if (!A || !B || !C) return fail(OZ2H_EINVAL, "NULL pointer");
-    dim3 grid((unsigned)(N / cfg.bn), (unsigned)(M / cfg.bm), 1);
-    st = launch_gemm_kernel<true>(cfg, grid, A, B, K, 0, 0, nullptr, 1, nullptr, 0, N, C, stream);
+    st = launch_i8gemm(cfg, M, N, K, A, B, C, stream);
     return st ? st : ok();
 }
 

@@ -1133,7 +1133,7 @@ __device__ __forceinline__ int lds_swz(int r) { return (r & 7) ^ ((r >> 3) & 1);
 // inverses exist): acc = P0 w0 -> + P2 -> * w1 -> + Ps -> * w2.  Between the
 // products |acc| <= m/2, so acc + K 127^2 < 2^31 stays exact.
 // Blocks run the two-limb moduli first (they are three times longer).
-// RAW = true: plain int32 output of a single plane (exactness tests).
+// RAW = true: plain int32 output of a single plane (the stage call's longer products).
 struct GemmArgs {
     const int8_t *A, *B;
     int64_t kpad, a_ps, b_ps;
@@ -1432,6 +1432,121 @@ __global__ __launch_bounds__(64 * WR * WC, gemm_waves(WR * WC, ST)) void k_resge
     }
     const int l = RAW ? 0 : L - 1 - (int)zi;
     gemm_tile<WR, WC, ST, RAW>(args, mt, nt, l);
+}
+
+// Plain int32 product C = A B^T of one plane (the stage call), (2 WM) x (2 WN) tiles of four waves
+// in 2 x 2, each WM x WN of v_mfma_i32_32x32x32_i8 blocks.  k-tiles of 128 bytes move global ->
+// LDS by direct loads into three stages, two tiles ahead of the multiplies; chunk c of LDS row r
+// is stored at c ^ lds_swz(r), applied to the global addresses.
+//
+// What bounds it: one block per compute unit, so the k-loop itself, without a fold or reduction
+// that other blocks could cover: half the barriers per byte of k_resgemm's 64-byte k-tiles
+// (k_resgemm / this one, 128 x 128: 4096^3 94 / 88 us, 2048^3 16.3 / 14.6, 2048 x 2048 x 512
+// 10.0 / 8.9; 256 x 128: 8192^3 590 / 570, 2048 x 2048 x 512 10.8 / 10.2).
+template <int WM, int WN, int S>
+__device__ __forceinline__ int8_t *i8_stage() {
+    __shared__ __attribute__((aligned(1024))) int8_t st[(2 * WM + 2 * WN) * TBK];
+    return st;
+}
+
+template <int WM, int WN>
+__global__ __launch_bounds__(256) void k_i8gemm(const int8_t *__restrict__ A, const int8_t *__restrict__ B,
+                                                int64_t K, int32_t *__restrict__ C, int64_t ldc, XcdMap xm) {
+    constexpr int BM = 2 * WM, BN = 2 * WN, FM = WM / 32, FN = WN / 32;
+    constexpr int NLA = BM / 32, NL = (BM + BN) / 32;   // direct loads per wave per k-tile
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1;
+    uint32_t mt = blockIdx.y, nt = blockIdx.x;
+    if (xm.on) {
+        const uint32_t x = blockIdx.x & 7u, u = blockIdx.x >> 3;
+        mt = (x / xm.rx) * xm.h + u / xm.w;
+        nt = (x % xm.rx) * xm.w + u % xm.w;
+    }
+    const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
+    const int nk = (int)(K / TBK);
+
+    uint32_t goff[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const int R = 32 * i + 8 * wave + (lane >> 3);
+        goff[i] = (uint32_t)((i < NLA ? R : R - BM) * K) + (((lane & 7) ^ lds_swz(R)) << 4);
+    }
+    const int8_t *Ab = A + m0 * K, *Bb = B + n0 * K;
+    // the next k-tile; near the end the last one again, so that the number of loads in flight
+    // behind a tile is always the same
+    int lk = 0;
+    auto issue = [&](auto s_) OZ2H_INL {
+        int8_t *dst = i8_stage<WM, WN, decltype(s_)::value>();
+        const int8_t *a = Ab + (int64_t)lk * TBK, *b = Bb + (int64_t)lk * TBK;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            __builtin_amdgcn_global_load_lds((const void *)((i < NLA ? a : b) + goff[i]),
+                                             (__attribute__((address_space(3))) void *)(dst + (4 * i + wave) * 1024),
+                                             16, 0, 0);
+        lk = min(lk + 1, nk - 1);
+    };
+
+    v16i acc[FM][FN];
+#pragma unroll
+    for (int x = 0; x < FM; ++x)
+#pragma unroll
+        for (int y = 0; y < FN; ++y) acc[x][y] = v16i{};
+    const int frow = lane & 31;
+    v4i fa[2][FM], fb[2][FN];
+    auto fetch = [&](int set, int ks, const int8_t *cA, const int8_t *cB) OZ2H_INL {
+        const int fo = frow * TBK + (((2 * ks + (lane >> 5)) ^ lds_swz(frow)) << 4);
+#pragma unroll
+        for (int x = 0; x < FM; ++x) fa[set][x] = *(const v4i *)(cA + (wr * WM + x * 32) * TBK + fo);
+#pragma unroll
+        for (int y = 0; y < FN; ++y) fb[set][y] = *(const v4i *)(cB + (wc * WN + y * 32) * TBK + fo);
+    };
+    // one k-tile from stage S; the one two ahead goes into the stage before S, which every wave
+    // finished reading before the barrier
+    auto body = [&](auto s_) OZ2H_INL {
+        constexpr int S = decltype(s_)::value;
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));   // own loads of this tile landed
+        __builtin_amdgcn_s_barrier();                // everyone's did
+        issue(std::integral_constant<int, (S + 2) % 3>{});
+        const int8_t *cA = i8_stage<WM, WN, S>(), *cB = cA + BM * TBK;
+        fetch(0, 0, cA, cB);
+        auto kstep = [&](auto k_) OZ2H_INL {
+            constexpr int ks = decltype(k_)::value;
+            if constexpr (ks + 1 < 4) fetch((ks + 1) & 1, ks + 1, cA, cB);
+#pragma unroll
+            for (int x = 0; x < FM; ++x)
+#pragma unroll
+                for (int y = 0; y < FN; ++y)
+                    acc[x][y] =
+                        __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks & 1][x], fb[ks & 1][y], acc[x][y], 0, 0, 0);
+            if constexpr (ks + 1 < 4) __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, FM * FN, 0);
+        };
+        kstep(std::integral_constant<int, 0>{});
+        kstep(std::integral_constant<int, 1>{});
+        kstep(std::integral_constant<int, 2>{});
+        kstep(std::integral_constant<int, 3>{});
+    };
+    issue(std::integral_constant<int, 0>{});
+    issue(std::integral_constant<int, 1>{});
+    int t = 0;
+    for (; t + 3 <= nk; t += 3) {
+        body(std::integral_constant<int, 0>{});
+        body(std::integral_constant<int, 1>{});
+        body(std::integral_constant<int, 2>{});
+    }
+    if (t < nk) body(std::integral_constant<int, 0>{});
+    if (t + 1 < nk) body(std::integral_constant<int, 1>{});
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no load still writing LDS past the block's end
+
+    int32_t *base = C + (m0 + wr * WM + 4 * (lane >> 5)) * ldc + n0 + wc * WN + (lane & 31);
+#pragma unroll
+    for (int x = 0; x < FM; ++x)
+#pragma unroll
+        for (int y = 0; y < FN; ++y)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                base[(int64_t)(x * 32 + 8 * (e >> 2) + (e & 3)) * ldc + y * 32] = acc[x][y][e];
 }
 
 // one residue GEMM of a complex product (the 3M / 4M schemes): the plain launch's block

@@ -129,3 +129,11 @@ def test_thin_rule(oz, large, p):
     for X, Y, ops in ((A, B, (0, 0)), (B, A, (1, 1))):
         C, D = oz.gemm(auto, X, Y, *ops), oz.gemm(square, X, Y, *ops)
         assert all(torch.equal(a, b) for a, b in ((C.sign, D.sign), (C.exp, D.exp), (C.limbs, D.limbs)))
+
+
+# one to four k-tiles (three stages), and both sides of the rule for long products of few blocks
+@pytest.mark.parametrize("M,N,K", [(256, 256, 128), (256, 256, 256), (256, 512, 384), (256, 256, 512), (256, 256, 1920),
+                                   (256, 256, 2048), (512, 768, 2176), (4352, 4096, 2048)])
+@pytest.mark.parametrize("tile", [1, 2, 3])
+def test_i8gemm_rule(oz, M, N, K, tile):
+    test_i8gemm(oz, M, N, K, tile)
