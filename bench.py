@@ -208,9 +208,9 @@ def device_operands(cfg, seed):
     return oz2h.DeviceMP(sa, ea, la, p), oz2h.DeviceMP(sb, eb, lb, p)
 
 
-def kernel_names(plan, flags):
-    """The stage-2 / stage-4 kernels a plain call of this plan launches (the dominant one
-    where a stage has two)."""
+def kernel_names(plan, flags, M, N, K):
+    """The stage-2, -3 and -4 kernels a plain M x N x K call of this plan launches (the dominant
+    one where a stage has two), by the library's rules."""
     from paper_2609_27831_amd import oz2h
     if (flags & oz2h.FLAG_RESIDUES_MMA) and plan.nw32 >= 8:
         res = "k_residues_mma"
@@ -219,8 +219,17 @@ def kernel_names(plan, flags):
     if (flags & oz2h.FLAG_CRT_MMA) and 16 <= plan.nd32 <= 160 and plan.L <= (127 if plan.nd32 <= 32 else 255):
         crt = "k_crt_mma"
     else:
-        crt = "k_crt_row_sums" if plan.nd32 > 48 else "k_crt_units"
-    return res, crt
+        units = plan.nd32 <= 32 or (plan.nd32 <= 48 and M * N >= 131072)
+        crt = "k_crt_units" if units else "k_crt_row_sums"
+
+    def up(x, q):
+        return -(-x // q) * q
+
+    kpad = up(K, 256 if K > 1024 else 128)
+    a128, sq = up(M, 128) * up(N, 128), up(M, 256) * up(N, 256)
+    big = (kpad % 256 == 0 and plan.L * (sq // 65536) >= 320
+           and (sq * 16 <= a128 * 17 or (kpad >= 1024 and sq * 3 <= a128 * 4)))
+    return res, "k_resgemm8" if big else "k_resgemm", crt
 
 
 def time_plain(name, Ad, Bd, steps, warmup, flags=0):
@@ -254,7 +263,7 @@ def time_plain(name, Ad, Bd, steps, warmup, flags=0):
     flops = 2.0 * M * N * K
     nl = (p + 63) // 64
     L, G, nd32, nw32 = plan.L, plan.G, plan.nd32, plan.nw32
-    res_k, crt_k = kernel_names(plan, flags)
+    res_k, gemm_k, crt_k = kernel_names(plan, flags, M, N, K)
     # algorithmic work per stage (per launch = per step)
     res_bytes = (M * K + K * N) * (8 * nl + 5) + (M * K + K * N) * G
     units = L - plan.L1 // 2                       # a pair of one-limb moduli counts once
@@ -263,8 +272,6 @@ def time_plain(name, Ad, Bd, steps, warmup, flags=0):
     gemm_bytes = G * (M * K + K * N) + L * M * N * 2
     crt_bytes = L * M * N * 2 + M * N * (8 * nl + 5)
     crt_fma = M * N * units * nd32                 # weight x digit multiply-adds
-    tiles = -(-M // 256) * -(-N // 256)
-    gemm_k = "k_resgemm8" if L * tiles >= 320 else "k_resgemm"
     phases = {n: {"ms": round(phase_ms[n], 4),
                   "effective_gflops": round(flops / (phase_ms[n] * 1e-3) / 1e9, 2)}
               for n in PHASES}

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(64 * kResWaves) void k_residues_grouped(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ResTab tb{P.resid, P.rgrp, P.p, P.nl, P.t, P.nw32, P.rgroups};
     residue_wave<NW>(res_side(P, sg.side, ws), tb, lb % sg.nbx,
-                     (lb / sg.nbx * kResWaves + wave) * (res_ept(NW ? NW : 31) / 2),
+                     (lb / sg.nbx * kResWaves + wave) * (res_ept(NW ? NW : kResMaxWords) / 2),
                      words + wave * (res_wave_lds(NW ? NW : P.nw32) / 4));
 }
 

@@ -371,8 +371,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // EPT bytes leave as one store, 128 bytes per row of a plane.  The weights and moduli are
 // wave-uniform scalar loads; units go in groups of four of one kind.  NW > 0 (integers of
 // exactly NW words): EPT = 4, the words stay in registers, as signed doubles, for every group.
-// NW = 0 (wider ones): EPT = 2, which leaves LDS for two waves per SIMD at 31 words; the words
-// are read again for every four groups.
+// NW = 0 (wider ones): EPT = 2, which leaves LDS for three waves per SIMD at 23 words where 4
+// would leave one; the words are read again for every four groups.
 //
 // What bounds it: up to 12 words the plane stores and operand reads (8192^3, p = 113: 8.4 GB,
 // 1.8 ms at the rate of a copy) and VALU issue about as much, above that issue and LDS.
@@ -601,7 +601,7 @@ __global__ __launch_bounds__(64 * kResWaves) void k_residues(ResArgs a) {
     const ResSide sa = a.side[sd];
     const int64_t lb = (int64_t)blockIdx.x - (sd ? a.blocks0 : 0), nbx = sa.kpad / 128;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    residue_wave<NW>(sa, a.tab, lb % nbx, (lb / nbx * kResWaves + wave) * (res_ept(NW ? NW : 31) / 2),
+    residue_wave<NW>(sa, a.tab, lb % nbx, (lb / nbx * kResWaves + wave) * (res_ept(NW ? NW : kResMaxWords) / 2),
                      words + wave * (res_wave_lds(NW ? NW : a.tab.nw32) / 4), blockIdx.y, a.parts);
 }
 
@@ -2649,13 +2649,14 @@ __global__ __launch_bounds__(BT, BT == 64 ? 2 : 1) void k_crt_mma(CrtArgs a) {
 // p = 2048 36.1 to 34.4).
 //   k_crt_row_sums: a wave takes 64 consecutive entries and one group of 16 digits.  Lane j
 //     of row q owns digit 16 dg + j of the row's entries 16 q + i (i < 16) and keeps, per
-//     chunk of 16 moduli, their 16 digit constants in registers; lane m of the row loads v of
-//     modulus 16 c + m for the row's 16 entries, and each multiply-add takes v from lane m by
+//     chunk of 16 units, their 16 digit constants in registers; lane m of the row loads v of
+//     unit 16 c + m for the row's 16 entries, and each multiply-add takes v from lane m by
 //     a DPP row broadcast.  The 16 sums of an entry then go through LDS to one lane, which
 //     carries them into 16 digits in [0, 2^32) and a carry-out (digit-major in the
-//     workspace: digit k of entry e at dig[k * estride + e]).  Blocks are one wave; the
-//     digit groups of a tile run on one XCD (block b goes to XCD b mod 8), so that the tile's
-//     v planes are read from HBM once and then from that XCD's L2.
+//     workspace: digit k of entry e at dig[k * estride + e]).  Blocks are four waves, four
+//     consecutive tiles of one digit group; the digit groups of a tile run on one XCD (block b
+//     goes to XCD b mod 8), so that its v planes are read from HBM once and then from that
+//     XCD's L2.
 //   k_crt_row_finish: one entry per thread: the groups' carry-outs are added in, S's nd32
 //     digits land in an LDS column, and from there as in the matrix-core CRT: beta from the
 //     top digits (the paper's alpha - 1 when the estimate is within 2^-30 of a half-integer),

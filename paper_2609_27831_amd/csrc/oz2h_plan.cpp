@@ -247,9 +247,6 @@ void build_crt_mma_tables(PlanHost &h, const std::vector<uint32_t> &mods, const 
     h.crt_mma = true;
 }
 
-// Digit tables of the direct CRT over h.L terms: S = sum_l v_l coef_l with coef_l = P / m_l
-// (or a multiple of it), as balanced base-2^32 digits (|d| <= 2^31), plus P's digits and
-// the top-digit estimate of S / P.
 // Balanced base-2^32 digits of a into out[0 .. n); false if they do not fit.
 bool balanced_digits(const Nat &a, int n, double *out) {
     int64_t carry = 0;
@@ -314,6 +311,9 @@ int crt_unit_tables(PlanHost &h, const std::vector<Nat> &coef, std::string &err)
     return 0;
 }
 
+// Digit tables of the direct CRT over h.L terms: S = sum_l v_l coef_l with coef_l = P / m_l
+// (or a multiple of it), as balanced base-2^32 digits (|d| <= 2^31), by terms and by units, plus
+// P's digits and the top-digit estimate of S / P.
 int crt_tables(PlanHost &h, const Nat &P, const std::vector<Nat> &coef, std::string &err) {
     h.pbits = nat_bitlen(P);
     h.nd32 = (h.pbits + 31) / 32 + 2;   // two digits of headroom (subsection on the batched CRT)

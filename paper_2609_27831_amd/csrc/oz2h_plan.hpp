@@ -38,9 +38,9 @@ constexpr int64_t crt_row_first(int64_t nent, int64_t tile, int q) {
 // (2048^2 entries, units against rows: 37 digits 0.65 / 1.26 ms, 45: 1.24 / 1.46, 56: 2.1 - 2.3 /
 // 2.3, 62: 2.6 - 2.8 / 2.6)
 constexpr int kCrtUnitMaxDigits = 48;
-constexpr int kCrtMmaMaxDigits = 160;   // of the matrix-core CRT
 // ... its digits in steps of 2 up to 32 and of 4 above, one kernel each
 constexpr int crt_unit_digits(int nd32) { return nd32 <= 32 ? (nd32 + 1) / 2 * 2 : (nd32 + 3) / 4 * 4; }
+constexpr int kCrtMmaMaxDigits = 160;   // of the matrix-core CRT
 constexpr int kMaxModuli = 512;       // fp64-exact CRT digit sums need L * 2^44 < 2^53
 constexpr int kMaxWords = 256;        // words of the widest integer
 // fp64-exact residue sums, digits of up to 2^31 against centred weights below 2^15 (a pair's
@@ -174,8 +174,9 @@ struct PlanHost {
     std::vector<double> crt_udig;    // [units][crt_und]: balanced base-2^32 digits
     int crt_ndg = 0;       // row-broadcast CRT: groups of 16 digits
     int crt_rnpair = 0;    // row-broadcast CRT: pairs of one-limb moduli among its units
-    int crt_lpad = 0;      // ... moduli padded to a multiple of 16
-    std::vector<double> crt_row;     // [16 crt_ndg][crt_lpad]: digit d of P/m_l at [d][l]
+    int crt_lpad = 0;      // ... units padded to a multiple of 16
+    std::vector<double> crt_row;     // [16 crt_ndg][crt_lpad]: digit d of unit u's coefficient,
+                                     // P / m_l or P / (m_a m_b), at [d][u]
     bool crt_mma_wide = false;   // set before build_plan: its tables beyond nd32 = 32 as well
     bool crt_mma = false;  // matrix-core CRT tables built (nd32 <= 32, L <= 127; wide: nd32 <=
                            // kCrtMmaMaxDigits, L <= 255)
