@@ -450,9 +450,19 @@ int launch_gemm8(const PlanHost &h, int64_t mpad, int64_t npad, const GemmArgsZ 
 // Blocks that have a compute unit to themselves take four LDS stages and read a k-tile ahead of
 // its products (1024 x 1024 x 4096, one plane: 19.0 us against 22.5; 128 x 128 x 4096, p = 256,
 // 66 moduli: 56 / 79); more blocks, or few k-tiles, do better with two stages and three blocks
-// per unit (3328 x 3072 x 384, p = 256: 1015 / 827; 384 x 384 x 4096, p = 113, 360 blocks: 67 / 64).
-bool gemm_deep(dim3 grid, int64_t kpad) {
-    return (int64_t)grid.x * grid.y * grid.z <= kGemm8Blocks && kpad >= 512;
+// per unit (3328 x 3072 x 384, p = 256: 1015 / 827; whole products, four / two: 2048^3, p = 256
+// 1787 / 1710 us, 1500 x 1500 x 2100, p = 113 554 / 514).  But where the tiles do not divide
+// among the XCDs a k-tile comes from further away than one ahead hides: from 1024 on with more
+// blocks than run at a time (768), from 2048 on with more than half of those (610 x 824 x 4096,
+// p = 53, 840 blocks, 247 / 289, 2048 134 / 141, 1024 86.1 / 87.0; 640 x 640 x 4096, p = 1024 3456 /
+// 3695; 300 x 300 x 4096, p = 256, 630 blocks, 316 / 354, 384 x 384, p = 113, 378, 140 / 138;
+// 640 x 640, p = 53, 600, 2048 109 / 110, 1024 71.8 / 70.3).  64-wide tiles gain nothing there
+// (8 x 3000 x 4096, p = 113 470 / 458).
+bool gemm_deep(GemmCfg cfg, const XcdMap &xm, dim3 grid, int64_t kpad) {
+    const int64_t blocks = (int64_t)grid.x * grid.y * grid.z, least = 3 * kGemm8Blocks;
+    if (!xm.on && cfg.bm >= 128 && cfg.bn >= 128 && kpad >= 1024 && blocks > (kpad >= 2048 ? least / 2 : least))
+        return true;
+    return blocks <= kGemm8Blocks && kpad >= 512;
 }
 
 int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b, int64_t kpad,
@@ -460,7 +470,7 @@ int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b,
                        int64_t v_ps, int64_t ldv, hipStream_t s) {
     const GemmArgs g{a, b, kpad, a_ps, b_ps, mi, v, v_ps, ldv, nullptr};
     const XcdMap xm = xcd_map_for(cfg, grid);
-    const bool deep = gemm_deep(grid, g.kpad);
+    const bool deep = gemm_deep(cfg, xm, grid, g.kpad);
 #define OZ2H_RGEMM(WR, WC)                                                                  \
     do {                                                                                    \
         if (deep) k_resgemm<WR, WC, 4, false><<<grid, 64 * WR * WC, 0, s>>>(g, L, xm);      \
@@ -481,7 +491,7 @@ int launch_gemm_kernel(GemmCfg cfg, dim3 grid, const int8_t *a, const int8_t *b,
 int launch_i8gemm(GemmCfg cfg, int64_t M, int64_t N, int64_t K, const int8_t *a, const int8_t *b, int32_t *c,
                   hipStream_t s) {
     dim3 grid((unsigned)(N / cfg.bn), (unsigned)(M / cfg.bm), 1);
-    const bool rg = cfg.bm != cfg.bn && gemm_deep(grid, K) && K >= 2048;
+    const bool rg = cfg.bm != cfg.bn && (int64_t)grid.x * grid.y <= kGemm8Blocks && K >= 2048;
     const XcdMap xm = xcd_map_for(cfg, grid);
     const GemmArgs g{a, b, K, 0, 0, nullptr, nullptr, 0, N, c};
     if (rg && cfg.bm == 256) k_resgemm<4, 2, 4, true><<<grid, 512, 0, s>>>(g, 1, xm);
@@ -1484,7 +1494,7 @@ int launch_resgemm_z(const oz2h_plan *pl, GemmCfg cfg, int64_t mpad, int64_t npa
     const GemmArgsZ g{{a, b, kpad, mpad * kpad, npad * kpad, pl->d_info, v, mpad * npad, npad, nullptr}, v2};
     if (cfg.bm == 256 && cfg.bn == 256) return launch_gemm8(h, mpad, npad, g, mode, s);
     const XcdMap xm = xcd_map_for(cfg, grid);
-    const bool deep = gemm_deep(grid, kpad);
+    const bool deep = gemm_deep(cfg, xm, grid, kpad);
 #define OZ2H_ZG(WR, WC, ST)                                                                            \
     do {                                                                                               \
         if (mode == ZADD) k_resgemm_z<WR, WC, ST, ZADD><<<grid, 64 * WR * WC, 0, s>>>(g, h.L, xm);     \

@@ -137,3 +137,14 @@ def test_thin_rule(oz, large, p):
 @pytest.mark.parametrize("tile", [1, 2, 3])
 def test_i8gemm_rule(oz, M, N, K, tile):
     test_i8gemm(oz, M, N, K, tile)
+
+
+# tiles that do not divide among the XCDs: four stages from 2048 on, or from 1024 with more than 768 blocks
+@pytest.mark.parametrize("M,N,K,p", [(600, 580, 1000, 113), (600, 580, 1030, 113), (300, 290, 1030, 113), (300, 290, 2000, 113),
+                                     (300, 290, 2170, 53), (610, 824, 2048, 53)])
+def test_depth_rule(oz, M, N, K, p):
+    import torch
+    A, B = dev_mp(synth.mp_random(M, M, K, p, -9, 9)), dev_mp(synth.mp_random(N, K, N, p, -9, 9))
+    print(f"depth {M} x {N} x {K}, p = {p}", flush=True)
+    C, D = (oz.gemm(oz.Plan.create(p, K, oz.default_opts(tile=t)), A, B) for t in (oz.TILE_AUTO, oz.TILE_256x128))
+    assert all(torch.equal(a, b) for a, b in ((C.sign, D.sign), (C.exp, D.exp), (C.limbs, D.limbs)))
