@@ -646,9 +646,11 @@ int launch_crt(const oz2h_plan *pl, int64_t M, int64_t N, const int16_t *u, int6
             int st = check_launch("CRT digit sums");
             if (st) return st;
             const unsigned nb2 = (unsigned)((rc.nent + 63) / 64);
-            const size_t lds2 = (size_t)kCrtFinS * h.nd32 * sizeof(uint32_t);
-            if (round) k_crt_row_finish<true><<<nb2, 64, lds2, s>>>(ca, ra);
-            else k_crt_row_finish<false><<<nb2, 64, lds2, s>>>(ca, ra);
+            const bool stash = round && (h.p + 63) / 64 <= kCrtStashLimbs && M * N >= kCrtStashEntries;
+            const size_t lds2 = (size_t)(stash ? kCrtFinS : 64) * h.nd32 * sizeof(uint32_t);
+            if (stash) k_crt_row_finish<true, true><<<nb2, 64, lds2, s>>>(ca, ra);
+            else if (round) k_crt_row_finish<true, false><<<nb2, 64, lds2, s>>>(ca, ra);
+            else k_crt_row_finish<false, false><<<nb2, 64, lds2, s>>>(ca, ra);
             return check_launch("CRT finish");
         }
     }

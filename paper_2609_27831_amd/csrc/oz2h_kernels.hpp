@@ -2139,9 +2139,14 @@ __device__ __forceinline__ bool crt_finish(const CrtArgs &a, int64_t i, int64_t 
 // A wave whose lanes hold stashed limbs (crt_finish; columns kCrtFinS words apart, lane e's at
 // sdig + e; oi: its output entry) stores them with consecutive lanes at consecutive limbs: a lane
 // storing its own entry's limbs touches 64 lines with every store (CRT at 2048^2, row kernels,
-// p = 1024 3.03 to 2.83 ms, p = 800 2.19 to 2.05; no difference for records of whole lines,
-// p = 2048).
+// p = 1024 3.03 to 2.83 ms, p = 800 2.19 to 2.05).  Records of 30 limbs and more nearly fill their
+// lines with each entry's own stores, and the wider columns cost a wave of LDS; few entries stay
+// in the caches (finish kernel, stashed / not: 24 limbs 214 / 256 us at 1000^2, 29 282 / 311, 30
+// 345 / 309, 40 537 / 457; 24 limbs 93 / 100 at 620^2, 27 109 / 109; at 300^2 19 31 / 24, 25 40 / 35,
+// 29 45 / 42).
 constexpr int kCrtFinS = 65;   // LDS words between the digits of a column
+constexpr int kCrtStashLimbs = 29;
+constexpr int64_t kCrtStashEntries = 262144;
 __device__ __forceinline__ void store_limbs(const CrtArgs &a, const uint32_t *sdig, bool stashed, int64_t oi) {
     const uint64_t mask = __ballot(stashed);
     if (!mask) return;
@@ -2876,9 +2881,11 @@ __global__ __launch_bounds__(256) void k_crt_row_sums(CrtRowArgs a) {
 // c^ = S - beta P digit by digit in binary64 (every term an integer below 2^43: exact) and
 // keeps its low nd32 digits in an LDS column, c^ in two's complement (|c^| < P/2, so the
 // top digit is sign extension); on the paper's alpha - 1 path the column holds R in [0, 3P).
-template <bool ROUND>
+// STASH: limbs stored together (columns kCrtFinS words apart, 64 without)
+template <bool ROUND, bool STASH>
 __global__ __launch_bounds__(64) void k_crt_row_finish(CrtArgs a, CrtRowArgs r) {
     extern __shared__ __attribute__((aligned(16))) uint32_t sdig[];
+    constexpr int CS = STASH ? kCrtFinS : 64;
     const int tid = threadIdx.x;
     const int64_t ep = (int64_t)blockIdx.x * 64 + tid;
     const int64_t i = ep / r.ldv, jj = ep - i * r.ldv;
@@ -2886,7 +2893,7 @@ __global__ __launch_bounds__(64) void k_crt_row_finish(CrtArgs a, CrtRowArgs r) 
     bool stashed = false;
     if (live) {
         const int nd32 = a.nd32, nt = a.nt;
-        uint32_t *col = sdig + tid;   // digit k at col[kCrtFinS k]
+        uint32_t *col = sdig + tid;   // digit k at col[CS k]
         // groups holding digits below nd32 (at least three: this kernel runs for nd32 > 32)
         const int ng = min(r.ndg, (nd32 + 15) / 16);
         auto ldg = [&](int g, uint32_t (&dv)[16], int32_t &co) {
@@ -2931,7 +2938,7 @@ __global__ __launch_bounds__(64) void k_crt_row_finish(CrtArgs a, CrtRowArgs r) 
         auto digit = [&](int k, uint32_t d, double add, uint32_t pk) {
             const double x = fma(-beta, (double)pk, (double)d + add + cy);
             const double hi = floor(x * 0x1p-32);
-            col[kCrtFinS * k] = (uint32_t)fma(-hi, 0x1p32, x);
+            col[CS * k] = (uint32_t)fma(-hi, 0x1p32, x);
             cy = hi;
         };
         auto pass = [&](int g, const uint32_t (&dv)[16], int32_t co) {
@@ -2955,10 +2962,10 @@ __global__ __launch_bounds__(64) void k_crt_row_finish(CrtArgs a, CrtRowArgs r) 
             pass(g + 1, db, cb);
         }
         if (g < ng) pass(g, da, ca);
-        const int64_t sgn = !slow && (int32_t)col[kCrtFinS * (nd32 - 1)] < 0 ? -1 : 0;
-        stashed = crt_finish<ROUND, ROUND>(a, i, jj, col, kCrtFinS, slow, sgn);
+        const int64_t sgn = !slow && (int32_t)col[CS * (nd32 - 1)] < 0 ? -1 : 0;
+        stashed = crt_finish<ROUND, STASH>(a, i, jj, col, CS, slow, sgn);
     }
-    if constexpr (ROUND) store_limbs(a, sdig, stashed, i * a.ldc + jj);
+    if constexpr (STASH) store_limbs(a, sdig, stashed, i * a.ldc + jj);
 }
 
 // planes [G][R][C] (int8, row stride ldi) -> [G][Co][Ro] (row stride Ro), zero where

@@ -164,3 +164,18 @@ def test_row_kernels_of_custom_sets(oz, c_oracle, n1, n2, p):
     sh = lambda x: (1 if x > 0 else -1) * (abs(x) << t - p if t >= p else abs(x) >> p - t)
     a, b = (np.vectorize(sh, otypes=[object])(x) for x in (a, b))
     assert list(oz.limbs_to_ints(cm.cpu().numpy().view(np.uint64), cs.cpu().numpy())) == list(np.dot(a, b).ravel())
+
+
+# limbs stored together or by each entry: the rule's limbs and entries
+@pytest.mark.parametrize("M,N,p", [(512, 512, 1856), (512, 512, 1857), (512, 511, 1856), (513, 513, 1030)])
+def test_row_finish_stores(oz, M, N, p):
+    """Rows of a product of many entries against the same rows on their own."""
+    K = 3
+    A, B = dev_mp(synth.mp_random(p, M, K, p, -3, 3)), dev_mp(synth.mp_random(p + 1, K, N, p, -3, 3))
+    print(f"row finish {M} x {N}, p = {p}", flush=True)
+    plan = oz.Plan.create(p, K)
+    C = oz.gemm(plan, A, B)
+    for r in (0, 77, M - 1):
+        X = oz.DeviceMP(A.sign[r:r + 1], A.exp[r:r + 1], A.limbs[r:r + 1], p)
+        D = oz.gemm(plan, X, B)
+        assert (C.sign[r] == D.sign[0]).all() and (C.exp[r] == D.exp[0]).all() and (C.limbs[r] == D.limbs[0]).all()
