@@ -142,18 +142,24 @@ GemmCfg least_gemm(int64_t M, int tile) {
 
 // Automatic choice for L moduli (L = 0: no 256 x 256 tiles).
 // 256 x 256 (k_resgemm8) from 320 (modulus, tile) items on, where the output pads to at most
-// 1/16 more than with 128 x 128 tiles, or 1/3 more from kpad = 1024 on.  GEMM stage, 128 x 128
+// 1/16 more than with 128 x 128 tiles, or 1/4 from kpad = 1024 on, or there 1/3 where it then
+// has at most half more entries than the product.  GEMM stage, 128 x 128
 // against it: 1024^3, p = 256: 178 / 155 us; 3328 x 3072 x 768, p = 256: 1290 / 1085;
 // 512 x 512 x 1024, p = 256 (280 items, the second round of 256 blocks nearly empty) and
 // 640 x 640 x 1024 (pads 1.44 times) were even or worse.
 // Else 128 x 128: with three blocks per compute unit it beats 256 x 128 (3328 x 3072 x 640,
 // p = 256: 1154 / 1504 us; 2048 x 2048 x 384, p = 512: 617 / 796; 1024^3: even).
+// Whole products of 53 to 2048 bits and K = 1024 to 4096, 128 x 128 against 256 x 256: 1.02 to 1.29
+// times where they pad 1.11 to 1.23 (0.97 to 1.19 at 1.20; complex 0.92 to 1.15 there); at 4/3 0.98
+// to 1.10 for 384 x 512 and 384 x 1280, but 0.89 to 1.01 for 256 x 300, 300 x 2000 and 176 x 258, as
+// residues and CRT work on the padding too.
 GemmCfg choose_gemm(int64_t M, int64_t N, int tile, int64_t kpad, int L) {
     if (tile != OZ2H_TILE_AUTO) return tile_cfg(tile);
     const int64_t a128 = round_up(M, 128) * round_up(N, 128);
     const int64_t sq = round_up(M, 256) * round_up(N, 256);
     if (kpad % (2 * GBK) == 0 && L * (sq / (256 * 256)) >= 320 &&
-        (sq * 16 <= a128 * 17 || (kpad >= 1024 && sq * 3 <= a128 * 4)))
+        (sq * 16 <= a128 * 17 ||
+         (kpad >= 1024 && (sq * 4 <= a128 * 5 || (sq * 3 <= a128 * 4 && sq * 2 <= M * N * 3)))))
         return {256, 256};
     return least_gemm(M, tile);
 }

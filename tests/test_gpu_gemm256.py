@@ -142,3 +142,13 @@ def test_noalloc_near_its_limit(oz):
     A, B = dev_mp(synth.mp_random(60, M, K, p, -5, 5)), dev_mp(synth.mp_random(61, K, N, p, -5, 5))
     print("noalloc near the limit", flush=True)
     assert _same(oz.gemm_noalloc(plan, A, B, out=oz.empty_mp(M, N, p)), oz.gemm(plan, A, B))
+
+
+# padding by a third more for a product that nearly fills 128 x 128 tiles and one that does not, and by less
+@pytest.mark.parametrize("M,N", [(384, 500), (256, 300), (500, 1100), (512, 600)])
+def test_padding_rule(oz, M, N):
+    K, p = 1100, 512
+    A, B = dev_mp(synth.mp_random(90, M, K, p, -5, 5)), dev_mp(synth.mp_random(91, K, N, p, -5, 5))
+    print(f"padding {M} x {N}", flush=True)
+    C = oz.gemm(oz.Plan.create(p, K), A, B)
+    assert _same(C, oz.gemm(oz.Plan.create(p, K, oz.default_opts(tile=oz.TILE_256x128)), A, B))
