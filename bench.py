@@ -229,7 +229,8 @@ def kernel_names(plan, flags, M, N, K):
     a128, sq = up(M, 128) * up(N, 128), up(M, 256) * up(N, 256)
     pads = sq * 16 <= a128 * 17 or (kpad >= 1024 and (
         sq * 4 <= a128 * 5 or (sq * 3 <= a128 * 4 and sq * 2 <= M * N * 3)))
-    big = kpad % 256 == 0 and plan.L * (sq // 65536) >= 320 and pads
+    big = (kpad % 256 == 0 and plan.L * (sq // 65536) >= 320 and pads
+           and (sq > 65536 or kpad <= up(K, 128)))
     return res, "k_resgemm8" if big else "k_resgemm", crt
 
 

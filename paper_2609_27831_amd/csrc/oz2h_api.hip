@@ -152,12 +152,13 @@ GemmCfg least_gemm(int64_t M, int tile) {
 // Whole products of 53 to 2048 bits and K = 1024 to 4096, 128 x 128 against 256 x 256: 1.02 to 1.29
 // times where they pad 1.11 to 1.23 (0.97 to 1.19 at 1.20; complex 0.92 to 1.15 there); at 4/3 0.98
 // to 1.10 for 384 x 512 and 384 x 1280, but 0.89 to 1.01 for 256 x 300, 300 x 2000 and 176 x 258, as
-// residues and CRT work on the padding too.
-GemmCfg choose_gemm(int64_t M, int64_t N, int tile, int64_t kpad, int L) {
+// residues and CRT work on the padding too.  One tile per modulus and K padded further than for
+// 128 x 128: 156 x 137 x 1331, p = 2048 713 / 766 us, 1280 695 / 681.
+GemmCfg choose_gemm(int64_t M, int64_t N, int64_t K, int tile, int64_t kpad, int L) {
     if (tile != OZ2H_TILE_AUTO) return tile_cfg(tile);
     const int64_t a128 = round_up(M, 128) * round_up(N, 128);
     const int64_t sq = round_up(M, 256) * round_up(N, 256);
-    if (kpad % (2 * GBK) == 0 && L * (sq / (256 * 256)) >= 320 &&
+    if (kpad % (2 * GBK) == 0 && L * (sq / (256 * 256)) >= 320 && (sq > 256 * 256 || kpad <= round_up(K, GBK)) &&
         (sq * 16 <= a128 * 17 ||
          (kpad >= 1024 && (sq * 4 <= a128 * 5 || (sq * 3 <= a128 * 4 && sq * 2 <= M * N * 3)))))
         return {256, 256};
@@ -199,7 +200,7 @@ size_t crt_gdig_bytes(const PlanHost &h, int64_t M, int64_t N);
 Layout layout_for(const PlanHost &h, int64_t M, int64_t N, bool least = false, bool handles = false) {
     Layout w{};
     w.cfg = least ? least_gemm(M, h.tile)
-                  : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(h.K), h.L);
+                  : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.K, h.tile, kpad_for(h.K), h.L);
     w.kpad = handles ? kpad_for(h.K) : kpad_of(w.cfg, h.K);
     if (!least && !h.grad && h.tile == OZ2H_TILE_AUTO) {
         if (N <= 64 && thin_tiles(M, h.L)) w.cfg = {256, 64};
@@ -458,15 +459,15 @@ int launch_gemm8(const PlanHost &h, int64_t mpad, int64_t npad, const GemmArgsZ 
 // 66 moduli: 56 / 79); more blocks, or few k-tiles, do better with two stages and three blocks
 // per unit (3328 x 3072 x 384, p = 256: 1015 / 827; whole products, four / two: 2048^3, p = 256
 // 1787 / 1710 us, 1500 x 1500 x 2100, p = 113 554 / 514).  But where the tiles do not divide
-// among the XCDs a k-tile comes from further away than one ahead hides: from 1024 on with more
-// blocks than run at a time (768), from 2048 on with more than half of those (610 x 824 x 4096,
-// p = 53, 840 blocks, 247 / 289, 2048 134 / 141, 1024 86.1 / 87.0; 640 x 640 x 4096, p = 1024 3456 /
-// 3695; 300 x 300 x 4096, p = 256, 630 blocks, 316 / 354, 384 x 384, p = 113, 378, 140 / 138;
-// 640 x 640, p = 53, 600, 2048 109 / 110, 1024 71.8 / 70.3).  64-wide tiles gain nothing there
-// (8 x 3000 x 4096, p = 113 470 / 458).
+// among the XCDs a k-tile comes from further away than one ahead hides: from 2048 on, and from
+// 1024 with more blocks than run at a time (768) (610 x 824 x 4096, p = 53, 840 blocks, 247 / 289,
+// 2048 134 / 141, 1024 86.1 / 87.0; 640 x 640 x 4096, p = 1024 3456 / 3695; 300 x 300 x 4096,
+// p = 256, 630 blocks, 316 / 354; 200 x 200 x 4096, p = 300, 312, 274 / 290, 2048 136 / 141, 1024
+// 94.8 / 96.7; 384 x 384 x 4096, p = 113, 378, 140 / 138, 1024 57.2 / 55.6).  64-wide tiles gain
+// nothing there (8 x 3000 x 4096, p = 113 470 / 458).
 bool gemm_deep(GemmCfg cfg, const XcdMap &xm, dim3 grid, int64_t kpad) {
-    const int64_t blocks = (int64_t)grid.x * grid.y * grid.z, least = 3 * kGemm8Blocks;
-    if (!xm.on && cfg.bm >= 128 && cfg.bn >= 128 && kpad >= 1024 && blocks > (kpad >= 2048 ? least / 2 : least))
+    const int64_t blocks = (int64_t)grid.x * grid.y * grid.z;
+    if (!xm.on && cfg.bm >= 128 && cfg.bn >= 128 && (kpad >= 2048 || (kpad >= 1024 && blocks > 3 * kGemm8Blocks)))
         return true;
     return blocks <= kGemm8Blocks && kpad >= 512;
 }
@@ -877,7 +878,7 @@ F64Layout layout_f64(const oz2h_plan *pl, int64_t M, int64_t N) {
     const PlanHost *h8 = pl->i8 ? &pl->i8->h : nullptr;
     F64Layout w{};
     w.kpad = round_up(std::max<int64_t>(h.K, 1), GBK);
-    w.cfg = h8 ? choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h8->tile, w.kpad, 0)
+    w.cfg = h8 ? choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.K, h8->tile, w.kpad, 0)
                : GemmCfg{128, 128};
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
@@ -1470,7 +1471,7 @@ struct ZLayout {
 ZLayout zlayout_for(const PlanHost &h, int scheme, int64_t M, int64_t N, int64_t K, bool least = false) {
     ZLayout w{};
     w.cfg = least ? least_gemm(M, h.tile)
-                  : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), h.tile, kpad_for(K), h.L);
+                  : choose_gemm(std::max<int64_t>(M, 1), std::max<int64_t>(N, 1), K, h.tile, kpad_for(K), h.L);
     w.kpad = kpad_of(w.cfg, K);
     w.mpad = round_up(std::max<int64_t>(M, 1), w.cfg.bm);
     w.npad = round_up(std::max<int64_t>(N, 1), w.cfg.bn);
@@ -1702,7 +1703,7 @@ BwdLayout bwd_layout(const PlanHost &h) {
     const int64_t M = h.gM, N = h.gN, K = h.K;
     const int64_t orows[2] = {M, K}, ocols[2] = {K, N}, contr[2] = {N, M};
     for (int sd = 0; sd < 2; ++sd) {
-        b.cfg[sd] = choose_gemm(orows[sd], ocols[sd], h.tile, kpad_for(contr[sd]), h.L);
+        b.cfg[sd] = choose_gemm(orows[sd], ocols[sd], contr[sd], h.tile, kpad_for(contr[sd]), h.L);
         b.kpad[sd] = kpad_of(b.cfg[sd], contr[sd]);
         b.mpad[sd] = round_up(orows[sd], b.cfg[sd].bm);
         b.npad[sd] = round_up(ocols[sd], b.cfg[sd].bn);
@@ -1959,7 +1960,7 @@ int oz2h_residue_gemm(const oz2h_plan *plan, int64_t mpad, int64_t npad, int64_t
     if (!a_planes || !b_planes || !v) return fail(OZ2H_EINVAL, "NULL pointer");
     GemmCfg cfg = tile_cfg(plan->h.tile);
     if (plan->h.tile == OZ2H_TILE_AUTO && mpad % 256 == 0) {
-        cfg = choose_gemm(mpad, npad, OZ2H_TILE_AUTO, kpad, npad % 256 == 0 ? plan->h.L : 0);
+        cfg = choose_gemm(mpad, npad, kpad, OZ2H_TILE_AUTO, kpad, npad % 256 == 0 ? plan->h.L : 0);
     }
     if (mpad % cfg.bm || npad % cfg.bn)
         return fail(OZ2H_EINVAL, "mpad, npad must be multiples of the %dx%d tile", cfg.bm, cfg.bn);
@@ -2153,8 +2154,8 @@ void tune_store(uint64_t sig, const TuneRec &r) {
 constexpr int kBigTiles = 3;
 int item_class(const oz2h_batched_plan *bp, int b) {
     if (bp->tile != OZ2H_TILE_AUTO) return bp->tile - 1;
-    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, OZ2H_TILE_AUTO, bp->pd[b].kpad,
-                                  bp->hosts[b].L);
+    const GemmCfg c = choose_gemm(bp->probs[b].M, bp->probs[b].N, bp->probs[b].K, OZ2H_TILE_AUTO,
+                                  bp->pd[b].kpad, bp->hosts[b].L);
     return c.bm == 256 ? kBigTiles : OZ2H_TILE_128x128 - 1;
 }
 
@@ -2500,7 +2501,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         P.rpad[1] = round_up(q.N, 256);
         P.K = q.K;
         // (whatever tile setting the plan has now: oz2h_batched_set_config changes it)
-        P.kpad = kpad_of(choose_gemm(q.M, q.N, OZ2H_TILE_AUTO, kpad_for(q.K), h.L), q.K);
+        P.kpad = kpad_of(choose_gemm(q.M, q.N, q.K, OZ2H_TILE_AUTO, kpad_for(q.K), h.L), q.K);
         P.p = h.p;
         P.nl = (h.p + 63) / 64;
         P.t = h.t;
