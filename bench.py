@@ -681,7 +681,7 @@ def measure_int8_gemm_context(steps, warmup):
         torch.cuda.synchronize()
         return (time.perf_counter() - t0) * 1e3 / steps
 
-    tile = oz2h.TILE_256x128   # the residue GEMMs' block tile at these sizes
+    tile = oz2h.TILE_256x128   # the largest block tile of the raw int8 product
     ms_core = timed(lambda: oz2h.i8gemm(A, Bt, tile))
     ms_lib = timed(lambda: torch._int_mm(A, Bt.t()))
     same = bool(torch.equal(oz2h.i8gemm(A, Bt, tile), torch._int_mm(A, Bt.t())))
