@@ -2316,6 +2316,26 @@ int launch_batched_front(oz2h_batched_plan *bp, const BatchChunk &ch, char *ws, 
     return OZ2H_OK;
 }
 
+// The unit CRT's launches follow one another, one per digit count of a chunk's products.  Products
+// of few entries do not fill the chip and join those of the next larger count, with zeros for the
+// digits above their own.  Whole batches of two products of n x n x 64 and two of 40 x 40 x 64,
+// apart / together: p = 53 and 256, n = 32 132 / 123 us, 256 143 / 129, 512 177 / 166, 724 191 / 191;
+// 200 and 256, 256 205 / 187, 512 230 / 211; 360 and 500, 512 330 / 325, 724 462 / 469; 113 and 330,
+// 512 212 / 207, 1024 274 / 297.
+constexpr int64_t kCrtShareEntries = 524288;
+void share_unit_crt(std::vector<PlanHost> &hosts, const oz2h_problem *probs) {
+    std::map<int, int64_t> entries;
+    for (size_t b = 0; b < hosts.size(); ++b)
+        if (hosts[b].nd32 <= kCrtUnitMaxDigits) entries[hosts[b].crt_und] += probs[b].M * probs[b].N;
+    for (auto x = entries.begin(); x != entries.end(); ++x) {
+        const auto y = std::next(x);
+        if (y == entries.end() || x->second > kCrtShareEntries || crt_unit_ept(x->first) != crt_unit_ept(y->first)) continue;
+        for (PlanHost &h : hosts)
+            if (h.crt_und == x->first) crt_unit_widen(h, y->first);
+        y->second += x->second;
+    }
+}
+
 int launch_batched_crt(oz2h_batched_plan *bp, const BatchChunk &ch, char *ws, hipStream_t s) {
     for (auto &c : ch.crt) {
         if (!c.blocks) continue;
@@ -2443,6 +2463,7 @@ int oz2h_batched_plan_create(int32_t count, const oz2h_problem *probs, const oz2
         if (st) return fail(st, "problem %d: %s", b, err.c_str());
         bp->hosts[b].flags = o->flags;
     }
+    share_unit_crt(bp->hosts, probs);
 
     // device table layout
     size_t off = 0;

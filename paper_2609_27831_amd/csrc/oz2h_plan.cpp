@@ -511,6 +511,14 @@ void build_residue_rows(PlanHost &h, const std::vector<uint32_t> &mods, int wide
     }
 }
 
+void crt_unit_widen(PlanHost &h, int und) {
+    std::vector<double> wide(h.crt_units.size() * und, 0.0);
+    for (size_t u = 0; u < h.crt_units.size(); ++u)
+        std::copy_n(&h.crt_udig[u * h.crt_und], h.crt_und, &wide[u * und]);
+    h.crt_udig.swap(wide);
+    h.crt_und = und;
+}
+
 int build_plan(int p, int t, int64_t K, const std::vector<uint32_t> &mods_in, PlanHost &h,
                std::string &err, int wmax, const std::vector<uint32_t> *extra) {
     if (mods_in.empty() || (int)mods_in.size() > kMaxModuli) {

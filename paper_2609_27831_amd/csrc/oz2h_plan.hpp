@@ -210,6 +210,9 @@ int select_moduli_bits(double need, std::vector<uint32_t> &mods, double &log2P, 
 int build_plan(int p, int t, int64_t K, const std::vector<uint32_t> &mods, PlanHost &out,
                std::string &err, int wmax = 0, const std::vector<uint32_t> *extra = nullptr);
 
+// The unit CRT's digit table with und digits a unit, more than now: zeros above.
+void crt_unit_widen(PlanHost &h, int und);
+
 // Largest binary64 modulus for contraction length K (Eq. fp64bound, capped so that a
 // residue splits into two 11-bit CRT terms).
 uint32_t f64_modulus_bound(int64_t K);

@@ -267,3 +267,29 @@ def test_batched_full_workload(oz, c_oracle):
             f"product {i}"
     print(f"batched full workload: loop compared {time.time() - t0:.1f}s", flush=True)
     bp.destroy()
+
+
+@pytest.mark.parametrize("shapes", [
+    # (M, N, K, p): digits of several counts in one launch of the unit CRT, up to 26 (two columns a
+    # lane; p = 24, 53, 113, 200, 256, 330) and from there on (one; p = 360, 420, 500)
+    [(9, 7, 33, 24), (30, 41, 64, 53), (33, 57, 561, 200), (223, 133, 19, 256), (64, 65, 40, 330)],
+    [(31, 2, 20, 53), (17, 19, 300, 360), (40, 23, 70, 420), (5, 80, 128, 500)],
+    # one side of 524288 entries and the other
+    [(724, 724, 16, 53), (8, 9, 10, 256)], [(725, 724, 16, 53), (8, 9, 10, 256)],
+    # wider products beside them, which the unit CRT does not take
+    [(20, 30, 40, 113), (20, 30, 40, 700), (25, 16, 90, 256)]])
+def test_batched_unit_crt_digit_counts(oz, shapes):
+    import torch
+    probs, plain = [], []
+    for i, (M, N, K, p) in enumerate(shapes):
+        A, B = synth.operands_for(900 + i, M, N, K, p, -4, 4)
+        probs.append((dev_mp(A), dev_mp(B), oz.empty_mp(M, N, p), 0, 0))
+        plain.append(oz.gemm(oz.Plan.create(p, K), probs[i][0], probs[i][1], 0, 0))
+    bp = oz.BatchedPlan(probs)
+    ws = bp.workspace()
+    print("batched", shapes, flush=True)
+    bp.run_eager(ws)
+    torch.cuda.synchronize()
+    for (_, _, C, _, _), Cp in zip(probs, plain):
+        for x, y in zip(_host(C), _host(Cp)):
+            assert np.array_equal(x, y)
